@@ -66,6 +66,24 @@ struct eck_model {
 };
 
 namespace eck {
+// What a scoring launch needs to reduce its scores to the least legal one per segment of seg_len candidates as well
+struct MinArgs {
+    const uint8_t *legal; // or NULL: all legal
+    uint64_t seg_len;
+    uint32_t *min_key;    // [n / seg_len], preset to 0xFFFFFFFF
+    uint32_t tiles_per_seg; // bf16 kernel: seg_len / (candidates per tile) when that is whole (set by the launcher), else 0
+};
+
+// order-preserving key of a float: unsigned comparison of keys = comparison of the numbers
+__device__ __forceinline__ uint32_t score_order_key(float x)
+{
+    const uint32_t u = __float_as_uint(x);
+    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+}
+
+// forward pass of an fp32 model (score_f32.hip); mn: also the minima, or NULL
+int32_t score_f32(const eck_model *m, const float *feat, uint64_t ld, uint64_t n, float *out, const MinArgs *mn,
+                  hipStream_t stream);
 // re-derive the packed weights from theta (BF16 models); enqueued on stream
 int32_t model_repack(eck_model *m, hipStream_t stream);
 // Adam steps of a BF16 model in two launches per step (refit.hip): whether that path takes this call, the bytes it

@@ -242,96 +242,9 @@ extern "C" int32_t eck_model_get_state(const eck_model *m, float *blob, uint64_t
     return ECK_OK;
 }
 
-// ------------------------------------------------------------ fp32 forward
+// ------------------------------------------------------------ bf16 forward
 
 namespace {
-
-constexpr int F32_TILE = 32; // candidates per block
-
-// 256 threads = 32 candidates x 8 unit groups.  Activations of the three
-// layers sit in LDS as [unit][candidate]; weights come straight from theta
-// (each load is shared by the 32 candidate lanes).  Accumulation is a plain
-// in-order fp32 FMA chain per output.
-__global__ __launch_bounds__(256) void score_f32_kernel(const float *__restrict__ theta, int F, int H1, int H2,
-                                                        uint64_t off_w1, uint64_t off_b1, uint64_t off_w2,
-                                                        uint64_t off_b2, uint64_t off_w3, uint64_t off_b3,
-                                                        const float *__restrict__ feat, uint64_t ld, uint64_t n,
-                                                        float *__restrict__ out)
-{
-    extern __shared__ float act[];
-    float *a0 = act, *a1 = a0 + F * F32_TILE, *a2 = a1 + H1 * F32_TILE;
-    const int c = threadIdx.x & 31, ug = threadIdx.x >> 5;
-    const uint64_t cand = (uint64_t)blockIdx.x * F32_TILE + c;
-    for (int i = ug; i < F; i += 8) a0[i * F32_TILE + c] = cand < n ? feat[(uint64_t)i * ld + cand] : 0.0f;
-    __syncthreads();
-    for (int j = ug; j < H1; j += 8) {
-        float acc = theta[off_b1 + j];
-        const float *w = theta + off_w1 + j;
-        for (int i = 0; i < F; ++i) acc = fmaf(a0[i * F32_TILE + c], w[(uint64_t)i * H1], acc);
-        a1[j * F32_TILE + c] = fmaxf(acc, 0.0f);
-    }
-    __syncthreads();
-    for (int j = ug; j < H2; j += 8) {
-        float acc = theta[off_b2 + j];
-        const float *w = theta + off_w2 + j;
-        for (int i = 0; i < H1; ++i) acc = fmaf(a1[i * F32_TILE + c], w[(uint64_t)i * H2], acc);
-        a2[j * F32_TILE + c] = fmaxf(acc, 0.0f);
-    }
-    __syncthreads();
-    if (ug == 0 && cand < n) {
-        float acc = theta[off_b3];
-        for (int i = 0; i < H2; ++i) acc = fmaf(a2[i * F32_TILE + c], theta[off_w3 + i], acc);
-        out[cand] = acc;
-    }
-}
-
-// The same network with four consecutive units per thread and pass (hidden widths that are multiples of four): one
-// activation read and one 16-byte weight load feed four multiply-adds, a quarter of the loads per multiply-add.  Every
-// output is still the same in-order chain, so the scores are the bits the kernel above gives.
-__global__ __launch_bounds__(256) void score_f32x4_kernel(const float *__restrict__ theta, int F, int H1, int H2,
-                                                          uint64_t off_w1, uint64_t off_b1, uint64_t off_w2,
-                                                          uint64_t off_b2, uint64_t off_w3, uint64_t off_b3,
-                                                          const float *__restrict__ feat, uint64_t ld, uint64_t n,
-                                                          float *__restrict__ out)
-{
-    extern __shared__ float act[];
-    float *a0 = act, *a1 = a0 + F * F32_TILE, *a2 = a1 + H1 * F32_TILE;
-    const int c = threadIdx.x & 31, ug = threadIdx.x >> 5;
-    const uint64_t cand = (uint64_t)blockIdx.x * F32_TILE + c;
-    for (int i = ug; i < F; i += 8) a0[i * F32_TILE + c] = cand < n ? feat[(uint64_t)i * ld + cand] : 0.0f;
-    __syncthreads();
-    auto layer = [&](const float *in, float *res, int K, int H, uint64_t off_w, uint64_t off_b) {
-        for (int j = 4 * ug; j < H; j += 32) {
-            float4 acc = *reinterpret_cast<const float4 *>(theta + off_b + j);
-            const float *w = theta + off_w + j;
-#pragma unroll 8
-            for (int i = 0; i < K; ++i) {
-                const float a = in[i * F32_TILE + c];
-                const float4 wv = *reinterpret_cast<const float4 *>(w + (uint64_t)i * H);
-                acc.x = fmaf(a, wv.x, acc.x);
-                acc.y = fmaf(a, wv.y, acc.y);
-                acc.z = fmaf(a, wv.z, acc.z);
-                acc.w = fmaf(a, wv.w, acc.w);
-            }
-            res[(j + 0) * F32_TILE + c] = fmaxf(acc.x, 0.0f);
-            res[(j + 1) * F32_TILE + c] = fmaxf(acc.y, 0.0f);
-            res[(j + 2) * F32_TILE + c] = fmaxf(acc.z, 0.0f);
-            res[(j + 3) * F32_TILE + c] = fmaxf(acc.w, 0.0f);
-        }
-    };
-    layer(a0, a1, F, H1, off_w1, off_b1);
-    __syncthreads();
-    layer(a1, a2, H1, H2, off_w2, off_b2);
-    __syncthreads();
-    if (ug == 0 && cand < n) {
-        float acc = theta[off_b3];
-#pragma unroll 8
-        for (int i = 0; i < H2; ++i) acc = fmaf(a2[i * F32_TILE + c], theta[off_w3 + i], acc);
-        out[cand] = acc;
-    }
-}
-
-// ------------------------------------------------------------ bf16 forward
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef short s16x2 __attribute__((ext_vector_type(2)));
@@ -490,19 +403,6 @@ __device__ __forceinline__ void wait_vm(bool dma_after)
 // its own over the scores.  Every lane keeps a running minimum for the segment its wavefront is in; the lanes are
 // combined and handed to memory with one integer atomic when the wavefront moves on to another segment or ends; a
 // wavefront whose 32 NC candidates straddle two segments sends them one by one.  The legality flags of a tile travel with its features.
-struct MinArgs {
-    const uint8_t *legal; // or NULL: all legal
-    uint64_t seg_len;
-    uint32_t *min_key;    // [n / seg_len], preset to 0xFFFFFFFF
-    uint32_t tiles_per_seg; // seg_len / (candidates per tile) when that is whole (set by the launcher), else 0
-};
-
-__device__ __forceinline__ uint32_t score_order_key(float x)
-{
-    const uint32_t u = __float_as_uint(x);
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-
 template <int F, int H1, int H2, int NC, bool FEAT_BF16, bool WIDE_ROWS, bool WITH_MIN>
 __global__ __launch_bounds__(256) void score_bf16_kernel(const unsigned char *__restrict__ packed, PackedLayout L,
                                                          const void *__restrict__ feat, uint64_t ld, uint64_t n,
@@ -977,17 +877,6 @@ int32_t launch_bf16(const eck_model *m, const void *feat, int32_t feat_dtype, ui
     return ECK_OK;
 }
 
-// least order key per segment of fp32 scores (the small fp32 models, whose forward kernel has no matrix-core epilogue)
-__global__ __launch_bounds__(256) void min_key_kernel(const float *__restrict__ score, const uint8_t *__restrict__ legal,
-                                                      uint64_t n, uint64_t seg_len, uint32_t *__restrict__ min_key)
-{
-    const uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const float v = score[i];
-    if ((legal && !legal[i]) || v != v) return;
-    (void)__hip_atomic_fetch_min(min_key + i / seg_len, score_order_key(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 __global__ void fill_keys_kernel(uint32_t *p, uint32_t n)
 {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -1016,31 +905,7 @@ int32_t score_any(const eck_model *m, const void *feat, int32_t feat_dtype, uint
     if (WITH_MIN) {
         hipLaunchKernelGGL(fill_keys_kernel, dim3((n_segments + 255) / 256), dim3(256), 0, st, mn.min_key, n_segments);
     }
-    if (m->dtype == ECK_F32) {
-        const size_t lds = (size_t)(F + H1 + H2) * F32_TILE * sizeof(float);
-        ECK_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(score_f32_kernel),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        const uint64_t blocks = (n + F32_TILE - 1) / F32_TILE;
-        if (blocks > 0x7FFFFFFFull) return ECK_EUNSUPPORTED;
-        // (parameter offsets are then multiples of four floats as well, and the state is 256-byte aligned)
-        const bool by_four = H1 % 4 == 0 && H2 % 4 == 0;
-        if (by_four) {
-            ECK_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(score_f32x4_kernel),
-                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-            hipLaunchKernelGGL(score_f32x4_kernel, dim3((unsigned)blocks), dim3(256), lds, st, m->d_state, F, H1, H2,
-                               m->off_w[0], m->off_b[0], m->off_w[1], m->off_b[1], m->off_w[2], m->off_b[2],
-                               (const float *)feat, ld, n, score_out);
-        } else {
-            hipLaunchKernelGGL(score_f32_kernel, dim3((unsigned)blocks), dim3(256), lds, st, m->d_state, F, H1, H2,
-                               m->off_w[0], m->off_b[0], m->off_w[1], m->off_b[1], m->off_w[2], m->off_b[2],
-                               (const float *)feat, ld, n, score_out);
-        }
-        if (WITH_MIN)
-            hipLaunchKernelGGL(min_key_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, score_out, mn.legal, n,
-                               mn.seg_len, mn.min_key);
-        ECK_HIP_TRY(hipGetLastError());
-        return ECK_OK;
-    }
+    if (m->dtype == ECK_F32) return score_f32(m, (const float *)feat, ld, n, score_out, WITH_MIN ? &mn : nullptr, st);
     // four candidate tiles per wavefront (half the weight traffic per candidate) where 256 or fewer hidden units
     // leave the registers for it, the features arrive as bf16 and groups of four stay inside a row (the flags of
     // four candidates are then one 4-byte load)

@@ -70,6 +70,44 @@ def test_fp32_model_widths_with_and_without_four_units_per_thread(G, widths):
     assert G.within(got, want, oracle.score_magnitude(widths, theta, f32, n=n), 1e-5) <= 1.0
 
 
+@pytest.mark.parametrize("widths", [[32, 1, 1, 1], [64, 17, 48, 1], [32, 33, 5, 1], [64, 304, 80, 1], [64, 500, 497, 1]])
+def test_fp32_model_tile_edges(G, widths):
+    """hidden widths that leave 1-4 tiles of 16 units to a wavefront, remainders in both layers and in the reduction;
+    candidate counts around a tile and around each change of the block's size.  A candidate's score is the same bits
+    whatever its place and n; the least legal key of a segment is numpy's, also where a tile straddles segments."""
+    counts = [1, 15, 16, 17, 63, 65, 1000]
+    if max(widths[1:]) <= 64:
+        counts += [512 * 16 - 3, 512 * 16 * 4 + 1, 512 * 16 * 8 + 16, 512 * 16 * 16 + 5]
+    most = counts[-1]
+    f32, _ = _features("c1" if widths[0] == 32 else "c2", 6400 if widths[0] == 32 else most + (most & 1), widths[0])
+    f32 = np.ascontiguousarray(np.tile(f32, (1, -(-most // f32.shape[1]) + 1))[:, :most + (most & 1)])
+    theta = synth.mlp_theta(widths, 7, bias_scale=0.4)
+    model = G.make_model(widths, eck.F32, theta)
+    dev = G.to_dev(f32)
+    full = G.score_gpu(model, dev, most)
+    want = oracle.score(widths, theta, f32, n=most)
+    assert G.within(full, want, oracle.score_magnitude(widths, theta, f32, n=most), 1e-5) <= 1.0
+    for n in counts[:-1]:
+        assert np.array_equal(G.score_gpu(model, dev, n), full[:n]), n
+    rng = np.random.default_rng(3)
+    for n, segments in ((1000, 1), (1000, 8), (999, 37), (most, 1)):
+        legal = (rng.random(n) < 0.2).astype(np.uint8)
+        score = torch.zeros(n, dtype=torch.float32, device="cuda")
+        key = torch.zeros(segments, dtype=torch.int32, device="cuda")
+        eck.costmodel_score_min(model, dev, n, score, G.to_dev(legal), segments, key)
+        torch.cuda.synchronize()
+        assert np.array_equal(score.cpu().numpy(), full[:n])
+        for s in range(segments):
+            of = slice(s * (n // segments), (s + 1) * (n // segments))
+            least = full[:n][of][legal[of] != 0]
+            got = int(key[s].item()) & 0xFFFFFFFF
+            if least.size == 0:
+                assert got == 0xFFFFFFFF
+            else:
+                bits = int(np.float32(least.min()).view(np.uint32))
+                assert got == bits ^ (0xFFFFFFFF if bits >> 31 else 0x80000000)
+
+
 @pytest.mark.parametrize("widths,cfg,n", [([64, 256, 256, 1], "c2", 5000), ([64, 512, 512, 1], None, 4133),
                                           ([64, 128, 128, 1], "c3", 1500), ([32, 64, 64, 1], "c1", 6400)])
 def test_bf16_model(G, widths, cfg, n):
