@@ -2,14 +2,16 @@
 // Adam on the weighted squared error of Eq. (1)  (Alg. 1: ModelUpdate, SNR;
 // Sec. 6.4).  HIP, gfx950.
 //
-// One optimisation step is a short chain of launches of one strided tile GEMM
-// (forward, the three weight-gradient products with the bias gradient folded
-// in as an extra all-ones row, the two back-propagated deltas), a one-block
-// loss/delta kernel and an element-wise Adam kernel.  For BF16 models the five
-// large products run on the matrix cores with bf16 operands (weights,
-// activations and back-propagated deltas rounded as they are staged) and fp32
-// accumulation; the width-1 products of the output layer stay in fp32.  All
-// reductions have a fixed order, so a run is reproducible bit for bit.
+// The steps of fp32 models, and of BF16 models whose minibatch is a multiple of
+// 64 rows, take two launches each (refit_f32.hip, refit.hip).  Here are the
+// labels, the SNR, and the steps of the other BF16 minibatches: a short chain of
+// launches of one strided tile GEMM on the matrix cores (forward, the three
+// weight-gradient products with the bias gradient folded in as an extra all-ones
+// row, the two back-propagated deltas; bf16 operands, weights, activations and
+// back-propagated deltas rounded as they are staged, fp32 accumulation), a
+// row-local loss/delta kernel and an element-wise Adam kernel; the width-1
+// products of the output layer stay in fp32.  All reductions have a fixed order,
+// so a run is reproducible bit for bit.
 #include <algorithm>
 #include <cmath>
 
@@ -44,80 +46,9 @@ struct GemmArgs {
     int round_a, round_b, round_c; // pass operands / result through bf16
 };
 
-constexpr int TM = 64, TN = 64, TK = 16;
+constexpr int TM = 64, TN = 64;
 
-__global__ __launch_bounds__(256) void gemm_kernel(GemmArgs first, GemmArgs second)
-{
-    const GemmArgs g = blockIdx.z ? second : first;
-    if ((int)blockIdx.x * TN >= g.N || (int)blockIdx.y * TM >= g.M) return;
-    __shared__ float As[TK][TM + 4];
-    __shared__ float Bs[TK][TN + 4];
-    const int tid = threadIdx.x;
-    const int tx = tid & 15, ty = tid >> 4; // 16 x 16 threads, 4 x 4 outputs each
-    const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TN;
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < g.K; k0 += TK) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int e = tid + 256 * q;
-            {
-                const int m = e & (TM - 1), k = e >> 6;
-                const int gm = m0 + m, gk = k0 + k;
-                float v = 0.0f;
-                if (gm < g.M && gk < g.K) {
-                    if (gm == g.a_ones_row) v = 1.0f;
-                    else {
-                        const int64_t at = (int64_t)gm * g.sa_m + (int64_t)gk * g.sa_k;
-                        v = g.a_is_bf16 ? __uint_as_float((uint32_t)reinterpret_cast<const uint16_t *>(g.A)[at] << 16)
-                                        : reinterpret_cast<const float *>(g.A)[at];
-                        if (g.round_a) v = through_bf16(v);
-                    }
-                }
-                As[k][m] = v;
-            }
-            {
-                const int n = e & (TN - 1), k = e >> 6;
-                const int gn = n0 + n, gk = k0 + k;
-                float v = 0.0f;
-                if (gn < g.N && gk < g.K) {
-                    v = g.B[(int64_t)gk * g.sb_k + (int64_t)gn * g.sb_n];
-                    if (g.round_b) v = through_bf16(v);
-                }
-                Bs[k][n] = v;
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < TK; ++k) {
-            float a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = As[k][ty * 4 + i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = Bs[k][tx * 4 + j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int m = m0 + ty * 4 + i, n = n0 + tx * 4 + j;
-            if (m >= g.M || n >= g.N) continue;
-            float v = acc[i][j];
-            if (g.bias) v += g.round_b ? through_bf16(g.bias[n]) : g.bias[n];
-            if (g.relu) v = fmaxf(v, 0.0f);
-            const int64_t at = (int64_t)m * g.ldc + n;
-            if (g.mask && !(g.mask[at] > 0.0f)) v = 0.0f;
-            if (g.round_c) v = through_bf16(v);
-            g.C[at] = v;
-        }
-}
-
-// The same product on the matrix cores for BF16 models: both operands are rounded to bf16 while they
+// The product on the matrix cores for BF16 models: both operands are rounded to bf16 while they
 // are staged into LDS, accumulation is fp32 (v_mfma_f32_32x32x16_bf16).  64 x 64 output tile per block,
 // one 32 x 32 quadrant per wavefront, 64-deep stages; the next stage's operands are already in
 // flight (in registers) while the current one is multiplied.
@@ -429,6 +360,12 @@ UpdWs upd_layout(const eck_model *m, uint64_t n_pairs, int mb)
     w.scalars = o; o = align(o + sizeof(Scalars));
     w.y = o;       o = align(o + n_pairs * 4);
     w.pred = o;    o = align(o + n_pairs * 4);
+    w.h1 = w.h2 = w.dy = w.lterm = w.d2 = w.d1 = w.grad = o;
+    if (m->dtype == ECK_F32) { // its two-launch steps keep all their buffers themselves
+        w.refit = o;
+        w.total = o + refit_f32_workspace_bytes(m, mb);
+        return w;
+    }
     w.h1 = o;      o = align(o + (uint64_t)mb * m->widths[1] * 4);
     w.h2 = o;      o = align(o + (uint64_t)mb * m->widths[2] * 4);
     w.dy = o;      o = align(o + (uint64_t)mb * 4);
@@ -437,23 +374,20 @@ UpdWs upd_layout(const eck_model *m, uint64_t n_pairs, int mb)
     w.d1 = o;      o = align(o + (uint64_t)mb * m->widths[1] * 4);
     w.grad = o;    o = align(o + m->n_params * 4);
     w.refit = o;   // the two-launch step of BF16 models keeps its own buffers behind the others
-    if (m->dtype == ECK_BF16 && mb % 64 == 0) o += refit_workspace_bytes(m, mb);
+    if (mb % 64 == 0) o += refit_workspace_bytes(m, mb);
     w.total = o;
     return w;
 }
 
 // One launch for one product, or for two products that do not depend on each other (grid.z = 2).
-void launch_gemm(const GemmArgs &g, hipStream_t st, bool matrix_cores = false, const GemmArgs *also = nullptr)
+void launch_gemm(const GemmArgs &g, hipStream_t st, const GemmArgs *also = nullptr)
 {
     const GemmArgs &h = also ? *also : g;
     const dim3 grid((std::max(g.N, h.N) + TN - 1) / TN, (std::max(g.M, h.M) + TM - 1) / TM, also ? 2 : 1);
-    if (matrix_cores) {
-        // set per call: the attribute belongs to the current device
-        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(gemm_mfma_kernel),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)GEMM_MFMA_LDS);
-        hipLaunchKernelGGL(gemm_mfma_kernel, grid, dim3(256 * KG), GEMM_MFMA_LDS, st, g, h);
-    }
-    else hipLaunchKernelGGL(gemm_kernel, grid, dim3(256), 0, st, g, h);
+    // set per call: the attribute belongs to the current device
+    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(gemm_mfma_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)GEMM_MFMA_LDS);
+    hipLaunchKernelGGL(gemm_mfma_kernel, grid, dim3(256 * KG), GEMM_MFMA_LDS, st, g, h);
 }
 
 } // namespace
@@ -490,7 +424,6 @@ extern "C" int32_t costmodel_update(eck_model *m, const void *feat, int32_t feat
     float *d1 = reinterpret_cast<float *>(base + w.d1), *grad = reinterpret_cast<float *>(base + w.grad);
     const int F = m->widths[0], H1 = m->widths[1], H2 = m->widths[2], B = minibatch;
     const uint64_t P = m->n_params;
-    const int bf = m->dtype == ECK_BF16;
     float *theta = m->d_state;
     const int elem = feat_dtype == ECK_BF16 ? 2 : 4;
 
@@ -509,7 +442,16 @@ extern "C" int32_t costmodel_update(eck_model *m, const void *feat, int32_t feat
         ECK_HIP_TRY(hipGetLastError());
         return model_repack(m, st);
     }
+    if (m->dtype == ECK_F32) {
+        rc = refit_f32_steps(m, static_cast<const float *>(feat), ld, y, n_pairs, n_steps, minibatch, lr, beta1, beta2, eps,
+                             &sc->bad, &sc->loss, base + w.refit, st);
+        if (rc != ECK_OK) return rc;
+        hipLaunchKernelGGL(finish_kernel, dim3(1), dim3(64), 0, st, theta, P, n_steps, sc, snr_out, loss_out);
+        ECK_HIP_TRY(hipGetLastError());
+        return ECK_OK;
+    }
     const uint64_t nb = n_pairs / (uint64_t)B;
+    const int bf = 1; // the operands are rounded to bf16
     for (int s = 0; s < n_steps; ++s) {
         const uint64_t row0 = ((uint64_t)s % nb) * (uint64_t)B;
         const void *x = static_cast<const char *>(feat) + row0 * elem; // X(r, f) = feat[f*ld + row0 + r]
@@ -517,11 +459,11 @@ extern "C" int32_t costmodel_update(eck_model *m, const void *feat, int32_t feat
         // h1 = relu(X W1 + b1)
         g = GemmArgs{x, elem == 2, 1, (int64_t)ld, -1, theta + m->off_w[0], H1, 1, h1, H1, B, H1, F,
                      theta + m->off_b[0], 1, nullptr, bf, bf, bf};
-        launch_gemm(g, st, bf);
+        launch_gemm(g, st);
         // h2 = relu(h1 W2 + b2)
         g = GemmArgs{h1, 0, H1, 1, -1, theta + m->off_w[1], H2, 1, h2, H2, B, H2, H1,
                      theta + m->off_b[1], 1, nullptr, 0, bf, 0};
-        launch_gemm(g, st, bf);
+        launch_gemm(g, st);
         // output layer forward + loss + backward into d2, then its weight gradient
         hipLaunchKernelGGL(output_layer_kernel, dim3((B + 3) / 4), dim3(256), 0, st, h2, theta + m->off_w[2],
                            theta + m->off_b[2], H2, B, y + row0, bf, pred, dy, lterm, d2);
@@ -531,11 +473,11 @@ extern "C" int32_t costmodel_update(eck_model *m, const void *feat, int32_t feat
         g = GemmArgs{h1, 0, 1, H1, H1, d2, H2, 1, grad + m->off_w[1], H2, H1 + 1, H2, B, nullptr, 0, nullptr, 0, 0, 0};
         // d1 = (d2 W2^T) where h1 > 0: needs d2 only, like the product above, so both go in one launch
         const GemmArgs back{d2, 0, H2, 1, -1, theta + m->off_w[1], 1, H2, d1, H1, B, H1, H2, nullptr, 0, h1, 0, bf, 0};
-        launch_gemm(g, st, bf, &back);
+        launch_gemm(g, st, &back);
         // [gW1 ; gb1] = [X ; 1]^T d1
         g = GemmArgs{x, elem == 2, (int64_t)ld, 1, F, d1, H1, 1, grad + m->off_w[0], H1, F + 1, H1, B, nullptr, 0, nullptr,
                      bf, 0, 0};
-        launch_gemm(g, st, bf);
+        launch_gemm(g, st);
         hipLaunchKernelGGL(adam_kernel, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, st, theta, grad, P, s, lr, beta1,
                            beta2, eps, sc);
     }

@@ -61,6 +61,46 @@ def test_fp32_trajectory(G):
     assert G.within(pred_g, pred_o, oracle.score_magnitude(widths, st[:P].astype(np.float32), f32), 1e-3) <= 1.0
 
 
+@pytest.mark.parametrize("widths,n_pairs,minibatch", [([32, 1, 1, 1], 8, 1), ([64, 17, 48, 1], 45, 15), ([32, 33, 5, 1], 34, 17),
+                                                      ([64, 128, 128, 1], 500, 250), ([64, 300, 96, 1], 256, 128),
+                                                      ([64, 500, 497, 1], 66, 33), ([64, 4, 512, 1], 1040, 520)])
+def test_fp32_steps_at_tile_edges(G, widths, n_pairs, minibatch):
+    """hidden widths and minibatches around the tiles of the two-launch step: one to four 16-unit tiles per wavefront,
+    remainders in units, reduction and rows.  After one step the moments are 0.1 g and 0.001 g^2, so they compare the
+    gradient: a sum of n fp32 products is off by at most n 2^-24 of the sum of their magnitudes, the longest here is
+    520, and the norms of sum and magnitudes differ by less than a factor of 30: 1e-3 (measured below 1e-6).  The second
+    moment's factor 1 - beta2 is rounded to fp32, 5e-5 off."""
+    F = widths[0]
+    P = synth.param_count(widths)
+    f32, _, _ = _pairs(n_pairs + (n_pairs & 1))
+    f32 = np.ascontiguousarray(f32[:F])
+    e = synth.measured_energy(f32[:, :n_pairs], 13)
+    theta = synth.mlp_theta(widths, 3, bias_scale=0.1)
+    model = G.make_model(widths, eck.F32, theta)
+    st = _oracle_state(theta)
+    feat = G.to_dev(f32)
+    snr_g, loss_g = G.update_gpu(model, feat, e, 1, minibatch)
+    snr_o, loss_o = oracle.update(widths, st, f32, e, 1, minibatch)
+    assert abs(snr_g - snr_o) <= 1e-4 * snr_o and abs(loss_g - loss_o) <= 1e-4 * loss_o
+    got = model.get_state().cpu().numpy().astype(np.float64)
+    for lo, hi, tol in ((P, 2 * P, 1e-3), (2 * P, 3 * P, 3e-3)):
+        off = np.linalg.norm(got[lo:hi] - st[lo:hi]) / np.linalg.norm(st[lo:hi])
+        assert off <= tol, off
+    assert got[3 * P] == 1.0
+    # a parameter moves by lr against its gradient's sign; where the gradient vanishes, rounding decides
+    d = np.abs(got[:P] - st[:P])
+    clear = np.abs(st[P:2 * P]) > 1e-4 * np.abs(st[P:2 * P]).max()
+    assert d[clear].max() <= 1e-5 and d.max() <= 2.001e-3
+    # the minibatches after the first: the whole buffer once, the same bits every time
+    again = G.make_model(widths, eck.F32, theta)
+    steps = n_pairs // minibatch
+    G.update_gpu(again, feat, e, steps, minibatch)
+    assert np.isfinite(again.get_state().cpu().numpy()).all()
+    twice = G.make_model(widths, eck.F32, theta)
+    G.update_gpu(twice, feat, e, steps, minibatch)
+    assert np.array_equal(twice.get_state().cpu().numpy(), again.get_state().cpu().numpy())
+
+
 def test_bf16_refit_config4(G):
     cfg = synth.CONFIGS["c4"]
     widths = cfg["widths"]
