@@ -297,14 +297,17 @@ __global__ __launch_bounds__(1024) void tree_labels_kernel(const float *__restri
     }
 }
 
-// bins of every (feature, pair), computed once per call
+// bins of every (feature, pair), computed once per call; row n_feat is 1 where feature 0 is not below +inf (the pairs
+// that go right at a node without a split, whose test is "feature 0 < +inf")
 __global__ void tree_bins_kernel(const void *__restrict__ feat, int is_bf16, uint64_t ld, uint64_t n_pairs, int n_feat,
                                  uint8_t *__restrict__ bins)
 {
     const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int f = blockIdx.y;
     if (i >= n_pairs || f >= n_feat) return;
-    bins[(uint64_t)f * n_pairs + i] = (uint8_t)bin_of(feature_value(feat, is_bf16, (uint64_t)f * ld + i));
+    const float x = feature_value(feat, is_bf16, (uint64_t)f * ld + i);
+    bins[(uint64_t)f * n_pairs + i] = (uint8_t)bin_of(x);
+    if (f == 0) bins[(uint64_t)n_feat * n_pairs + i] = x < __builtin_inff() ? 0 : 1;
 }
 
 // SNR = sum y^2 / sum (p - y)^2 (which == 0: the ensemble on entry) or the mean Eq.-(1) loss (which == 1)
@@ -572,26 +575,407 @@ __global__ void tree_finish_kernel(const BoostScalars *sc, float *snr_out, float
     *loss_out = sc->loss;
 }
 
+// ------------------------------------------------------------------- boosting, one launch per level
+//
+// With the few thousand pairs a search measures, a level is too little work for three launches (histograms, splits, moving
+// the pairs: 7.3 + 5.6 + 4.9 us at depth 6 with 1536 pairs).  Here a level is one: a block takes one feature and up to
+// sixteen nodes, first settles the level before -- reads the features' best splits of every node and works out
+// where each pair stands now, the same in every block, block (0, 0) writing it down -- then builds its histograms in LDS
+// and finds its best splits.  At level 0 the level before is the last one of the tree before: the pairs get their leaf's
+// value, from the split's left and right sums, and their new derivatives.  So a round of depth d takes d launches.
+// Every sum is an integer sum and every decision the one the three-launch path takes, so the trees are the same bits.
+
+// The pairs' counts are not needed: h = 2 / y is at least 2 for every valid label, so a side is empty exactly when its
+// sum of h is zero (and with an invalid label nothing splits).
+
+constexpr int LEVEL_THREADS = 1024;
+constexpr int LEVEL_SLOTS = 16;         // histograms of a block: one feature of up to sixteen nodes, a wavefront each
+constexpr int LEVEL_STRIDE = BINS + 1;  // cells from one histogram to the next: equal bins of neighbours in different banks
+constexpr int LEVEL_UNROLL = 4;         // pairs of a thread under way together
+
+struct SplitRecord { // the best split of one node on one feature
+    double gain;
+    uint32_t rank, pad;
+};
+
+struct SideSums {
+    long long g, h;
+};
+
+struct NodeTotals {
+    SideSums all;
+    SideSums odd; // the pairs whose feature 0 is not below +inf: they go right at a node that does not split
+};
+
+struct LevelArgs {
+    const uint8_t *bins; // [n_feat + 1][n]: the last row is 1 where feature 0 is not below +inf
+    uint32_t n;
+    int n_feat, depth;
+    const SplitRecord *rec_in; // of the level before: [nodes][n_feat]
+    const SideSums *left_in;   // ... the sums of those splits' left sides
+    const NodeTotals *tot_in;  // ... [nodes]
+    SplitRecord *rec_out;
+    SideSums *left_out;
+    NodeTotals *tot_out;
+    const uint8_t *at_in; // node within the level before, one byte per pair (not read when that level has one node)
+    uint8_t *at_out;
+    const float *p_in, *y;
+    float *p_out;
+    long long *gq, *hq;
+    uint8_t *nf; // the nodes of the level before, and (level 0) the leaves of the tree before
+    float *nt, *leaf;
+    double eta, lam;
+    const BoostScalars *sc;
+};
+
+struct Settled {
+    uint16_t feat[128]; // of every node of the level before: a pair goes left when its bin of feat is at most bin
+    uint16_t bin[128];
+    float leaf[256];
+};
+
+// The level before (`level_before`, the last one of a tree when `leaves` is set): the test of every node, and its leaves
+__device__ __forceinline__ void settle_level(const LevelArgs &a, int level_before, bool leaves, bool write, Settled &s)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+    const bool bad = a.sc->bad != 0;
+    for (int node = wave; node < 1 << level_before; node += waves) {
+        const SplitRecord *mine = a.rec_in + (uint64_t)node * a.n_feat;
+        double best = 0.0;
+        uint32_t best_rank = 0xFFFFFFFFu;
+        for (int f = lane; f < a.n_feat; f += 64) {
+            const SplitRecord o = mine[f];
+            if (better_split(o.gain, o.rank, best, best_rank)) {
+                best = o.gain;
+                best_rank = o.rank;
+            }
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            const double og = __shfl_xor(best, off);
+            const uint32_t orank = __shfl_xor(best_rank, off);
+            if (better_split(og, orank, best, best_rank)) {
+                best = og;
+                best_rank = orank;
+            }
+        }
+        if (lane) continue;
+        const bool split = !bad && best_rank != 0xFFFFFFFFu && best > 0.0;
+        s.feat[node] = (uint16_t)(split ? best_rank / BINS : a.n_feat);
+        s.bin[node] = (uint16_t)(split ? best_rank % BINS : 0);
+        if (write) {
+            a.nf[node] = (uint8_t)(split ? best_rank / BINS : 0);
+            a.nt[node] = split ? (float)((best_rank % BINS) + 1) * 0.25f : __builtin_inff();
+        }
+        if (leaves) {
+            const NodeTotals t = a.tot_in[node];
+            SideSums side[2];
+            side[0] = split ? a.left_in[(uint64_t)node * a.n_feat + best_rank / BINS] : SideSums{t.all.g - t.odd.g, t.all.h - t.odd.h};
+            side[1] = SideSums{t.all.g - side[0].g, t.all.h - side[0].h};
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const float v = side[k].h && !bad ? (float)(-a.eta * (double)side[k].g / ((double)side[k].h + a.lam)) : 0.0f;
+                s.leaf[2 * node + k] = v;
+                if (write) a.leaf[2 * node + k] = v;
+            }
+        }
+    }
+}
+
+// where pair i goes from node j of the level before
+__device__ __forceinline__ uint32_t child_of(const LevelArgs &a, const Settled &s, uint32_t j, uint32_t i)
+{
+    return 2 * j + (a.bins[(uint64_t)s.feat[j] * a.n + i] <= s.bin[j] ? 0u : 1u);
+}
+
+// first_tree: level 0 of the call's first tree, nothing to settle
+template <bool ROOT>
+__global__ __launch_bounds__(LEVEL_THREADS) void tree_level_kernel(LevelArgs a, int level, int first_tree)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char level_lds[];
+    constexpr int CELLS = LEVEL_SLOTS * LEVEL_STRIDE;
+    unsigned long long *hg = reinterpret_cast<unsigned long long *>(level_lds); // [LEVEL_SLOTS][LEVEL_STRIDE]
+    unsigned long long *hh = hg + CELLS;
+    __shared__ Settled settled;
+    __shared__ unsigned long long odd_g[LEVEL_SLOTS], odd_h[LEVEL_SLOTS];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int f = blockIdx.x, node0 = blockIdx.y * LEVEL_SLOTS;
+    const int in_group = min(LEVEL_SLOTS, (1 << level) - node0);
+    // Copies of each histogram while the level has few nodes, neighbouring lanes to different ones: features take few
+    // values, and atomics of a wavefront on one cell go one after the other.
+    const int copies = LEVEL_SLOTS / in_group; // (a power of two, like in_group)
+    const bool write = blockIdx.x == 0 && blockIdx.y == 0;
+    {
+        uint4 *z = reinterpret_cast<uint4 *>(level_lds);
+        for (int e = tid; e < CELLS * 16 / 16; e += LEVEL_THREADS) z[e] = make_uint4(0, 0, 0, 0);
+        if (tid < LEVEL_SLOTS) odd_g[tid] = odd_h[tid] = 0;
+    }
+    const int level_before = ROOT ? a.depth - 1 : level - 1;
+    const bool settles = !ROOT || !first_tree;
+    const bool placed = settles && level_before > 0; // the level before had several nodes: at_in says which
+    if (settles) settle_level(a, level_before, ROOT, write, settled);
+    __syncthreads();
+    for (uint32_t base = tid; base < a.n; base += LEVEL_UNROLL * LEVEL_THREADS) {
+        uint32_t i[LEVEL_UNROLL], r[LEVEL_UNROLL];
+        long long g[LEVEL_UNROLL], h[LEVEL_UNROLL];
+        uint8_t b[LEVEL_UNROLL], odd[LEVEL_UNROLL];
+#pragma unroll
+        for (int u = 0; u < LEVEL_UNROLL; ++u) {
+            i[u] = min(base + u * LEVEL_THREADS, a.n - 1); // (past the end the last pair again, not counted)
+            b[u] = a.bins[(uint64_t)f * a.n + i[u]];
+            odd[u] = f == 0 ? a.bins[(uint64_t)a.n_feat * a.n + i[u]] : (uint8_t)0;
+            r[u] = placed ? a.at_in[i[u]] : 0;
+        }
+        if (ROOT) {
+            float p[LEVEL_UNROLL], y[LEVEL_UNROLL];
+#pragma unroll
+            for (int u = 0; u < LEVEL_UNROLL; ++u) {
+                p[u] = a.p_in[i[u]];
+                y[u] = a.y[i[u]];
+            }
+#pragma unroll
+            for (int u = 0; u < LEVEL_UNROLL; ++u) {
+                if (settles) p[u] = p[u] + settled.leaf[child_of(a, settled, r[u], i[u])];
+                const double yi = (double)y[u], d = (double)p[u] - yi;
+                g[u] = quantise(2.0 * d / yi);
+                h[u] = quantise(2.0 / yi);
+                r[u] = 0;
+                if (write) {
+                    a.p_out[i[u]] = p[u];
+                    a.gq[i[u]] = g[u];
+                    a.hq[i[u]] = h[u];
+                }
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < LEVEL_UNROLL; ++u) {
+                g[u] = a.gq[i[u]];
+                h[u] = a.hq[i[u]];
+                r[u] = child_of(a, settled, r[u], i[u]);
+                if (write) a.at_out[i[u]] = (uint8_t)r[u];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < LEVEL_UNROLL; ++u) {
+            const uint32_t rr = r[u] - (uint32_t)node0; // wraps for nodes below the group
+            if (rr >= (uint32_t)in_group || base + u * LEVEL_THREADS >= a.n) continue;
+            const uint32_t cell = (rr * copies + (lane & (copies - 1))) * LEVEL_STRIDE + b[u];
+            atomicAdd(&hg[cell], (unsigned long long)g[u]);
+            atomicAdd(&hh[cell], (unsigned long long)h[u]);
+            if (odd[u]) {
+                atomicAdd(&odd_g[rr], (unsigned long long)g[u]);
+                atomicAdd(&odd_h[rr], (unsigned long long)h[u]);
+            }
+        }
+    }
+    __syncthreads();
+    if (copies > 1) { // into the first copy
+        for (int e = tid; e < in_group * 2 * BINS; e += LEVEL_THREADS) {
+            const int node = e / (2 * BINS), bin = e % BINS;
+            unsigned long long *cell = (e / BINS % 2 ? hh : hg) + node * copies * LEVEL_STRIDE + bin;
+            unsigned long long sum = cell[0];
+            for (int k = 1; k < copies; ++k) sum += cell[k * LEVEL_STRIDE];
+            cell[0] = sum;
+        }
+        __syncthreads();
+    }
+    // a wavefront per node, 64 bins at a time; gains and ties as in tree_split_kernel.  An empty bin splits like the bin
+    // before it, which has the lower rank, so only bins with pairs are evaluated, and stretches without any are skipped.
+    if (wave >= in_group) return;
+    long long g[4], h[4];
+    SideSums total = {0, 0};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int cell = wave * copies * LEVEL_STRIDE + 64 * q + lane;
+        g[q] = (long long)hg[cell];
+        h[q] = (long long)hh[cell];
+        total.g += g[q];
+        total.h += h[q];
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        total.g += __shfl_xor(total.g, off);
+        total.h += __shfl_xor(total.h, off);
+    }
+    double best = 0.0;
+    uint32_t best_rank = 0xFFFFFFFFu;
+    SideSums best_left = {0, 0}, before = {0, 0};
+    const double parent = (double)total.g * (double)total.g / ((double)total.h + a.lam);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        if (!__any(h[q] != 0)) continue;
+        long long pg = g[q], ph = h[q];
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const long long ug = __shfl_up(pg, off), uh = __shfl_up(ph, off);
+            if (lane >= off) {
+                pg += ug;
+                ph += uh;
+            }
+        }
+        const SideSums left = {before.g + pg, before.h + ph};
+        before.g += __shfl(pg, 63);
+        before.h += __shfl(ph, 63);
+        const int bin = 64 * q + lane;
+        if (h[q] == 0 || bin >= 255 || left.h == total.h) continue;
+        const SideSums right = {total.g - left.g, total.h - left.h};
+        const double gain = (double)left.g * (double)left.g / ((double)left.h + a.lam) +
+                            (double)right.g * (double)right.g / ((double)right.h + a.lam) - parent;
+        const uint32_t rank = (uint32_t)f * BINS + (uint32_t)bin;
+        if (gain > best || (gain == best && gain > 0.0 && rank < best_rank)) {
+            best = gain;
+            best_rank = rank;
+            best_left = left;
+        }
+    }
+    const uint32_t own_rank = best_rank;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        const double og = __shfl_xor(best, off);
+        const uint32_t orank = __shfl_xor(best_rank, off);
+        if (better_split(og, orank, best, best_rank)) {
+            best = og;
+            best_rank = orank;
+        }
+    }
+    const uint64_t at = (uint64_t)(node0 + wave) * a.n_feat + f;
+    if (best_rank != 0xFFFFFFFFu && own_rank == best_rank) a.left_out[at] = best_left; // (ranks are distinct: one lane)
+    if (lane == 0) {
+        a.rec_out[at] = SplitRecord{best, best_rank, 0};
+        if (f == 0) a.tot_out[node0 + wave] = NodeTotals{total, {(long long)odd_g[wave], (long long)odd_h[wave]}};
+    }
+}
+
+// one block: the last tree's last level, the pairs' final predictions, the mean Eq.-(1) loss, and the call's results
+__global__ __launch_bounds__(1024) void tree_last_kernel(LevelArgs a, int any_tree, BoostScalars *sc, float *snr_out, float *loss_out)
+{
+    __shared__ Settled settled;
+    __shared__ double scratch[1024];
+    if (any_tree) settle_level(a, a.depth - 1, true, true, settled);
+    __syncthreads();
+    double sum = 0.0;
+    for (uint32_t i = threadIdx.x; i < a.n; i += 1024) {
+        float p = a.p_in[i];
+        if (any_tree) p = p + settled.leaf[child_of(a, settled, a.depth > 1 ? a.at_in[i] : 0u, i)];
+        const double yi = a.y[i], d = (double)p - yi;
+        sum += d * d / yi;
+    }
+    sum = block_sum_f64(sum, scratch);
+    if (threadIdx.x == 0) {
+        *snr_out = sc->snr;
+        *loss_out = sc->bad ? sc->loss : (float)(sum / (double)a.n);
+    }
+}
+
+// Most pairs the one-launch levels take: every block goes over all of them, which the split of the pairs over blocks in
+// the three-launch path overtakes in the end.  us per call of eight rounds at depth 6 with 64 features, one launch per
+// level against three: 512 pairs 434 / 774, 4096 534 / 968, 16384 916 / 1246, 65536 2404 / 2805 (depth 3, 32 features,
+// 32768 pairs: 704 / 781).
+constexpr uint64_t LEVEL_MAX_PAIRS = 65536;
+
 struct BoostWs {
     uint64_t scalars, y, p, gq, hq, at, bins, hist, partial, total;
+    uint64_t p2, at2, rec, left, tot; // one launch per level: second halves of ping-pong pairs, the two levels' records
 };
 
 BoostWs boost_layout(const eck_trees *m, uint64_t n_pairs)
 {
     auto up = [](uint64_t v) { return (v + 255) & ~255ull; };
-    BoostWs w;
+    const uint64_t nodes = (uint64_t)1 << (m->depth - 1); // of the last level
+    BoostWs w = {};
     uint64_t o = 0;
     w.scalars = o; o = up(o + sizeof(BoostScalars));
     w.y = o; o = up(o + n_pairs * 4);
     w.p = o; o = up(o + n_pairs * 4);
     w.gq = o; o = up(o + n_pairs * 8);
     w.hq = o; o = up(o + n_pairs * 8);
-    w.at = o; o = up(o + n_pairs * 4);
-    w.bins = o; o = up(o + n_pairs * (uint64_t)m->n_feat);
-    w.hist = o; o = up(o + ((uint64_t)1 << (m->depth - 1)) * m->n_feat * BINS * 3 * 8);
-    w.partial = o; o = up(o + ((uint64_t)1 << (m->depth - 1)) * ((m->n_feat + SPLIT_FEATS - 1) / SPLIT_FEATS) * sizeof(SplitPartial));
+    w.bins = o; o = up(o + n_pairs * (uint64_t)(m->n_feat + 1));
+    if (n_pairs <= LEVEL_MAX_PAIRS) {
+        w.p2 = o; o = up(o + n_pairs * 4);
+        w.at = o; o = up(o + n_pairs);
+        w.at2 = o; o = up(o + n_pairs);
+        w.rec = o; o = up(o + 2 * nodes * m->n_feat * sizeof(SplitRecord));
+        w.left = o; o = up(o + 2 * nodes * m->n_feat * sizeof(SideSums));
+        w.tot = o; o = up(o + 2 * nodes * sizeof(NodeTotals));
+    } else {
+        w.at = o; o = up(o + n_pairs * 4);
+        w.hist = o; o = up(o + nodes * m->n_feat * BINS * 3 * 8);
+        w.partial = o; o = up(o + nodes * ((m->n_feat + SPLIT_FEATS - 1) / SPLIT_FEATS) * sizeof(SplitPartial));
+        // a workspace made for many pairs serves fewer, too
+        const uint64_t fewer = boost_layout(m, LEVEL_MAX_PAIRS).total;
+        if (o < fewer) o = fewer;
+    }
     w.total = o;
     return w;
+}
+
+// the boosting rounds of treemodel_update, one launch per level
+int32_t boost_levels(eck_trees *m, char *base, const BoostWs &w, uint64_t n_pairs, int32_t n_rounds, float eta, double lam,
+                     float *snr_out, float *loss_out, hipStream_t st)
+{
+    const size_t nodes = ((size_t)1 << m->depth) - 1, leaves = (size_t)1 << m->depth, last_nodes = (size_t)1 << (m->depth - 1);
+    BoostScalars *sc = reinterpret_cast<BoostScalars *>(base + w.scalars);
+    LevelArgs a = {};
+    a.bins = reinterpret_cast<const uint8_t *>(base + w.bins);
+    a.n = (uint32_t)n_pairs;
+    a.n_feat = m->n_feat;
+    a.depth = m->depth;
+    a.y = reinterpret_cast<const float *>(base + w.y);
+    a.gq = reinterpret_cast<long long *>(base + w.gq);
+    a.hq = reinterpret_cast<long long *>(base + w.hq);
+    a.eta = (double)eta;
+    a.lam = lam;
+    a.sc = sc;
+    SplitRecord *rec[2];
+    SideSums *left[2];
+    NodeTotals *tot[2];
+    uint8_t *at[2] = {reinterpret_cast<uint8_t *>(base + w.at), reinterpret_cast<uint8_t *>(base + w.at2)};
+    float *p[2] = {reinterpret_cast<float *>(base + w.p), reinterpret_cast<float *>(base + w.p2)};
+    for (int k = 0; k < 2; ++k) {
+        rec[k] = reinterpret_cast<SplitRecord *>(base + w.rec) + k * last_nodes * a.n_feat;
+        left[k] = reinterpret_cast<SideSums *>(base + w.left) + k * last_nodes * a.n_feat;
+        tot[k] = reinterpret_cast<NodeTotals *>(base + w.tot) + k * last_nodes;
+    }
+    constexpr size_t LDS = (size_t)LEVEL_SLOTS * LEVEL_STRIDE * 16;
+    ECK_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(tree_level_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS));
+    ECK_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(tree_level_kernel<false>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS));
+    int side = 0, p_side = 0; // which half of each pair holds the level before / the predictions
+    // what a launch settles: level `before` of tree t (its nodes, and its leaves when that was the last level)
+    auto settle = [&](size_t t, int before) {
+        a.nf = m->d_feat + t * nodes + (((size_t)1 << before) - 1);
+        a.nt = m->d_thr + t * nodes + (((size_t)1 << before) - 1);
+        a.leaf = m->d_leaf + t * leaves;
+        a.rec_in = rec[side];
+        a.left_in = left[side];
+        a.tot_in = tot[side];
+        a.at_in = at[side];
+    };
+    for (int32_t r = 0; r < n_rounds; ++r) {
+        const size_t t = (size_t)m->n_trees + r;
+        for (int l = 0; l < m->depth; ++l) {
+            if (l > 0) settle(t, l - 1);
+            else if (r > 0) settle(t - 1, m->depth - 1);
+            a.rec_out = rec[side ^ 1];
+            a.left_out = left[side ^ 1];
+            a.tot_out = tot[side ^ 1];
+            a.at_out = at[side ^ 1];
+            const dim3 grid((unsigned)m->n_feat, (unsigned)(((1 << l) + LEVEL_SLOTS - 1) / LEVEL_SLOTS));
+            if (l == 0) {
+                a.p_in = p[p_side];
+                a.p_out = p[p_side ^ 1];
+                hipLaunchKernelGGL(tree_level_kernel<true>, grid, dim3(LEVEL_THREADS), LDS, st, a, l, r == 0 ? 1 : 0);
+                p_side ^= 1;
+            } else {
+                hipLaunchKernelGGL(tree_level_kernel<false>, grid, dim3(LEVEL_THREADS), LDS, st, a, l, 0);
+            }
+            side ^= 1;
+        }
+    }
+    if (n_rounds > 0) settle((size_t)m->n_trees + n_rounds - 1, m->depth - 1);
+    a.p_in = p[p_side];
+    hipLaunchKernelGGL(tree_last_kernel, dim3(1), dim3(1024), 0, st, a, n_rounds > 0 ? 1 : 0, sc, snr_out, loss_out);
+    ECK_HIP_TRY(hipGetLastError());
+    return ECK_OK;
 }
 
 } // namespace
@@ -723,6 +1107,11 @@ extern "C" int32_t treemodel_update(eck_trees *m, const void *feat, int32_t feat
     hipLaunchKernelGGL(tree_quality_kernel, dim3(1), dim3(1024), 0, st, p, y, n_pairs, 0, sc);
     hipLaunchKernelGGL(tree_bins_kernel, dim3(pair_blocks, m->n_feat), dim3(256), 0, st, feat, is_bf16, ld, n_pairs,
                        m->n_feat, bins);
+    if (n_pairs <= LEVEL_MAX_PAIRS) {
+        rc = boost_levels(m, base, w, n_pairs, n_rounds, eta, lam, snr_out, loss_out, st);
+        if (rc == ECK_OK) m->n_trees += n_rounds;
+        return rc;
+    }
     {
         // the histogram buffer starts clear; from then on the split kernel clears what it reads
         const uint64_t words = ((uint64_t)1 << (m->depth - 1)) * m->n_feat * BINS * 3;

@@ -192,6 +192,39 @@ def test_boosting_appends_the_oracles_trees(G, n_pairs, depth, rounds, bf16):
     assert np.isfinite(loss_g) and loss_g > 0
 
 
+@pytest.mark.parametrize("n_pairs,n_feat,depth,rounds", [(1, 3, 1, 3), (2, 1, 2, 2), (3, 70, 5, 3), (1023, 5, 6, 3), (1025, 64, 1, 4),
+                                                        (4096, 17, 8, 2), (4097, 130, 3, 2), (20000, 4, 7, 2),
+                                                        (65536, 3, 2, 2), (65537, 3, 2, 2)])
+def test_boosting_on_any_features(G, n_pairs, n_feat, depth, rounds):
+    """few and many pairs, on both sides of the number where a level becomes three launches; one to 130 features, deep
+    and flat trees; features with few distinct values, constant ones, negative, huge, infinite and NaN values; energies
+    over twelve orders of magnitude (clamped derivatives); no regularisation.  Trees are the oracle's, bit for bit, also
+    in a workspace made for more pairs."""
+    rng = np.random.default_rng(n_pairs + n_feat)
+    ld = n_pairs + (n_pairs & 1) + 2
+    x = (rng.standard_normal((n_feat, ld)) * 3 + 8).astype(np.float32)
+    x[::3] = np.round(x[::3])
+    x[1::5] = 7.25
+    odd = rng.random(x.shape) < 0.02
+    x[odd] = rng.choice(np.array([np.nan, np.inf, -np.inf, -1.0, -0.0, 63.75, 64.0, 1e30], dtype=np.float32), int(odd.sum()))
+    e = np.exp(rng.standard_normal(n_pairs) * (4.0 if n_pairs % 2 else 0.3)).astype(np.float32)
+    eta, lam, base = float(np.float32(0.3)), 0.0, float(np.float32(0.5))
+    nf, nt, lf = _empty(depth, rounds)
+    snr_o, loss_o = oracle.trees_boost(n_feat, depth, nf, nt, lf, 0, rounds, base, x, e, eta=eta, lam=lam)
+    for more in (0, 100000):
+        trees = eck.Trees(n_feat, depth, rounds, base)
+        snr = torch.zeros(1, dtype=torch.float32, device="cuda")
+        loss = torch.zeros(1, dtype=torch.float32, device="cuda")
+        ws = torch.full((eck.treemodel_update_workspace_bytes(trees, n_pairs + more),), 255, dtype=torch.uint8, device="cuda")
+        eck.treemodel_update(trees, G.to_dev(x), torch.from_numpy(e).cuda(), rounds, snr, loss, ws, eta=eta, lam=lam)
+        torch.cuda.synchronize()
+        a, b, c = (t.cpu().numpy() for t in trees.get())
+        assert np.array_equal(a, nf), "split features differ"
+        assert np.array_equal(b, nt), "thresholds differ"
+        assert np.array_equal(c.view(np.uint32), lf.view(np.uint32)), "leaf values differ"
+        assert abs(snr.item() - snr_o) <= 1e-6 * snr_o and abs(loss.item() - loss_o) <= 1e-6 * loss_o
+
+
 def test_boosting_in_two_calls_equals_one_call_and_improves_the_fit(G):
     f32, b16, e = _pairs(4096)
     eta, lam, base = float(np.float32(0.3)), float(np.float32(1.0)), float(np.float32(0.5))
