@@ -6,9 +6,9 @@
 // "x[feature_j] < threshold_j"; true -> node 2j+1, false (also NaN) -> node 2j+2; after d tests the walk stands
 // on node (2^d - 1) + leaf.  A node that does not split has threshold +inf.
 //
-// Scoring: one candidate per lane.  A block stages the features of 256 candidates and a chunk of trees in LDS
+// Scoring: one candidate per lane.  A block stages the features of its candidates and a chunk of trees in LDS
 // and walks eight trees at a time per lane (eight independent chains of dependent LDS reads); leaf values are
-// added in fp32 in tree order, so the result does not depend on how trees are chunked or interleaved.
+// added in fp32 in tree order, so the result does not depend on how trees are chunked, shared or interleaved.
 //
 // Boosting: gradient statistics are rounded to integers of resolution 2^-20 and summed with integer atomics,
 // so every histogram, and with it every split decision, is independent of the order of execution; gains are
@@ -26,6 +26,7 @@ struct eck_trees {
     uint8_t *d_feat = nullptr; // [capacity][2^d - 1]
     float *d_thr = nullptr;    // [capacity][2^d - 1]
     float *d_leaf = nullptr;   // [capacity][2^d]
+    uint32_t *d_word = nullptr; // [capacity][2^d] the nodes as the scoring kernel reads them for bfloat16 features, from 1 on
     int device = -1;
 };
 
@@ -44,89 +45,228 @@ __device__ __forceinline__ float feature_value(const void *feat, int is_bf16, ui
 
 // ------------------------------------------------------------------------------------------------ scoring
 
-// LDS per tree of a chunk: nodes as (threshold bits, feature) pairs, then the leaves
-__host__ __device__ inline uint32_t tree_lds_bytes(int depth) { return ((1u << depth) - 1u) * 8u + (1u << depth) * 4u; }
+// A node as it sits in LDS.  With fp32 features: the threshold's bits and the byte offset of the feature's row.  With
+// bfloat16 features one word, which halves the node reads and puts the nodes of a tree of depth six in different banks:
+// the feature's number plus one in the lower half, and above it sixteen bits chosen such that the word, read as a float,
+// is a threshold of the same comparison: for every bfloat16 x (infinities, both zeros and NaN included)
+//   x < t  <=>  x < word.
+// The lower half is never zero, so a positive word lies strictly between two neighbouring bfloat16 values, above the one
+// in its upper half, and a negative one below it; hence the largest bfloat16 below a positive t, and the truncation of a
+// negative one; +inf becomes the largest finite value (all but +inf and NaN are below the word), a zero of either sign
+// becomes -0 (the negative values, denormals too, are below it), and -inf and NaN give a negative NaN (nothing is;
+// x minus it is a positive one: the subtraction negates its second operand).
+__device__ __forceinline__ uint32_t bf16_node(float t, uint32_t feature)
+{
+    const uint32_t u = __float_as_uint(t);
+    uint32_t upper;
+    if (t != t || u == 0xFF800000u) upper = 0xFF80u;
+    else if ((u << 1) == 0) upper = 0x8000u;
+    else if (u >> 31) upper = u >> 16;
+    else upper = (u - 1) >> 16; // the largest bfloat16 below t: truncation unless t is one itself
+    return upper << 16 | (feature + 1);
+}
 
-// SCORE_BLOCK: candidates, and threads, per block
-template <bool FEAT_BF16, int SCORE_BLOCK>
-__global__ __launch_bounds__(SCORE_BLOCK) void tree_score_kernel(const uint8_t *__restrict__ node_feat,
+__host__ __device__ inline uint32_t tree_lds_bytes(int depth, bool feat_bf16)
+{
+    return (feat_bf16 ? (1u << depth) * 4u : ((1u << depth) - 1u) * 8u) + (1u << depth) * 4u;
+}
+
+// The scoring kernel's numbering for bfloat16 features: children of i are 2i + 1 when x < t and 2i when not, the other
+// way round than the arrays', so that the sign of x - t is the step.  Node i (numbered from 1) of the arrays sits at
+__device__ __forceinline__ uint32_t mirrored(uint32_t i) { return i ? (3u << (31 - __clz((int)i))) - 1u - i : 0u; }
+
+// An ensemble handed over: the arrays, and the words of its nodes (one launch instead of a copy per array).  Also, with the
+// arrays in place already, just the words.
+__global__ void tree_set_kernel(const uint8_t *nf, const float *nt, const float *leaf, int n_feat, int depth, int n_trees,
+                                uint8_t *nf_out, float *nt_out, float *leaf_out, uint32_t *words)
+{
+    const uint32_t nodes = (1u << depth) - 1u, e = blockIdx.x * blockDim.x + threadIdx.x, t = e >> depth, i = e & nodes;
+    if (t >= (uint32_t)n_trees) return;
+    const uint64_t from = (uint64_t)t * nodes + (i ? i - 1 : 0); // word 0 is not read
+    const uint8_t f = nf[from];
+    const float thr = nt[from];
+    words[(t << depth) + mirrored(i)] = bf16_node(thr, min((uint32_t)f, (uint32_t)n_feat - 1u));
+    if (nf_out && i) {
+        nf_out[from] = f;
+        nt_out[from] = thr;
+    }
+    if (leaf_out) leaf_out[e] = leaf[e];
+}
+
+// C candidates per block, its trees shared between S groups of C threads.
+//   S == 1: every thread walks all trees of its candidate.  bfloat16 features stay that: a wavefront takes every second
+//     of 128 candidates, so that its lanes read different words, hence banks, of whatever rows they are at.
+//   S > 1, for few candidates: group s walks every S-th set of eight trees, the leaves meet in LDS and the first group
+//     adds them up.  Features are kept as floats.
+// What bounds it: vector instructions, then the two dependent LDS reads of a visit (node, feature value).  A visit takes
+// four: the node's address, the feature value's (mask and join), the difference to the threshold, and the step, which
+// shifts the difference's sign into the node's number.  Measured, 100 trees of depth 6 on 2^20 candidates: 140 us (two
+// thirds of the cycles issue vector instructions, two fifths move LDS data; no bank conflicts); with eight-byte nodes, a
+// compare into a mask and an add with carry 156 us.  Without effect: more wavefronts (trees shared by two groups over
+// 256 or 384 candidates, 158-165 us), the first two levels' nodes through the scalar cache; nodes gathered from the L1
+// instead of the LDS: 184 us for a quarter of them.
+template <bool FEAT_BF16, int C, int S>
+__global__ __launch_bounds__(C *S) void tree_score_kernel(const uint8_t *__restrict__ node_feat,
                                                           const float *__restrict__ node_thr,
-                                                          const float *__restrict__ leaf, int n_feat, int depth,
+                                                          const float *__restrict__ leaf,
+                                                          const uint32_t *__restrict__ words, int n_feat, int depth,
                                                           int n_trees, int chunk_trees, float base,
                                                           const void *__restrict__ feat, uint64_t ld, uint64_t n,
-                                                          float *__restrict__ out, uint32_t n_tiles)
+                                                          float *__restrict__ out, uint32_t n_tiles, int wide_loads)
 {
-    using Elem = typename std::conditional<FEAT_BF16, uint16_t, float>::type;
+    constexpr int T = C * S;
+    constexpr bool HALF = FEAT_BF16 && S == 1;
+    using Elem = typename std::conditional<FEAT_BF16, uint16_t, float>::type; // in memory
+    using Cell = typename std::conditional<HALF, uint16_t, float>::type;      // in LDS
+    using Node = typename std::conditional<FEAT_BF16, uint32_t, uint2>::type;
+    constexpr uint32_t ROW = C * sizeof(Cell); // bytes from one feature's row to the next
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const uint32_t nodes = (1u << depth) - 1u, leaves = 1u << depth;
-    Elem *x_lds = reinterpret_cast<Elem *>(lds); // [n_feat][SCORE_BLOCK]
-    uint2 *node_lds = reinterpret_cast<uint2 *>(lds + (size_t)n_feat * SCORE_BLOCK * sizeof(Elem)); // [chunk][nodes]
-    float *leaf_lds = reinterpret_cast<float *>(node_lds + (size_t)chunk_trees * nodes);      // [chunk][leaves]
-    const int tid = threadIdx.x;
+    // Nodes from one tree to the next in LDS.  With bfloat16 features a tree's leaves follow its words, so that after the
+    // last level i is the leaf's place, too.
+    const uint32_t stride = FEAT_BF16 ? 2 * leaves : nodes;
+    Cell *x_lds = reinterpret_cast<Cell *>(lds);                                   // [n_feat][C]
+    Node *node_lds = reinterpret_cast<Node *>(lds + (size_t)n_feat * ROW);         // [chunk][nodes]
+    float *leaf_lds = reinterpret_cast<float *>(node_lds + (size_t)chunk_trees * stride); // fp32: [chunk][leaves]
+    float *val_lds = leaf_lds + (FEAT_BF16 ? 0 : (size_t)chunk_trees * leaves);    // S > 1: [chunk][C] leaves reached
+    const int tid = threadIdx.x, within = tid % C, slot = tid / C;
+    // this thread's candidate in the tile
+    const int mine = HALF ? 2 * ((within >> 7) * 64 + (within & 63)) + ((within >> 6) & 1) : within;
     // where the dynamic LDS starts within the workgroup's allocation (the hand-written loads below take raw LDS
     // addresses)
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds;
+    const uint32_t lane_at = lds_base + (uint32_t)mine * sizeof(Cell); // of this candidate in row 0
+    // HALF: where a word's feature value is: the row's offset bits of the word, joined by the lane's place (the LDS holds
+    // nothing but the dynamic part, which starts at zero), in one instruction; else the row's number times ROW plus that
+    constexpr uint32_t ROW_BITS = 0xFFFFu & ~(ROW - 1u);
+    auto place_of = [&](uint32_t word) {
+        uint32_t at;
+        if constexpr (HALF) asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(at) : "v"(word), "s"(ROW_BITS), "v"(lane_at));
+        else asm("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(at) : "v"(word), "s"(ROW), "v"(lane_at - ROW));
+        return at;
+    };
     const Elem *feat_e = reinterpret_cast<const Elem *>(feat);
+    auto cell_of = [](Elem v) {
+        if constexpr (FEAT_BF16 && !HALF) return __uint_as_float((uint32_t)v << 16);
+        else return (Cell)v;
+    };
+
+    uint32_t upper[WALKS]; // HALF: feature values as they arrive, in the upper halves
+#pragma unroll
+    for (int w = 0; w < WALKS; ++w) upper[w] = 0;
 
     for (uint32_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-        const uint64_t cand = (uint64_t)tile * SCORE_BLOCK + tid;
+        const uint64_t first_cand = (uint64_t)tile * C;
         __syncthreads(); // the previous tile's walks are over
-        // Sixteen rows at a time, every load and store unconditional (a lane beyond n re-reads the last candidate,
-        // a row beyond n_feat the last row, and stores that same value where it already is): with a condition on
-        // either side the compiler waits for each load right before its store, one round trip per feature.
-        {
-            const uint64_t col = cand < n ? cand : n - 1;
-            for (int f0 = 0; f0 < n_feat; f0 += 16) {
+        if (wide_loads && first_cand + C <= n) {
+            // sixteen bytes of a row per load; eight loads of a thread under way together
+            constexpr int PER = 16 / sizeof(Elem), LOADS = C / PER; // elements per load, loads per row
+            typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
+            for (int e0 = 0; e0 < n_feat * LOADS; e0 += 8 * T) {
+                u32x4 v[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    const int e = min(e0 + k * T + tid, n_feat * LOADS - 1);
+                    v[k] = *reinterpret_cast<const u32x4 *>(feat_e + (uint64_t)(e / LOADS) * ld + first_cand + (e % LOADS) * PER);
+                }
+#pragma unroll
+                for (int k = 0; k < 8; ++k) { // (past the end: the last piece again, where it already is)
+                    const int e = min(e0 + k * T + tid, n_feat * LOADS - 1);
+                    Cell *to = x_lds + e * PER;
+                    if constexpr (sizeof(Cell) == sizeof(Elem)) {
+                        *reinterpret_cast<uint4 *>(to) = make_uint4(v[k][0], v[k][1], v[k][2], v[k][3]);
+                    } else {
+                        float4 *f = reinterpret_cast<float4 *>(to);
+                        f[0] = make_float4(__uint_as_float(v[k][0] << 16), __uint_as_float(v[k][0] & 0xFFFF0000u),
+                                           __uint_as_float(v[k][1] << 16), __uint_as_float(v[k][1] & 0xFFFF0000u));
+                        f[1] = make_float4(__uint_as_float(v[k][2] << 16), __uint_as_float(v[k][2] & 0xFFFF0000u),
+                                           __uint_as_float(v[k][3] << 16), __uint_as_float(v[k][3] & 0xFFFF0000u));
+                    }
+                }
+            }
+        } else {
+            // Sixteen rows at a time, every load and store unconditional (a lane beyond n re-reads the last candidate,
+            // a row beyond n_feat the last row, and stores that same value where it already is): with a condition on
+            // either side the compiler waits for each load right before its store, one round trip per feature.
+            const uint64_t col = first_cand + within < n ? first_cand + within : n - 1;
+            for (int f0 = slot * 16; f0 < n_feat; f0 += 16 * S) {
                 Elem v[16];
 #pragma unroll
                 for (int k = 0; k < 16; ++k) v[k] = feat_e[(uint64_t)min(f0 + k, n_feat - 1) * ld + col];
 #pragma unroll
-                for (int k = 0; k < 16; ++k) x_lds[min(f0 + k, n_feat - 1) * SCORE_BLOCK + tid] = v[k];
+                for (int k = 0; k < 16; ++k) x_lds[min(f0 + k, n_feat - 1) * C + within] = cell_of(v[k]);
+            }
+        }
+        if constexpr (HALF) {
+            // A NaN counts as not below any threshold; a negative one would look negative to the walks.  Features hardly
+            // ever hold one, so the block looks at what it staged and rewrites it only when there is one.
+            uint32_t *flag = reinterpret_cast<uint32_t *>(node_lds); // (the trees are staged later)
+            if (tid == 0) *flag = 0;
+            __syncthreads();
+            uint32_t *pairs = reinterpret_cast<uint32_t *>(x_lds);
+            typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+            u16x2 most = {0, 0};
+            for (int e = tid; e < n_feat * (C / 8); e += T) {
+                const uint4 v = reinterpret_cast<const uint4 *>(pairs)[e];
+                const uint32_t q[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                for (int k = 0; k < 4; ++k) most = __builtin_elementwise_max(most, __builtin_bit_cast(u16x2, q[k] & 0x7FFF7FFFu));
+            }
+            if (most[0] > 0x7F80u || most[1] > 0x7F80u) *flag = 1;
+            __syncthreads();
+            if (*flag) {
+                for (int e = tid; e < n_feat * (C / 2); e += T) {
+                    uint32_t v = pairs[e];
+                    if ((v & 0x7FFFu) > 0x7F80u) v &= ~0x8000u;
+                    if ((v & 0x7FFF0000u) > 0x7F800000u) v &= ~0x80000000u;
+                    pairs[e] = v;
+                }
             }
         }
         float acc = base;
         for (int t0 = 0; t0 < n_trees; t0 += chunk_trees) {
             const int in_chunk = min(chunk_trees, n_trees - t0);
+            const int walked = (in_chunk + WALKS - 1) / WALKS * WALKS; // the chunk has room for whole sets of walks
             __syncthreads(); // features staged / previous chunk consumed
-            for (uint32_t e = tid; e < (uint32_t)in_chunk * nodes; e += SCORE_BLOCK) {
-                const uint32_t f = min((uint32_t)node_feat[(uint64_t)t0 * nodes + e], (uint32_t)n_feat - 1u);
-                node_lds[e] = make_uint2(__float_as_uint(node_thr[(uint64_t)t0 * nodes + e]), f * (uint32_t)(SCORE_BLOCK * sizeof(Elem)));
-            }
-            for (uint32_t e = tid; e < (uint32_t)in_chunk * leaves; e += SCORE_BLOCK) leaf_lds[e] = leaf[(uint64_t)t0 * leaves + e];
-            __syncthreads();
-            // feature value from the byte offset of its row (a node's second word)
-            auto x_of = [&](uint32_t row_bytes) {
-                const Elem v = *reinterpret_cast<const Elem *>(lds + row_bytes + tid * sizeof(Elem));
-                if (FEAT_BF16) return __uint_as_float((uint32_t)v << 16);
-                else return (float)v;
-            };
-            // Nodes are numbered from 1 here (children of i: 2i and 2i + 1), so that one step is
-            // i <- i + i + (x < t ? 0 : 1): a compare into a scalar mask and an add with that mask as carry-in,
-            // two vector instructions, written out because the compiler makes three of it.  Four walks per
-            // statement keep the compares four instructions ahead of the adds that read their masks.
-            int t = 0;
-            for (; t + WALKS <= in_chunk; t += WALKS) {
-                uint32_t i[WALKS], upper[WALKS];
-#pragma unroll
-                for (int w = 0; w < WALKS; ++w) {
-                    i[w] = 1;
-                    upper[w] = 0;
+            // (padding up to whole sets of walks: any tree)
+            if constexpr (FEAT_BF16) {
+                for (uint32_t e = tid; e < (uint32_t)walked * leaves; e += T) {
+                    const uint64_t from = (uint64_t)t0 * leaves + min(e, (uint32_t)in_chunk * leaves - 1);
+                    const uint32_t to = (e >> depth) * stride, i = e & nodes;
+                    const float value = leaf[from];
+                    uint32_t word = words[from];
+                    // HALF: the row's byte offset in place of its number; below it, outside the mask, a one that keeps
+                    // the lower half from being zero
+                    if (HALF) word = (word & 0xFFFF0000u) | (((word & 0xFFFFu) - 1u) * ROW + 1u);
+                    node_lds[to + i] = word;
+                    node_lds[to + leaves + (nodes - i)] = __float_as_uint(value); // (mirrored, like the nodes)
                 }
-                const uint2 *first = node_lds + (size_t)t * nodes - 1; // node i of tree w at first[w * nodes + i]
-                for (int l = 0; l < depth; ++l) {
-                    uint2 nd[WALKS];
+            } else {
+                for (uint32_t e = tid; e < (uint32_t)walked * leaves; e += T)
+                    leaf_lds[e] = leaf[(uint64_t)t0 * leaves + min(e, (uint32_t)in_chunk * leaves - 1)];
+                for (uint32_t e = tid; e < (uint32_t)walked * nodes; e += T) {
+                    const uint64_t from = (uint64_t)t0 * nodes + min(e, (uint32_t)in_chunk * nodes - 1);
+                    const uint32_t f = min((uint32_t)node_feat[from], (uint32_t)n_feat - 1u);
+                    node_lds[e] = make_uint2(__float_as_uint(node_thr[from]), f * ROW);
+                }
+            }
+            __syncthreads();
+            // Nodes are numbered from 1 here, children of i: 2i and 2i + 1.
+            for (int t = slot * WALKS; t < walked; t += S * WALKS) {
+                uint32_t i[WALKS];
 #pragma unroll
-                    for (int w = 0; w < WALKS; ++w) nd[w] = first[(size_t)w * nodes + i[w]];
-                    float x[WALKS];
-                    if constexpr (FEAT_BF16 && WALKS == 8) {
+                for (int w = 0; w < WALKS; ++w) i[w] = 1;
+                // node i of tree w at first[w * stride + i]
+                const Node *first = node_lds + (size_t)t * stride - (FEAT_BF16 ? 0 : 1);
+                // feature values at `at`, and one step of every walk
+                auto read_x = [&](const uint32_t(&at)[WALKS], float(&x)[WALKS]) {
+                    if constexpr (HALF) {
+                        static_assert(WALKS == 8, "written out for eight walks");
                         // A bfloat16 is the upper half of the float of the same value.  The load below writes
                         // only the upper half of its destination, whose lower half is zero from the start and
                         // stays so: the float arrives ready, without a shift.  The compiler has no such load, so
                         // it is issued here, followed by its wait; nothing but these two statements touches the
                         // eight registers in between.
-                        uint32_t at[WALKS];
-#pragma unroll
-                        for (int w = 0; w < WALKS; ++w) at[w] = lds_base + nd[w].y + tid * 2;
                         asm volatile("ds_read_u16_d16_hi %0, %8\n\t"
                                      "ds_read_u16_d16_hi %1, %9\n\t"
                                      "ds_read_u16_d16_hi %2, %10\n\t"
@@ -146,70 +286,110 @@ __global__ __launch_bounds__(SCORE_BLOCK) void tree_score_kernel(const uint8_t *
                         for (int w = 0; w < WALKS; ++w) x[w] = __uint_as_float(upper[w]);
                     } else {
 #pragma unroll
-                        for (int w = 0; w < WALKS; ++w) x[w] = x_of(nd[w].y);
+                        for (int w = 0; w < WALKS; ++w) x[w] = *reinterpret_cast<const float *>(lds + (at[w] - lds_base));
                     }
+                };
+                auto step = [&](const float(&x)[WALKS], const float(&thr)[WALKS]) {
+                    if constexpr (HALF) {
+                        // i <- 2i + sign(x - t): x < t exactly when the difference is negative (denormals are kept, no
+                        // NaN here is negative)
 #pragma unroll
-                    for (int w = 0; w < WALKS; w += 4) {
-                        unsigned long long m0, m1, m2, m3;
-                        asm("v_cmp_nlt_f32_e64 %4, %8, %12\n\t"
-                            "v_cmp_nlt_f32_e64 %5, %9, %13\n\t"
-                            "v_cmp_nlt_f32_e64 %6, %10, %14\n\t"
-                            "v_cmp_nlt_f32_e64 %7, %11, %15\n\t"
-                            "v_addc_co_u32_e64 %0, %4, %0, %0, %4\n\t"
-                            "v_addc_co_u32_e64 %1, %5, %1, %1, %5\n\t"
-                            "v_addc_co_u32_e64 %2, %6, %2, %2, %6\n\t"
-                            "v_addc_co_u32_e64 %3, %7, %3, %3, %7"
-                            : "+v"(i[w]), "+v"(i[w + 1]), "+v"(i[w + 2]), "+v"(i[w + 3]), "=&s"(m0), "=&s"(m1), "=&s"(m2),
-                              "=&s"(m3)
-                            : "v"(x[w]), "v"(x[w + 1]), "v"(x[w + 2]), "v"(x[w + 3]), "v"(__uint_as_float(nd[w].x)),
-                              "v"(__uint_as_float(nd[w + 1].x)), "v"(__uint_as_float(nd[w + 2].x)),
-                              "v"(__uint_as_float(nd[w + 3].x)));
+                        for (int w = 0; w < WALKS; ++w) i[w] = __builtin_amdgcn_alignbit(i[w], __float_as_uint(x[w] - thr[w]), 31u);
+                    } else {
+                        // i <- i + i + (outcome of the comparison): a compare into a scalar mask and an add with that
+                        // mask as carry-in, written out because the compiler makes three instructions of it.  Four walks
+                        // per statement keep the compares four instructions ahead of the adds that read their masks.
+#define ECK_STEP(CMP)                                                                                                          \
+    asm(CMP " %4, %8, %12\n\t" CMP " %5, %9, %13\n\t" CMP " %6, %10, %14\n\t" CMP " %7, %11, %15\n\t"                            \
+            "v_addc_co_u32_e64 %0, %4, %0, %0, %4\n\t"                                                                         \
+            "v_addc_co_u32_e64 %1, %5, %1, %1, %5\n\t"                                                                         \
+            "v_addc_co_u32_e64 %2, %6, %2, %2, %6\n\t"                                                                         \
+            "v_addc_co_u32_e64 %3, %7, %3, %3, %7"                                                                             \
+        : "+v"(i[w]), "+v"(i[w + 1]), "+v"(i[w + 2]), "+v"(i[w + 3]), "=&s"(m0), "=&s"(m1), "=&s"(m2), "=&s"(m3)               \
+        : "v"(x[w]), "v"(x[w + 1]), "v"(x[w + 2]), "v"(x[w + 3]), "v"(thr[w]), "v"(thr[w + 1]), "v"(thr[w + 2]), "v"(thr[w + 3]))
+#pragma unroll
+                        for (int w = 0; w < WALKS; w += 4) {
+                            unsigned long long m0, m1, m2, m3;
+                            if constexpr (FEAT_BF16) ECK_STEP("v_cmp_lt_f32_e64"); // (mirrored)
+                            else ECK_STEP("v_cmp_nlt_f32_e64");
+                        }
+#undef ECK_STEP
                     }
-                }
-                const float *lf = leaf_lds + (size_t)t * leaves;
-                float v[WALKS];
-#pragma unroll
-                for (int w = 0; w < WALKS; ++w) v[w] = lf[(size_t)w * leaves + i[w] - leaves]; // i in [2^d, 2^(d+1))
-#pragma unroll
-                for (int w = 0; w < WALKS; ++w) acc = acc + v[w]; // tree order
-            }
-            for (; t < in_chunk; ++t) {
-                uint32_t j = 0;
-                const uint2 *nd = node_lds + (size_t)t * nodes;
+                };
+                float x[WALKS], thr[WALKS];
+                uint32_t at[WALKS];
                 for (int l = 0; l < depth; ++l) {
-                    const uint2 a = nd[j];
-                    j = 2 * j + (x_of(a.y) < __uint_as_float(a.x) ? 1u : 2u);
+                    Node nd[WALKS];
+#pragma unroll
+                    for (int w = 0; w < WALKS; ++w) nd[w] = first[(size_t)w * stride + i[w]];
+#pragma unroll
+                    for (int w = 0; w < WALKS; ++w) {
+                        if constexpr (FEAT_BF16) {
+                            thr[w] = __uint_as_float(nd[w]);
+                            at[w] = place_of(nd[w]);
+                        } else {
+                            thr[w] = __uint_as_float(nd[w].x);
+                            at[w] = lane_at + nd[w].y;
+                        }
+                    }
+                    read_x(at, x);
+                    step(x, thr);
                 }
-                acc = acc + leaf_lds[(size_t)t * leaves + j - nodes];
+                float v[WALKS]; // i in [2^d, 2^(d+1))
+#pragma unroll
+                for (int w = 0; w < WALKS; ++w) {
+                    if constexpr (FEAT_BF16) v[w] = __uint_as_float(first[(size_t)w * stride + i[w]]);
+                    else v[w] = leaf_lds[(size_t)(t + w) * leaves + i[w] - leaves];
+                }
+                if constexpr (S == 1) {
+                    if (t + WALKS <= in_chunk) {
+#pragma unroll
+                        for (int w = 0; w < WALKS; ++w) acc = acc + v[w]; // tree order
+                    } else {
+#pragma unroll
+                        for (int w = 0; w < WALKS; ++w) acc = t + w < in_chunk ? acc + v[w] : acc;
+                    }
+                } else {
+#pragma unroll
+                    for (int w = 0; w < WALKS; ++w) val_lds[(size_t)(t + w) * C + within] = v[w];
+                }
+            }
+            if constexpr (S > 1) {
+                __syncthreads();
+                if (slot == 0) {
+                    int t = 0;
+                    for (; t + WALKS <= in_chunk; t += WALKS) {
+                        float v[WALKS];
+#pragma unroll
+                        for (int w = 0; w < WALKS; ++w) v[w] = val_lds[(size_t)(t + w) * C + within];
+#pragma unroll
+                        for (int w = 0; w < WALKS; ++w) acc = acc + v[w]; // tree order
+                    }
+                    for (; t < in_chunk; ++t) acc = acc + val_lds[(size_t)t * C + within];
+                }
             }
         }
-        if (cand < n) out[cand] = acc;
+        if (slot == 0 && first_cand + mine < n) out[first_cand + mine] = acc;
     }
 }
 
-int32_t launch_score(const eck_trees *m, int n_trees, const void *feat, int32_t feat_dtype, uint64_t ld, uint64_t n,
-                     float *out, hipStream_t st)
+template <bool FEAT_BF16, int C, int S>
+int32_t launch_score_as(const eck_trees *m, int n_trees, const void *feat, uint64_t ld, uint64_t n, float *out, hipStream_t st)
 {
-    const size_t elem = feat_dtype == ECK_BF16 ? 2 : 4;
-    const size_t per_tree = tree_lds_bytes(m->depth);
-    const size_t lds_cu = 156 * 1024;
-    // 512 candidates per block when two such blocks fit a compute unit (a staged chunk of trees then serves
-    // twice as many candidates; measured 2.49 against 2.70 ms for 256, and 2.71 ms for one block of 1024), else 256
-    const size_t floor512 = (size_t)m->n_feat * 512 * elem + WALKS * per_tree;
-    const int block = 2 * floor512 <= lds_cu ? 512 : 256;
-    const uint64_t tiles64 = (n + block - 1) / block;
+    const size_t per_tree = tree_lds_bytes(m->depth, FEAT_BF16) + (S > 1 ? C * 4 : 0);
+    const size_t x_bytes = (size_t)m->n_feat * C * (FEAT_BF16 && S == 1 ? 2 : 4), lds_cu = 156 * 1024;
+    const uint64_t tiles64 = (n + C - 1) / C;
     if (tiles64 > 0xFFFFFFFFull) return ECK_EUNSUPPORTED;
-    const size_t x_bytes = (size_t)m->n_feat * block * elem;
     // Trees per chunk.  The walks are chains of dependent LDS reads, so what counts is how many wavefronts a
     // compute unit holds: the smallest chunk (one group of simultaneous walks) beside the feature tile lets
     // the most blocks share the 160 KB; blocks per unit = what fits, chunk = what is left of a block's share.
-    const size_t floor_bytes = x_bytes + WALKS * per_tree;
+    const size_t floor_bytes = x_bytes + S * WALKS * per_tree;
     if (floor_bytes > lds_cu) return ECK_EUNSUPPORTED;
     size_t blocks_cu = lds_cu / floor_bytes;
-    if (blocks_cu > (size_t)(2048 / block)) blocks_cu = 2048 / block; // 2048 threads per unit
+    if (blocks_cu > (size_t)(2048 / (C * S))) blocks_cu = 2048 / (C * S); // 2048 threads per unit
     const size_t share = lds_cu / blocks_cu;
     int chunk = (int)((share - x_bytes) / per_tree);
-    chunk -= chunk % WALKS;
+    chunk -= chunk % (S * WALKS);
     const int rounded = (n_trees + WALKS - 1) / WALKS * WALKS;
     if (n_trees > 0 && chunk > rounded) chunk = rounded;
     if (chunk < WALKS) chunk = WALKS;
@@ -219,14 +399,53 @@ int32_t launch_score(const eck_trees *m, int n_trees, const void *feat, int32_t 
     const uint32_t n_tiles = (uint32_t)tiles64;
     const uint32_t want = (uint32_t)cus * (uint32_t)blocks_cu;
     const uint32_t grid = n_tiles < want ? n_tiles : want;
-    auto kern = feat_dtype == ECK_BF16 ? (block == 512 ? tree_score_kernel<true, 512> : tree_score_kernel<true, 256>)
-                                       : (block == 512 ? tree_score_kernel<false, 512> : tree_score_kernel<false, 256>);
+    // rows of whole words: sixteen bytes of a row in one load
+    const int wide_loads = ((uintptr_t)feat & 3) == 0 && (FEAT_BF16 ? ld % 2 == 0 : true);
+    auto kern = tree_score_kernel<FEAT_BF16, C, S>;
     ECK_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                     (int)lds));
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(block), lds, st, m->d_feat, m->d_thr, m->d_leaf, m->n_feat, m->depth,
-                       n_trees, chunk, m->base, feat, ld, n, out, n_tiles);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(C * S), lds, st, m->d_feat, m->d_thr, m->d_leaf, m->d_word, m->n_feat, m->depth,
+                       n_trees, chunk, m->base, feat, ld, n, out, n_tiles, wide_loads);
     ECK_HIP_TRY(hipGetLastError());
     return ECK_OK;
+}
+
+// Up to these numbers of candidates a block takes 64 or 128 of them and shares the trees between eight or four groups of
+// threads: blocks of 512 would leave compute units idle, and every tree would wait for the one before.  us per call, 100
+// trees of depth 6, eight groups / four / one: 1000 candidates 8.5 / 14.5 / 27, 32768 11.2 / 14.7 / 28, 65536 25 / 15.5 / 28,
+// 131072 52 / 36 / 28 (the four-group figure at 65536 fills the chip exactly).
+constexpr uint64_t EIGHT_GROUPS_MOST = 32768, FOUR_GROUPS_MOST = 65536;
+
+template <bool FEAT_BF16>
+int32_t launch_score_of(const eck_trees *m, int n_trees, const void *feat, uint64_t ld, uint64_t n, float *out, hipStream_t st)
+{
+    // refused as ever: 256 candidates' features and eight trees with eight-byte nodes have to fit a compute unit
+    const size_t lds_cu = 156 * 1024, elem = FEAT_BF16 ? 2 : 4, eight = WALKS * tree_lds_bytes(m->depth, false);
+    if ((size_t)m->n_feat * 256 * elem + eight > lds_cu) return ECK_EUNSUPPORTED;
+    const size_t small_tree = tree_lds_bytes(m->depth, FEAT_BF16);
+    if (n <= EIGHT_GROUPS_MOST && (size_t)m->n_feat * 64 * 4 + 64 * (small_tree + 64 * 4) <= lds_cu)
+        return launch_score_as<FEAT_BF16, 64, 8>(m, n_trees, feat, ld, n, out, st);
+    if (n <= FOUR_GROUPS_MOST && 2 * ((size_t)m->n_feat * 128 * 4 + 32 * (small_tree + 128 * 4)) <= lds_cu)
+        return launch_score_as<FEAT_BF16, 128, 4>(m, n_trees, feat, ld, n, out, st);
+    if constexpr (FEAT_BF16) {
+        // a row's offset has to fit a word's lower half
+        if (m->n_feat <= 64) return launch_score_as<true, 512, 1>(m, n_trees, feat, ld, n, out, st);
+        if (m->n_feat <= 128) return launch_score_as<true, 256, 1>(m, n_trees, feat, ld, n, out, st);
+        return launch_score_as<true, 128, 1>(m, n_trees, feat, ld, n, out, st);
+    } else {
+        // 512 candidates per block when two such blocks fit a compute unit (a staged chunk of trees then serves twice as
+        // many candidates), else 256
+        if (2 * ((size_t)m->n_feat * 512 * 4 + WALKS * small_tree) <= lds_cu)
+            return launch_score_as<false, 512, 1>(m, n_trees, feat, ld, n, out, st);
+        return launch_score_as<false, 256, 1>(m, n_trees, feat, ld, n, out, st);
+    }
+}
+
+int32_t launch_score(const eck_trees *m, int n_trees, const void *feat, int32_t feat_dtype, uint64_t ld, uint64_t n,
+                     float *out, hipStream_t st)
+{
+    return feat_dtype == ECK_BF16 ? launch_score_of<true>(m, n_trees, feat, ld, n, out, st)
+                                  : launch_score_of<false>(m, n_trees, feat, ld, n, out, st);
 }
 
 // ----------------------------------------------------------------------------------------------- boosting
@@ -996,11 +1215,13 @@ extern "C" int32_t eck_trees_create(int32_t n_feat, int32_t depth, int32_t capac
     const size_t nodes = ((size_t)1 << depth) - 1, leaves = (size_t)1 << depth;
     if (hipGetDevice(&m->device) != hipSuccess || hipMalloc((void **)&m->d_feat, capacity * nodes) != hipSuccess ||
         hipMalloc((void **)&m->d_thr, capacity * nodes * 4) != hipSuccess ||
-        hipMalloc((void **)&m->d_leaf, capacity * leaves * 4) != hipSuccess) {
+        hipMalloc((void **)&m->d_leaf, capacity * leaves * 4) != hipSuccess ||
+        hipMalloc((void **)&m->d_word, capacity * leaves * 4) != hipSuccess) {
         (void)hipGetLastError();
         if (m->d_feat) (void)hipFree(m->d_feat);
         if (m->d_thr) (void)hipFree(m->d_thr);
         if (m->d_leaf) (void)hipFree(m->d_leaf);
+        if (m->d_word) (void)hipFree(m->d_word);
         delete m;
         return ECK_EDEVICE;
     }
@@ -1015,6 +1236,7 @@ extern "C" void eck_trees_destroy(eck_trees *m)
     (void)hipFree(m->d_feat);
     (void)hipFree(m->d_thr);
     (void)hipFree(m->d_leaf);
+    (void)hipFree(m->d_word);
     delete m;
 }
 
@@ -1034,9 +1256,10 @@ extern "C" int32_t eck_trees_set(eck_trees *m, int32_t n_trees, const uint8_t *n
     const size_t nodes = ((size_t)1 << m->depth) - 1, leaves = (size_t)1 << m->depth;
     hipStream_t st = as_stream(stream);
     if (n_trees) {
-        ECK_HIP_TRY(hipMemcpyAsync(m->d_feat, node_feat, n_trees * nodes, hipMemcpyDeviceToDevice, st));
-        ECK_HIP_TRY(hipMemcpyAsync(m->d_thr, node_thr, n_trees * nodes * 4, hipMemcpyDeviceToDevice, st));
-        ECK_HIP_TRY(hipMemcpyAsync(m->d_leaf, leaf, n_trees * leaves * 4, hipMemcpyDeviceToDevice, st));
+        const uint32_t slots = (uint32_t)n_trees << m->depth;
+        hipLaunchKernelGGL(tree_set_kernel, dim3((slots + 255) / 256), dim3(256), 0, st, node_feat, node_thr, leaf, m->n_feat,
+                           m->depth, n_trees, m->d_feat, m->d_thr, m->d_leaf, m->d_word);
+        ECK_HIP_TRY(hipGetLastError());
     }
     m->n_trees = n_trees;
     return ECK_OK;
@@ -1109,8 +1332,16 @@ extern "C" int32_t treemodel_update(eck_trees *m, const void *feat, int32_t feat
                        m->n_feat, bins);
     if (n_pairs <= LEVEL_MAX_PAIRS) {
         rc = boost_levels(m, base, w, n_pairs, n_rounds, eta, lam, snr_out, loss_out, st);
-        if (rc == ECK_OK) m->n_trees += n_rounds;
-        return rc;
+        if (rc != ECK_OK) return rc;
+        if (n_rounds > 0) {
+            const size_t t = (size_t)m->n_trees;
+            hipLaunchKernelGGL(tree_set_kernel, dim3((unsigned)((((size_t)n_rounds << m->depth) + 255) / 256)), dim3(256), 0, st,
+                               m->d_feat + t * nodes, m->d_thr + t * nodes, nullptr, m->n_feat, m->depth, n_rounds, nullptr, nullptr,
+                               nullptr, m->d_word + t * leaves);
+            ECK_HIP_TRY(hipGetLastError());
+        }
+        m->n_trees += n_rounds;
+        return ECK_OK;
     }
     {
         // the histogram buffer starts clear; from then on the split kernel clears what it reads
@@ -1143,6 +1374,12 @@ extern "C" int32_t treemodel_update(eck_trees *m, const void *feat, int32_t feat
     }
     hipLaunchKernelGGL(tree_quality_kernel, dim3(1), dim3(1024), 0, st, p, y, n_pairs, 1, sc);
     hipLaunchKernelGGL(tree_finish_kernel, dim3(1), dim3(64), 0, st, sc, snr_out, loss_out);
+    if (n_rounds > 0) {
+        const size_t t = (size_t)m->n_trees;
+        hipLaunchKernelGGL(tree_set_kernel, dim3((unsigned)((((size_t)n_rounds << m->depth) + 255) / 256)), dim3(256), 0, st,
+                           m->d_feat + t * nodes, m->d_thr + t * nodes, nullptr, m->n_feat, m->depth, n_rounds, nullptr, nullptr,
+                           nullptr, m->d_word + t * leaves);
+    }
     ECK_HIP_TRY(hipGetLastError());
     m->n_trees += n_rounds;
     return ECK_OK;

@@ -157,6 +157,43 @@ def test_score_special_values_and_thresholds_between_bfloat16_values(G):
     assert np.array_equal(got_f32, want)
 
 
+@pytest.mark.parametrize("n_feat,depth,T,n", [(64, 6, 11, 98305 + 512), (3, 1, 1, 100000), (65, 8, 9, 98400), (130, 5, 17, 98817),
+                                              (64, 6, 100, 40001), (64, 8, 70, 33000), (7, 3, 8, 513), (200, 2, 9, 1000), (64, 6, 0, 77)])
+@pytest.mark.parametrize("bf16", [True, False])
+def test_scores_of_every_block_shape(G, n_feat, depth, T, n, bf16):
+    """few, some and many candidates (64, 128 and 512, 256 or 128 per block, the trees shared between eight, four and one
+    group of threads), with last blocks that are full, almost full and almost empty, trees that do not fill the last set
+    of eight, rows that start on odd addresses; thresholds and features at and around each other, with both zeros,
+    denormals, infinities and NaN of both signs.  Bit for bit the oracle's sums in tree order."""
+    if not bf16 and n_feat == 200:
+        pytest.skip("the features of 256 candidates do not fit the LDS in fp32: refused")
+    rng = np.random.default_rng(n + T)
+    ld = n + 3 + (n & 1)
+    bits = (rng.integers(0, 40, (n_feat, ld)) * 16 + 0x3F80).astype(np.uint16)
+    special = np.array([0x0000, 0x8000, 0x0001, 0x8001, 0x7F80, 0xFF80, 0x7FC0, 0xFFC0, 0x7F7F, 0xFF7F, 0x7F81, 0xFF81], dtype=np.uint16)
+    pick = rng.random(bits.shape) < 0.05
+    bits[pick] = rng.choice(special, int(pick.sum()))
+    bits[rng.random(bits.shape) < 0.3] ^= 0x8000
+    x = oracle.bf16_bits_to_f32(bits)
+    nodes = (1 << depth) - 1
+    nf = rng.integers(0, n_feat, (T, nodes)).astype(np.uint8)
+    nt = x.ravel()[rng.integers(0, x.size, (T, nodes))].astype(np.float32)
+    with np.errstate(invalid="ignore"):
+        side = rng.integers(0, 4, (T, nodes))
+        nt = np.where(side == 0, np.nextafter(nt, np.float32(np.inf)), np.where(side == 1, np.nextafter(nt, np.float32(-np.inf)), nt)).astype(np.float32)
+    lf = rng.standard_normal((T, 1 << depth)).astype(np.float32)
+    trees = eck.Trees(n_feat, depth, max(T, 1), 0.25)
+    if T:
+        _load(trees, G, nf, nt, lf)
+    if bf16:
+        feat = G.to_dev(bits).view(torch.bfloat16)
+    else:
+        feat = G.to_dev(np.ascontiguousarray(x))
+    with np.errstate(invalid="ignore"):
+        want = oracle.trees_predict(n_feat, depth, nf, nt, lf, 0.25, x, n=n, fp32_sequential=True).astype(np.float32)
+    assert np.array_equal(_score(trees, feat, n), want)
+
+
 def _boost_gpu(trees, feat_dev, e, rounds, eta, lam):
     snr = torch.zeros(1, dtype=torch.float32, device="cuda")
     loss = torch.zeros(1, dtype=torch.float32, device="cuda")
