@@ -313,8 +313,9 @@ uint64_t topk_select_rank_workspace_bytes(uint64_t n, uint32_t n_segments, uint3
  * (+inf padding), count_out uint32 [S] = min(k, #feasible).  NaN energies or
  * latencies are never feasible.  All pointers device; ws device, 16-byte aligned.
  * The score arrays are read once (THRESHOLD with a finite alpha reads the
- * latencies once more, for L_min; RANK reads once per stage); the result does
- * not depend on the order of execution.
+ * latencies once more, for L_min; RANK with a partial gate reads the latencies
+ * once and the energies of the gated candidates); the result does not depend on
+ * the order of execution.
  * Errors: EINVAL (nulls, n == 0, k == 0, bad mode, alpha < 1 or NaN), ESHAPE
  * (n % n_segments, k > n/n_segments, segment longer than 2^32-2), EUNSUPPORTED
  * (k or a partial m_latency > ECK_MAX_K), EWORKSPACE, EALIGN (ws). */

@@ -30,7 +30,7 @@ constexpr int ITEMS = ECK_TOPK_ITEMS;                // composites a thread hold
 constexpr uint64_t NONE = ~0ull;         // no candidate (a NaN score never makes a composite, so no composite is all ones)
 constexpr uint32_t LATMIN_PARTS = 256;   // most per-block latency minima per segment
 
-enum Pred { PRED_PLAIN = 0, PRED_THRESHOLD = 1, PRED_RANK_STAGE_A = 2, PRED_RANK_STAGE_B = 3 };
+enum Pred { PRED_PLAIN = 0, PRED_THRESHOLD = 1, PRED_RANK = 2 };
 enum Source { SRC_SCORES_VEC = 0, SRC_SCORES = 1, SRC_LIST = 2 };
 
 __device__ __forceinline__ uint32_t order_key(float x)
@@ -53,16 +53,15 @@ struct SelectArgs {
     float slack_factor;         // alpha - 1 (THRESHOLD)
     int alpha_inf;
     const uint32_t *lat_parts;  // THRESHOLD: [S][lat_parts_n] least latency order keys, one per block of latmin_kernel
-    uint32_t lat_parts_n;
-    const uint64_t *lat_thr;    // RANK stage B: [S] feasible = latency composite <= lat_thr[s]
+    uint32_t lat_parts_n;       // 0: one block holds the whole segment and finds the least key itself
     const uint64_t *list_in;    // SRC_LIST: [S][list_len] composites of the level before, NONE where empty
     uint64_t list_len;
     uint64_t *list_out;         // not the last level: [S][gridDim.x][k]
-    uint32_t k;
-    uint32_t *idx_out;          // last level: the result ...
+    uint32_t k;                 // composites this tournament selects; RANK: by latency, m_latency of them ...
+    uint32_t k_energy;          // ... among which the last level selects this many by energy (else 0)
+    uint32_t *idx_out;          // last level: the result
     float *energy_out;
     uint32_t *count_out;
-    uint64_t *thr_out;          // ... or (RANK stage A) only the composite the k-th smallest does not exceed
 };
 
 // ---------------------------------------------------------------- latency minimum (THRESHOLD)
@@ -115,23 +114,11 @@ constexpr uint32_t SMALL = 512;          // a selection among at most this many 
 
 // order key of a legal candidate's value under predicate PRED, or NO_KEY if infeasible
 template <int PRED>
-__device__ __forceinline__ uint32_t feasible_key(const SelectArgs &a, uint32_t i, float e, float l, float tau,
-                                                 uint64_t lat_thr)
+__device__ __forceinline__ uint32_t feasible_key(float e, float l, float tau)
 {
-    float value;
-    if (PRED == PRED_RANK_STAGE_A) {
-        value = l;
-    } else {
-        value = e;
-        if (PRED == PRED_THRESHOLD) {
-            if (!(l <= tau)) return NO_KEY;
-        } else if (PRED == PRED_RANK_STAGE_B) {
-            if (l != l) return NO_KEY;
-            if ((((uint64_t)order_key(l) << a.idx_bits) | i) > lat_thr) return NO_KEY;
-        }
-    }
-    if (value != value) return NO_KEY;
-    return order_key(value);
+    if (PRED == PRED_THRESHOLD && !(l <= tau)) return NO_KEY;
+    const float value = PRED == PRED_RANK ? l : e;
+    return value != value ? NO_KEY : order_key(value);
 }
 
 // LDS of a block: the digit histogram of the radix select, or the arrays of the direct ranking (never both at
@@ -259,6 +246,9 @@ __device__ __forceinline__ void rank_pool(uint32_t kept, uint32_t k, Shared<T> &
             const uint64_t mine = sh.small.pool[entry];
             const uint32_t lo = part * span, hi = lo + span < kept ? lo + span : kept;
             uint32_t smaller = 0;
+            // (eight reads under way at a time: one by one their latency adds up, 34.2 against 30.9 us for the 128 fastest
+            // of 2^20 and their 64 of least energy, 98 against 69 us for 64 segments of 2^18)
+#pragma unroll 8
             for (uint32_t j = lo; j < hi; ++j) smaller += sh.small.pool[j] < mine;
             if (smaller) atomicAdd(&sh.small.rank[entry], smaller);
         }
@@ -459,7 +449,7 @@ template <int T, int SRC, int PRED>
 __device__ __forceinline__ void gather_scores(const SelectArgs &a, uint32_t s, Shared<T> &sh, uint64_t (&c)[ITEMS],
                                               uint32_t *kept, bool *bounded)
 {
-    constexpr bool NEED_E = PRED != PRED_RANK_STAGE_A, NEED_L = PRED != PRED_PLAIN;
+    constexpr bool NEED_E = PRED != PRED_RANK, NEED_L = PRED != PRED_PLAIN;
     const uint64_t seg_base = (uint64_t)s * a.seg_len;
     const uint64_t start = (uint64_t)blockIdx.x * (T * ITEMS);
     // VEC: every load of the thread is issued here, before anything waits; none depends on another (the flags
@@ -483,7 +473,6 @@ __device__ __forceinline__ void gather_scores(const SelectArgs &a, uint32_t s, S
     }
     // the gate, while the loads are under way
     float tau = 0.0f;
-    uint64_t lat_thr = 0;
     if (PRED == PRED_THRESHOLD) {
         // tau = L_min + (alpha - 1) |L_min|, product and sum rounded separately; L_min from the per-block minima
         if (a.alpha_inf) {
@@ -491,6 +480,27 @@ __device__ __forceinline__ void gather_scores(const SelectArgs &a, uint32_t s, S
         } else {
             uint32_t best = 0xFFFFFFFFu;
             for (uint32_t p = threadIdx.x; p < a.lat_parts_n; p += T) best = min(best, a.lat_parts[(uint64_t)s * a.lat_parts_n + p]);
+            if (a.lat_parts_n == 0) { // the segment is this block's chunk
+                if (SRC == SRC_SCORES_VEC) {
+#pragma unroll
+                    for (int j = 0; j < ITEMS / 4; ++j) {
+                        const uint64_t i = start + ((uint64_t)j * T + threadIdx.x) * 4;
+                        const float lv[4] = {l[j].x, l[j].y, l[j].z, l[j].w};
+#pragma unroll
+                        for (int t = 0; t < 4; ++t)
+                            if (i < a.seg_len && ((flags[j] >> (8 * t)) & 0xFFu) && lv[t] == lv[t]) best = min(best, order_key(lv[t]));
+                    }
+                } else {
+#pragma unroll
+                    for (int j = 0; j < ITEMS; ++j) {
+                        const uint64_t i = start + (uint64_t)j * T + threadIdx.x;
+                        if (i < a.seg_len && (!a.legal || a.legal[seg_base + i])) {
+                            const float v = a.latency[seg_base + i];
+                            if (v == v) best = min(best, order_key(v));
+                        }
+                    }
+                }
+            }
 #pragma unroll
             for (int off = 32; off > 0; off >>= 1) best = min(best, (uint32_t)__shfl_xor((int)best, off));
             if (threadIdx.x == 0) sh.lat_min = 0xFFFFFFFFu;
@@ -505,8 +515,6 @@ __device__ __forceinline__ void gather_scores(const SelectArgs &a, uint32_t s, S
                 tau = __fadd_rn(lmin, __fmul_rn(a.slack_factor, fabsf(lmin)));
             }
         }
-    } else if (PRED == PRED_RANK_STAGE_B) {
-        lat_thr = a.lat_thr[s];
     }
     // order keys of the feasible candidates (32 bits each: the index is implied by the position), their least
     // per thread, the bound from those
@@ -542,8 +550,7 @@ __device__ __forceinline__ void gather_scores(const SelectArgs &a, uint32_t s, S
             const float lv[4] = {NEED_L ? l[j].x : 0.0f, NEED_L ? l[j].y : 0.0f, NEED_L ? l[j].z : 0.0f, NEED_L ? l[j].w : 0.0f};
 #pragma unroll
             for (int t = 0; t < 4; ++t)
-                key[4 * j + t] = ((f >> (8 * t)) & 0xFFu) ? feasible_key<PRED>(a, (uint32_t)i + t, ev[t], lv[t], tau, lat_thr)
-                                                          : NO_KEY;
+                key[4 * j + t] = ((f >> (8 * t)) & 0xFFu) ? feasible_key<PRED>(ev[t], lv[t], tau) : NO_KEY;
         }
     } else {
 #pragma unroll
@@ -553,8 +560,7 @@ __device__ __forceinline__ void gather_scores(const SelectArgs &a, uint32_t s, S
             if (i < a.seg_len) {
                 const uint64_t g = seg_base + i;
                 if (!a.legal || a.legal[g])
-                    v = feasible_key<PRED>(a, (uint32_t)i, NEED_E ? a.energy[g] : 0.0f, NEED_L ? a.latency[g] : 0.0f, tau,
-                                           lat_thr);
+                    v = feasible_key<PRED>(NEED_E ? a.energy[g] : 0.0f, NEED_L ? a.latency[g] : 0.0f, tau);
             }
             key[j] = v;
         }
@@ -588,20 +594,38 @@ __device__ __forceinline__ void gather_scores(const SelectArgs &a, uint32_t s, S
 // Selection among the gathered composites, then either the block's k slots of list_out (unused slots NONE) or,
 // last level, the result.
 template <int T>
-__device__ __forceinline__ void select_and_emit(const SelectArgs &a, uint32_t s, const uint64_t (&c)[ITEMS], uint32_t kept,
+__device__ __forceinline__ void select_and_emit(const SelectArgs &a, uint32_t s, uint64_t (&c)[ITEMS], uint32_t kept,
                                                 bool bounded, bool last_level, Shared<T> &sh, uint64_t *sort_buf)
 {
     bool ranked;
     uint64_t thr;
-    const uint32_t n_selected = select_kept<T>(c, kept, bounded, a.k, 32 + a.idx_bits, sh, &ranked, &thr);
-    if (last_level && a.thr_out) {
-        // RANK stage A: feasible = latency composite <= the k-th smallest (everything legal when fewer than k exist)
-        if (threadIdx.x == 0) {
-            uint64_t gate = NONE;
-            if (n_selected == a.k) gate = ranked ? sh.small.ranked[a.k - 1] : thr;
-            a.thr_out[s] = gate;
+    uint32_t n_selected = select_kept<T>(c, kept, bounded, a.k, 32 + a.idx_bits, sh, &ranked, &thr);
+    const uint32_t k_out = a.k_energy ? a.k_energy : a.k;
+    if (last_level && a.k_energy) {
+        // RANK: these are the segment's fastest.  Their energies, fetched by index, take the latencies' place, and the
+        // same selection runs once more, on what the block holds: no second pass over the score arrays.
+        if (ranked) {
+#pragma unroll
+            for (int j = 0; j < ITEMS; ++j) {
+                const uint32_t i = (uint32_t)j * T + threadIdx.x;
+                c[j] = i < n_selected ? sh.small.ranked[i] : NONE; // (at most SMALL)
+            }
         }
-        return;
+#pragma unroll
+        for (int j = 0; j < ITEMS; ++j) {
+            const uint64_t idx = c[j] & ((1ull << a.idx_bits) - 1);
+            uint64_t next = NONE;
+            if (c[j] != NONE && (ranked || c[j] <= thr)) {
+                const float e = a.energy[(uint64_t)s * a.seg_len + idx];
+                if (e == e) next = ((uint64_t)order_key(e) << a.idx_bits) | idx;
+            }
+            c[j] = next;
+        }
+        __syncthreads(); // everything of the first selection has been read
+        for (uint32_t i = threadIdx.x; i < SMALL; i += T) sh.small.rank[i] = 0;
+        if (threadIdx.x == 0) sh.cursor = 0;
+        kept = count_candidates<T>(c, sh);
+        n_selected = select_kept<T>(c, kept, false, k_out, 32 + a.idx_bits, sh, &ranked, &thr);
     }
     if (!last_level) {
         uint64_t *out = a.list_out + ((uint64_t)s * gridDim.x + blockIdx.x) * a.k;
@@ -622,17 +646,17 @@ __device__ __forceinline__ void select_and_emit(const SelectArgs &a, uint32_t s,
     const uint64_t idx_mask = (1ull << a.idx_bits) - 1;
     auto emit = [&](uint32_t i, uint64_t v) {
         const bool valid = i < n_selected;
-        a.idx_out[(uint64_t)s * a.k + i] = valid ? (uint32_t)(v & idx_mask) : 0xFFFFFFFFu;
-        a.energy_out[(uint64_t)s * a.k + i] = valid ? key_to_float((uint32_t)(v >> a.idx_bits)) : __builtin_inff();
+        a.idx_out[(uint64_t)s * k_out + i] = valid ? (uint32_t)(v & idx_mask) : 0xFFFFFFFFu;
+        a.energy_out[(uint64_t)s * k_out + i] = valid ? key_to_float((uint32_t)(v >> a.idx_bits)) : __builtin_inff();
     };
     if (threadIdx.x == 0) a.count_out[s] = n_selected;
     if (ranked) {
-        for (uint32_t i = threadIdx.x; i < a.k; i += T) emit(i, i < n_selected ? sh.small.ranked[i] : 0);
+        for (uint32_t i = threadIdx.x; i < k_out; i += T) emit(i, i < n_selected ? sh.small.ranked[i] : 0);
         return;
     }
     // bitonic sort of the selection (padded to a power of two with NONE)
     uint32_t pow2 = 2;
-    while (pow2 < a.k) pow2 <<= 1;
+    while (pow2 < k_out) pow2 <<= 1;
     for (uint32_t i = threadIdx.x; i < pow2; i += T) sort_buf[i] = NONE;
     if (threadIdx.x == 0) sh.cursor = 0;
     __syncthreads();
@@ -662,7 +686,7 @@ __device__ __forceinline__ void select_and_emit(const SelectArgs &a, uint32_t s,
                 v = (lower == ascending) ? lo : hi;
             }
         }
-        if (i < a.k) emit(i, v);
+        if (i < k_out) emit(i, v);
         return;
     }
     for (uint32_t size = 2; size <= pow2; size <<= 1)
@@ -679,7 +703,7 @@ __device__ __forceinline__ void select_and_emit(const SelectArgs &a, uint32_t s,
             }
             __syncthreads();
         }
-    for (uint32_t i = threadIdx.x; i < a.k; i += T) emit(i, i < n_selected ? sort_buf[i] : 0);
+    for (uint32_t i = threadIdx.x; i < k_out; i += T) emit(i, i < n_selected ? sort_buf[i] : 0);
 }
 
 // One block = T threads x ITEMS candidates of segment blockIdx.y: a chunk of the score arrays, or the same number
@@ -739,10 +763,11 @@ Plan plan_for(uint64_t seg_len, uint32_t n_seg, uint32_t k)
 }
 
 struct WsLayout {
-    uint64_t lat_parts, lat_thr, list_a, list_b, total;
+    uint64_t lat_parts, list_a, list_b, total;
 };
 
-// m_latency: the latency gate of a RANK-mode call when it needs a stage of its own, else 0
+// m_latency: the latency gate of a RANK-mode call when it does not admit the whole segment, else 0.  (The larger of the
+// two plans: a workspace made for a gate serves a call without one, too.)
 WsLayout ws_layout(uint64_t seg_len, uint32_t n_seg, uint32_t k, uint32_t m_latency)
 {
     Plan p = plan_for(seg_len, n_seg, k);
@@ -753,8 +778,7 @@ WsLayout ws_layout(uint64_t seg_len, uint32_t n_seg, uint32_t k, uint32_t m_late
     }
     WsLayout w;
     w.lat_parts = 0;
-    w.lat_thr = w.lat_parts + (uint64_t)n_seg * LATMIN_PARTS * sizeof(uint32_t);
-    w.list_a = w.lat_thr + (((uint64_t)n_seg * sizeof(uint64_t) + 15) & ~15ull);
+    w.list_a = w.lat_parts + (uint64_t)n_seg * LATMIN_PARTS * sizeof(uint32_t);
     w.list_b = w.list_a + (uint64_t)n_seg * p.list_a * sizeof(uint64_t);
     w.total = w.list_b + (uint64_t)n_seg * p.list_b * sizeof(uint64_t);
     return w;
@@ -770,9 +794,9 @@ template <int T, int SRC, int PRED>
 void launch_select(const SelectArgs &a, uint32_t blocks, uint32_t n_seg, hipStream_t st)
 {
     size_t lds = (sizeof(Shared<T>) + 15) & ~(size_t)15;
-    if (blocks == 1 && !a.thr_out) {
+    if (blocks == 1) {
         uint32_t pow2 = 2;
-        while (pow2 < a.k) pow2 <<= 1;
+        while (pow2 < (a.k_energy ? a.k_energy : a.k)) pow2 <<= 1;
         lds += (size_t)pow2 * sizeof(uint64_t);
     }
     hipLaunchKernelGGL((select_kernel<T, SRC, PRED>), dim3(blocks, n_seg), dim3(T), lds, st, a);
@@ -786,7 +810,7 @@ void launch_level0(const SelectArgs &a, uint32_t blocks, uint32_t n_seg, bool ve
 }
 
 // All levels of one selection of a.k per segment: level 0 on the score arrays, further levels on the lists.
-// The last level writes idx/energy/count (or thr_out when that is set).
+// The last level writes idx/energy/count.
 template <int PRED>
 int32_t run_tournament(SelectArgs a, uint32_t n_seg, bool vec, uint64_t *list_a, uint64_t *list_b, hipStream_t st)
 {
@@ -880,7 +904,6 @@ int32_t eck::topk_select_impl(const float *energy, const float *latency, const u
     a.energy_out = energy_out;
     a.count_out = count_out;
     uint32_t *lat_parts = reinterpret_cast<uint32_t *>((char *)ws + w.lat_parts);
-    uint64_t *lat_thr = reinterpret_cast<uint64_t *>((char *)ws + w.lat_thr);
     uint64_t *list_a = reinterpret_cast<uint64_t *>((char *)ws + w.list_a);
     uint64_t *list_b = reinterpret_cast<uint64_t *>((char *)ws + w.list_b);
 
@@ -894,8 +917,9 @@ int32_t eck::topk_select_impl(const float *energy, const float *latency, const u
             // L_min came with the call (one order key per segment)
             a.lat_parts = known_min;
             a.lat_parts_n = 1;
-        } else if (!a.alpha_inf) {
-            // L_min first: one pass over the latencies, a slice of the segment per block
+        } else if (!a.alpha_inf && plan_for(seg_len, n_segments, k).blocks0 > 1) {
+            // L_min first: one pass over the latencies, a slice of the segment per block (a segment that one block
+            // holds needs none: that block finds it, 4 us less)
             uint64_t parts = (seg_len + 4095) / 4096;
             if (parts > LATMIN_PARTS) parts = LATMIN_PARTS;
             uint64_t slice = (seg_len + parts - 1) / parts;
@@ -916,13 +940,11 @@ int32_t eck::topk_select_impl(const float *energy, const float *latency, const u
         b.alpha_inf = 1;
         return run_tournament<PRED_THRESHOLD>(b, n_segments, vec, list_a, list_b, st);
     }
-    SelectArgs first = a;
-    first.k = m_latency;
-    first.thr_out = lat_thr;
-    const int32_t rc = run_tournament<PRED_RANK_STAGE_A>(first, n_segments, vec, list_a, list_b, st);
-    if (rc != ECK_OK) return rc;
-    a.lat_thr = lat_thr;
-    return run_tournament<PRED_RANK_STAGE_B>(a, n_segments, vec, list_a, list_b, st);
+    // the m_latency fastest by latency, of these k by energy in the last level's block: two launches where a second
+    // tournament over the gated scores took four (46 against 34 us on 2^20, 128 fastest, k = 64)
+    a.k = m_latency;
+    a.k_energy = k;
+    return run_tournament<PRED_RANK>(a, n_segments, vec, list_a, list_b, st);
 }
 
 extern "C" int32_t topk_select(const float *energy, const float *latency, const uint8_t *legal, uint64_t n,

@@ -170,3 +170,34 @@ def test_rank_gate_limits_and_workspace(G):
     assert call(4096, need) == eck.OK and call(n, need) == eck.OK
     torch.cuda.synchronize()
     assert cnt.item() == 16 and idx.cpu().numpy().tolist() == list(range(16))
+
+
+@pytest.mark.parametrize("segments,seg_len,k,m", [(1, 40, 1, 1), (3, 1000, 511, 512), (1, 16384, 512, 513), (1, 16385, 513, 514),
+                                                  (2, 70001, 100, 2000), (1, 300000, 1500, 4096), (5, 4097, 300, 256),
+                                                  (64, 20000, 7, 255), (1, 9000, 4000, 4096)])
+@pytest.mark.parametrize("odd", [False, True])
+def test_rank_gate_and_energies_in_one_tournament(G, segments, seg_len, k, m, odd):
+    """gates around the sizes where the block's method changes, segments that one block holds and segments of several
+    levels; ties in latency and energy; odd: few legal candidates (fewer than the gate in some segments, none in the last),
+    NaN energies among the fastest, infinities, NaN latencies"""
+    rng = np.random.default_rng(seg_len + k)
+    n = segments * seg_len
+    energy = (np.round(rng.standard_normal(n) * 50) / 50).astype(np.float32)
+    latency = (np.round(rng.standard_normal(n) * 200) / 200).astype(np.float32)
+    legal = None
+    if odd:
+        legal = (rng.random(n) < min(1.0, 0.7 * m / seg_len)).astype(np.uint8)
+        legal[n - seg_len:] = 0
+        for values in (energy, latency):
+            where = rng.random(n) < 0.1
+            values[where] = rng.choice(np.array([np.nan, np.inf, -np.inf, -0.0, 0.0], dtype=np.float32), int(where.sum()))
+    got = G.topk_gpu(energy, latency, legal, segments, k, mode=eck.SELECT_RANK, m_latency=m)
+    want = oracle.topk(energy, latency, legal, segments, k, mode=oracle.SEL_RANK, m_latency=m)
+    for a, b in zip(got, want):
+        assert np.array_equal(a, b)
+    # and the gate of the threshold mode where one block finds the least latency of its segment itself
+    with np.errstate(invalid="ignore"):
+        got = G.topk_gpu(energy, latency, legal, segments, k, alpha=1.3)
+        want = oracle.topk(energy, latency, legal, segments, k, alpha=1.3)
+    for a, b in zip(got, want):
+        assert np.array_equal(a, b)
