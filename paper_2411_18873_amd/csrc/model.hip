@@ -908,8 +908,22 @@ int32_t score_any(const eck_model *m, const void *feat, int32_t feat_dtype, uint
     if (m->dtype == ECK_F32) return score_f32(m, (const float *)feat, ld, n, score_out, WITH_MIN ? &mn : nullptr, st);
     // four candidate tiles per wavefront (half the weight traffic per candidate) where 256 or fewer hidden units
     // leave the registers for it, the features arrive as bf16 and groups of four stay inside a row (the flags of
-    // four candidates are then one 4-byte load)
-    const bool four = feat_dtype == ECK_BF16 && ld % 4 == 0 && ((uintptr_t)feat & 7) == 0 &&
+    // four candidates are then one 4-byte load) -- unless a compute unit has few blocks to work through and their
+    // number is odd at two tiles a wavefront (256 candidates a block), so that the last block of four tiles would
+    // be half work for nothing.  Measured, us at 256 / 128 units, two tiles against four:
+    //   1 block   (30 000 to 65 536 candidates) 10.4 against 15.6 / 6.2 against 8.0
+    //   2 blocks  (131 072)                     19.2 against 18.9 / 10.2 against 10.1
+    //   3 blocks  (196 608)                     28.0 against 31.3 / 13.3 against 15.0
+    //   5 blocks  (327 680)                     42.5 against 44.3 / 19.6 against 20.6
+    //   7 blocks  (458 752)                     57.1 against 57.3 / 25.3 against 25.8
+    //   9 blocks  (589 824)                     72.0 against 70.7 / 31.2 against 30.8
+    // With the running minima a block also costs atomics: 3 blocks at 128 units take 42.6 against 36.9 us, so there
+    // only a single block counts.
+    int cus = 256;
+    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, m->device);
+    const uint64_t blocks_a_cu = (n + 256 * (uint64_t)cus - 1) / (256 * (uint64_t)cus);
+    const bool two = blocks_a_cu % 2 == 1 && blocks_a_cu <= (WITH_MIN ? 1 : 5);
+    const bool four = !two && feat_dtype == ECK_BF16 && ld % 4 == 0 && ((uintptr_t)feat & 7) == 0 &&
                       (!WITH_MIN || !mn.legal || ((uintptr_t)mn.legal & 3) == 0);
     if (F == 64 && H1 == 512 && H2 == 512) return launch_bf16<64, 512, 512, 2, WITH_MIN>(m, feat, feat_dtype, ld, n, score_out, mn, st);
     if (F == 64 && H1 == 256 && H2 == 256 && four)

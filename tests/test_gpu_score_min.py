@@ -152,3 +152,24 @@ def test_selection_with_known_minima(G, n, S, k):
             assert np.array_equal(got[2], other[2])
             assert np.array_equal(got[0], other[0])
             assert np.array_equal(got[1].view(np.uint32), other[1].view(np.uint32))
+
+
+@pytest.mark.parametrize("h", [256, 128])
+def test_candidates_score_alike_however_many_blocks_a_call_has(G, h):
+    """Calls around one to five blocks of 256 candidates per compute unit, where two candidate tiles per wavefront and
+    four change places: every candidate's bits are those of one call of six such blocks (four tiles), itself checked
+    against the plain call of misaligned rows (two tiles), and so are the minima."""
+    widths = [64, h, h, 1]
+    unit = 256 * torch.cuda.get_device_properties(0).multi_processor_count
+    total = 6 * unit
+    _, b16 = _features(5003, 64)
+    some = G.bf16_dev(b16)
+    feat = some.repeat(1, total // 5003 + 1)[:, :total].contiguous()
+    model = G.make_model(widths, eck.BF16, synth.mlp_theta(widths, 8, bf16=True, bias_scale=0.5))
+    full = G.score_gpu(model, feat, total)
+    assert np.array_equal(G.score_gpu(model, feat[:, :5006].contiguous(), 5006), full[:5006])
+    for n in (1, 255, unit - 1, unit, unit + 1, 2 * unit + 4, 3 * unit - 3, 3 * unit + 2, 5 * unit, 5 * unit + 1):
+        assert np.array_equal(G.score_gpu(model, feat, n), full[:n]), n
+        got, keys = _score_min(G, model, feat, n, None, 1)
+        assert np.array_equal(got, full[:n]), n
+        assert np.array_equal(keys, _want_keys(full[:n], None, 1)), n
