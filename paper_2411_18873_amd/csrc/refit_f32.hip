@@ -10,7 +10,8 @@
 // each product's loads: weights are requested before the barrier or the product that precedes theirs, several groups of
 // sixteen rows of the reduction at a time.  Every sum has a fixed order.
 // Measured, 64-128-128-1 on minibatches of 250: 136 us per step launched one product at a time (a vector kernel of two
-// blocks for most of them, 30 us each), 16 us in two launches (rows 10.9, weights 5.3); 64-512-512-1, 512 rows: 290 and 70.
+// blocks for most of them, 30 us each), 16 us in two launches (rows 10.5, weights 5.4; a block of its own for the bias
+// corrections took 0.85 us a step off the rows kernel); 64-512-512-1, 512 rows: 290 and 70.
 #include "f32_tiles.h"
 
 using namespace eck;
@@ -159,12 +160,19 @@ __device__ __forceinline__ void store_units(float *row, int unit0, int width, co
     }
 }
 
-// One block = 16 minibatch rows; wavefront w owns units 16 J w .. of both hidden layers, J tiles (one or two up to 256
+// One block = 16 minibatch rows, and one more for Adam's bias corrections; wavefront w owns units 16 J w .. of both hidden layers, J tiles (one or two up to 256
 // units, so that the products of a layer are spread over as many wavefronts as there are).
 template <int J>
 __global__ __launch_bounds__(64 * WAVES, 2) void step_rows_f32_kernel(StepF32 a)
 {
     constexpr int DEPTH = J <= 2 ? 8 : 4, E = 4 * J;
+    if (blockIdx.x == gridDim.x - 1) { // the block of Adam's bias corrections, one lane each
+        if (threadIdx.x < 2) {
+            const double t = (double)a.theta[3 * a.P] + a.step_in_call + 1; // t itself is advanced once, after the last step
+            a.corr[threadIdx.x] = (float)(1.0 - pow((double)(threadIdx.x ? a.beta2 : a.beta1), t));
+        }
+        return;
+    }
     extern __shared__ __attribute__((aligned(16))) unsigned char rows_lds[];
     const int F = a.F, H1 = a.H1, H2 = a.H2, r1 = (H1 + 15) / 16 * 4, r2 = (H2 + 15) / 16 * 4;
     f32x4 *x_l = reinterpret_cast<f32x4 *>(rows_lds); // [F / 4][ROWS]
@@ -197,7 +205,6 @@ __global__ __launch_bounds__(64 * WAVES, 2) void step_rows_f32_kernel(StepF32 a)
         target = a.y[a.row0 + min(r0 + tid, a.rows - 1)];
         bias3 = a.theta[a.off_b3];
     }
-    const float step_count = (blockIdx.x == 0 && tid == threads - 1) ? a.theta[3 * a.P] : 0.0f;
     for (int e = tid; e < F / 4 * ROWS; e += threads) {
         const int row = e % ROWS, four = e / ROWS;
         const uint64_t col = a.row0 + min(r0 + row, a.rows - 1);
@@ -280,11 +287,6 @@ __global__ __launch_bounds__(64 * WAVES, 2) void step_rows_f32_kernel(StepF32 a)
 #pragma unroll
         for (int e = 0; e < E; ++e) d1[e] = h1[e] > 0.0f ? acc[e % J][e / J] : 0.0f;
         store_units<J>(a.d1 + (int64_t)(r0 + c) * H1, unit0, H1, d1);
-    }
-    if (blockIdx.x == 0 && tid == threads - 1) {
-        const double t = (double)step_count + a.step_in_call + 1; // t itself is advanced once, after the last step
-        a.corr[0] = (float)(1.0 - pow((double)a.beta1, t));
-        a.corr[1] = (float)(1.0 - pow((double)a.beta2, t));
     }
 }
 
@@ -541,7 +543,7 @@ int32_t eck::refit_f32_steps(const eck_model *m, const float *feat, uint64_t ld,
         a.row0 = ((uint64_t)s % nb) * (uint64_t)minibatch;
         a.step_in_call = s;
         a.report_loss = s == n_steps - 1;
-        hipLaunchKernelGGL(rows_kernel, dim3(a.padded / ROWS), dim3(64 * waves), lds, st, a);
+        hipLaunchKernelGGL(rows_kernel, dim3(a.padded / ROWS + 1), dim3(64 * waves), lds, st, a);
         hipLaunchKernelGGL(step_weights_f32_kernel, dim3(blocks2 + blocks1 + out_blocks), dim3(64 * WAVES), 0, st, a, blocks2, blocks1);
     }
     ECK_HIP_TRY(hipGetLastError());
