@@ -160,8 +160,9 @@ __device__ __forceinline__ void store_units(float *row, int unit0, int width, co
     }
 }
 
-// One block = 16 minibatch rows, and one more for Adam's bias corrections; wavefront w owns units 16 J w .. of both hidden layers, J tiles (one or two up to 256
-// units, so that the products of a layer are spread over as many wavefronts as there are).
+// One block = 16 minibatch rows, and one more block for Adam's bias corrections; wavefront w owns units 16 J w .. of both
+// hidden layers, J tiles (one or two up to 256 units, so that the products of a layer are spread over as many wavefronts
+// as there are).
 template <int J>
 __global__ __launch_bounds__(64 * WAVES, 2) void step_rows_f32_kernel(StepF32 a)
 {
