@@ -421,3 +421,24 @@ def test_reduction_parallel_spaces_batched(G):
     mixed = [mine[0], eck.Space(problems[1], eck.SPACE_SPLIT)]
     with pytest.raises(eck.EckError):
         eck.features_compute_batch(mixed, genes, n, 64, eck.F32, feat, None, legal)
+
+
+@pytest.mark.parametrize("n,ld,kinds", [(1, 1, 1), (2, 5, 1), (257, 300, 1), (4099, 4099, 3), (70001, 70008, 900), (1 << 18, 1 << 18, 1 << 17)])
+def test_dedup_clears_flags_of_many_and_few_occurrences(G, n, ld, kinds):
+    """Many candidates of few tuples, lower indices arriving late, tuples that differ in the last gene only; flags that
+    were any non-zero value come out as one."""
+    import torch
+    rng = np.random.default_rng(n)
+    genes = np.zeros((5, ld), dtype=np.uint16)
+    genes[1] = 7
+    which = rng.integers(0, kinds, ld)
+    genes[3], genes[4] = which >> 8, which & 255
+    want = oracle.dedup(np.ascontiguousarray(genes[:, :n]))
+    dev = G.to_dev(genes)
+    for overwrite in (True, False):
+        before = rng.choice(np.array([0, 1, 2, 255], dtype=np.uint8), n)
+        flags = G.to_dev(before)
+        eck.candidates_dedup(dev, n, flags, overwrite=overwrite)
+        torch.cuda.synchronize()
+        expected = want if overwrite else (want != 0) & (before != 0)
+        assert np.array_equal(flags.cpu().numpy(), np.asarray(expected, dtype=np.uint8))
