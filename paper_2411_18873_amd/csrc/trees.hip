@@ -15,6 +15,7 @@
 // evaluated in fp64 from those integers.
 #include "eck_internal.h"
 
+#include <atomic>
 #include <new>
 #include <type_traits>
 
@@ -136,8 +137,9 @@ __global__ __launch_bounds__(C *S) void tree_score_kernel(const uint8_t *__restr
     // addresses)
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds;
     const uint32_t lane_at = lds_base + (uint32_t)mine * sizeof(Cell); // of this candidate in row 0
-    // HALF: where a word's feature value is: the row's offset bits of the word, joined by the lane's place (the LDS holds
-    // nothing but the dynamic part, which starts at zero), in one instruction; else the row's number times ROW plus that
+    // HALF: where a word's feature value is: the row's offset bits of the word, joined by the lane's place, in one
+    // instruction -- right as long as the dynamic part starts at zero, which the launcher makes sure of; else the row's
+    // number times ROW plus that
     constexpr uint32_t ROW_BITS = 0xFFFFu & ~(ROW - 1u);
     auto place_of = [&](uint32_t word) {
         uint32_t at;
@@ -402,6 +404,17 @@ int32_t launch_score_as(const eck_trees *m, int n_trees, const void *feat, uint6
     // rows of whole words: sixteen bytes of a row in one load
     const int wide_loads = ((uintptr_t)feat & 3) == 0 && (FEAT_BF16 ? ld % 2 == 0 : true);
     auto kern = tree_score_kernel<FEAT_BF16, C, S>;
+    if (FEAT_BF16 && S == 1) {
+        // The walks' joined addresses need the dynamic LDS at zero, where it starts unless the kernel declares a
+        // __shared__ variable; a build in which it does is refused (asked of the runtime once per kernel).
+        static std::atomic<bool> starts_at_zero{false};
+        if (!starts_at_zero.load(std::memory_order_relaxed)) {
+            hipFuncAttributes attr;
+            ECK_HIP_TRY(hipFuncGetAttributes(&attr, reinterpret_cast<const void *>(kern)));
+            if (attr.sharedSizeBytes != 0) return ECK_EDEVICE;
+            starts_at_zero.store(true, std::memory_order_relaxed);
+        }
+    }
     ECK_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                     (int)lds));
     hipLaunchKernelGGL(kern, dim3(grid), dim3(C * S), lds, st, m->d_feat, m->d_thr, m->d_leaf, m->d_word, m->n_feat, m->depth,
