@@ -1099,11 +1099,25 @@ __global__ __launch_bounds__(1024) void tree_last_kernel(LevelArgs a, int any_tr
     }
 }
 
-// Most pairs the one-launch levels take: every block goes over all of them, which the split of the pairs over blocks in
-// the three-launch path overtakes in the end.  us per call of eight rounds at depth 6 with 64 features, one launch per
-// level against three: 512 pairs 434 / 774, 4096 534 / 968, 16384 916 / 1246, 65536 2404 / 2805 (depth 3, 32 features,
-// 32768 pairs: 704 / 781).
-constexpr uint64_t LEVEL_MAX_PAIRS = 65536;
+// Most pairs the one-launch levels take.  Every block of such a level goes over all pairs, however few features there are;
+// the three launches share the pairs between blocks, and their histograms cost less with fewer features.  So the lines lie
+// lower with fewer features, and for deeper trees, whose lower levels spread a histogram's atomics over many nodes.  They
+// are where eight rounds took as long one way as the other, the least over features of some fifty values, of six values and
+// those of sampled convolution schedules.  us per call, one launch per level against three, on schedules' features:
+//   64 features, depth 6: 512 pairs 434 / 774, 16384 916 / 1246, 65536 2404 / 2805 (depth 8: 4519 / 6439)
+//   32 features, depth 6: 8192 pairs 1.36 times as fast, 16384 1.01 times, 32768 0.94 times, 65536 0.77 times
+//   8 features: depth 6, 8192 pairs 1.24 times, 16384 0.92 times; depth 3, 32768 pairs 1.03 times or more
+//   1 feature, depth 8: 8192 pairs 0.96 times, 16384 0.72 times, 65536 0.42 times
+uint64_t level_max_pairs(const eck_trees *m)
+{
+    constexpr uint32_t MOST = 65536;
+    // by depth from three on; fewer than 16, 32, 48 and 64 features
+    constexpr uint32_t most[ECK_MAX_TREE_DEPTH - 2][4] = {{32768, 32768, 49152, MOST},  {22528, 22528, 24576, 32768},
+                                                          {16384, 16384, 19456, 28672}, {12288, 14336, 20480, 49152},
+                                                          {9216, 12288, 24576, 49152},  {7168, 11264, 28672, MOST}};
+    if (m->depth < 3 || m->n_feat >= 64) return MOST;
+    return most[m->depth - 3][m->n_feat / 16];
+}
 
 struct BoostWs {
     uint64_t scalars, y, p, gq, hq, at, bins, hist, partial, total;
@@ -1122,7 +1136,7 @@ BoostWs boost_layout(const eck_trees *m, uint64_t n_pairs)
     w.gq = o; o = up(o + n_pairs * 8);
     w.hq = o; o = up(o + n_pairs * 8);
     w.bins = o; o = up(o + n_pairs * (uint64_t)(m->n_feat + 1));
-    if (n_pairs <= LEVEL_MAX_PAIRS) {
+    if (n_pairs <= level_max_pairs(m)) {
         w.p2 = o; o = up(o + n_pairs * 4);
         w.at = o; o = up(o + n_pairs);
         w.at2 = o; o = up(o + n_pairs);
@@ -1134,7 +1148,7 @@ BoostWs boost_layout(const eck_trees *m, uint64_t n_pairs)
         w.hist = o; o = up(o + nodes * m->n_feat * BINS * 3 * 8);
         w.partial = o; o = up(o + nodes * ((m->n_feat + SPLIT_FEATS - 1) / SPLIT_FEATS) * sizeof(SplitPartial));
         // a workspace made for many pairs serves fewer, too
-        const uint64_t fewer = boost_layout(m, LEVEL_MAX_PAIRS).total;
+        const uint64_t fewer = boost_layout(m, level_max_pairs(m)).total;
         if (o < fewer) o = fewer;
     }
     w.total = o;
@@ -1343,7 +1357,7 @@ extern "C" int32_t treemodel_update(eck_trees *m, const void *feat, int32_t feat
     hipLaunchKernelGGL(tree_quality_kernel, dim3(1), dim3(1024), 0, st, p, y, n_pairs, 0, sc);
     hipLaunchKernelGGL(tree_bins_kernel, dim3(pair_blocks, m->n_feat), dim3(256), 0, st, feat, is_bf16, ld, n_pairs,
                        m->n_feat, bins);
-    if (n_pairs <= LEVEL_MAX_PAIRS) {
+    if (n_pairs <= level_max_pairs(m)) {
         rc = boost_levels(m, base, w, n_pairs, n_rounds, eta, lam, snr_out, loss_out, st);
         if (rc != ECK_OK) return rc;
         if (n_rounds > 0) {

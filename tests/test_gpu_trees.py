@@ -262,6 +262,73 @@ def test_boosting_on_any_features(G, n_pairs, n_feat, depth, rounds):
         assert abs(snr.item() - snr_o) <= 1e-6 * snr_o and abs(loss.item() - loss_o) <= 1e-6 * loss_o
 
 
+def _odd_features(n_feat, ld, seed):
+    """few and many distinct values, constants, negative, huge, infinite and NaN ones"""
+    rng = np.random.default_rng(seed)
+    x = (rng.standard_normal((n_feat, ld)) * 3 + 8).astype(np.float32)
+    x[::3] = np.round(x[::3])
+    x[1::5] = 7.25
+    odd = rng.random(x.shape) < 0.02
+    x[odd] = rng.choice(np.array([np.nan, np.inf, -np.inf, -1.0, -0.0, 63.75, 64.0, 1e30], dtype=np.float32), int(odd.sum()))
+    return x, rng
+
+
+def _boost_both(G, trees, x, bf16, e, rounds, eta, lam, arrays, have):
+    """one call on the device and on the oracle, `have` trees held before: everything equal, bit for bit"""
+    bits = (x.view(np.uint32) >> 16).astype(np.uint16)
+    ref = oracle.bf16_bits_to_f32(bits) if bf16 else x
+    nf, nt, lf = arrays
+    snr_o, loss_o = oracle.trees_boost(trees.n_feat, trees.depth, nf, nt, lf, have, rounds, trees.base_score, ref[:, :e.size], e,
+                                       eta=eta, lam=lam)
+    snr_g, loss_g = _boost_gpu(trees, G.bf16_dev(bits) if bf16 else G.to_dev(x), e, rounds, eta, lam)
+    total = have + rounds
+    assert trees.n_trees == total
+    if total:
+        a, b, c = (t.cpu().numpy() for t in trees.get())
+        assert np.array_equal(a, nf[:total]), "split features differ"
+        assert np.array_equal(b, nt[:total]), "thresholds differ"
+        assert np.array_equal(c.view(np.uint32), lf[:total].view(np.uint32)), "leaf values differ"
+    assert np.isnan(snr_g) == np.isnan(snr_o) and np.isnan(loss_g) == np.isnan(loss_o)
+    if not np.isnan(snr_o):
+        assert abs(snr_g - snr_o) <= 1e-6 * snr_o and abs(loss_g - loss_o) <= 1e-6 * loss_o
+    return ref
+
+
+@pytest.mark.parametrize("n_pairs,n_feat,depth,rounds,bf16", [(7168, 9, 8, 2, True), (7169, 9, 8, 2, True), (9217, 15, 7, 2, False),
+                                                             (12288, 5, 6, 3, False), (12289, 5, 6, 3, True), (14337, 17, 6, 2, False),
+                                                             (20480, 33, 6, 2, True), (20481, 33, 6, 2, True), (28673, 48, 5, 2, False),
+                                                             (32769, 31, 3, 3, True), (65537, 64, 6, 2, True), (65539, 70, 4, 2, False)])
+def test_boosting_on_either_side_of_the_one_launch_levels(G, n_pairs, n_feat, depth, rounds, bf16):
+    """Above a number of pairs that falls with the depth and the lack of features a level is three launches: several
+    groups of features and of nodes, bfloat16 and fp32 features, the largest levels.  The trees are the oracle's."""
+    x, rng = _odd_features(n_feat, n_pairs + (n_pairs & 1) + 2, n_pairs + n_feat)
+    e = np.exp(rng.standard_normal(n_pairs) * (4.0 if n_pairs % 2 else 0.3)).astype(np.float32)
+    trees = eck.Trees(n_feat, depth, rounds, 0.5)
+    _boost_both(G, trees, x, bf16, e, rounds, float(np.float32(0.3)), 0.5, _empty(depth, rounds), 0)
+
+
+def test_three_launch_levels_append_reject_and_report(G):
+    """At a size whose levels are three launches: trees appended to those held, an energy that is no number (empty trees,
+    predictions unchanged), and no rounds at all (the ensemble's quality, nothing appended)."""
+    n_pairs, n_feat, depth = 13001, 9, 6
+    x, rng = _odd_features(n_feat, n_pairs + 1, 3)
+    e = np.exp(rng.standard_normal(n_pairs) * 0.3).astype(np.float32)
+    eta, lam = float(np.float32(0.3)), 1.0
+    arrays = _empty(depth, 8)
+    trees = eck.Trees(n_feat, depth, 8, 0.5)
+    _boost_both(G, trees, x, True, e, 3, eta, lam, arrays, 0)
+    ref = _boost_both(G, trees, x, True, e, 2, eta, lam, arrays, 3)
+    feat = G.bf16_dev((x.view(np.uint32) >> 16).astype(np.uint16))
+    before = _score(trees, feat, n_pairs)
+    want = oracle.trees_predict(n_feat, depth, *(t[:5] for t in arrays), 0.5, ref, n=n_pairs, fp32_sequential=True)
+    assert np.array_equal(before, want.astype(np.float32))
+    bad = e.copy()
+    bad[n_pairs - 1] = np.inf
+    _boost_both(G, trees, x, True, bad, 2, eta, lam, arrays, 5)
+    assert np.array_equal(_score(trees, feat, n_pairs), before)
+    _boost_both(G, trees, x, True, e, 0, eta, lam, arrays, 7)
+
+
 def test_boosting_in_two_calls_equals_one_call_and_improves_the_fit(G):
     f32, b16, e = _pairs(4096)
     eta, lam, base = float(np.float32(0.3)), float(np.float32(1.0)), float(np.float32(0.5))
