@@ -130,7 +130,8 @@ __global__ __launch_bounds__(C *S) void tree_score_kernel(const uint8_t *__restr
     Node *node_lds = reinterpret_cast<Node *>(lds + (size_t)n_feat * ROW);         // [chunk][nodes]
     float *leaf_lds = reinterpret_cast<float *>(node_lds + (size_t)chunk_trees * stride); // fp32: [chunk][leaves]
     float *val_lds = leaf_lds + (FEAT_BF16 ? 0 : (size_t)chunk_trees * leaves);    // S > 1: [chunk][C] leaves reached
-    const int tid = threadIdx.x, within = tid % C, slot = tid / C;
+    // (the compiler cannot tell that a wavefront has one slot: left to itself it works a walk's tree addresses out per lane)
+    const int tid = threadIdx.x, within = tid % C, slot = S == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid / C);
     // this thread's candidate in the tile
     const int mine = HALF ? 2 * ((within >> 7) * 64 + (within & 63)) + ((within >> 6) & 1) : within;
     // where the dynamic LDS starts within the workgroup's allocation (the hand-written loads below take raw LDS
