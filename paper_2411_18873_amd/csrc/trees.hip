@@ -229,38 +229,75 @@ __global__ __launch_bounds__(C *S) void tree_score_kernel(const uint8_t *__restr
         float acc = base;
         for (int t0 = 0; t0 < n_trees; t0 += chunk_trees) {
             const int in_chunk = min(chunk_trees, n_trees - t0);
-            const int walked = (in_chunk + WALKS - 1) / WALKS * WALKS; // the chunk has room for whole sets of walks
             __syncthreads(); // features staged / previous chunk consumed
-            // (padding up to whole sets of walks: any tree)
+            // Four loads of a thread and array under way together (past the end: the last element again, where it already
+            // is): with one at a time a chunk takes a round trip to memory per T elements.
+            constexpr int AHEAD = 4;
             if constexpr (FEAT_BF16) {
-                for (uint32_t e = tid; e < (uint32_t)walked * leaves; e += T) {
-                    const uint64_t from = (uint64_t)t0 * leaves + min(e, (uint32_t)in_chunk * leaves - 1);
-                    const uint32_t to = (e >> depth) * stride, i = e & nodes;
-                    const float value = leaf[from];
-                    uint32_t word = words[from];
-                    // HALF: the row's byte offset in place of its number; below it, outside the mask, a one that keeps
-                    // the lower half from being zero
-                    if (HALF) word = (word & 0xFFFF0000u) | (((word & 0xFFFFu) - 1u) * ROW + 1u);
-                    node_lds[to + i] = word;
-                    node_lds[to + leaves + (nodes - i)] = __float_as_uint(value); // (mirrored, like the nodes)
+                const uint32_t count = (uint32_t)in_chunk * leaves;
+                for (uint32_t e0 = tid; e0 < count; e0 += AHEAD * T) {
+                    float value[AHEAD];
+                    uint32_t word[AHEAD];
+#pragma unroll
+                    for (int k = 0; k < AHEAD; ++k) {
+                        const uint64_t from = (uint64_t)t0 * leaves + min(e0 + k * T, count - 1);
+                        value[k] = leaf[from];
+                        word[k] = words[from];
+                    }
+#pragma unroll
+                    for (int k = 0; k < AHEAD; ++k) {
+                        const uint32_t e = min(e0 + k * T, count - 1), to = (e >> depth) * stride, i = e & nodes;
+                        // HALF: the row's byte offset in place of its number; below it, outside the mask, a one that keeps
+                        // the lower half from being zero
+                        if (HALF) word[k] = (word[k] & 0xFFFF0000u) | (((word[k] & 0xFFFFu) - 1u) * ROW + 1u);
+                        node_lds[to + i] = word[k];
+                        node_lds[to + leaves + (nodes - i)] = __float_as_uint(value[k]); // (mirrored, like the nodes)
+                    }
                 }
             } else {
-                for (uint32_t e = tid; e < (uint32_t)walked * leaves; e += T)
-                    leaf_lds[e] = leaf[(uint64_t)t0 * leaves + min(e, (uint32_t)in_chunk * leaves - 1)];
-                for (uint32_t e = tid; e < (uint32_t)walked * nodes; e += T) {
-                    const uint64_t from = (uint64_t)t0 * nodes + min(e, (uint32_t)in_chunk * nodes - 1);
-                    const uint32_t f = min((uint32_t)node_feat[from], (uint32_t)n_feat - 1u);
-                    node_lds[e] = make_uint2(__float_as_uint(node_thr[from]), f * ROW);
+                const uint32_t n_leaves = (uint32_t)in_chunk * leaves, n_nodes = (uint32_t)in_chunk * nodes;
+                for (uint32_t e0 = tid; e0 < n_leaves; e0 += AHEAD * T) {
+                    float value[AHEAD], thr[AHEAD];
+                    uint8_t f[AHEAD];
+#pragma unroll
+                    for (int k = 0; k < AHEAD; ++k) { // (a tree has one leaf more than nodes)
+                        const uint64_t node = (uint64_t)t0 * nodes + min(e0 + k * T, n_nodes - 1);
+                        value[k] = leaf[(uint64_t)t0 * leaves + min(e0 + k * T, n_leaves - 1)];
+                        thr[k] = node_thr[node];
+                        f[k] = node_feat[node];
+                    }
+#pragma unroll
+                    for (int k = 0; k < AHEAD; ++k) {
+                        leaf_lds[min(e0 + k * T, n_leaves - 1)] = value[k];
+                        node_lds[min(e0 + k * T, n_nodes - 1)] =
+                            make_uint2(__float_as_uint(thr[k]), min((uint32_t)f[k], (uint32_t)n_feat - 1u) * ROW);
+                    }
                 }
             }
             __syncthreads();
             // Nodes are numbered from 1 here, children of i: 2i and 2i + 1.
-            for (int t = slot * WALKS; t < walked; t += S * WALKS) {
+            // Bytes from the nodes (and with fp32 features, the leaves) of a set's first tree to those of each walk's; past the
+            // chunk's end the last tree is walked again.
+            uint32_t node_off[WALKS], leaf_off[WALKS];
+#pragma unroll
+            for (int w = 0; w < WALKS; ++w) {
+                node_off[w] = w * stride * sizeof(Node);
+                leaf_off[w] = w * leaves * 4;
+            }
+            for (int t = slot * WALKS; t < in_chunk; t += S * WALKS) {
+                if (t + WALKS > in_chunk) {
+#pragma unroll
+                    for (int w = 0; w < WALKS; ++w) {
+                        node_off[w] = min(w, in_chunk - 1 - t) * stride * sizeof(Node);
+                        leaf_off[w] = min(w, in_chunk - 1 - t) * leaves * 4;
+                    }
+                }
                 uint32_t i[WALKS];
 #pragma unroll
                 for (int w = 0; w < WALKS; ++w) i[w] = 1;
-                // node i of tree w at first[w * stride + i]
-                const Node *first = node_lds + (size_t)t * stride - (FEAT_BF16 ? 0 : 1);
+                const unsigned char *first_node = reinterpret_cast<const unsigned char *>(node_lds + (size_t)t * stride - (FEAT_BF16 ? 0 : 1));
+                const unsigned char *first_leaf = reinterpret_cast<const unsigned char *>(leaf_lds + (size_t)t * leaves - leaves);
+                auto node_at = [&](int w) { return reinterpret_cast<const Node *>(first_node + node_off[w])[i[w]]; };
                 // feature values at `at`, and one step of every walk
                 auto read_x = [&](const uint32_t(&at)[WALKS], float(&x)[WALKS]) {
                     if constexpr (HALF) {
@@ -324,7 +361,7 @@ __global__ __launch_bounds__(C *S) void tree_score_kernel(const uint8_t *__restr
                 for (int l = 0; l < depth; ++l) {
                     Node nd[WALKS];
 #pragma unroll
-                    for (int w = 0; w < WALKS; ++w) nd[w] = first[(size_t)w * stride + i[w]];
+                    for (int w = 0; w < WALKS; ++w) nd[w] = node_at(w);
 #pragma unroll
                     for (int w = 0; w < WALKS; ++w) {
                         if constexpr (FEAT_BF16) {
@@ -341,8 +378,8 @@ __global__ __launch_bounds__(C *S) void tree_score_kernel(const uint8_t *__restr
                 float v[WALKS]; // i in [2^d, 2^(d+1))
 #pragma unroll
                 for (int w = 0; w < WALKS; ++w) {
-                    if constexpr (FEAT_BF16) v[w] = __uint_as_float(first[(size_t)w * stride + i[w]]);
-                    else v[w] = leaf_lds[(size_t)(t + w) * leaves + i[w] - leaves];
+                    if constexpr (FEAT_BF16) v[w] = __uint_as_float(node_at(w));
+                    else v[w] = reinterpret_cast<const float *>(first_leaf + leaf_off[w])[i[w]];
                 }
                 if constexpr (S == 1) {
                     if (t + WALKS <= in_chunk) {
