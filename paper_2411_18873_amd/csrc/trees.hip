@@ -154,6 +154,25 @@ __global__ __launch_bounds__(C *S) void tree_score_kernel(const uint8_t *__restr
         else return (Cell)v;
     };
 
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
+    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+    // HALF: a NaN counts as not below any threshold, but a negative one would look negative to the walks: it is staged as a
+    // positive one.  Features hardly ever hold one, so whole rows are only looked at, and rewritten when there is one.
+    constexpr uint32_t BF16_INF = 0x7F80u;
+    auto positive_nans = [](uint32_t two) {
+        if ((two & 0x7FFFu) > BF16_INF) two &= ~0x8000u;
+        if ((two & 0x7FFF0000u) > BF16_INF << 16) two &= ~0x80000000u;
+        return two;
+    };
+
+    // sixteen bytes moved towards the first by 1 to 127 bits
+    auto shifted = [](u32x4 v, uint32_t bits) {
+        uint64_t lo = (uint64_t)v[1] << 32 | v[0], hi = (uint64_t)v[3] << 32 | v[2];
+        if (bits >= 64) lo = hi >> (bits - 64), hi = 0;
+        else lo = lo >> bits | hi << (64 - bits), hi >>= bits;
+        return u32x4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
+    };
+
     uint32_t upper[WALKS]; // HALF: feature values as they arrive, in the upper halves
 #pragma unroll
     for (int w = 0; w < WALKS; ++w) upper[w] = 0;
@@ -161,20 +180,47 @@ __global__ __launch_bounds__(C *S) void tree_score_kernel(const uint8_t *__restr
     for (uint32_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
         const uint64_t first_cand = (uint64_t)tile * C;
         __syncthreads(); // the previous tile's walks are over
-        if (wide_loads && first_cand + C <= n) {
-            // sixteen bytes of a row per load; eight loads of a thread under way together
+        if (wide_loads) {
+            // Sixteen bytes of a row per load; up to eight loads of a thread under way together, fewer for the last ones.
+            // Columns past n are not read: in the last tile a piece that would reach past them is read from further left and
+            // shifted.
             constexpr int PER = 16 / sizeof(Elem), LOADS = C / PER; // elements per load, loads per row
-            typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
-            for (int e0 = 0; e0 < n_feat * LOADS; e0 += 8 * T) {
-                u32x4 v[8];
+            const bool inside = first_cand + C <= n;
+            const uint64_t last = (n - PER) & ~(uint64_t)(FEAT_BF16 ? 1 : 0); // (whole words)
+            const int pieces = n_feat * LOADS;
+            auto stage = [&](auto loads, auto whole, int e0) {
+                constexpr int N = decltype(loads)::value;
+                constexpr bool WHOLE = decltype(whole)::value; // every piece of the tile lies inside
+                u32x4 v[N];
 #pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    const int e = min(e0 + k * T + tid, n_feat * LOADS - 1);
-                    v[k] = *reinterpret_cast<const u32x4 *>(feat_e + (uint64_t)(e / LOADS) * ld + first_cand + (e % LOADS) * PER);
+                for (int k = 0; k < N; ++k) {
+                    const int e = min(e0 + k * T + tid, pieces - 1);
+                    const uint64_t col = first_cand + (e % LOADS) * PER;
+                    v[k] = *reinterpret_cast<const u32x4 *>(feat_e + (uint64_t)(e / LOADS) * ld + (WHOLE || col < last ? col : last));
+                }
+                if constexpr (!WHOLE) {
+#pragma unroll
+                    for (int k = 0; k < N; ++k) {
+                        const uint64_t col = first_cand + min(e0 + k * T + tid, pieces - 1) % LOADS * PER;
+                        if (col > last && col < last + PER) v[k] = shifted(v[k], (uint32_t)(col - last) * (8 * sizeof(Elem)));
+                    }
+                }
+                if constexpr (HALF) {
+                    u16x2 most = {0, 0};
+#pragma unroll
+                    for (int k = 0; k < N; ++k)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) most = __builtin_elementwise_max(most, __builtin_bit_cast(u16x2, v[k][q] & 0x7FFF7FFFu));
+                    if (__any(most[0] > BF16_INF || most[1] > BF16_INF)) {
+#pragma unroll
+                        for (int k = 0; k < N; ++k)
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) v[k][q] = positive_nans(v[k][q]);
+                    }
                 }
 #pragma unroll
-                for (int k = 0; k < 8; ++k) { // (past the end: the last piece again, where it already is)
-                    const int e = min(e0 + k * T + tid, n_feat * LOADS - 1);
+                for (int k = 0; k < N; ++k) { // (past the end: the last piece again, where it already is)
+                    const int e = min(e0 + k * T + tid, pieces - 1);
                     Cell *to = x_lds + e * PER;
                     if constexpr (sizeof(Cell) == sizeof(Elem)) {
                         *reinterpret_cast<uint4 *>(to) = make_uint4(v[k][0], v[k][1], v[k][2], v[k][3]);
@@ -186,6 +232,21 @@ __global__ __launch_bounds__(C *S) void tree_score_kernel(const uint8_t *__restr
                                            __uint_as_float(v[k][3] << 16), __uint_as_float(v[k][3] & 0xFFFF0000u));
                     }
                 }
+            };
+            auto stage_all = [&](auto whole) {
+                int e0 = 0;
+                for (; pieces - e0 > 2 * T; e0 += 8 * T) stage(std::integral_constant<int, 8>(), whole, e0);
+                for (; e0 < pieces; e0 += T) stage(std::integral_constant<int, 1>(), whole, e0);
+            };
+            if (inside) stage_all(std::true_type());
+            else stage_all(std::false_type());
+            if (FEAT_BF16 && !inside && n % 2) { // the last of an odd number of columns is beyond the last whole word
+                __syncthreads();
+                for (int f = tid; f < n_feat; f += T) {
+                    Elem v = feat_e[(uint64_t)f * ld + n - 1];
+                    if constexpr (HALF) v = (uint16_t)positive_nans(v);
+                    x_lds[f * C + (int)(n - 1 - first_cand)] = cell_of(v);
+                }
             }
         } else {
             // Sixteen rows at a time, every load and store unconditional (a lane beyond n re-reads the last candidate,
@@ -196,34 +257,12 @@ __global__ __launch_bounds__(C *S) void tree_score_kernel(const uint8_t *__restr
                 Elem v[16];
 #pragma unroll
                 for (int k = 0; k < 16; ++k) v[k] = feat_e[(uint64_t)min(f0 + k, n_feat - 1) * ld + col];
+                if constexpr (HALF) {
+#pragma unroll
+                    for (int k = 0; k < 16; ++k) v[k] = (uint16_t)positive_nans(v[k]);
+                }
 #pragma unroll
                 for (int k = 0; k < 16; ++k) x_lds[min(f0 + k, n_feat - 1) * C + within] = cell_of(v[k]);
-            }
-        }
-        if constexpr (HALF) {
-            // A NaN counts as not below any threshold; a negative one would look negative to the walks.  Features hardly
-            // ever hold one, so the block looks at what it staged and rewrites it only when there is one.
-            uint32_t *flag = reinterpret_cast<uint32_t *>(node_lds); // (the trees are staged later)
-            if (tid == 0) *flag = 0;
-            __syncthreads();
-            uint32_t *pairs = reinterpret_cast<uint32_t *>(x_lds);
-            typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
-            u16x2 most = {0, 0};
-            for (int e = tid; e < n_feat * (C / 8); e += T) {
-                const uint4 v = reinterpret_cast<const uint4 *>(pairs)[e];
-                const uint32_t q[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                for (int k = 0; k < 4; ++k) most = __builtin_elementwise_max(most, __builtin_bit_cast(u16x2, q[k] & 0x7FFF7FFFu));
-            }
-            if (most[0] > 0x7F80u || most[1] > 0x7F80u) *flag = 1;
-            __syncthreads();
-            if (*flag) {
-                for (int e = tid; e < n_feat * (C / 2); e += T) {
-                    uint32_t v = pairs[e];
-                    if ((v & 0x7FFFu) > 0x7F80u) v &= ~0x8000u;
-                    if ((v & 0x7FFF0000u) > 0x7F800000u) v &= ~0x80000000u;
-                    pairs[e] = v;
-                }
             }
         }
         float acc = base;
@@ -275,33 +314,33 @@ __global__ __launch_bounds__(C *S) void tree_score_kernel(const uint8_t *__restr
                 }
             }
             __syncthreads();
-            // Nodes are numbered from 1 here, children of i: 2i and 2i + 1.
-            // Bytes from the nodes (and with fp32 features, the leaves) of a set's first tree to those of each walk's; past the
-            // chunk's end the last tree is walked again.
+            // One set of walks, from tree t of the chunk on.  Nodes are numbered from 1 here, children of i: 2i and 2i + 1.
+            // Bytes from the nodes (and with fp32 features, the leaves) of the set's first tree to those of each walk's: past
+            // the chunk's end the last tree is walked again.
             uint32_t node_off[WALKS], leaf_off[WALKS];
 #pragma unroll
             for (int w = 0; w < WALKS; ++w) {
                 node_off[w] = w * stride * sizeof(Node);
                 leaf_off[w] = w * leaves * 4;
             }
-            for (int t = slot * WALKS; t < in_chunk; t += S * WALKS) {
-                if (t + WALKS > in_chunk) {
+            auto walk = [&](auto walks, int t) {
+                constexpr int W = decltype(walks)::value;
+                if (t + W > in_chunk) {
 #pragma unroll
-                    for (int w = 0; w < WALKS; ++w) {
+                    for (int w = 0; w < W; ++w) {
                         node_off[w] = min(w, in_chunk - 1 - t) * stride * sizeof(Node);
                         leaf_off[w] = min(w, in_chunk - 1 - t) * leaves * 4;
                     }
                 }
-                uint32_t i[WALKS];
+                uint32_t i[W];
 #pragma unroll
-                for (int w = 0; w < WALKS; ++w) i[w] = 1;
+                for (int w = 0; w < W; ++w) i[w] = 1;
                 const unsigned char *first_node = reinterpret_cast<const unsigned char *>(node_lds + (size_t)t * stride - (FEAT_BF16 ? 0 : 1));
                 const unsigned char *first_leaf = reinterpret_cast<const unsigned char *>(leaf_lds + (size_t)t * leaves - leaves);
                 auto node_at = [&](int w) { return reinterpret_cast<const Node *>(first_node + node_off[w])[i[w]]; };
                 // feature values at `at`, and one step of every walk
-                auto read_x = [&](const uint32_t(&at)[WALKS], float(&x)[WALKS]) {
-                    if constexpr (HALF) {
-                        static_assert(WALKS == 8, "written out for eight walks");
+                auto read_x = [&](const uint32_t(&at)[W], float(&x)[W]) {
+                    if constexpr (HALF && W == 8) {
                         // A bfloat16 is the upper half of the float of the same value.  The load below writes
                         // only the upper half of its destination, whose lower half is zero from the start and
                         // stays so: the float arrives ready, without a shift.  The compiler has no such load, so
@@ -323,19 +362,23 @@ __global__ __launch_bounds__(C *S) void tree_score_kernel(const uint8_t *__restr
                                      : "+v"(upper[0]), "+v"(upper[1]), "+v"(upper[2]), "+v"(upper[3]), "+v"(upper[4]),
                                        "+v"(upper[5]), "+v"(upper[6]), "+v"(upper[7]));
 #pragma unroll
-                        for (int w = 0; w < WALKS; ++w) x[w] = __uint_as_float(upper[w]);
+                        for (int w = 0; w < W; ++w) x[w] = __uint_as_float(upper[w]);
                     } else {
 #pragma unroll
-                        for (int w = 0; w < WALKS; ++w) x[w] = *reinterpret_cast<const float *>(lds + (at[w] - lds_base));
+                        for (int w = 0; w < W; ++w) {
+                            const Cell v = *reinterpret_cast<const Cell *>(lds + (at[w] - lds_base));
+                            if constexpr (HALF) x[w] = __uint_as_float((uint32_t)v << 16);
+                            else x[w] = v;
+                        }
                     }
                 };
-                auto step = [&](const float(&x)[WALKS], const float(&thr)[WALKS]) {
+                auto step = [&](const float(&x)[W], const float(&thr)[W]) {
                     if constexpr (HALF) {
                         // i <- 2i + sign(x - t): x < t exactly when the difference is negative (denormals are kept, no
                         // NaN here is negative)
 #pragma unroll
-                        for (int w = 0; w < WALKS; ++w) i[w] = __builtin_amdgcn_alignbit(i[w], __float_as_uint(x[w] - thr[w]), 31u);
-                    } else {
+                        for (int w = 0; w < W; ++w) i[w] = __builtin_amdgcn_alignbit(i[w], __float_as_uint(x[w] - thr[w]), 31u);
+                    } else if constexpr (W == 8) {
                         // i <- i + i + (outcome of the comparison): a compare into a scalar mask and an add with that
                         // mask as carry-in, written out because the compiler makes three instructions of it.  Four walks
                         // per statement keep the compares four instructions ahead of the adds that read their masks.
@@ -348,22 +391,25 @@ __global__ __launch_bounds__(C *S) void tree_score_kernel(const uint8_t *__restr
         : "+v"(i[w]), "+v"(i[w + 1]), "+v"(i[w + 2]), "+v"(i[w + 3]), "=&s"(m0), "=&s"(m1), "=&s"(m2), "=&s"(m3)               \
         : "v"(x[w]), "v"(x[w + 1]), "v"(x[w + 2]), "v"(x[w + 3]), "v"(thr[w]), "v"(thr[w + 1]), "v"(thr[w + 2]), "v"(thr[w + 3]))
 #pragma unroll
-                        for (int w = 0; w < WALKS; w += 4) {
+                        for (int w = 0; w < W; w += 4) {
                             unsigned long long m0, m1, m2, m3;
                             if constexpr (FEAT_BF16) ECK_STEP("v_cmp_lt_f32_e64"); // (mirrored)
                             else ECK_STEP("v_cmp_nlt_f32_e64");
                         }
 #undef ECK_STEP
+                    } else {
+#pragma unroll
+                        for (int w = 0; w < W; ++w) i[w] = 2 * i[w] + ((x[w] < thr[w]) == FEAT_BF16 ? 1u : 0u);
                     }
                 };
-                float x[WALKS], thr[WALKS];
-                uint32_t at[WALKS];
+                float x[W], thr[W];
+                uint32_t at[W];
                 for (int l = 0; l < depth; ++l) {
-                    Node nd[WALKS];
+                    Node nd[W];
 #pragma unroll
-                    for (int w = 0; w < WALKS; ++w) nd[w] = node_at(w);
+                    for (int w = 0; w < W; ++w) nd[w] = node_at(w);
 #pragma unroll
-                    for (int w = 0; w < WALKS; ++w) {
+                    for (int w = 0; w < W; ++w) {
                         if constexpr (FEAT_BF16) {
                             thr[w] = __uint_as_float(nd[w]);
                             at[w] = place_of(nd[w]);
@@ -375,24 +421,29 @@ __global__ __launch_bounds__(C *S) void tree_score_kernel(const uint8_t *__restr
                     read_x(at, x);
                     step(x, thr);
                 }
-                float v[WALKS]; // i in [2^d, 2^(d+1))
+                float v[W]; // i in [2^d, 2^(d+1))
 #pragma unroll
-                for (int w = 0; w < WALKS; ++w) {
+                for (int w = 0; w < W; ++w) {
                     if constexpr (FEAT_BF16) v[w] = __uint_as_float(node_at(w));
                     else v[w] = reinterpret_cast<const float *>(first_leaf + leaf_off[w])[i[w]];
                 }
                 if constexpr (S == 1) {
-                    if (t + WALKS <= in_chunk) {
+                    if (t + W <= in_chunk) {
 #pragma unroll
-                        for (int w = 0; w < WALKS; ++w) acc = acc + v[w]; // tree order
+                        for (int w = 0; w < W; ++w) acc = acc + v[w]; // tree order
                     } else {
 #pragma unroll
-                        for (int w = 0; w < WALKS; ++w) acc = t + w < in_chunk ? acc + v[w] : acc;
+                        for (int w = 0; w < W; ++w) acc = t + w < in_chunk ? acc + v[w] : acc;
                     }
                 } else {
 #pragma unroll
-                    for (int w = 0; w < WALKS; ++w) val_lds[(size_t)(t + w) * C + within] = v[w];
+                    for (int w = 0; w < W; ++w) val_lds[(size_t)(t + w) * C + within] = v[w];
                 }
+            };
+            for (int t = slot * WALKS; t < in_chunk; t += S * WALKS) {
+                // (the last one or two trees of a chunk alone: six walks of eight would be for nothing)
+                if (in_chunk - t > 2) walk(std::integral_constant<int, WALKS>(), t);
+                else walk(std::integral_constant<int, 2>(), t);
             }
             if constexpr (S > 1) {
                 __syncthreads();
@@ -439,8 +490,8 @@ int32_t launch_score_as(const eck_trees *m, int n_trees, const void *feat, uint6
     const uint32_t n_tiles = (uint32_t)tiles64;
     const uint32_t want = (uint32_t)cus * (uint32_t)blocks_cu;
     const uint32_t grid = n_tiles < want ? n_tiles : want;
-    // rows of whole words: sixteen bytes of a row in one load
-    const int wide_loads = ((uintptr_t)feat & 3) == 0 && (FEAT_BF16 ? ld % 2 == 0 : true);
+    // rows of whole words, sixteen bytes or more: sixteen bytes of a row in one load
+    const int wide_loads = ((uintptr_t)feat & 3) == 0 && (FEAT_BF16 ? ld % 2 == 0 && n >= 8 : n >= 4);
     auto kern = tree_score_kernel<FEAT_BF16, C, S>;
     if (FEAT_BF16 && S == 1) {
         // The walks' joined addresses need the dynamic LDS at zero, where it starts unless the kernel declares a
