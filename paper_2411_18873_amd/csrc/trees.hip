@@ -512,12 +512,13 @@ int32_t launch_score_as(const eck_trees *m, int n_trees, const void *feat, uint6
     return ECK_OK;
 }
 
-// Up to these numbers of candidates a block takes 64 or 128 of them and shares the trees between eight or four groups of
-// threads: blocks of 512 would leave compute units idle, and every tree would wait for the one before.  us per call, 100
-// trees of depth 6, eight groups / four / one: 1000 candidates 8.5 / 14.5 / 27, 32768 11.2 / 14.7 / 28, 65536 25 / 15.5 / 28,
-// 131072 52 / 36 / 28 (the four-group figure at 65536 fills the chip exactly).
-constexpr uint64_t EIGHT_GROUPS_MOST = 32768, FOUR_GROUPS_MOST = 65536;
-
+// For few candidates a block takes 64 or 128 of them and shares the trees between eight or four groups of threads: blocks of
+// 512 would leave compute units idle, and every tree would wait for the one before.  Up to two such blocks per compute unit;
+// with sixteen trees or fewer, where six of eight groups have none, one of 64 candidates.  Deep trees and many features leave
+// no room in the LDS (depth 8 with 64 features): one group then.  us per call on 256 units, eight groups / four / one, 64
+// features, depth 6, bfloat16 unless said:
+//   100 trees: 1000 candidates 7.7 / 10.9 / 22, 32768 10.2 / 11.3 / 23, 65536 17.7 / 14.9 / 23, 131072 32 / 27 / 23
+//   16 trees: 32768 6.3 / 6.3 / 6.5, fp32 6.8 / 6.2 / 6.2; depth 8 with 8 features 7.7 / - / 7.3, 8 trees 7.0 / - / 6.3
 template <bool FEAT_BF16>
 int32_t launch_score_of(const eck_trees *m, int n_trees, const void *feat, uint64_t ld, uint64_t n, float *out, hipStream_t st)
 {
@@ -525,9 +526,12 @@ int32_t launch_score_of(const eck_trees *m, int n_trees, const void *feat, uint6
     const size_t lds_cu = 156 * 1024, elem = FEAT_BF16 ? 2 : 4, eight = WALKS * tree_lds_bytes(m->depth, false);
     if ((size_t)m->n_feat * 256 * elem + eight > lds_cu) return ECK_EUNSUPPORTED;
     const size_t small_tree = tree_lds_bytes(m->depth, FEAT_BF16);
-    if (n <= EIGHT_GROUPS_MOST && (size_t)m->n_feat * 64 * 4 + 64 * (small_tree + 64 * 4) <= lds_cu)
+    int cus = 256;
+    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, m->device);
+    const uint64_t units = (uint64_t)cus;
+    if (n <= (n_trees > 2 * WALKS ? 2 : 1) * 64 * units && (size_t)m->n_feat * 64 * 4 + 64 * (small_tree + 64 * 4) <= lds_cu)
         return launch_score_as<FEAT_BF16, 64, 8>(m, n_trees, feat, ld, n, out, st);
-    if (n <= FOUR_GROUPS_MOST && 2 * ((size_t)m->n_feat * 128 * 4 + 32 * (small_tree + 128 * 4)) <= lds_cu)
+    if (n <= 2 * 128 * units && 2 * ((size_t)m->n_feat * 128 * 4 + 32 * (small_tree + 128 * 4)) <= lds_cu)
         return launch_score_as<FEAT_BF16, 128, 4>(m, n_trees, feat, ld, n, out, st);
     if constexpr (FEAT_BF16) {
         // a row's offset has to fit a word's lower half
