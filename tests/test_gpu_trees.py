@@ -194,6 +194,35 @@ def test_scores_of_every_block_shape(G, n_feat, depth, T, n, bf16):
     assert np.array_equal(_score(trees, feat, n), want)
 
 
+@pytest.mark.parametrize("n_feat,depth", [(3, 3), (64, 6), (72, 5), (130, 4)])
+@pytest.mark.parametrize("bf16", [True, False])
+def test_scores_of_last_tiles_and_last_trees(G, n_feat, depth, bf16):
+    """Numbers of candidates on every side of a tile and of a sixteen-byte load, rows as short as they may be (nothing to
+    read behind the last candidate of the last row), and numbers of trees that leave one, two, three or more for the last
+    set of walks; more and fewer than sixteen, where the block's shape changes.  Bit for bit."""
+    rng = np.random.default_rng(n_feat)
+    most = 16400
+    bits = (rng.integers(0, 40, (n_feat, most)) * 16 + 0x3F80).astype(np.uint16)
+    special = np.array([0x0000, 0x8000, 0x7F80, 0xFF80, 0x7FC0, 0xFFC0, 0x7F81, 0xFF81], dtype=np.uint16)
+    pick = rng.random(bits.shape) < 0.05
+    bits[pick] = rng.choice(special, int(pick.sum()))
+    x = oracle.bf16_bits_to_f32(bits)
+    nodes = (1 << depth) - 1
+    for T in (1, 2, 3, 10, 17):
+        nf = rng.integers(0, n_feat, (T, nodes)).astype(np.uint8)
+        nt = x.ravel()[rng.integers(0, x.size, (T, nodes))].astype(np.float32)
+        lf = rng.standard_normal((T, 1 << depth)).astype(np.float32)
+        trees = eck.Trees(n_feat, depth, T, 0.25)
+        _load(trees, G, nf, nt, lf)
+        with np.errstate(invalid="ignore"):
+            want = oracle.trees_predict(n_feat, depth, nf, nt, lf, 0.25, x, n=most, fp32_sequential=True).astype(np.float32)
+        for n in (1, 7, 8, 9, 64, 65, 71, 127, 128, 130, 513, 16384, 16385, 16393):
+            ld = n + (n & 1)                                      # (an odd row length takes bfloat16 rows element by element)
+            cut = np.ascontiguousarray((bits if bf16 else x)[:, :ld])
+            feat = G.to_dev(cut).view(torch.bfloat16) if bf16 else G.to_dev(cut)
+            assert np.array_equal(_score(trees, feat, n), want[:n]), (T, n)
+
+
 def _boost_gpu(trees, feat_dev, e, rounds, eta, lam):
     snr = torch.zeros(1, dtype=torch.float32, device="cuda")
     loss = torch.zeros(1, dtype=torch.float32, device="cuda")
