@@ -113,7 +113,7 @@ __global__ __launch_bounds__(C *S) void tree_score_kernel(const uint8_t *__restr
                                                           const uint32_t *__restrict__ words, int n_feat, int depth,
                                                           int n_trees, int chunk_trees, float base,
                                                           const void *__restrict__ feat, uint64_t ld, uint64_t n,
-                                                          float *__restrict__ out, uint32_t n_tiles, int wide_loads)
+                                                          float *__restrict__ out, uint32_t n_tiles)
 {
     constexpr int T = C * S;
     constexpr bool HALF = FEAT_BF16 && S == 1;
@@ -154,7 +154,7 @@ __global__ __launch_bounds__(C *S) void tree_score_kernel(const uint8_t *__restr
         else return (Cell)v;
     };
 
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(2))); // (rows of odd length start anywhere)
     typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
     // HALF: a NaN counts as not below any threshold, but a negative one would look negative to the walks: it is staged as a
     // positive one.  Features hardly ever hold one, so whole rows are only looked at, and rewritten when there is one.
@@ -180,13 +180,13 @@ __global__ __launch_bounds__(C *S) void tree_score_kernel(const uint8_t *__restr
     for (uint32_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
         const uint64_t first_cand = (uint64_t)tile * C;
         __syncthreads(); // the previous tile's walks are over
-        if (wide_loads) {
+        if (n >= 16 / sizeof(Elem)) {
             // Sixteen bytes of a row per load; up to eight loads of a thread under way together, fewer for the last ones.
             // Columns past n are not read: in the last tile a piece that would reach past them is read from further left and
             // shifted.
             constexpr int PER = 16 / sizeof(Elem), LOADS = C / PER; // elements per load, loads per row
             const bool inside = first_cand + C <= n;
-            const uint64_t last = (n - PER) & ~(uint64_t)(FEAT_BF16 ? 1 : 0); // (whole words)
+            const uint64_t last = n - PER;
             const int pieces = n_feat * LOADS;
             auto stage = [&](auto loads, auto whole, int e0) {
                 constexpr int N = decltype(loads)::value;
@@ -240,15 +240,7 @@ __global__ __launch_bounds__(C *S) void tree_score_kernel(const uint8_t *__restr
             };
             if (inside) stage_all(std::true_type());
             else stage_all(std::false_type());
-            if (FEAT_BF16 && !inside && n % 2) { // the last of an odd number of columns is beyond the last whole word
-                __syncthreads();
-                for (int f = tid; f < n_feat; f += T) {
-                    Elem v = feat_e[(uint64_t)f * ld + n - 1];
-                    if constexpr (HALF) v = (uint16_t)positive_nans(v);
-                    x_lds[f * C + (int)(n - 1 - first_cand)] = cell_of(v);
-                }
-            }
-        } else {
+        } else { // rows of less than sixteen bytes
             // Sixteen rows at a time, every load and store unconditional (a lane beyond n re-reads the last candidate,
             // a row beyond n_feat the last row, and stores that same value where it already is): with a condition on
             // either side the compiler waits for each load right before its store, one round trip per feature.
@@ -490,8 +482,6 @@ int32_t launch_score_as(const eck_trees *m, int n_trees, const void *feat, uint6
     const uint32_t n_tiles = (uint32_t)tiles64;
     const uint32_t want = (uint32_t)cus * (uint32_t)blocks_cu;
     const uint32_t grid = n_tiles < want ? n_tiles : want;
-    // rows of whole words, sixteen bytes or more: sixteen bytes of a row in one load
-    const int wide_loads = ((uintptr_t)feat & 3) == 0 && (FEAT_BF16 ? ld % 2 == 0 && n >= 8 : n >= 4);
     auto kern = tree_score_kernel<FEAT_BF16, C, S>;
     if (FEAT_BF16 && S == 1) {
         // The walks' joined addresses need the dynamic LDS at zero, where it starts unless the kernel declares a
@@ -507,7 +497,7 @@ int32_t launch_score_as(const eck_trees *m, int n_trees, const void *feat, uint6
     ECK_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                     (int)lds));
     hipLaunchKernelGGL(kern, dim3(grid), dim3(C * S), lds, st, m->d_feat, m->d_thr, m->d_leaf, m->d_word, m->n_feat, m->depth,
-                       n_trees, chunk, m->base, feat, ld, n, out, n_tiles, wide_loads);
+                       n_trees, chunk, m->base, feat, ld, n, out, n_tiles);
     ECK_HIP_TRY(hipGetLastError());
     return ECK_OK;
 }

@@ -217,8 +217,7 @@ def test_scores_of_last_tiles_and_last_trees(G, n_feat, depth, bf16):
         with np.errstate(invalid="ignore"):
             want = oracle.trees_predict(n_feat, depth, nf, nt, lf, 0.25, x, n=most, fp32_sequential=True).astype(np.float32)
         for n in (1, 7, 8, 9, 64, 65, 71, 127, 128, 130, 513, 16384, 16385, 16393):
-            ld = n + (n & 1)                                      # (an odd row length takes bfloat16 rows element by element)
-            cut = np.ascontiguousarray((bits if bf16 else x)[:, :ld])
+            cut = np.ascontiguousarray((bits if bf16 else x)[:, :n])   # rows of odd length where n is odd
             feat = G.to_dev(cut).view(torch.bfloat16) if bf16 else G.to_dev(cut)
             assert np.array_equal(_score(trees, feat, n), want[:n]), (T, n)
 
