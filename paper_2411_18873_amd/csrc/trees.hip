@@ -336,8 +336,8 @@ __global__ __launch_bounds__(C *S) void tree_score_kernel(const uint8_t *__restr
                         // A bfloat16 is the upper half of the float of the same value.  The load below writes
                         // only the upper half of its destination, whose lower half is zero from the start and
                         // stays so: the float arrives ready, without a shift.  The compiler has no such load, so
-                        // it is issued here, followed by its wait; nothing but these two statements touches the
-                        // eight registers in between.
+                        // it is issued here, and waited for in the same statement: the compiler takes the eight
+                        // registers for written when it ends.
                         asm volatile("ds_read_u16_d16_hi %0, %8\n\t"
                                      "ds_read_u16_d16_hi %1, %9\n\t"
                                      "ds_read_u16_d16_hi %2, %10\n\t"
@@ -345,14 +345,12 @@ __global__ __launch_bounds__(C *S) void tree_score_kernel(const uint8_t *__restr
                                      "ds_read_u16_d16_hi %4, %12\n\t"
                                      "ds_read_u16_d16_hi %5, %13\n\t"
                                      "ds_read_u16_d16_hi %6, %14\n\t"
-                                     "ds_read_u16_d16_hi %7, %15"
-                                     : "+v"(upper[0]), "+v"(upper[1]), "+v"(upper[2]), "+v"(upper[3]), "+v"(upper[4]),
-                                       "+v"(upper[5]), "+v"(upper[6]), "+v"(upper[7])
+                                     "ds_read_u16_d16_hi %7, %15\n\t"
+                                     "s_waitcnt lgkmcnt(0)"
+                                     : "+&v"(upper[0]), "+&v"(upper[1]), "+&v"(upper[2]), "+&v"(upper[3]), "+&v"(upper[4]),
+                                       "+&v"(upper[5]), "+&v"(upper[6]), "+&v"(upper[7])
                                      : "v"(at[0]), "v"(at[1]), "v"(at[2]), "v"(at[3]), "v"(at[4]), "v"(at[5]), "v"(at[6]),
                                        "v"(at[7]));
-                        asm volatile("s_waitcnt lgkmcnt(0)"
-                                     : "+v"(upper[0]), "+v"(upper[1]), "+v"(upper[2]), "+v"(upper[3]), "+v"(upper[4]),
-                                       "+v"(upper[5]), "+v"(upper[6]), "+v"(upper[7]));
 #pragma unroll
                         for (int w = 0; w < W; ++w) x[w] = __uint_as_float(upper[w]);
                     } else {
