@@ -396,6 +396,29 @@ __device__ __forceinline__ uint32_t count_candidates(const uint64_t (&c)[ITEMS],
     return kept;
 }
 
+// The candidates among c bounded and the survivors compacted into the pool, which sh.cursor counts (it must have been set to
+// zero); returns their number.  For k <= SMALL; with more no bound can leave few enough for the direct ranking.
+template <int T>
+__device__ __forceinline__ uint32_t bound_candidates(uint64_t (&c)[ITEMS], uint32_t k, Shared<T> &sh, bool *bounded)
+{
+    uint64_t least = NONE;
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) least = c[j] < least ? c[j] : least;
+    const uint64_t bound = block_bound<T, uint64_t>(least, k, NONE, sh);
+    *bounded = bound != NONE;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+        if (c[j] > bound) c[j] = NONE; // bound == NONE keeps everything
+        if (c[j] != NONE) {
+            const uint32_t slot = atomicAdd(&sh.cursor, 1u);
+            if (slot < SMALL) sh.small.pool[slot] = c[j];
+        }
+    }
+    __syncthreads();
+    return sh.cursor;
+}
+
 // The block's share of a list of composites (the selections of the level before): held in c, bounded, the
 // survivors compacted into the pool.
 template <int T>
@@ -418,28 +441,12 @@ __device__ __forceinline__ void gather_list(const uint64_t *in, uint64_t list_le
         return;
     }
     const uint32_t per_thread = (uint32_t)((share + T - 1) / T); // <= ITEMS
-    uint64_t least = NONE;
 #pragma unroll
     for (int j = 0; j < ITEMS; ++j) {
         const uint64_t i = (uint64_t)threadIdx.x * per_thread + j;
-        uint64_t v = NONE;
-        if ((uint32_t)j < per_thread && i < share) v = in[start + i];
-        c[j] = v;
-        least = v < least ? v : least;
+        c[j] = (uint32_t)j < per_thread && i < share ? in[start + i] : NONE;
     }
-    const uint64_t bound = block_bound<T, uint64_t>(least, k, NONE, sh);
-    *bounded = bound != NONE;
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-        if (c[j] > bound) c[j] = NONE; // bound == NONE keeps everything
-        if (c[j] != NONE) {
-            const uint32_t slot = atomicAdd(&sh.cursor, 1u);
-            if (slot < SMALL) sh.small.pool[slot] = c[j];
-        }
-    }
-    __syncthreads();
-    *kept = sh.cursor;
+    *kept = bound_candidates<T>(c, k, sh, bounded);
 }
 
 // The block's chunk of T * ITEMS candidates of segment s (four consecutive candidates per load where VEC allows
@@ -603,7 +610,10 @@ __device__ __forceinline__ void select_and_emit(const SelectArgs &a, uint32_t s,
     const uint32_t k_out = a.k_energy ? a.k_energy : a.k;
     if (last_level && a.k_energy) {
         // RANK: these are the segment's fastest.  Their energies, fetched by index, take the latencies' place, and the
-        // same selection runs once more, on what the block holds: no second pass over the score arrays.
+        // same selection runs once more, on what the block holds: no second pass over the score arrays.  (More than SMALL
+        // are bounded first, as in every level: the 600 or 4096 fastest of 16384 and their 64 of least energy, 22.5 and
+        // 24.4 us without the bound, 20 with it.)
+        const bool many = !ranked && k_out <= SMALL;
         if (ranked) {
 #pragma unroll
             for (int j = 0; j < ITEMS; ++j) {
@@ -624,8 +634,9 @@ __device__ __forceinline__ void select_and_emit(const SelectArgs &a, uint32_t s,
         __syncthreads(); // everything of the first selection has been read
         for (uint32_t i = threadIdx.x; i < SMALL; i += T) sh.small.rank[i] = 0;
         if (threadIdx.x == 0) sh.cursor = 0;
-        kept = count_candidates<T>(c, sh);
-        n_selected = select_kept<T>(c, kept, false, k_out, 32 + a.idx_bits, sh, &ranked, &thr);
+        bounded = false;
+        kept = many ? bound_candidates<T>(c, k_out, sh, &bounded) : count_candidates<T>(c, sh);
+        n_selected = select_kept<T>(c, kept, bounded, k_out, 32 + a.idx_bits, sh, &ranked, &thr);
     }
     if (!last_level) {
         uint64_t *out = a.list_out + ((uint64_t)s * gridDim.x + blockIdx.x) * a.k;

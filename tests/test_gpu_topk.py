@@ -201,3 +201,24 @@ def test_rank_gate_and_energies_in_one_tournament(G, segments, seg_len, k, m, od
         want = oracle.topk(energy, latency, legal, segments, k, alpha=1.3)
     for a, b in zip(got, want):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("segments,seg_len,k,m", [(1, 6400, 1, 4096), (1, 16384, 64, 513), (3, 16384, 512, 4096), (64, 4096, 33, 600),
+                                                  (1, 1 << 18, 64, 4096), (5, 700, 17, 640)])
+@pytest.mark.parametrize("few", [False, True])
+def test_energies_of_wide_gates(G, segments, seg_len, k, m, few):
+    """More gated candidates than are ranked directly, of which the block bounds the energies before it selects: distinct
+    energies, and few distinct ones (ties by the thousand at the bound); NaN energies and unlaunchable candidates, by which a
+    segment may have fewer than the gate admits or than are asked for."""
+    rng = np.random.default_rng(seg_len + k + m)
+    n = segments * seg_len
+    e = rng.standard_normal(n).astype(np.float32)
+    lat = (rng.random(n) + 0.5).astype(np.float32)
+    if few:
+        e = np.round(e).astype(np.float32)
+        lat = np.round(lat * 8).astype(np.float32)
+        e[rng.random(n) < 0.3] = np.nan
+    legal = (rng.random(n) < 0.8).astype(np.uint8)
+    legal[n - seg_len // 2:] = 0
+    _same(G.topk_gpu(e, lat, legal, segments, k, mode=eck.SELECT_RANK, m_latency=m),
+          oracle.topk(e, lat, legal, segments, k, mode=oracle.SEL_RANK, m_latency=m))
