@@ -917,12 +917,17 @@ int32_t score_any(const eck_model *m, const void *feat, int32_t feat_dtype, uint
     //   5 blocks  (327 680)                     42.5 against 44.3 / 19.6 against 20.6
     //   7 blocks  (458 752)                     57.1 against 57.3 / 25.3 against 25.8
     //   9 blocks  (589 824)                     72.0 against 70.7 / 31.2 against 30.8
-    // With the running minima a block also costs atomics: 3 blocks at 128 units take 42.6 against 36.9 us, so there
-    // only a single block counts.
+    // With the running minima every wavefront ends in an atomic, too, twice as many at two tiles, and those on the keys of
+    // 32 neighbouring segments, one cache line, go one after the other at 10 ns each.  So there only a single block counts,
+    // and no more candidates per line than what it gains pays for.  One segment, two tiles against four: 16384 candidates
+    // 14.5 against 19.3 / 10.5 against 11.4 us, 24576 16.5 against 20.1 / 12.0 against 12.0, 49152 20.9 against 22.3 / 16.4
+    // against 14.1, 65536 24.1 against 23.6 / 19.3 against 15.6; 64 segments, 65536: 17.6 against 20.6 / 12.7 against 12.5.
     int cus = 256;
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, m->device);
     const uint64_t blocks_a_cu = (n + 256 * (uint64_t)cus - 1) / (256 * (uint64_t)cus);
-    const bool two = blocks_a_cu % 2 == 1 && blocks_a_cu <= (WITH_MIN ? 1 : 5);
+    const uint64_t key_lines = ((uint64_t)n_segments + 31) / 32;
+    const bool two = WITH_MIN ? blocks_a_cu == 1 && n <= (H1 >= 256 ? 53248 : 22528) * key_lines
+                              : blocks_a_cu % 2 == 1 && blocks_a_cu <= 5;
     const bool four = !two && feat_dtype == ECK_BF16 && ld % 4 == 0 && ((uintptr_t)feat & 7) == 0 &&
                       (!WITH_MIN || !mn.legal || ((uintptr_t)mn.legal & 3) == 0);
     if (F == 64 && H1 == 512 && H2 == 512) return launch_bf16<64, 512, 512, 2, WITH_MIN>(m, feat, feat_dtype, ld, n, score_out, mn, st);

@@ -173,3 +173,23 @@ def test_candidates_score_alike_however_many_blocks_a_call_has(G, h):
         got, keys = _score_min(G, model, feat, n, None, 1)
         assert np.array_equal(got, full[:n]), n
         assert np.array_equal(keys, _want_keys(full[:n], None, 1)), n
+
+
+@pytest.mark.parametrize("h", [128, 256])
+@pytest.mark.parametrize("segments", [1, 32, 33])
+def test_minima_where_the_tiles_of_a_wavefront_change(G, h, segments):
+    """Around the numbers of candidates, by segment keys that share a cache line, up to which a wavefront takes two tiles
+    instead of four: scores have the bits of one larger call, the minima are theirs."""
+    widths = [64, h, h, 1]
+    _, b16 = _features(5003, 64)
+    total = 107008
+    feat = G.bf16_dev(b16).repeat(1, total // 5003 + 1)[:, :total].contiguous()
+    model = G.make_model(widths, eck.BF16, synth.mlp_theta(widths, 8, bf16=True, bias_scale=0.5))
+    full = G.score_gpu(model, feat, total)
+    rng = np.random.default_rng(h)
+    legal = (rng.random(total) < 0.7).astype(np.uint8)
+    most = (53248 if h == 256 else 22528) * ((segments + 31) // 32)
+    for n in (most - most % segments, (most // segments + 1) * segments, 65536 // segments * segments):
+        got, keys = _score_min(G, model, feat, n, legal[:n], segments)
+        assert np.array_equal(got, full[:n]), n
+        assert np.array_equal(keys, _want_keys(full[:n], legal[:n], segments)), n
