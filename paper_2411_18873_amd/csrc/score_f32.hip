@@ -219,9 +219,12 @@ int32_t launch(const eck_model *m, const float *feat, uint64_t ld, uint64_t n, f
     // As few wavefronts as four tiles each allow share a layer (two tiles each: 67.7 against 63.4 us, 64-128-128-1 on
     // 131072 candidates; 165 against 153 us, 64-256-256-1 on 100003).  Four candidate tiles per wavefront quarter the
     // weight reads per candidate; fewer when blocks that large would leave compute units without two of them.  At least
-    // four wavefronts a block (63 against 94 us at 128 units), as long as that leaves enough blocks, too.
-    int cand_slots = unit_slots < 4 ? 4 / unit_slots : 1, ct = 4;
+    // four wavefronts a block (63 against 94 us at 128 units), as long as that leaves enough blocks, too.  Narrow models with
+    // many candidates wait for the features: two candidate tiles leave the registers for twice as many wavefronts (2^20
+    // candidates, four against two: 32-1-1-1 65.8 and 53.3 us, 32-64-64-1 160 and 153; 2^18 15.5 and 14.1, 41 and 41; 2^17
+    // 8.0 and 8.2, 20.1 and 22.2).
     const uint64_t tiles = (n + 15) / 16;
+    int cand_slots = unit_slots < 4 ? 4 / unit_slots : 1, ct = unit_slots == 1 && tiles >= 16384 ? 2 : 4;
     while (ct > 1 && tiles < 512ull * cand_slots * ct) ct /= 2;
     while (cand_slots > 1 && tiles < 512ull * cand_slots * ct) cand_slots /= 2;
     const int cands = 16 * ct * cand_slots, rows4 = ((F > H1 ? F : H1) + 15) / 16 * 4;

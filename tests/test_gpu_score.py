@@ -239,3 +239,18 @@ def test_set_get_state_roundtrip(G):
     model.set_state(G.to_dev(blob[:P]))
     back = model.get_state().cpu().numpy()
     assert np.array_equal(back[:P], blob[:P]) and np.all(back[P:] == 0)
+
+
+@pytest.mark.parametrize("widths", [[32, 1, 1, 1], [64, 50, 30, 1], [32, 64, 64, 1]])
+def test_narrow_fp32_models_on_many_candidates(G, widths):
+    """Two candidate tiles per wavefront from 2^18 - 15 candidates on, four below: each candidate has the bits it has in a
+    call of few, checked against the oracle."""
+    some = 5003
+    f32, _ = _features("c1" if widths[0] == 32 else "c2", some + 1, widths[0])
+    theta = synth.mlp_theta(widths, 6, bias_scale=0.4)
+    model = G.make_model(widths, eck.F32, theta)
+    few = G.score_gpu(model, G.to_dev(f32), some)
+    assert G.within(few, oracle.score(widths, theta, f32, n=some), oracle.score_magnitude(widths, theta, f32, n=some), 1e-5) <= 1.0
+    for n in (262128, 262129, 300001):
+        feat = G.to_dev(np.ascontiguousarray(f32[:, np.arange(n + 1) % some]))
+        assert np.array_equal(G.score_gpu(model, feat, n), few[np.arange(n) % some]), n
