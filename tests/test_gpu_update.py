@@ -266,3 +266,50 @@ def test_bf16_refit_every_model_shape_and_both_step_paths(G, widths, mb):
     G.update_gpu(c, feat, e, 5, mb)
     sa = a.get_state().cpu().numpy()
     assert np.array_equal(sa, b.get_state().cpu().numpy()) and np.array_equal(sa, c.get_state().cpu().numpy())
+
+
+@pytest.mark.parametrize("widths,n_pairs,minibatch", [([64, 17, 48, 1], 45, 15), ([32, 33, 5, 1], 34, 17), ([64, 128, 128, 1], 500, 250),
+                                                      ([64, 500, 497, 1], 66, 33), ([64, 300, 96, 1], 256, 128)])
+def test_fp32_later_minibatches(G, widths, n_pairs, minibatch):
+    """Every minibatch of the buffer and the first again, against the oracle: row offsets that are no multiple of a tile,
+    padding rows left by the step before, bias corrections of the second step and later.  With lr = 1e-6 a weight whose
+    vanishing gradient takes the other sign is 2e-6 off per step, 1e-4 of the weights' size at most, so the moments and
+    the last minibatch's loss are bounded as after one step (n 2^-24 of the magnitudes summed, n <= 500: 1e-3, and 5e-5
+    more in the second moment, whose factor 1 - beta2 is rounded to fp32)."""
+    F, P = widths[0], synth.param_count(widths)
+    f32, _, _ = _pairs(n_pairs + (n_pairs & 1))
+    f32 = np.ascontiguousarray(f32[:F])
+    e = synth.measured_energy(f32[:, :n_pairs], 13)
+    theta = synth.mlp_theta(widths, 3, bias_scale=0.1)
+    for steps in (2, n_pairs // minibatch + 1):
+        model = G.make_model(widths, eck.F32, theta)
+        st = _oracle_state(theta)
+        snr_g, loss_g = G.update_gpu(model, G.to_dev(f32), e, steps, minibatch, lr=1e-6)
+        snr_o, loss_o = oracle.update(widths, st, f32, e, steps, minibatch, lr=1e-6)
+        assert abs(snr_g - snr_o) <= 1e-4 * snr_o and abs(loss_g - loss_o) <= 1e-3 * loss_o
+        got = model.get_state().cpu().numpy().astype(np.float64)
+        for lo, hi, tol in ((P, 2 * P, 1e-3), (2 * P, 3 * P, 3e-3)):
+            off = np.linalg.norm(got[lo:hi] - st[lo:hi]) / np.linalg.norm(st[lo:hi])
+            assert off <= tol, (steps, off)
+        assert got[3 * P] == steps
+        # each step moves a weight by lr times a ratio of corrected moments, equal on both sides where the gradient is clear
+        clear = np.abs(st[P:2 * P]) > 1e-3 * np.abs(st[P:2 * P]).max()
+        moved_g, moved_o = got[:P] - theta, st[:P] - theta
+        assert np.abs(moved_g - moved_o)[clear].max() <= 1e-6 * 0.05 * steps + 2.0 ** -24 * steps * np.abs(theta).max()
+
+
+@pytest.mark.parametrize("widths,minibatch", [([64, 17, 48, 1], 15), ([64, 256, 256, 1], 64)])
+def test_data_error_leaves_an_fp32_model_alone(G, widths, minibatch):
+    n = 4 * minibatch
+    f32, _, e = _pairs(n + (n & 1))
+    e = e[:n].copy()
+    model = G.make_model(widths, eck.F32, synth.mlp_theta(widths, 4, bias_scale=0.1))
+    feat = G.to_dev(f32)
+    G.update_gpu(model, feat, e, 5, minibatch)                       # moments and a step count to leave alone
+    before = model.get_state().cpu().numpy()
+    for value in (0.0, -1.0, np.nan, np.inf):
+        bad = e.copy()
+        bad[n - 1] = value
+        snr, loss = G.update_gpu(model, feat, bad, 3, minibatch)
+        assert math.isnan(snr) and math.isnan(loss)
+        assert np.array_equal(model.get_state().cpu().numpy().view(np.uint32), before.view(np.uint32))
