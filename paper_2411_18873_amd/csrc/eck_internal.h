@@ -81,6 +81,10 @@ __device__ __forceinline__ uint32_t score_order_key(float x)
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+// Block barrier that orders LDS traffic only, for kernels whose wavefronts exchange nothing but LDS data: loads of weights for a
+// later phase stay on their way across it (__syncthreads() would wait for them).
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // forward pass of an fp32 model (score_f32.hip); mn: also the minima, or NULL
 int32_t score_f32(const eck_model *m, const float *feat, uint64_t ld, uint64_t n, float *out, const MinArgs *mn,
                   hipStream_t stream);

@@ -50,11 +50,6 @@ __device__ __forceinline__ int64_t frag_at(int n, int k, int K)
     return ((int64_t)((n >> 5) * (K >> 4) + (k >> 4)) * 64 + 32 * ((k >> 3) & 1) + (n & 31)) * 8 + (k & 7);
 }
 
-// Block barrier that orders LDS traffic only.  __syncthreads() also waits for every global load and store the
-// wavefront has in flight (its fence covers global memory); these kernels keep weight fragments for a later phase on
-// their way across barriers on purpose, and what they exchange between wavefronts goes through LDS alone.
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 struct StepArgs {
     const void *feat;   // [F][ld] bf16 or fp32, minibatch row r = column row0 + r
     uint64_t ld, row0;

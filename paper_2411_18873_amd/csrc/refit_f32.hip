@@ -42,10 +42,6 @@ struct StepF32 {
     float lr, beta1, beta2, eps;
 };
 
-// Block barrier that orders LDS traffic only: what the wavefronts exchange goes through LDS alone, and weights for a later
-// phase stay on their way across it (__syncthreads() would wait for them).
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 // A slice of the way back through a layer: rows = the layer's inputs, reduction = its outputs, so a lane's four steps of
 // a group are neighbours in a row of W.  Rows past K re-read the last one and are never used.
 template <int J>

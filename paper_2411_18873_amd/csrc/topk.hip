@@ -33,12 +33,6 @@ constexpr uint32_t LATMIN_PARTS = 256;   // most per-block latency minima per se
 enum Pred { PRED_PLAIN = 0, PRED_THRESHOLD = 1, PRED_RANK = 2 };
 enum Source { SRC_SCORES_VEC = 0, SRC_SCORES = 1, SRC_LIST = 2 };
 
-__device__ __forceinline__ uint32_t order_key(float x)
-{
-    const uint32_t u = __float_as_uint(x);
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-
 __device__ __forceinline__ float key_to_float(uint32_t k)
 {
     return __uint_as_float((k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k);
@@ -86,14 +80,14 @@ __global__ __launch_bounds__(256) void latmin_kernel(const float *__restrict__ l
             const float lv[4] = {l.x, l.y, l.z, l.w};
 #pragma unroll
             for (int t = 0; t < 4; ++t)
-                if (((flags >> (8 * t)) & 0xFFu) && lv[t] == lv[t]) best = min(best, order_key(lv[t]));
+                if (((flags >> (8 * t)) & 0xFFu) && lv[t] == lv[t]) best = min(best, score_order_key(lv[t]));
         }
     } else {
         for (uint64_t i = lo + threadIdx.x; i < hi; i += 256) {
             const uint64_t g = seg_base + i;
             if (legal && !legal[g]) continue;
             const float l = latency[g];
-            if (l == l) best = min(best, order_key(l));
+            if (l == l) best = min(best, score_order_key(l));
         }
     }
 #pragma unroll
@@ -118,7 +112,7 @@ __device__ __forceinline__ uint32_t feasible_key(float e, float l, float tau)
 {
     if (PRED == PRED_THRESHOLD && !(l <= tau)) return NO_KEY;
     const float value = PRED == PRED_RANK ? l : e;
-    return value != value ? NO_KEY : order_key(value);
+    return value != value ? NO_KEY : score_order_key(value);
 }
 
 // LDS of a block: the digit histogram of the radix select, or the arrays of the direct ranking (never both at
@@ -495,7 +489,7 @@ __device__ __forceinline__ void gather_scores(const SelectArgs &a, uint32_t s, S
                         const float lv[4] = {l[j].x, l[j].y, l[j].z, l[j].w};
 #pragma unroll
                         for (int t = 0; t < 4; ++t)
-                            if (i < a.seg_len && ((flags[j] >> (8 * t)) & 0xFFu) && lv[t] == lv[t]) best = min(best, order_key(lv[t]));
+                            if (i < a.seg_len && ((flags[j] >> (8 * t)) & 0xFFu) && lv[t] == lv[t]) best = min(best, score_order_key(lv[t]));
                     }
                 } else {
 #pragma unroll
@@ -503,7 +497,7 @@ __device__ __forceinline__ void gather_scores(const SelectArgs &a, uint32_t s, S
                         const uint64_t i = start + (uint64_t)j * T + threadIdx.x;
                         if (i < a.seg_len && (!a.legal || a.legal[seg_base + i])) {
                             const float v = a.latency[seg_base + i];
-                            if (v == v) best = min(best, order_key(v));
+                            if (v == v) best = min(best, score_order_key(v));
                         }
                     }
                 }
@@ -627,7 +621,7 @@ __device__ __forceinline__ void select_and_emit(const SelectArgs &a, uint32_t s,
             uint64_t next = NONE;
             if (c[j] != NONE && (ranked || c[j] <= thr)) {
                 const float e = a.energy[(uint64_t)s * a.seg_len + idx];
-                if (e == e) next = ((uint64_t)order_key(e) << a.idx_bits) | idx;
+                if (e == e) next = ((uint64_t)score_order_key(e) << a.idx_bits) | idx;
             }
             c[j] = next;
         }

@@ -716,7 +716,7 @@ __global__ __launch_bounds__(BLOCK) void tree_hist_lds_kernel(const uint8_t *__r
 // the groups' results.  The fp64 divisions of a node are thus spread over up to 64 compute units instead of
 // one.  Every cell read is set back to zero, so that the histogram buffer is clear again for the next level
 // without a pass of its own.
-struct SplitPartial {
+struct SplitRecord { // the best split of one node on one feature, or on a group of features
     double gain;
     uint32_t rank, pad;
 };
@@ -728,7 +728,7 @@ __device__ __forceinline__ bool better_split(double og, uint32_t orank, double g
 }
 
 __global__ __launch_bounds__(SPLIT_FEATS * 64) void tree_split_kernel(unsigned long long *__restrict__ hist, int n_feat,
-                                                                      double lam, SplitPartial *__restrict__ partial)
+                                                                      double lam, SplitRecord *__restrict__ partial)
 {
     const uint32_t r = blockIdx.x; // node within the level
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -809,7 +809,7 @@ __global__ __launch_bounds__(SPLIT_FEATS * 64) void tree_split_kernel(unsigned l
                 best = s_gain[w];
                 best_rank = s_rank[w];
             }
-        SplitPartial out;
+        SplitRecord out;
         out.gain = best;
         out.rank = best_rank;
         out.pad = 0;
@@ -821,18 +821,18 @@ __global__ __launch_bounds__(SPLIT_FEATS * 64) void tree_split_kernel(unsigned l
 // groups' partial results: every pair standing on a node arrives at the same (feature, threshold) and writes it
 // (equal values, so the order does not matter); nodes no pair stands on keep "does not split".
 __global__ void tree_partition_kernel(const void *__restrict__ feat, int is_bf16, uint64_t ld, uint64_t n_pairs,
-                                      const SplitPartial *__restrict__ partial, uint32_t groups, uint32_t first_node,
+                                      const SplitRecord *__restrict__ partial, uint32_t groups, uint32_t first_node,
                                       const BoostScalars *sc, uint8_t *__restrict__ nf, float *__restrict__ nt,
                                       uint32_t *__restrict__ at)
 {
     const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n_pairs) return;
     const uint32_t j = at[i];
-    const SplitPartial *mine = partial + (uint64_t)(j - first_node) * groups;
+    const SplitRecord *mine = partial + (uint64_t)(j - first_node) * groups;
     double best = 0.0;
     uint32_t best_rank = 0xFFFFFFFFu;
     for (uint32_t g = 0; g < groups; ++g) {
-        const SplitPartial o = mine[g];
+        const SplitRecord o = mine[g];
         if (better_split(o.gain, o.rank, best, best_rank)) {
             best = o.gain;
             best_rank = o.rank;
@@ -905,11 +905,6 @@ constexpr int LEVEL_THREADS = 1024;
 constexpr int LEVEL_SLOTS = 16;         // histograms of a block: one feature of up to sixteen nodes, a wavefront each
 constexpr int LEVEL_STRIDE = BINS + 1;  // cells from one histogram to the next: equal bins of neighbours in different banks
 constexpr int LEVEL_UNROLL = 4;         // pairs of a thread under way together
-
-struct SplitRecord { // the best split of one node on one feature
-    double gain;
-    uint32_t rank, pad;
-};
 
 struct SideSums {
     long long g, h;
@@ -1227,7 +1222,7 @@ BoostWs boost_layout(const eck_trees *m, uint64_t n_pairs)
     } else {
         w.at = o; o = up(o + n_pairs * 4);
         w.hist = o; o = up(o + nodes * m->n_feat * BINS * 3 * 8);
-        w.partial = o; o = up(o + nodes * ((m->n_feat + SPLIT_FEATS - 1) / SPLIT_FEATS) * sizeof(SplitPartial));
+        w.partial = o; o = up(o + nodes * ((m->n_feat + SPLIT_FEATS - 1) / SPLIT_FEATS) * sizeof(SplitRecord));
         // a workspace made for many pairs serves fewer, too
         const uint64_t fewer = boost_layout(m, level_max_pairs(m)).total;
         if (o < fewer) o = fewer;
@@ -1424,7 +1419,7 @@ extern "C" int32_t treemodel_update(eck_trees *m, const void *feat, int32_t feat
     uint32_t *at = reinterpret_cast<uint32_t *>(base + w.at);
     uint8_t *bins = reinterpret_cast<uint8_t *>(base + w.bins);
     unsigned long long *hist = reinterpret_cast<unsigned long long *>(base + w.hist);
-    SplitPartial *partial = reinterpret_cast<SplitPartial *>(base + w.partial);
+    SplitRecord *partial = reinterpret_cast<SplitRecord *>(base + w.partial);
     const unsigned split_groups = (unsigned)((m->n_feat + SPLIT_FEATS - 1) / SPLIT_FEATS);
     const int is_bf16 = feat_dtype == ECK_BF16;
     const uint32_t nodes = (1u << m->depth) - 1u, leaves = 1u << m->depth;

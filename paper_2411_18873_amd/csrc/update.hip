@@ -40,10 +40,10 @@ struct GemmArgs {
     float *C;
     int64_t ldc;
     int M, N, K;
-    const float *bias; // added per column n, or NULL
+    const float *bias; // added per column n, rounded to bf16, or NULL
     int relu;
     const float *mask; // same layout as C: result kept where mask > 0, else 0; or NULL
-    int round_a, round_b, round_c; // pass operands / result through bf16
+    int round_c; // pass the result through bf16
 };
 
 constexpr int TM = 64, TN = 64;
@@ -167,7 +167,7 @@ __global__ __launch_bounds__(256 * KG) void gemm_mfma_kernel(GemmArgs first, Gem
         const int m = m0 + wm + 8 * (q >> 2) + 4 * h + (q & 3), n = n0 + wn + c;
         if (m >= g.M || n >= g.N) continue;
         float v = acc[q];
-        if (g.bias) v += g.round_b ? through_bf16(g.bias[n]) : g.bias[n];
+        if (g.bias) v += through_bf16(g.bias[n]);
         if (g.relu) v = fmaxf(v, 0.0f);
         const int64_t at = (int64_t)m * g.ldc + n;
         if (g.mask && !(g.mask[at] > 0.0f)) v = 0.0f;
@@ -274,7 +274,7 @@ __global__ void finish_kernel(float *state, uint64_t P, int n_steps, const Scala
 // The dot product is a fixed-order tree (per-lane strided partial sums, then a butterfly).
 __global__ __launch_bounds__(256) void output_layer_kernel(const float *__restrict__ h2, const float *__restrict__ theta_w3,
                                                            const float *__restrict__ theta_b3, int H2, int rows,
-                                                           const float *__restrict__ y, int round_w,
+                                                           const float *__restrict__ y,
                                                            float *__restrict__ pred, float *__restrict__ dy,
                                                            float *__restrict__ loss_terms, float *__restrict__ d2)
 {
@@ -283,12 +283,12 @@ __global__ __launch_bounds__(256) void output_layer_kernel(const float *__restri
     const float *row = h2 + (int64_t)r * H2;
     float part = 0.0f;
     for (int j = lane; j < H2; j += 64) {
-        const float w = round_w ? through_bf16(theta_w3[j]) : theta_w3[j];
+        const float w = through_bf16(theta_w3[j]);
         part = fmaf(row[j], w, part);
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off);
-    const float b3 = round_w ? through_bf16(theta_b3[0]) : theta_b3[0];
+    const float b3 = through_bf16(theta_b3[0]);
     const float p = part + b3, t = y[r], d = p - t;
     const float g = 2.0f * d / (t * (float)rows);
     if (lane == 0) {
@@ -297,7 +297,7 @@ __global__ __launch_bounds__(256) void output_layer_kernel(const float *__restri
         loss_terms[r] = d * d / t;
     }
     for (int j = lane; j < H2; j += 64) {
-        const float w = round_w ? through_bf16(theta_w3[j]) : theta_w3[j];
+        const float w = through_bf16(theta_w3[j]);
         d2[(int64_t)r * H2 + j] = row[j] > 0.0f ? g * w : 0.0f;
     }
 }
@@ -451,32 +451,30 @@ extern "C" int32_t costmodel_update(eck_model *m, const void *feat, int32_t feat
         return ECK_OK;
     }
     const uint64_t nb = n_pairs / (uint64_t)B;
-    const int bf = 1; // the operands are rounded to bf16
     for (int s = 0; s < n_steps; ++s) {
         const uint64_t row0 = ((uint64_t)s % nb) * (uint64_t)B;
         const void *x = static_cast<const char *>(feat) + row0 * elem; // X(r, f) = feat[f*ld + row0 + r]
         GemmArgs g;
         // h1 = relu(X W1 + b1)
         g = GemmArgs{x, elem == 2, 1, (int64_t)ld, -1, theta + m->off_w[0], H1, 1, h1, H1, B, H1, F,
-                     theta + m->off_b[0], 1, nullptr, bf, bf, bf};
+                     theta + m->off_b[0], 1, nullptr, 1};
         launch_gemm(g, st);
         // h2 = relu(h1 W2 + b2)
         g = GemmArgs{h1, 0, H1, 1, -1, theta + m->off_w[1], H2, 1, h2, H2, B, H2, H1,
-                     theta + m->off_b[1], 1, nullptr, 0, bf, 0};
+                     theta + m->off_b[1], 1, nullptr, 0};
         launch_gemm(g, st);
         // output layer forward + loss + backward into d2, then its weight gradient
         hipLaunchKernelGGL(output_layer_kernel, dim3((B + 3) / 4), dim3(256), 0, st, h2, theta + m->off_w[2],
-                           theta + m->off_b[2], H2, B, y + row0, bf, pred, dy, lterm, d2);
+                           theta + m->off_b[2], H2, B, y + row0, pred, dy, lterm, d2);
         hipLaunchKernelGGL(output_grad_kernel, dim3((H2 + 1 + 63) / 64), dim3(1024), 0, st, h2, dy, H2, B,
                            grad + m->off_w[2], lterm, sc, s == n_steps - 1);
         // [gW2 ; gb2] = [h1 ; 1]^T d2
-        g = GemmArgs{h1, 0, 1, H1, H1, d2, H2, 1, grad + m->off_w[1], H2, H1 + 1, H2, B, nullptr, 0, nullptr, 0, 0, 0};
+        g = GemmArgs{h1, 0, 1, H1, H1, d2, H2, 1, grad + m->off_w[1], H2, H1 + 1, H2, B, nullptr, 0, nullptr, 0};
         // d1 = (d2 W2^T) where h1 > 0: needs d2 only, like the product above, so both go in one launch
-        const GemmArgs back{d2, 0, H2, 1, -1, theta + m->off_w[1], 1, H2, d1, H1, B, H1, H2, nullptr, 0, h1, 0, bf, 0};
+        const GemmArgs back{d2, 0, H2, 1, -1, theta + m->off_w[1], 1, H2, d1, H1, B, H1, H2, nullptr, 0, h1, 0};
         launch_gemm(g, st, &back);
         // [gW1 ; gb1] = [X ; 1]^T d1
-        g = GemmArgs{x, elem == 2, (int64_t)ld, 1, F, d1, H1, 1, grad + m->off_w[0], H1, F + 1, H1, B, nullptr, 0, nullptr,
-                     bf, 0, 0};
+        g = GemmArgs{x, elem == 2, (int64_t)ld, 1, F, d1, H1, 1, grad + m->off_w[0], H1, F + 1, H1, B, nullptr, 0, nullptr, 0};
         launch_gemm(g, st);
         hipLaunchKernelGGL(adam_kernel, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, st, theta, grad, P, s, lr, beta1,
                            beta2, eps, sc);
