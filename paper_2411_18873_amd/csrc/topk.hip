@@ -390,14 +390,11 @@ __device__ __forceinline__ uint32_t count_candidates(const uint64_t (&c)[ITEMS],
     return kept;
 }
 
-// The candidates among c bounded and the survivors compacted into the pool, which sh.cursor counts (it must have been set to
-// zero); returns their number.  For k <= SMALL; with more no bound can leave few enough for the direct ranking.
+// The candidates among c, of which `least` is the least, bounded and the survivors compacted into the pool, which sh.cursor
+// counts (it must have been set to zero); returns their number.
 template <int T>
-__device__ __forceinline__ uint32_t bound_candidates(uint64_t (&c)[ITEMS], uint32_t k, Shared<T> &sh, bool *bounded)
+__device__ __forceinline__ uint32_t bound_candidates(uint64_t (&c)[ITEMS], uint64_t least, uint32_t k, Shared<T> &sh, bool *bounded)
 {
-    uint64_t least = NONE;
-#pragma unroll
-    for (int j = 0; j < ITEMS; ++j) least = c[j] < least ? c[j] : least;
     const uint64_t bound = block_bound<T, uint64_t>(least, k, NONE, sh);
     *bounded = bound != NONE;
     __syncthreads();
@@ -435,12 +432,16 @@ __device__ __forceinline__ void gather_list(const uint64_t *in, uint64_t list_le
         return;
     }
     const uint32_t per_thread = (uint32_t)((share + T - 1) / T); // <= ITEMS
+    uint64_t least = NONE;
 #pragma unroll
     for (int j = 0; j < ITEMS; ++j) {
         const uint64_t i = (uint64_t)threadIdx.x * per_thread + j;
-        c[j] = (uint32_t)j < per_thread && i < share ? in[start + i] : NONE;
+        uint64_t v = NONE;
+        if ((uint32_t)j < per_thread && i < share) v = in[start + i];
+        c[j] = v;
+        least = v < least ? v : least;
     }
-    *kept = bound_candidates<T>(c, k, sh, bounded);
+    *kept = bound_candidates<T>(c, least, k, sh, bounded);
 }
 
 // The block's chunk of T * ITEMS candidates of segment s (four consecutive candidates per load where VEC allows
@@ -596,7 +597,8 @@ __device__ __forceinline__ void gather_scores(const SelectArgs &a, uint32_t s, S
 // last level, the result.
 template <int T>
 __device__ __forceinline__ void select_and_emit(const SelectArgs &a, uint32_t s, uint64_t (&c)[ITEMS], uint32_t kept,
-                                                bool bounded, bool last_level, Shared<T> &sh, uint64_t *sort_buf)
+                                                bool bounded, bool last_level, bool bound_energies, Shared<T> &sh,
+                                                uint64_t *sort_buf)
 {
     bool ranked;
     uint64_t thr;
@@ -604,10 +606,9 @@ __device__ __forceinline__ void select_and_emit(const SelectArgs &a, uint32_t s,
     const uint32_t k_out = a.k_energy ? a.k_energy : a.k;
     if (last_level && a.k_energy) {
         // RANK: these are the segment's fastest.  Their energies, fetched by index, take the latencies' place, and the
-        // same selection runs once more, on what the block holds: no second pass over the score arrays.  (More than SMALL
-        // are bounded first, as in every level: the 600 or 4096 fastest of 16384 and their 64 of least energy, 22.5 and
-        // 24.4 us without the bound, 20 with it.)
-        const bool many = !ranked && k_out <= SMALL;
+        // same selection runs once more, on what the block holds: no second pass over the score arrays.  More than are
+        // ranked directly are bounded first where it pays: the 600 or 4096 fastest of 16384 and their 64 of least energy, 24.5
+        // us without the bound, 20 with it; but of 1000 20.0 and 24.4, and their 512 of least energy 31.5 and 37.
         if (ranked) {
 #pragma unroll
             for (int j = 0; j < ITEMS; ++j) {
@@ -629,7 +630,14 @@ __device__ __forceinline__ void select_and_emit(const SelectArgs &a, uint32_t s,
         for (uint32_t i = threadIdx.x; i < SMALL; i += T) sh.small.rank[i] = 0;
         if (threadIdx.x == 0) sh.cursor = 0;
         bounded = false;
-        kept = many ? bound_candidates<T>(c, k_out, sh, &bounded) : count_candidates<T>(c, sh);
+        if (bound_energies && n_selected > SMALL && k_out <= SMALL / 4) {
+            uint64_t least = NONE;
+#pragma unroll
+            for (int j = 0; j < ITEMS; ++j) least = c[j] < least ? c[j] : least;
+            kept = bound_candidates<T>(c, least, k_out, sh, &bounded);
+        } else {
+            kept = count_candidates<T>(c, sh);
+        }
         n_selected = select_kept<T>(c, kept, bounded, k_out, 32 + a.idx_bits, sh, &ranked, &thr);
     }
     if (!last_level) {
@@ -734,7 +742,10 @@ __global__ __launch_bounds__(T) void select_kernel(SelectArgs a)
     if (threadIdx.x == 0) sh.cursor = 0;
     if (SRC == SRC_LIST) gather_list<T>(a.list_in + (uint64_t)s * a.list_len, a.list_len, (uint64_t)blockIdx.x * (T * ITEMS), a.k, sh, c, &kept, &bounded);
     else gather_scores<T, SRC, PRED>(a, s, sh, c, &kept, &bounded);
-    select_and_emit<T>(a, s, c, kept, bounded, gridDim.x == 1, sh, sort_buf);
+    // (RANK: a whole segment's candidates lie spread over what the threads hold, and a radix select over them is slow; a short
+    // segment or a list of selections is dense, and some wavefronts may hold none of it)
+    const bool spread = SRC != SRC_LIST && a.seg_len > 4 * (T - 64);
+    select_and_emit<T>(a, s, c, kept, bounded, gridDim.x == 1, spread, sh, sort_buf);
 }
 
 // ---------------------------------------------------------------- host side
