@@ -280,9 +280,9 @@ int32_t costmodel_score(const eck_model *model, const void *feat, int32_t feat_d
  * (Alg. 1 LatencyEvaAndPick; the latency gate of Sec. 4.3) in the pass that
  * produces the latencies, so that topk_select_known_min need not read them a
  * second time.  legal: device uint8 [n] or NULL (all legal); min_key_out:
- * device uint32 [n_segments], overwritten.  BF16 models fold the reduction
- * into the scoring kernel (integer atomics: the result does not depend on the
- * order of execution).
+ * device uint32 [n_segments], overwritten.  The reduction is part of the
+ * scoring kernel (integer atomics: the result does not depend on the order of
+ * execution).
  * Errors as costmodel_score; also EINVAL (min_key_out NULL, n_segments 0),
  * ESHAPE (n % n_segments, more than 65535 segments), EALIGN (legal odd). */
 int32_t costmodel_score_min(const eck_model *model, const void *feat, int32_t feat_dtype, uint64_t ld, uint64_t n,

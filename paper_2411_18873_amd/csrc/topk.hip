@@ -240,7 +240,7 @@ __device__ __forceinline__ void rank_pool(uint32_t kept, uint32_t k, Shared<T> &
             const uint64_t mine = sh.small.pool[entry];
             const uint32_t lo = part * span, hi = lo + span < kept ? lo + span : kept;
             uint32_t smaller = 0;
-            // (eight reads under way at a time: one by one their latency adds up, 34.2 against 30.9 us for the 128 fastest
+            // (eight reads under way at a time: one by one their latency adds up, 34 against 31 us for the 128 fastest
             // of 2^20 and their 64 of least energy, 98 against 69 us for 64 segments of 2^18)
 #pragma unroll 8
             for (uint32_t j = lo; j < hi; ++j) smaller += sh.small.pool[j] < mine;
@@ -957,7 +957,7 @@ int32_t eck::topk_select_impl(const float *energy, const float *latency, const u
         return run_tournament<PRED_THRESHOLD>(b, n_segments, vec, list_a, list_b, st);
     }
     // the m_latency fastest by latency, of these k by energy in the last level's block: two launches where a second
-    // tournament over the gated scores took four (46 against 34 us on 2^20, 128 fastest, k = 64)
+    // tournament over the gated scores took four (45 against 31 us on 2^20, 128 fastest, k = 64)
     a.k = m_latency;
     a.k_energy = k;
     return run_tournament<PRED_RANK>(a, n_segments, vec, list_a, list_b, st);

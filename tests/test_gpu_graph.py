@@ -1,4 +1,4 @@
-"""GPU: the calls of a search step recorded into a HIP graph and replayed.  Config 1 (6400 schedules, six dependent
+"""GPU: the calls of a search step recorded into a HIP graph and replayed.  Config 1 (6400 schedules, five dependent
 launches) is bound by launch latency, which is what a graph is for; the library's calls allocate nothing, clear their
 workspaces with kernels and take the stream they are given, so they can be captured.  Every replay must reproduce the
 eager result bit for bit, with eager work and synchronisations between the replays and with new inputs in the captured

@@ -59,7 +59,7 @@ def test_fp32_model_wide_and_ragged(G):
 
 @pytest.mark.parametrize("widths", [[32, 50, 30, 1], [32, 52, 36, 1], [64, 7, 1, 1], [64, 512, 4, 1]])
 def test_fp32_model_widths_with_and_without_four_units_per_thread(G, widths):
-    """hidden widths that are multiples of four take the kernel with four units per thread, others the plain one"""
+    """hidden widths that are and are not multiples of four, and one unit: whole and partial tiles in either layer"""
     n = 1000 + 37
     f32, _ = _features("c1" if widths[0] == 32 else "c2", n + 1, widths[0])
     theta = synth.mlp_theta(widths, 6, bias_scale=0.4)
