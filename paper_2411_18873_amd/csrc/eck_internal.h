@@ -85,6 +85,20 @@ __device__ __forceinline__ uint32_t score_order_key(float x)
 // later phase stay on their way across it (__syncthreads() would wait for them).
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// Adam on parameter i of a state [theta | m | v | t] (bias-corrected, no weight decay) from its values as fetched earlier:
+// writes all three, returns the new weight.  c1, c2: 1 - beta^t of the step.
+__device__ __forceinline__ float adam_one(float *theta, uint64_t P, uint64_t i, float w, float m, float v, float g,
+                                          float beta1, float beta2, float lr, float eps, float c1, float c2)
+{
+    m = beta1 * m + (1.0f - beta1) * g;
+    v = beta2 * v + (1.0f - beta2) * g * g;
+    theta[P + i] = m;
+    theta[2 * P + i] = v;
+    const float next = w - lr * (m / c1) / (sqrtf(v / c2) + eps);
+    theta[i] = next;
+    return next;
+}
+
 // forward pass of an fp32 model (score_f32.hip); mn: also the minima, or NULL
 int32_t score_f32(const eck_model *m, const float *feat, uint64_t ld, uint64_t n, float *out, const MinArgs *mn,
                   hipStream_t stream);

@@ -282,19 +282,6 @@ __global__ __launch_bounds__((H1 > H2 ? H1 : H2) * 2) void step_rows_kernel(Step
 
 // --------------------------------------------------------------------------------------------- weights kernel
 
-// Adam on one parameter (bias-corrected, no weight decay) from its state as fetched earlier; returns the new value
-__device__ __forceinline__ float adam_one(float *theta, uint64_t P, uint64_t i, float w, float m, float v, float g,
-                                          float beta1, float beta2, float lr, float eps, float c1, float c2)
-{
-    m = beta1 * m + (1.0f - beta1) * g;
-    v = beta2 * v + (1.0f - beta2) * g * g;
-    theta[P + i] = m;
-    theta[2 * P + i] = v;
-    const float next = w - lr * (m / c1) / (sqrtf(v / c2) + eps);
-    theta[i] = next;
-    return next;
-}
-
 // Blocks, in order: the 32 x 32 tiles of W2 (H1/32 x H2/32), the tiles of W1 (F/32 x H1/32), then blocks of 16
 // columns of the output layer.  A tile block: C[m][n] = sum_r A[m][r] B[r][n] with both operands stored row-index
 // fastest (A = h1^T or x^T, B = d2^T or d1^T); wavefront w sums rows [w B/4, (w+1) B/4) -- its fragments fetched

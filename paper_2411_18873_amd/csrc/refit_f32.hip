@@ -295,14 +295,9 @@ struct Moments {
 
 __device__ __forceinline__ Moments load_moments(const StepF32 &a, uint64_t i) { return {a.theta[i], a.theta[a.P + i], a.theta[2 * a.P + i]}; }
 
-// Adam on one parameter (bias-corrected, no weight decay) from its state as fetched earlier
 __device__ __forceinline__ void adam_one(const StepF32 &a, uint64_t i, Moments s, float g, float c1, float c2)
 {
-    s.m = a.beta1 * s.m + (1.0f - a.beta1) * g;
-    s.v = a.beta2 * s.v + (1.0f - a.beta2) * g * g;
-    a.theta[a.P + i] = s.m;
-    a.theta[2 * a.P + i] = s.v;
-    a.theta[i] = s.w - a.lr * (s.m / c1) / (sqrtf(s.v / c2) + a.eps);
+    (void)eck::adam_one(a.theta, a.P, i, s.w, s.m, s.v, g, a.beta1, a.beta2, a.lr, a.eps, c1, c2);
 }
 
 // Blocks, in order: the 32 x 32 tiles of W2, those of W1, then blocks of 16 columns of the output layer.  A tile block:

@@ -252,12 +252,7 @@ __global__ void adam_kernel(float *__restrict__ state, const float *__restrict__
     if (i >= P) return;
     const double t = (double)state[3 * P] + step_in_call + 1; // t itself is advanced once, after the last step
     const float c1 = (float)(1.0 - pow((double)beta1, t)), c2 = (float)(1.0 - pow((double)beta2, t));
-    const float g = grad[i];
-    const float m = beta1 * state[P + i] + (1.0f - beta1) * g;
-    const float v = beta2 * state[2 * P + i] + (1.0f - beta2) * g * g;
-    state[P + i] = m;
-    state[2 * P + i] = v;
-    state[i] -= lr * (m / c1) / (sqrtf(v / c2) + eps);
+    (void)adam_one(state, P, i, state[i], state[P + i], state[2 * P + i], grad[i], beta1, beta2, lr, eps, c1, c2);
 }
 
 __global__ void finish_kernel(float *state, uint64_t P, int n_steps, const Scalars *sc, float *snr_out, float *loss_out)
