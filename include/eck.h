@@ -293,7 +293,9 @@ int32_t costmodel_score_min(const eck_model *model, const void *feat, int32_t fe
 
 /* Bytes of workspace topk_select needs for these sizes in THRESHOLD mode or
  * without latencies, and in RANK mode with m_latency (which adds the lists of
- * the latency stage).  0 on invalid sizes. */
+ * the latency stage).  0 on invalid sizes.  Some of it (about an eighth of a
+ * byte per candidate, under a finite alpha) only saves time: calls take a
+ * workspace without it, too. */
 uint64_t topk_select_workspace_bytes(uint64_t n, uint32_t n_segments, uint32_t k);
 uint64_t topk_select_rank_workspace_bytes(uint64_t n, uint32_t n_segments, uint32_t k, uint32_t m_latency);
 
@@ -343,7 +345,8 @@ int32_t topk_select_known_min(const float *energy, const float *latency, const u
  * the library's device image (one copy per GPU, held until the process ends).
  * The call allocates and frees nothing; its kernels are those of topk_select.
  * Sizes whose workspace (topk_select_workspace_bytes /
- * topk_select_rank_workspace_bytes) exceeds ECK_TOPK_STATIC_BYTES are refused
+ * topk_select_rank_workspace_bytes, without what only saves time) exceeds
+ * ECK_TOPK_STATIC_BYTES are refused
  * with ECK_EWORKSPACE before anything is launched.  All calls on one GPU share
  * the one array: calls that overlap in time on the same GPU (different streams
  * or host threads) race and must be serialised by the caller; calls on

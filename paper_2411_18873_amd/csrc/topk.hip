@@ -29,9 +29,13 @@ constexpr int BINS = 1 << DIGIT_BITS;
 constexpr int ITEMS = ECK_TOPK_ITEMS;                // composites a thread holds
 constexpr uint64_t NONE = ~0ull;         // no candidate (a NaN score never makes a composite, so no composite is all ones)
 constexpr uint32_t LATMIN_PARTS = 256;   // most per-block latency minima per segment
+constexpr int SCAN_CHUNK = 4096;         // candidates per block of the scan under the latency gate ...
+constexpr uint32_t SCAN_LIST = 128;      // ... entries of its list ...
+constexpr uint32_t SCAN_PARTS = 1024;    // ... and most of its blocks per segment
 
 enum Pred { PRED_PLAIN = 0, PRED_THRESHOLD = 1, PRED_RANK = 2 };
-enum Source { SRC_SCORES_VEC = 0, SRC_SCORES = 1, SRC_LIST = 2 };
+// (SRC_SCANNED: the scores, of which scan_kernel listed those that may be feasible)
+enum Source { SRC_SCORES_VEC = 0, SRC_SCORES = 1, SRC_LIST = 2, SRC_SCANNED_VEC = 3, SRC_SCANNED = 4 };
 
 __device__ __forceinline__ float key_to_float(uint32_t k)
 {
@@ -48,6 +52,8 @@ struct SelectArgs {
     int alpha_inf;
     const uint32_t *lat_parts;  // THRESHOLD: [S][lat_parts_n] least latency order keys, one per block of latmin_kernel
     uint32_t lat_parts_n;       // 0: one block holds the whole segment and finds the least key itself
+    const uint32_t *listed;     // SRC_SCANNED: [S][lat_parts_n] candidates under the gate of every chunk's own minimum ...
+    const uint64_t *scan_lists; // ... and [S][lat_parts_n][SCAN_LIST] the first of them, latency bits << 32 | index
     const uint64_t *list_in;    // SRC_LIST: [S][list_len] composites of the level before, NONE where empty
     uint64_t list_len;
     uint64_t *list_out;         // not the last level: [S][gridDim.x][k]
@@ -58,7 +64,16 @@ struct SelectArgs {
     uint32_t *count_out;
 };
 
-// ---------------------------------------------------------------- latency minimum (THRESHOLD)
+// ---------------------------------------------------------------- the latency gate (THRESHOLD)
+
+// tau = L_min + (alpha - 1) |L_min|, product and sum rounded separately; `best`: the order key of L_min, all ones when
+// nothing is legal (nothing will be feasible then either)
+__device__ __forceinline__ float gate_above(uint32_t best, float slack_factor)
+{
+    if (best == 0xFFFFFFFFu) return __builtin_inff();
+    const float lmin = key_to_float(best);
+    return __fadd_rn(lmin, __fmul_rn(slack_factor, fabsf(lmin)));
+}
 
 // least order key of a legal, non-NaN latency in this block's slice of the segment; no atomics, so nothing
 // has to be initialised: every block writes its slot
@@ -98,6 +113,95 @@ __global__ __launch_bounds__(256) void latmin_kernel(const float *__restrict__ l
     if (threadIdx.x == 0) {
         for (int w = 1; w < 4; ++w) best = min(best, wave_best[w]);
         parts[(uint64_t)s * gridDim.x + blockIdx.x] = best;
+    }
+}
+
+// One pass over latencies and flags for both the least latency and what lies under the gate.  A block takes SCAN_CHUNK
+// candidates of a segment, finds their least legal latency and lists those under the gate that this least latency would
+// open: a superset of the chunk's feasible candidates as long as the segment's gate lies no higher, which the next launch
+// checks, as it does that the list has not overflowed (it reads the chunk again otherwise).  Where a gate admits few,
+// the latencies are thus read once and energies only for the listed.  Bound by the stream of latencies and flags.  64
+// segments of 2^18, alpha = 1.1: SCANUS us here and LEVELUS in the next launch, where a pass for the minima took 14.6 and the
+// next one, reading the latencies again, 21.2.
+template <bool VEC>
+__global__ __launch_bounds__(256) void scan_kernel(const float *__restrict__ latency, const uint8_t *__restrict__ legal,
+                                                   uint64_t seg_len, float slack_factor, uint32_t *__restrict__ least,
+                                                   uint32_t *__restrict__ listed, uint64_t *__restrict__ lists)
+{
+    constexpr int PER = SCAN_CHUNK / 256;
+    __shared__ uint32_t wave_best[4], cursor;
+    const uint64_t seg_base = (uint64_t)blockIdx.y * seg_len, start = (uint64_t)blockIdx.x * SCAN_CHUNK;
+    const uint64_t slot = (uint64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    if (threadIdx.x == 0) cursor = 0;
+    float l[PER];
+    uint32_t on = 0; // bit j: candidate j is legal and its latency a number
+    auto index_of = [&](int j) -> uint64_t {
+        return VEC ? start + ((uint64_t)(j / 4) * 256 + threadIdx.x) * 4 + j % 4 : start + (uint64_t)j * 256 + threadIdx.x;
+    };
+    if (VEC) {
+        // every load of the thread before anything waits; groups past the end re-read the segment's first group
+        float4 l4[PER / 4];
+        uint32_t flags[PER / 4];
+#pragma unroll
+        for (int j = 0; j < PER / 4; ++j) {
+            const uint64_t i = index_of(4 * j), g = seg_base + (i < seg_len ? i : 0);
+            flags[j] = legal ? *reinterpret_cast<const uint32_t *>(legal + g) : 0x01010101u;
+            l4[j] = *reinterpret_cast<const float4 *>(latency + g);
+        }
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            l[j] = j % 4 == 0 ? l4[j / 4].x : j % 4 == 1 ? l4[j / 4].y : j % 4 == 2 ? l4[j / 4].z : l4[j / 4].w;
+            if (((flags[j / 4] >> (8 * (j % 4))) & 0xFFu) && index_of(j) < seg_len && l[j] == l[j]) on |= 1u << j;
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const uint64_t i = index_of(j), g = seg_base + (i < seg_len ? i : 0);
+            l[j] = latency[g];
+            if (i < seg_len && (!legal || legal[g]) && l[j] == l[j]) on |= 1u << j;
+        }
+    }
+    uint32_t best = 0xFFFFFFFFu;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) best = min(best, (on >> j) & 1u ? score_order_key(l[j]) : 0xFFFFFFFFu);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) best = min(best, (uint32_t)__shfl_xor((int)best, off));
+    if ((threadIdx.x & 63) == 0) wave_best[threadIdx.x >> 6] = best;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < 4; ++w) best = min(best, wave_best[w]);
+    const float tau = gate_above(best, slack_factor);
+    uint32_t under = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j)
+        if (l[j] <= tau) under |= 1u << j;
+    under &= on;
+    // places by a prefix sum over the wavefront and one LDS atomic (an atomic per thread: 10 us more where a gate admits
+    // everything); a wavefront that overflows the list alone writes nothing
+    const uint32_t mine = (uint32_t)__popc(under);
+    uint32_t upto = mine;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t up = (uint32_t)__shfl_up((int)upto, off);
+        if ((threadIdx.x & 63) >= (uint32_t)off) upto += up;
+    }
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+    uint32_t at = 0;
+    if ((threadIdx.x & 63) == 0 && total) at = atomicAdd(&cursor, total);
+    at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+    if (total && total <= SCAN_LIST && at < SCAN_LIST) {
+        at += upto - mine;
+#pragma unroll
+        for (int j = 0; j < PER; ++j)
+            if ((under >> j) & 1u) {
+                if (at < SCAN_LIST) lists[slot * SCAN_LIST + at] = ((uint64_t)__float_as_uint(l[j]) << 32) | index_of(j);
+                ++at;
+            }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        least[slot] = best;
+        listed[slot] = cursor;
     }
 }
 
@@ -444,12 +548,25 @@ __device__ __forceinline__ void gather_list(const uint64_t *in, uint64_t list_le
     *kept = bound_candidates<T>(c, least, k, sh, bounded);
 }
 
+// the least of a key over the block
+template <int T>
+__device__ __forceinline__ uint32_t block_least(uint32_t best, Shared<T> &sh)
+{
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) best = min(best, (uint32_t)__shfl_xor((int)best, off));
+    if (threadIdx.x == 0) sh.lat_min = 0xFFFFFFFFu;
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) atomicMin(&sh.lat_min, best);
+    __syncthreads();
+    return sh.lat_min;
+}
+
 // The block's chunk of T * ITEMS candidates of segment s (four consecutive candidates per load where VEC allows
 // it): order keys of the feasible ones, bounded, the survivors turned into composites (held in c and compacted into
-// the pool).
+// the pool).  `known`: the least of the segment's minima that this thread has looked at, or null: not looked yet.
 template <int T, int SRC, int PRED>
 __device__ __forceinline__ void gather_scores(const SelectArgs &a, uint32_t s, Shared<T> &sh, uint64_t (&c)[ITEMS],
-                                              uint32_t *kept, bool *bounded)
+                                              uint32_t *kept, bool *bounded, const uint32_t *known)
 {
     constexpr bool NEED_E = PRED != PRED_RANK, NEED_L = PRED != PRED_PLAIN;
     const uint64_t seg_base = (uint64_t)s * a.seg_len;
@@ -476,12 +593,12 @@ __device__ __forceinline__ void gather_scores(const SelectArgs &a, uint32_t s, S
     // the gate, while the loads are under way
     float tau = 0.0f;
     if (PRED == PRED_THRESHOLD) {
-        // tau = L_min + (alpha - 1) |L_min|, product and sum rounded separately; L_min from the per-block minima
+        // L_min from the per-block minima
         if (a.alpha_inf) {
             tau = __builtin_inff();
         } else {
-            uint32_t best = 0xFFFFFFFFu;
-            for (uint32_t p = threadIdx.x; p < a.lat_parts_n; p += T) best = min(best, a.lat_parts[(uint64_t)s * a.lat_parts_n + p]);
+            uint32_t best = known ? *known : 0xFFFFFFFFu;
+            for (uint32_t p = threadIdx.x; !known && p < a.lat_parts_n; p += T) best = min(best, a.lat_parts[(uint64_t)s * a.lat_parts_n + p]);
             if (a.lat_parts_n == 0) { // the segment is this block's chunk
                 if (SRC == SRC_SCORES_VEC) {
 #pragma unroll
@@ -503,19 +620,7 @@ __device__ __forceinline__ void gather_scores(const SelectArgs &a, uint32_t s, S
                     }
                 }
             }
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) best = min(best, (uint32_t)__shfl_xor((int)best, off));
-            if (threadIdx.x == 0) sh.lat_min = 0xFFFFFFFFu;
-            __syncthreads();
-            if ((threadIdx.x & 63) == 0) atomicMin(&sh.lat_min, best);
-            __syncthreads();
-            best = sh.lat_min;
-            if (best == 0xFFFFFFFFu) {
-                tau = __builtin_inff(); // nothing legal: nothing will be feasible either
-            } else {
-                const float lmin = key_to_float(best);
-                tau = __fadd_rn(lmin, __fmul_rn(a.slack_factor, fabsf(lmin)));
-            }
+            tau = gate_above(block_least<T>(best, sh), a.slack_factor);
         }
     }
     // order keys of the feasible candidates (32 bits each: the index is implied by the position), their least
@@ -591,6 +696,47 @@ __device__ __forceinline__ void gather_scores(const SelectArgs &a, uint32_t s, S
     }
     __syncthreads();
     *kept = sh.cursor;
+}
+
+// The same from what scan_kernel listed of the chunk, one list entry per thread: false when the lists do not tell (one
+// overflowed, or the segment's gate lies above the one that a list was made under), the same answer in every thread.
+// *best: the least of the segment's minima among those that this thread looked at.
+template <int T>
+__device__ __forceinline__ bool gather_scanned(const SelectArgs &a, uint32_t s, Shared<T> &sh, uint64_t (&c)[ITEMS],
+                                               uint32_t *kept, bool *bounded, uint32_t *best)
+{
+    constexpr uint32_t LISTS = (uint32_t)(T * ITEMS) / SCAN_CHUNK; // of this block's chunk; at most SMALL entries
+    static_assert(LISTS * SCAN_LIST <= SMALL && LISTS * SCAN_LIST <= T, "");
+    const uint32_t *least = a.lat_parts + (uint64_t)s * a.lat_parts_n;
+    const uint32_t mine = threadIdx.x / SCAN_LIST, list = blockIdx.x * LISTS + mine;
+    const bool have = mine < LISTS && list < a.lat_parts_n;
+    uint32_t count = 0, own = 0xFFFFFFFFu;
+    uint64_t entry = 0; // (past the list's end: left over from earlier calls, not looked at)
+    if (have) {
+        count = a.listed[(uint64_t)s * a.lat_parts_n + list];
+        own = least[list];
+        entry = a.scan_lists[((uint64_t)s * a.lat_parts_n + list) * SCAN_LIST + threadIdx.x % SCAN_LIST];
+    }
+    *best = 0xFFFFFFFFu;
+    for (uint32_t p = threadIdx.x; p < a.lat_parts_n; p += T) *best = min(*best, least[p]);
+    // (where the gate admits much, the chunk's loads go out before the minima are reduced)
+    if (__syncthreads_or(count > SCAN_LIST)) return false;
+    const float tau = gate_above(block_least<T>(*best, sh), a.slack_factor);
+    // (a gate that is no number admits nothing, but compares with nothing either: read the chunk)
+    if (__syncthreads_or(have && !(tau <= gate_above(own, a.slack_factor)))) return false;
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) c[j] = NONE;
+    if (threadIdx.x % SCAN_LIST < count && __uint_as_float((uint32_t)(entry >> 32)) <= tau) {
+        const float e = a.energy[(uint64_t)s * a.seg_len + (uint32_t)entry];
+        if (e == e) {
+            c[0] = ((uint64_t)score_order_key(e) << a.idx_bits) | (uint32_t)entry;
+            sh.small.pool[atomicAdd(&sh.cursor, 1u)] = c[0];
+        }
+    }
+    __syncthreads();
+    *kept = sh.cursor;
+    *bounded = false;
+    return true;
 }
 
 // Selection among the gathered composites, then either the block's k slots of list_out (unused slots NONE) or,
@@ -741,7 +887,11 @@ __global__ __launch_bounds__(T) void select_kernel(SelectArgs a)
     for (uint32_t i = threadIdx.x; i < SMALL; i += T) sh.small.rank[i] = 0;
     if (threadIdx.x == 0) sh.cursor = 0;
     if (SRC == SRC_LIST) gather_list<T>(a.list_in + (uint64_t)s * a.list_len, a.list_len, (uint64_t)blockIdx.x * (T * ITEMS), a.k, sh, c, &kept, &bounded);
-    else gather_scores<T, SRC, PRED>(a, s, sh, c, &kept, &bounded);
+    else if (SRC == SRC_SCANNED_VEC || SRC == SRC_SCANNED) {
+        uint32_t best;
+        if (!gather_scanned<T>(a, s, sh, c, &kept, &bounded, &best))
+            gather_scores<T, SRC == SRC_SCANNED_VEC ? SRC_SCORES_VEC : SRC_SCORES, PRED>(a, s, sh, c, &kept, &bounded, &best);
+    } else gather_scores<T, SRC, PRED>(a, s, sh, c, &kept, &bounded, nullptr);
     // (RANK: a whole segment's candidates lie spread over what the threads hold, and a radix select over them is slow; a short
     // segment or a list of selections is dense, and some wavefronts may hold none of it)
     const bool spread = SRC != SRC_LIST && a.seg_len > 4 * (T - 64);
@@ -779,8 +929,17 @@ Plan plan_for(uint64_t seg_len, uint32_t n_seg, uint32_t k)
 }
 
 struct WsLayout {
-    uint64_t lat_parts, list_a, list_b, total;
+    uint64_t lat_parts, list_a, list_b, total; // what a call needs
+    uint64_t listed, scan_lists, full;         // and what scan_kernel writes, where it runs and the workspace holds it
 };
+
+// whether, and in how many chunks, scan_kernel takes a segment (every block of the next launch reads the minima of all of
+// its segment's chunks, hence the limit)
+uint64_t scan_parts(uint64_t seg_len, uint64_t blocks0)
+{
+    const uint64_t parts = (seg_len + SCAN_CHUNK - 1) / SCAN_CHUNK;
+    return blocks0 > 1 && parts <= SCAN_PARTS ? parts : 0;
+}
 
 // m_latency: the latency gate of a RANK-mode call when it does not admit the whole segment, else 0.  (The larger of the
 // two plans: a workspace made for a gate serves a call without one, too.)
@@ -797,6 +956,10 @@ WsLayout ws_layout(uint64_t seg_len, uint32_t n_seg, uint32_t k, uint32_t m_late
     w.list_a = w.lat_parts + (uint64_t)n_seg * LATMIN_PARTS * sizeof(uint32_t);
     w.list_b = w.list_a + (uint64_t)n_seg * p.list_a * sizeof(uint64_t);
     w.total = w.list_b + (uint64_t)n_seg * p.list_b * sizeof(uint64_t);
+    const uint64_t parts = m_latency ? 0 : n_seg * scan_parts(seg_len, p.blocks0);
+    w.scan_lists = (w.total + 15) & ~(uint64_t)15; // (least and listed: two words per chunk behind the lists)
+    w.listed = w.scan_lists + parts * SCAN_LIST * sizeof(uint64_t);
+    w.full = parts ? w.listed + 2 * parts * sizeof(uint32_t) : w.total;
     return w;
 }
 
@@ -821,6 +984,13 @@ void launch_select(const SelectArgs &a, uint32_t blocks, uint32_t n_seg, hipStre
 template <int T, int PRED>
 void launch_level0(const SelectArgs &a, uint32_t blocks, uint32_t n_seg, bool vec, hipStream_t st)
 {
+    if constexpr (PRED == PRED_THRESHOLD) {
+        if (a.listed) {
+            if (vec) launch_select<T, SRC_SCANNED_VEC, PRED>(a, blocks, n_seg, st);
+            else launch_select<T, SRC_SCANNED, PRED>(a, blocks, n_seg, st);
+            return;
+        }
+    }
     if (vec) launch_select<T, SRC_SCORES_VEC, PRED>(a, blocks, n_seg, st);
     else launch_select<T, SRC_SCORES, PRED>(a, blocks, n_seg, st);
 }
@@ -858,7 +1028,7 @@ int32_t run_tournament(SelectArgs a, uint32_t n_seg, bool vec, uint64_t *list_a,
 extern "C" uint64_t topk_select_workspace_bytes(uint64_t n, uint32_t n_segments, uint32_t k)
 {
     if (!sizes_ok(n, n_segments, k)) return 0;
-    return ws_layout(n / n_segments, n_segments, k, 0).total;
+    return ws_layout(n / n_segments, n_segments, k, 0).full;
 }
 
 extern "C" uint64_t topk_select_rank_workspace_bytes(uint64_t n, uint32_t n_segments, uint32_t k, uint32_t m_latency)
@@ -866,7 +1036,7 @@ extern "C" uint64_t topk_select_rank_workspace_bytes(uint64_t n, uint32_t n_segm
     if (!sizes_ok(n, n_segments, k) || m_latency == 0) return 0;
     const uint64_t seg_len = n / n_segments;
     if (m_latency < seg_len && m_latency > ECK_MAX_K) return 0;
-    return ws_layout(seg_len, n_segments, k, m_latency < seg_len ? m_latency : 0).total;
+    return ws_layout(seg_len, n_segments, k, m_latency < seg_len ? m_latency : 0).full;
 }
 
 namespace {
@@ -933,6 +1103,18 @@ int32_t eck::topk_select_impl(const float *energy, const float *latency, const u
             // L_min came with the call (one order key per segment)
             a.lat_parts = known_min;
             a.lat_parts_n = 1;
+        } else if (const uint64_t chunks = scan_parts(seg_len, plan_for(seg_len, n_segments, k).blocks0);
+                   !a.alpha_inf && chunks && ws_bytes >= w.full) {
+            // one pass over the latencies finds the least one and what its gate may admit
+            uint32_t *listed = reinterpret_cast<uint32_t *>((char *)ws + w.listed), *least = listed + n_segments * chunks;
+            uint64_t *lists = reinterpret_cast<uint64_t *>((char *)ws + w.scan_lists);
+            const dim3 grid((uint32_t)chunks, n_segments);
+            if (vec) hipLaunchKernelGGL(scan_kernel<true>, grid, dim3(256), 0, st, latency, legal, seg_len, a.slack_factor, least, listed, lists);
+            else hipLaunchKernelGGL(scan_kernel<false>, grid, dim3(256), 0, st, latency, legal, seg_len, a.slack_factor, least, listed, lists);
+            a.lat_parts = least;
+            a.lat_parts_n = (uint32_t)chunks;
+            a.listed = listed;
+            a.scan_lists = lists;
         } else if (!a.alpha_inf && plan_for(seg_len, n_segments, k).blocks0 > 1) {
             // L_min first: one pass over the latencies, a slice of the segment per block (a segment that one block
             // holds needs none: that block finds it, 4 us less)

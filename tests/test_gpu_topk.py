@@ -222,3 +222,40 @@ def test_energies_of_wide_gates(G, segments, seg_len, k, m, few):
     legal[n - seg_len // 2:] = 0
     _same(G.topk_gpu(e, lat, legal, segments, k, mode=eck.SELECT_RANK, m_latency=m),
           oracle.topk(e, lat, legal, segments, k, mode=oracle.SEL_RANK, m_latency=m))
+
+
+@pytest.mark.parametrize("segments,seg_len,k", [(1, 16385, 7), (3, 20000, 512), (64, 65536, 32), (2, 70001, 1), (5, 40000, 600)])
+@pytest.mark.parametrize("kind", ["few", "all", "rising", "falling", "negative", "none"])
+def test_candidates_listed_under_the_gate(G, segments, seg_len, k, kind):
+    """The pass that finds the least latency also lists what lies under the gate of each chunk's own minimum.  few: short
+    lists; all: every list overflows; rising, falling: only the first or the last chunk holds anything under the segment's
+    gate; negative latencies under alpha = 3.5, where a smaller minimum has the higher gate; no legal candidate in some
+    segments.  With the workspace of the query, and with one that does not hold the lists."""
+    import torch
+    rng = np.random.default_rng(seg_len + k)
+    n = segments * seg_len
+    e = rng.standard_normal(n).astype(np.float32)
+    lat = {"few": 2.0 + 0.4 * rng.standard_normal(n), "all": 10.0 + 0.05 * rng.standard_normal(n),
+           "negative": -3.0 + rng.standard_normal(n)}.get(kind, 1.0 + rng.random(n)).astype(np.float32)
+    if kind in ("rising", "falling"):
+        lat = np.sort(lat.reshape(segments, -1), axis=1)[:, ::1 if kind == "rising" else -1].reshape(-1).copy()
+    lat[rng.random(n) < 0.01] = np.nan
+    e[rng.random(n) < 0.01] = np.nan
+    legal = (rng.random(n) < 0.3).astype(np.uint8)
+    if kind == "none":
+        legal[:seg_len] = 0
+    alpha = 3.5 if kind == "negative" else 1.1
+    want = oracle.topk(e, lat, legal, segments, k, alpha=alpha)
+    _same(G.topk_gpu(e, lat, legal, segments, k, alpha=alpha), want)
+    _same(G.topk_gpu(e, lat, None, segments, k, alpha=alpha), oracle.topk(e, lat, None, segments, k, alpha=alpha))
+    # the call takes the smaller workspace that a selection without the lists needs
+    full = eck.topk_select_workspace_bytes(n, segments, k)
+    chunks = segments * -(-seg_len // 4096)
+    ed, ld, gd = G.to_dev(e), G.to_dev(lat), G.to_dev(legal)
+    idx = torch.zeros((segments, k), dtype=torch.int32, device="cuda")
+    eo = torch.zeros((segments, k), device="cuda")
+    cnt = torch.zeros(segments, dtype=torch.int32, device="cuda")
+    ws = torch.empty(full - chunks * (8 * 128 + 8), dtype=torch.uint8, device="cuda")
+    eck.topk_select(ed, ld, gd, segments, k, idx, eo, cnt, ws, alpha=alpha)
+    torch.cuda.synchronize()
+    _same((idx.cpu().numpy().view(np.uint32), eo.cpu().numpy(), cnt.cpu().numpy().view(np.uint32)), want)
