@@ -293,7 +293,7 @@ int32_t costmodel_score_min(const eck_model *model, const void *feat, int32_t fe
 
 /* Bytes of workspace topk_select needs for these sizes in THRESHOLD mode or
  * without latencies, and in RANK mode with m_latency (which adds the lists of
- * the latency stage).  0 on invalid sizes.  Some of it (about an eighth of a
+ * the latency stage).  0 on invalid sizes.  Some of it (about a quarter of a
  * byte per candidate, under a finite alpha) only saves time: calls take a
  * workspace without it, too. */
 uint64_t topk_select_workspace_bytes(uint64_t n, uint32_t n_segments, uint32_t k);

@@ -11,8 +11,8 @@
 // result.  The k smallest of a segment are among the k smallest of each chunk, so the result is exact;
 // no global atomics, no flags between blocks: blocks only meet at kernel boundaries, and the output does
 // not depend on execution order.  Inside a block: a cheap upper bound on its k-th smallest key first (from
-// the least key of every thread), then the few candidates under the bound are ranked against each other,
-// which selects and orders them at once; a radix select on LDS histograms takes over when many remain.
+// the least key of every thread), then the few candidates under the bound are sorted; a radix select on LDS histograms takes
+// over when many remain.
 #include <mutex>
 
 #include "eck_internal.h"
@@ -121,8 +121,8 @@ __global__ __launch_bounds__(256) void latmin_kernel(const float *__restrict__ l
 // open: a superset of the chunk's feasible candidates as long as the segment's gate lies no higher, which the next launch
 // checks, as it does that the list has not overflowed (it reads the chunk again otherwise).  Where a gate admits few,
 // the latencies are thus read once and energies only for the listed.  Bound by the stream of latencies and flags.  64
-// segments of 2^18, alpha = 1.1: SCANUS us here and LEVELUS in the next launch, where a pass for the minima took 14.6 and the
-// next one, reading the latencies again, 21.2.
+// segments of 2^18, alpha = 1.1: 14.5 us here and 10.2 in the next launch, where a pass for the minima alone takes 14.2 and the
+// next one, reading the latencies again, 21.2; where the gate admits everything, 15 and 35 against 14 and 33.
 template <bool VEC>
 __global__ __launch_bounds__(256) void scan_kernel(const float *__restrict__ latency, const uint8_t *__restrict__ legal,
                                                    uint64_t seg_len, float slack_factor, uint32_t *__restrict__ least,
@@ -208,7 +208,8 @@ __global__ __launch_bounds__(256) void scan_kernel(const float *__restrict__ lat
 // ---------------------------------------------------------------- one level of the tournament
 
 constexpr uint32_t NO_KEY = 0xFFFFFFFFu; // the order key of no number (only a NaN pattern maps to it): "not a candidate"
-constexpr uint32_t SMALL = 512;          // a selection among at most this many composites is ranked directly
+constexpr uint32_t SMALL = 1024;         // a selection among at most this many composites is ranked directly
+constexpr uint32_t BOUNDED = 512;        // selections of more are not bounded: at least as many lie under any bound
 
 // order key of a legal candidate's value under predicate PRED, or NO_KEY if infeasible
 template <int PRED>
@@ -225,11 +226,7 @@ template <int T>
 struct Shared {
     union {
         uint32_t hist[BINS];
-        struct {
-            uint64_t pool[SMALL];   // the composites left after the bound ...
-            uint64_t ranked[SMALL]; // ... the selection in ascending order ...
-            uint32_t rank[SMALL];   // ... and the number of smaller composites of each pool entry
-        } small;
+        uint64_t pool[SMALL]; // the composites left after the bound, then the selection in ascending order
     };
     uint32_t wave_sum[T / 64];
     uint64_t wave_bound[T / 64];
@@ -238,20 +235,46 @@ struct Shared {
     uint64_t any_composite; // radix select: one of the block's composites, to find the leading bits all of them share
 };
 
-// one compare-exchange step of a bitonic network over the 64 lanes of a wavefront
+// The value of the lane whose number differs in bit `stride`: data-parallel moves up to 8, half-row and half-wavefront swaps
+// above.  (A shuffle through the LDS crossbar takes some 100 cycles of latency, and the exchanges of a sort wait for each
+// other.)
+__device__ __forceinline__ uint32_t exchange_word(uint32_t v, uint32_t stride)
+{
+    const int x = (int)v;
+    switch (stride) {
+    case 1: return (uint32_t)__builtin_amdgcn_mov_dpp(x, 0xB1, 0xF, 0xF, true);  // quad_perm 1 0 3 2
+    case 2: return (uint32_t)__builtin_amdgcn_mov_dpp(x, 0x4E, 0xF, 0xF, true);  // quad_perm 2 3 0 1
+    case 4: return (uint32_t)__builtin_amdgcn_mov_dpp(__builtin_amdgcn_mov_dpp(x, 0x141, 0xF, 0xF, true), 0x1B, 0xF, 0xF, true); // row_half_mirror, quad_perm 3 2 1 0
+    case 8: return (uint32_t)__builtin_amdgcn_mov_dpp(x, 0x128, 0xF, 0xF, true); // row_ror:8
+    case 16: {
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false); // even rows twice, odd rows twice
+        return threadIdx.x & 16 ? r[0] : r[1];
+    }
+    default: {
+        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false); // lower half twice, upper half twice
+        return threadIdx.x & 32 ? r[0] : r[1];
+    }
+    }
+}
 template <class V>
 __device__ __forceinline__ V lane_exchange(V v, uint32_t stride);
 template <>
 __device__ __forceinline__ uint32_t lane_exchange<uint32_t>(uint32_t v, uint32_t stride)
 {
-    return (uint32_t)__shfl_xor((int)v, (int)stride);
+    return exchange_word(v, stride);
 }
 template <>
 __device__ __forceinline__ uint64_t lane_exchange<uint64_t>(uint64_t v, uint32_t stride)
 {
-    const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)v, (int)stride);
-    const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(v >> 32), (int)stride);
-    return ((uint64_t)hi << 32) | lo;
+    return ((uint64_t)exchange_word((uint32_t)(v >> 32), stride) << 32) | exchange_word((uint32_t)v, stride);
+}
+
+// the least of a wavefront's values, in every lane
+__device__ __forceinline__ uint32_t wave_least(uint32_t v)
+{
+#pragma unroll
+    for (uint32_t stride = 1; stride < 64; stride <<= 1) v = min(v, exchange_word(v, stride));
+    return v;
 }
 
 // the 64 values of a wavefront in ascending order over the lanes (bitonic sorting network)
@@ -322,40 +345,49 @@ __device__ __forceinline__ V block_bound(V least, uint32_t k, V none, Shared<T> 
     return (V)bound; // one wavefront without enough values makes `none` the bound
 }
 
-// Ranks the `kept` (<= SMALL) composites of sh.small.pool: the rank of a composite is the number of smaller ones,
-// which is selection and order at once (composites are distinct, so the ranks are a permutation).  With fewer
-// entries than threads the counting of one entry is shared by as many threads as the block can spare.  On return
-// sh.small.ranked[0 .. min(kept, k)) is the selection in ascending order.  sh.small.rank must be zero on entry.
+// Sorts the `kept` (<= SMALL) composites of sh.pool: runs of 64 in registers, a wavefront each, then the place of a
+// composite is the number of smaller ones in every run, by binary search (composites are distinct).  (Counting the smaller
+// ones entry by entry, shared between the threads, is as fast up to some 150; 512 among 256 threads took 10 us.)
 template <int T>
-__device__ __forceinline__ void rank_pool(uint32_t kept, uint32_t k, Shared<T> &sh)
+__device__ __forceinline__ void rank_pool(uint32_t kept, Shared<T> &sh)
 {
-    if (kept > T) {
-        for (uint32_t entry = threadIdx.x; entry < kept; entry += T) {
-            const uint64_t mine = sh.small.pool[entry];
-            uint32_t smaller = 0;
-            for (uint32_t j = 0; j < kept; ++j) smaller += sh.small.pool[j] < mine;
-            sh.small.rank[entry] = smaller;
-        }
-    } else if (kept) {
-        const uint32_t sharers = T / kept;                      // threads per entry, >= 1
-        const uint32_t span = (kept + sharers - 1) / sharers;   // pool entries each of them compares with
-        const uint32_t entry = threadIdx.x % kept, part = threadIdx.x / kept;
-        if (part < sharers) {
-            const uint64_t mine = sh.small.pool[entry];
-            const uint32_t lo = part * span, hi = lo + span < kept ? lo + span : kept;
-            uint32_t smaller = 0;
-            // (eight reads under way at a time: one by one their latency adds up, 34 against 31 us for the 128 fastest
-            // of 2^20 and their 64 of least energy, 98 against 69 us for 64 segments of 2^18)
-#pragma unroll 8
-            for (uint32_t j = lo; j < hi; ++j) smaller += sh.small.pool[j] < mine;
-            if (smaller) atomicAdd(&sh.small.rank[entry], smaller);
+    constexpr int W = T / 64, PER = SMALL / 64 > W ? SMALL / 64 / W : 1;
+    const uint32_t runs = (kept + 63) / 64, lane = threadIdx.x & 63;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    uint64_t v[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const uint32_t run = wave + (uint32_t)(i * W), at = 64 * run + lane;
+        v[i] = NONE;
+        if (run >= runs) continue;
+        if (at < kept) v[i] = sh.pool[at];
+        v[i] = wave_sort<uint64_t>(v[i]);
+        sh.pool[at] = v[i];
+    }
+    __syncthreads();
+    if (runs <= 1) return;
+    uint32_t place[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        place[i] = 0;
+        if (wave + (uint32_t)(i * W) >= runs) continue;
+        for (uint32_t q = 0; q < runs; q += 4) { // four searches at a time: one by one their reads wait for each other
+            uint32_t below[4] = {0, 0, 0, 0};
+#pragma unroll
+            for (uint32_t step = 32; step > 0; step >>= 1)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) below[t] += sh.pool[64 * (q + t) + below[t] + step - 1] < v[i] ? step : 0;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                below[t] += sh.pool[64 * (q + t) + below[t]] < v[i];
+                place[i] += q + t < runs ? below[t] : 0; // (past the last run: left over, not counted)
+            }
         }
     }
     __syncthreads();
-    for (uint32_t entry = threadIdx.x; entry < kept; entry += T) {
-        const uint32_t r = sh.small.rank[entry];
-        if (r < k) sh.small.ranked[r] = sh.small.pool[entry];
-    }
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+        if (v[i] != NONE) sh.pool[place[i]] = v[i];
     __syncthreads();
 }
 
@@ -445,10 +477,10 @@ __device__ uint64_t radix_threshold(const uint64_t (&c)[ITEMS], uint32_t k, uint
 }
 
 // The block's min(k, #candidates) smallest composites, c[j] = NONE standing for "no candidate" (entries above the
-// bound are set to NONE on the way).  Returns their number n.  Either *ranked is set and sh.small.ranked[0 .. n)
+// bound are set to NONE on the way).  Returns their number n.  Either *ranked is set and sh.pool[0 .. n)
 // holds them in ascending order, or it is clear and they are the composites c[j] <= *thr.
 // `kept`: how many entries of c are candidates within the bound; when at most SMALL, they are already in
-// sh.small.pool (the caller compacted them while it built c) and get ranked directly; more go through the radix
+// sh.pool (the caller compacted them while it built c) and get ranked directly; more go through the radix
 // select.  `bounded`: a bound was applied, which only happens when at least k candidates lie within it.
 template <int T>
 __device__ uint32_t select_kept(const uint64_t (&c)[ITEMS], uint32_t kept, bool bounded, uint32_t k, uint32_t total_bits,
@@ -458,7 +490,7 @@ __device__ uint32_t select_kept(const uint64_t (&c)[ITEMS], uint32_t kept, bool 
     *thr = NONE - 1; // every composite is below NONE
     *ranked = false;
     if (kept <= SMALL) {
-        rank_pool<T>(kept, k, sh);
+        rank_pool<T>(kept, sh);
         *ranked = true;
         return n;
     }
@@ -467,31 +499,41 @@ __device__ uint32_t select_kept(const uint64_t (&c)[ITEMS], uint32_t kept, bool 
     return n;
 }
 
-// Number of the block's candidates c[j] != NONE when no bound is applied (k > SMALL: at least k candidates survive
-// any bound, so the direct ranking only applies when the block has few candidates to begin with): per-thread
-// counts, added within the wavefront, one LDS atomic per wavefront.  With SMALL or fewer the candidates are
-// compacted into the pool for the direct ranking after all.  sh.cursor must have been set to zero.
-template <int T>
-__device__ __forceinline__ uint32_t count_candidates(const uint64_t (&c)[ITEMS], Shared<T> &sh)
+// Appends the composites c[j] for which take(j) to the pool, which sh.cursor counts; those past its end are counted only.
+// Places from ballots, one LDS atomic per wavefront.  (An atomic per composite, each behind the answer to the one before:
+// up to 1 us.)
+template <int T, class Take>
+__device__ __forceinline__ void append(const uint64_t (&c)[ITEMS], Take take, Shared<T> &sh)
 {
-    uint32_t mine = 0;
+    uint64_t on[ITEMS];
+    uint32_t total = 0;
 #pragma unroll
-    for (int j = 0; j < ITEMS; ++j) mine += c[j] != NONE;
+    for (int j = 0; j < ITEMS; ++j) {
+        on[j] = __ballot(take(j));
+        total += (uint32_t)__popcll(on[j]);
+    }
+    if (!total) return;
+    uint32_t base = 0;
+    if ((threadIdx.x & 63) == 0) base = atomicAdd(&sh.cursor, total);
+    base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) mine += (uint32_t)__shfl_xor((int)mine, off);
-    __syncthreads(); // the cursor's zero is in place
-    if ((threadIdx.x & 63) == 0 && mine) atomicAdd(&sh.cursor, mine);
+    for (int j = 0; j < ITEMS; ++j) {
+        if (!on[j]) continue;
+        const uint32_t at = __builtin_amdgcn_mbcnt_hi((uint32_t)(on[j] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)on[j], base));
+        if (take(j) && at < SMALL) sh.pool[at] = c[j];
+        base += (uint32_t)__popcll(on[j]);
+    }
+}
+
+// The number of the candidates c[j] != NONE, which are compacted into the pool as far as they go.  sh.cursor must have been
+// set to zero, and the pool's space be free.
+template <int T>
+__device__ __forceinline__ uint32_t keep_all(const uint64_t (&c)[ITEMS], Shared<T> &sh)
+{
     __syncthreads();
-    const uint32_t kept = sh.cursor;
-    if (kept > SMALL) return kept;
+    append<T>(c, [&](int j) { return c[j] != NONE; }, sh);
     __syncthreads();
-    if (threadIdx.x == 0) sh.cursor = 0;
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < ITEMS; ++j)
-        if (c[j] != NONE) sh.small.pool[atomicAdd(&sh.cursor, 1u)] = c[j];
-    __syncthreads();
-    return kept;
+    return sh.cursor;
 }
 
 // The candidates among c, of which `least` is the least, bounded and the survivors compacted into the pool, which sh.cursor
@@ -503,13 +545,8 @@ __device__ __forceinline__ uint32_t bound_candidates(uint64_t (&c)[ITEMS], uint6
     *bounded = bound != NONE;
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-        if (c[j] > bound) c[j] = NONE; // bound == NONE keeps everything
-        if (c[j] != NONE) {
-            const uint32_t slot = atomicAdd(&sh.cursor, 1u);
-            if (slot < SMALL) sh.small.pool[slot] = c[j];
-        }
-    }
+    for (int j = 0; j < ITEMS; ++j) c[j] = c[j] > bound ? NONE : c[j]; // bound == NONE keeps everything
+    append<T>(c, [&](int j) { return c[j] != NONE; }, sh);
     __syncthreads();
     return sh.cursor;
 }
@@ -520,11 +557,8 @@ template <int T>
 __device__ __forceinline__ void gather_list(const uint64_t *in, uint64_t list_len, uint64_t start, uint32_t k,
                                             Shared<T> &sh, uint64_t (&c)[ITEMS], uint32_t *kept, bool *bounded)
 {
-    // a thread takes consecutive entries, the block's share spread evenly over its threads: the lists of blocks
-    // that ranked their selection are ascending, so the least entries of the threads are spread over the lists'
-    // quantiles and the bound comes out tight
     const uint64_t share = list_len - start < (uint64_t)(T * ITEMS) ? list_len - start : (uint64_t)(T * ITEMS);
-    if (k > SMALL) {
+    if (k > BOUNDED) {
         // no bound can leave few enough for the direct ranking: plain coalesced loads, everything kept
 #pragma unroll
         for (int j = 0; j < ITEMS; ++j) {
@@ -532,16 +566,30 @@ __device__ __forceinline__ void gather_list(const uint64_t *in, uint64_t list_le
             c[j] = i < share ? in[start + i] : NONE;
         }
         *bounded = false;
-        *kept = count_candidates<T>(c, sh);
+        *kept = keep_all<T>(c, sh);
         return;
     }
-    const uint32_t per_thread = (uint32_t)((share + T - 1) / T); // <= ITEMS
+    // Neighbouring threads share a list, `near` of them, every near-th entry each, and the lists go round the wavefronts: the
+    // lists of blocks that ranked their selection are ascending, so the least entries of the threads are the first of each
+    // list and the bound comes out tight (64 lists of 128: 200 of 8192 entries left; 900 where a thread takes consecutive
+    // entries, which were then too many to rank directly).  Consecutive entries where whole lists do not go into the threads.
+    uint32_t per_thread = (uint32_t)((share + T - 1) / T), near = 0; // per_thread <= ITEMS
+#pragma unroll 1
+    for (uint32_t per = per_thread; per <= (uint32_t)ITEMS && !near; ++per) {
+        uint32_t n = 1;
+        while (n * per < k) n *= 2;
+        if (n <= 64 && (uint64_t)(T / n) * k >= share) near = n, per_thread = per;
+    }
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, stride = near ? near : 1;
+    const uint32_t at = near ? lane % near : 0; // in the list
+    const uint32_t first = near ? (lane / near * (T / 64) + wave) * k + at : threadIdx.x * per_thread;
+    const uint32_t room = near ? (k - at + near - 1) / near : per_thread; // (at < k + near)
     uint64_t least = NONE;
 #pragma unroll
     for (int j = 0; j < ITEMS; ++j) {
-        const uint64_t i = (uint64_t)threadIdx.x * per_thread + j;
+        const uint32_t i = first + (uint32_t)j * stride;
         uint64_t v = NONE;
-        if ((uint32_t)j < per_thread && i < share) v = in[start + i];
+        if ((uint32_t)j < per_thread && (uint32_t)j < room && i < share) v = in[start + i];
         c[j] = v;
         least = v < least ? v : least;
     }
@@ -552,8 +600,7 @@ __device__ __forceinline__ void gather_list(const uint64_t *in, uint64_t list_le
 template <int T>
 __device__ __forceinline__ uint32_t block_least(uint32_t best, Shared<T> &sh)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) best = min(best, (uint32_t)__shfl_xor((int)best, off));
+    best = wave_least(best);
     if (threadIdx.x == 0) sh.lat_min = 0xFFFFFFFFu;
     __syncthreads();
     if ((threadIdx.x & 63) == 0) atomicMin(&sh.lat_min, best);
@@ -672,11 +719,11 @@ __device__ __forceinline__ void gather_scores(const SelectArgs &a, uint32_t s, S
             key[j] = v;
         }
     }
-    if (a.k > SMALL) {
+    if (a.k > BOUNDED) {
 #pragma unroll
         for (int j = 0; j < ITEMS; ++j) c[j] = key[j] != NO_KEY ? ((uint64_t)key[j] << a.idx_bits) | index_of(j) : NONE;
         *bounded = false;
-        *kept = count_candidates<T>(c, sh);
+        *kept = keep_all<T>(c, sh);
         return;
     }
 #pragma unroll
@@ -685,15 +732,10 @@ __device__ __forceinline__ void gather_scores(const SelectArgs &a, uint32_t s, S
     *bounded = bound != NO_KEY;
     __syncthreads();
     // the candidates within the bound (all of one key, ties included) become composites
+    const uint32_t most = bound == NO_KEY ? NO_KEY - 1 : bound;
 #pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-        c[j] = NONE;
-        if (key[j] != NO_KEY && key[j] <= bound) {
-            c[j] = ((uint64_t)key[j] << a.idx_bits) | index_of(j);
-            const uint32_t slot = atomicAdd(&sh.cursor, 1u);
-            if (slot < SMALL) sh.small.pool[slot] = c[j];
-        }
-    }
+    for (int j = 0; j < ITEMS; ++j) c[j] = key[j] <= most ? ((uint64_t)key[j] << a.idx_bits) | index_of(j) : NONE;
+    append<T>(c, [&](int j) { return key[j] <= most; }, sh);
     __syncthreads();
     *kept = sh.cursor;
 }
@@ -706,7 +748,7 @@ __device__ __forceinline__ bool gather_scanned(const SelectArgs &a, uint32_t s, 
                                                uint32_t *kept, bool *bounded, uint32_t *best)
 {
     constexpr uint32_t LISTS = (uint32_t)(T * ITEMS) / SCAN_CHUNK; // of this block's chunk; at most SMALL entries
-    static_assert(LISTS * SCAN_LIST <= SMALL && LISTS * SCAN_LIST <= T, "");
+    static_assert(LISTS * SCAN_LIST <= SMALL && LISTS * SCAN_LIST <= (uint32_t)T, "");
     const uint32_t *least = a.lat_parts + (uint64_t)s * a.lat_parts_n;
     const uint32_t mine = threadIdx.x / SCAN_LIST, list = blockIdx.x * LISTS + mine;
     const bool have = mine < LISTS && list < a.lat_parts_n;
@@ -730,7 +772,7 @@ __device__ __forceinline__ bool gather_scanned(const SelectArgs &a, uint32_t s, 
         const float e = a.energy[(uint64_t)s * a.seg_len + (uint32_t)entry];
         if (e == e) {
             c[0] = ((uint64_t)score_order_key(e) << a.idx_bits) | (uint32_t)entry;
-            sh.small.pool[atomicAdd(&sh.cursor, 1u)] = c[0];
+            sh.pool[atomicAdd(&sh.cursor, 1u)] = c[0];
         }
     }
     __syncthreads();
@@ -753,13 +795,13 @@ __device__ __forceinline__ void select_and_emit(const SelectArgs &a, uint32_t s,
     if (last_level && a.k_energy) {
         // RANK: these are the segment's fastest.  Their energies, fetched by index, take the latencies' place, and the
         // same selection runs once more, on what the block holds: no second pass over the score arrays.  More than are
-        // ranked directly are bounded first where it pays: the 600 or 4096 fastest of 16384 and their 64 of least energy, 24.5
-        // us without the bound, 20 with it; but of 1000 20.0 and 24.4, and their 512 of least energy 31.5 and 37.
+        // sorted directly are bounded first where it pays: the 1100 or 4096 fastest of 16384 and their 64 of least energy, 24.4
+        // us without the bound, 20.4 with it.
         if (ranked) {
 #pragma unroll
             for (int j = 0; j < ITEMS; ++j) {
                 const uint32_t i = (uint32_t)j * T + threadIdx.x;
-                c[j] = i < n_selected ? sh.small.ranked[i] : NONE; // (at most SMALL)
+                c[j] = i < n_selected ? sh.pool[i] : NONE; // (at most SMALL)
             }
         }
 #pragma unroll
@@ -773,23 +815,22 @@ __device__ __forceinline__ void select_and_emit(const SelectArgs &a, uint32_t s,
             c[j] = next;
         }
         __syncthreads(); // everything of the first selection has been read
-        for (uint32_t i = threadIdx.x; i < SMALL; i += T) sh.small.rank[i] = 0;
         if (threadIdx.x == 0) sh.cursor = 0;
         bounded = false;
-        if (bound_energies && n_selected > SMALL && k_out <= SMALL / 4) {
+        if (bound_energies && n_selected > SMALL && k_out <= BOUNDED / 4) {
             uint64_t least = NONE;
 #pragma unroll
             for (int j = 0; j < ITEMS; ++j) least = c[j] < least ? c[j] : least;
             kept = bound_candidates<T>(c, least, k_out, sh, &bounded);
         } else {
-            kept = count_candidates<T>(c, sh);
+            kept = keep_all<T>(c, sh);
         }
         n_selected = select_kept<T>(c, kept, bounded, k_out, 32 + a.idx_bits, sh, &ranked, &thr);
     }
     if (!last_level) {
         uint64_t *out = a.list_out + ((uint64_t)s * gridDim.x + blockIdx.x) * a.k;
         if (ranked) {
-            for (uint32_t i = threadIdx.x; i < n_selected; i += T) out[i] = sh.small.ranked[i];
+            for (uint32_t i = threadIdx.x; i < n_selected; i += T) out[i] = sh.pool[i];
         } else {
             __syncthreads(); // the histogram's space is done with
             if (threadIdx.x == 0) sh.cursor = 0;
@@ -810,7 +851,7 @@ __device__ __forceinline__ void select_and_emit(const SelectArgs &a, uint32_t s,
     };
     if (threadIdx.x == 0) a.count_out[s] = n_selected;
     if (ranked) {
-        for (uint32_t i = threadIdx.x; i < k_out; i += T) emit(i, i < n_selected ? sh.small.ranked[i] : 0);
+        for (uint32_t i = threadIdx.x; i < k_out; i += T) emit(i, i < n_selected ? sh.pool[i] : 0);
         return;
     }
     // bitonic sort of the selection (padded to a power of two with NONE)
@@ -830,20 +871,20 @@ __device__ __forceinline__ void select_and_emit(const SelectArgs &a, uint32_t s,
         uint64_t v = i < pow2 ? sort_buf[i] : NONE;
         for (uint32_t size = 2; size <= pow2; size <<= 1) {
             const bool ascending = (i & size) == 0;
-            for (uint32_t stride = size >> 1; stride > 0; stride >>= 1) {
-                uint64_t other;
-                if (stride < 64) {
-                    other = lane_exchange<uint64_t>(v, stride);
-                } else {
-                    __syncthreads(); // the reads of the step before are done
-                    if (i < pow2) sort_buf[i] = v;
-                    __syncthreads();
-                    other = i < pow2 ? sort_buf[i ^ stride] : NONE;
-                }
+            auto merge = [&](uint32_t stride, uint64_t other) {
                 const bool lower = (i & stride) == 0; // this thread keeps the smaller one of an ascending pair
                 const uint64_t lo = v < other ? v : other, hi = v < other ? other : v;
                 v = (lower == ascending) ? lo : hi;
+            };
+            for (uint32_t stride = size >> 1; stride >= 64; stride >>= 1) {
+                __syncthreads(); // the reads of the step before are done
+                if (i < pow2) sort_buf[i] = v;
+                __syncthreads();
+                merge(stride, i < pow2 ? sort_buf[i ^ stride] : NONE);
             }
+#pragma unroll
+            for (uint32_t stride = 32; stride > 0; stride >>= 1)
+                if (stride < size) merge(stride, lane_exchange<uint64_t>(v, stride));
         }
         if (i < k_out) emit(i, v);
         return;
@@ -882,9 +923,7 @@ __global__ __launch_bounds__(T) void select_kernel(SelectArgs a)
     uint64_t c[ITEMS];
     uint32_t kept;
     bool bounded;
-    // the direct ranking's counters start at zero, the pool's cursor too (ordered before their use by the barriers
-    // of the gather step)
-    for (uint32_t i = threadIdx.x; i < SMALL; i += T) sh.small.rank[i] = 0;
+    // the pool's cursor starts at zero (ordered before its use by the barriers of the gather step)
     if (threadIdx.x == 0) sh.cursor = 0;
     if (SRC == SRC_LIST) gather_list<T>(a.list_in + (uint64_t)s * a.list_len, a.list_len, (uint64_t)blockIdx.x * (T * ITEMS), a.k, sh, c, &kept, &bounded);
     else if (SRC == SRC_SCANNED_VEC || SRC == SRC_SCANNED) {
@@ -900,9 +939,9 @@ __global__ __launch_bounds__(T) void select_kernel(SelectArgs a)
 
 // ---------------------------------------------------------------- host side
 
-// Threads per block for a selection of k per block: 1024 (chunks of 16384) when k is large, so that a level
-// still shrinks its input at least fourfold, or when the whole job is too small to fill the chip anyway and
-// fewer levels matter more; 256 (chunks of 4096) otherwise.
+// Threads per block for the least workspace: 1024 (chunks of 16384) when k is large, so that a level still shrinks its
+// input at least fourfold, or when the whole job is too small to fill the chip anyway and fewer levels matter more; 256
+// (chunks of 4096) otherwise.
 int threads_for(uint64_t seg_len, uint32_t n_seg, uint32_t k)
 {
     if (k > 256) return 1024;
@@ -911,26 +950,54 @@ int threads_for(uint64_t seg_len, uint32_t n_seg, uint32_t k)
 }
 
 struct Plan {
-    int threads;
-    uint64_t blocks0;     // level-0 blocks per segment
-    uint64_t list_a, list_b; // composites per segment in the two list buffers (level 0 writes A)
+    int threads, list_threads; // of a block on the scores, and on lists
+    uint64_t blocks0;          // level-0 blocks per segment
+    uint64_t list_a, list_b;   // composites per segment in the two list buffers (level 0 writes A)
 };
 
-Plan plan_for(uint64_t seg_len, uint32_t n_seg, uint32_t k)
+// launches on lists until one block holds what is left of a segment
+int list_levels(uint64_t list_len, uint32_t k, uint64_t chunk)
+{
+    int levels = 1;
+    for (uint64_t blocks = (list_len + chunk - 1) / chunk; blocks > 1; blocks = (blocks * k + chunk - 1) / chunk) ++levels;
+    return levels;
+}
+
+// `roomy`: the workspace is as large as the queries say; else the plan that the least workspace is for.  Smaller blocks wait
+// less at their barriers and put more compute units to work, larger ones leave shorter lists; the lines lie where the
+// measured times cross (us, blocks of 256 / 512 / 1024 threads on the scores, each with its best block on the lists):
+//   k = 16 of 2^16  11 / 13 / 12.5, of 2^21  16 / 13.5 / 14;  k = 64 of 2^20  17 / 14.6 / 14.9, of 2^21  - / 17.2 / 16.8;
+//   128 of 2^18  16 / 14.6 / 15.6, of 2^20  - / 17.7 / 16.8;  256 of 2^18  - / 18.6 / 18.8, of 2^20  42 / 30 / 21.5;
+//   512 of 2^18  36 / 26.6 / 24.5;  1024 of 2^20  50 / 44 / 48;  64 segments of 2^18: k = 32  32.8 / 32 / -, 128  39 / 36 / 43.
+//   One block a segment, of 6400: k = 128  - / 6.8 / 8.1, 512  - / 14.8 / 18.5;  of 4096: 16  6.9 / 6.9 / 6.9, RANK 32
+//   7.4 / 7.7 / 9.4, 256  12.3 / 7.2 / 8.1, 512  17.8 / 13.9 / 11.2;  of 8192: 512  - / 15.3 / 11.5.
+Plan plan_for(uint64_t seg_len, uint32_t n_seg, uint32_t k, bool roomy)
 {
     Plan p;
-    p.threads = threads_for(seg_len, n_seg, k);
-    const uint64_t chunk = (uint64_t)p.threads * ITEMS;
-    p.blocks0 = (seg_len + chunk - 1) / chunk;
+    p.threads = p.list_threads = threads_for(seg_len, n_seg, k);
+    auto chunk = [](int threads) { return (uint64_t)threads * ITEMS; };
+    auto blocks = [&](int threads) { return (seg_len + chunk(threads) - 1) / chunk(threads); };
+    if (roomy && seg_len <= chunk(1024)) {
+        p.threads = seg_len <= chunk(256) && k <= 64 ? 256 : seg_len <= chunk(512) && k <= 256 ? 512 : 1024;
+    } else if (roomy) {
+        p.threads = k <= 48 ? 256 : k <= 256 ? 512 : 1024;
+        if (p.threads == 256 && (blocks(256) * k > 4096 || n_seg * blocks(256) >= 2048)) p.threads = 512;
+        if (p.threads == 512 && blocks(512) * k > 8192) p.threads = 1024;
+        if (k > BOUNDED && k <= 1024 && list_levels(blocks(512) * k, k, chunk(1024)) == list_levels(blocks(1024) * k, k, chunk(1024)))
+            p.threads = 512;
+        p.list_threads = 256;
+        while (p.list_threads < 1024 && (blocks(p.threads) * k > chunk(p.list_threads) || 2 * k > (uint32_t)p.list_threads))
+            p.list_threads *= 2;
+    }
+    p.blocks0 = blocks(p.threads);
     p.list_a = p.blocks0 > 1 ? p.blocks0 * k : 0;
-    const uint64_t blocks1 = (p.list_a + chunk - 1) / chunk;
+    const uint64_t blocks1 = (p.list_a + chunk(p.list_threads) - 1) / chunk(p.list_threads);
     p.list_b = blocks1 > 1 ? blocks1 * k : 0;
     return p;
 }
 
 struct WsLayout {
-    uint64_t lat_parts, list_a, list_b, total; // what a call needs
-    uint64_t listed, scan_lists, full;         // and what scan_kernel writes, where it runs and the workspace holds it
+    uint64_t lat_parts, list_a, list_b, scan_lists, listed, total;
 };
 
 // whether, and in how many chunks, scan_kernel takes a segment (every block of the next launch reads the minima of all of
@@ -943,11 +1010,12 @@ uint64_t scan_parts(uint64_t seg_len, uint64_t blocks0)
 
 // m_latency: the latency gate of a RANK-mode call when it does not admit the whole segment, else 0.  (The larger of the
 // two plans: a workspace made for a gate serves a call without one, too.)
-WsLayout ws_layout(uint64_t seg_len, uint32_t n_seg, uint32_t k, uint32_t m_latency)
+WsLayout ws_layout(uint64_t seg_len, uint32_t n_seg, uint32_t k, uint32_t m_latency, bool roomy)
 {
-    Plan p = plan_for(seg_len, n_seg, k);
+    Plan p = plan_for(seg_len, n_seg, k, roomy);
+    const uint64_t parts = roomy ? n_seg * scan_parts(seg_len, p.blocks0) : 0;
     if (m_latency && m_latency < seg_len) {
-        const Plan q = plan_for(seg_len, n_seg, m_latency);
+        const Plan q = plan_for(seg_len, n_seg, m_latency, roomy);
         p.list_a = p.list_a > q.list_a ? p.list_a : q.list_a;
         p.list_b = p.list_b > q.list_b ? p.list_b : q.list_b;
     }
@@ -955,12 +1023,17 @@ WsLayout ws_layout(uint64_t seg_len, uint32_t n_seg, uint32_t k, uint32_t m_late
     w.lat_parts = 0;
     w.list_a = w.lat_parts + (uint64_t)n_seg * LATMIN_PARTS * sizeof(uint32_t);
     w.list_b = w.list_a + (uint64_t)n_seg * p.list_a * sizeof(uint64_t);
-    w.total = w.list_b + (uint64_t)n_seg * p.list_b * sizeof(uint64_t);
-    const uint64_t parts = m_latency ? 0 : n_seg * scan_parts(seg_len, p.blocks0);
-    w.scan_lists = (w.total + 15) & ~(uint64_t)15; // (least and listed: two words per chunk behind the lists)
-    w.listed = w.scan_lists + parts * SCAN_LIST * sizeof(uint64_t);
-    w.full = parts ? w.listed + 2 * parts * sizeof(uint32_t) : w.total;
+    w.scan_lists = w.list_b + (uint64_t)n_seg * p.list_b * sizeof(uint64_t);
+    w.listed = w.scan_lists + parts * SCAN_LIST * sizeof(uint64_t); // (with the minima: two words per chunk)
+    w.total = w.listed + 2 * parts * sizeof(uint32_t);
     return w;
+}
+
+// what the queries say
+uint64_t workspace_for(uint64_t seg_len, uint32_t n_seg, uint32_t k, uint32_t m_latency)
+{
+    const uint64_t least = ws_layout(seg_len, n_seg, k, m_latency, false).total, more = ws_layout(seg_len, n_seg, k, m_latency, true).total;
+    return least > more ? least : more;
 }
 
 bool sizes_ok(uint64_t n, uint32_t n_seg, uint32_t k)
@@ -998,14 +1071,15 @@ void launch_level0(const SelectArgs &a, uint32_t blocks, uint32_t n_seg, bool ve
 // All levels of one selection of a.k per segment: level 0 on the score arrays, further levels on the lists.
 // The last level writes idx/energy/count.
 template <int PRED>
-int32_t run_tournament(SelectArgs a, uint32_t n_seg, bool vec, uint64_t *list_a, uint64_t *list_b, hipStream_t st)
+int32_t run_tournament(SelectArgs a, uint32_t n_seg, bool vec, bool roomy, uint64_t *list_a, uint64_t *list_b, hipStream_t st)
 {
-    const Plan p = plan_for(a.seg_len, n_seg, a.k);
-    const uint64_t chunk = (uint64_t)p.threads * ITEMS;
+    const Plan p = plan_for(a.seg_len, n_seg, a.k, roomy);
+    const uint64_t chunk = (uint64_t)p.list_threads * ITEMS;
     uint64_t blocks = p.blocks0;
     if (blocks > 0x7FFFFFFFull) return ECK_EUNSUPPORTED;
     a.list_out = list_a;
     if (p.threads == 256) launch_level0<256, PRED>(a, (uint32_t)blocks, n_seg, vec, st);
+    else if (p.threads == 512) launch_level0<512, PRED>(a, (uint32_t)blocks, n_seg, vec, st);
     else launch_level0<1024, PRED>(a, (uint32_t)blocks, n_seg, vec, st);
     uint64_t *in = list_a, *out = list_b;
     while (blocks > 1) {
@@ -1013,7 +1087,8 @@ int32_t run_tournament(SelectArgs a, uint32_t n_seg, bool vec, uint64_t *list_a,
         a.list_len = blocks * a.k;
         a.list_out = out;
         blocks = (a.list_len + chunk - 1) / chunk;
-        if (p.threads == 256) launch_select<256, SRC_LIST, PRED_PLAIN>(a, (uint32_t)blocks, n_seg, st);
+        if (p.list_threads == 256) launch_select<256, SRC_LIST, PRED_PLAIN>(a, (uint32_t)blocks, n_seg, st);
+        else if (p.list_threads == 512) launch_select<512, SRC_LIST, PRED_PLAIN>(a, (uint32_t)blocks, n_seg, st);
         else launch_select<1024, SRC_LIST, PRED_PLAIN>(a, (uint32_t)blocks, n_seg, st);
         uint64_t *t = in;
         in = out;
@@ -1028,7 +1103,7 @@ int32_t run_tournament(SelectArgs a, uint32_t n_seg, bool vec, uint64_t *list_a,
 extern "C" uint64_t topk_select_workspace_bytes(uint64_t n, uint32_t n_segments, uint32_t k)
 {
     if (!sizes_ok(n, n_segments, k)) return 0;
-    return ws_layout(n / n_segments, n_segments, k, 0).full;
+    return workspace_for(n / n_segments, n_segments, k, 0);
 }
 
 extern "C" uint64_t topk_select_rank_workspace_bytes(uint64_t n, uint32_t n_segments, uint32_t k, uint32_t m_latency)
@@ -1036,7 +1111,7 @@ extern "C" uint64_t topk_select_rank_workspace_bytes(uint64_t n, uint32_t n_segm
     if (!sizes_ok(n, n_segments, k) || m_latency == 0) return 0;
     const uint64_t seg_len = n / n_segments;
     if (m_latency < seg_len && m_latency > ECK_MAX_K) return 0;
-    return ws_layout(seg_len, n_segments, k, m_latency < seg_len ? m_latency : 0).full;
+    return workspace_for(seg_len, n_segments, k, m_latency < seg_len ? m_latency : 0);
 }
 
 namespace {
@@ -1044,7 +1119,7 @@ namespace {
 // argument checks shared by the entry points; *need = bytes of workspace the call takes
 int32_t check_arguments(const float *energy, const float *latency, uint64_t n, uint32_t n_segments, uint32_t k, int32_t mode,
                         float alpha, uint32_t m_latency, const uint32_t *idx_out, const float *energy_out,
-                        const uint32_t *count_out, bool *stage_a, WsLayout *layout)
+                        const uint32_t *count_out, bool *stage_a, uint64_t *need)
 {
     if (!energy || !idx_out || !energy_out || !count_out || n == 0 || k == 0 || n_segments == 0) return ECK_EINVAL;
     if (mode != ECK_SELECT_THRESHOLD && mode != ECK_SELECT_RANK) return ECK_EINVAL;
@@ -1056,7 +1131,7 @@ int32_t check_arguments(const float *energy, const float *latency, uint64_t n, u
     // a latency gate that admits the whole segment needs no first stage
     *stage_a = latency && mode == ECK_SELECT_RANK && m_latency < seg_len;
     if (*stage_a && m_latency > ECK_MAX_K) return ECK_EUNSUPPORTED;
-    *layout = ws_layout(seg_len, n_segments, k, *stage_a ? m_latency : 0);
+    *need = ws_layout(seg_len, n_segments, k, *stage_a ? m_latency : 0, false).total;
     return ECK_OK;
 }
 
@@ -1068,13 +1143,17 @@ int32_t eck::topk_select_impl(const float *energy, const float *latency, const u
                               void *stream, const uint32_t *known_min)
 {
     bool stage_a;
-    WsLayout w;
+    uint64_t need;
     const int32_t bad = check_arguments(energy, latency, n, n_segments, k, mode, alpha, m_latency, idx_out, energy_out,
-                                        count_out, &stage_a, &w);
+                                        count_out, &stage_a, &need);
     if (bad != ECK_OK) return bad;
-    if (!ws || ws_bytes < w.total) return ECK_EWORKSPACE;
+    if (!ws || ws_bytes < need) return ECK_EWORKSPACE;
     if ((uintptr_t)ws & 15) return ECK_EALIGN;
     const uint64_t seg_len = n / n_segments;
+    WsLayout w = ws_layout(seg_len, n_segments, k, stage_a ? m_latency : 0, true);
+    const bool roomy = ws_bytes >= w.total;
+    if (!roomy) w = ws_layout(seg_len, n_segments, k, stage_a ? m_latency : 0, false);
+    const uint64_t blocks0 = plan_for(seg_len, n_segments, k, roomy).blocks0;
 
     SelectArgs a = {};
     a.energy = energy;
@@ -1097,14 +1176,13 @@ int32_t eck::topk_select_impl(const float *energy, const float *latency, const u
     // four candidates per load when every group of four is aligned in all three arrays
     const bool vec = seg_len % 4 == 0 && ((uintptr_t)energy & 15) == 0 && (!latency || ((uintptr_t)latency & 15) == 0) &&
                      (!legal || ((uintptr_t)legal & 3) == 0);
-    if (!latency) return run_tournament<PRED_PLAIN>(a, n_segments, vec, list_a, list_b, st);
+    if (!latency) return run_tournament<PRED_PLAIN>(a, n_segments, vec, roomy, list_a, list_b, st);
     if (mode == ECK_SELECT_THRESHOLD) {
         if (!a.alpha_inf && known_min) {
             // L_min came with the call (one order key per segment)
             a.lat_parts = known_min;
             a.lat_parts_n = 1;
-        } else if (const uint64_t chunks = scan_parts(seg_len, plan_for(seg_len, n_segments, k).blocks0);
-                   !a.alpha_inf && chunks && ws_bytes >= w.full) {
+        } else if (const uint64_t chunks = roomy ? scan_parts(seg_len, blocks0) : 0; !a.alpha_inf && chunks) {
             // one pass over the latencies finds the least one and what its gate may admit
             uint32_t *listed = reinterpret_cast<uint32_t *>((char *)ws + w.listed), *least = listed + n_segments * chunks;
             uint64_t *lists = reinterpret_cast<uint64_t *>((char *)ws + w.scan_lists);
@@ -1115,7 +1193,7 @@ int32_t eck::topk_select_impl(const float *energy, const float *latency, const u
             a.lat_parts_n = (uint32_t)chunks;
             a.listed = listed;
             a.scan_lists = lists;
-        } else if (!a.alpha_inf && plan_for(seg_len, n_segments, k).blocks0 > 1) {
+        } else if (!a.alpha_inf && blocks0 > 1) {
             // L_min first: one pass over the latencies, a slice of the segment per block (a segment that one block
             // holds needs none: that block finds it, 4 us less)
             uint64_t parts = (seg_len + 4095) / 4096;
@@ -1130,19 +1208,20 @@ int32_t eck::topk_select_impl(const float *energy, const float *latency, const u
             a.lat_parts = lat_parts;
             a.lat_parts_n = (uint32_t)parts;
         }
-        return run_tournament<PRED_THRESHOLD>(a, n_segments, vec, list_a, list_b, st);
+        return run_tournament<PRED_THRESHOLD>(a, n_segments, vec, roomy, list_a, list_b, st);
     }
     if (!stage_a) {
         // every legal candidate with a latency that is a number passes the gate
         SelectArgs b = a;
         b.alpha_inf = 1;
-        return run_tournament<PRED_THRESHOLD>(b, n_segments, vec, list_a, list_b, st);
+        return run_tournament<PRED_THRESHOLD>(b, n_segments, vec, roomy, list_a, list_b, st);
     }
     // the m_latency fastest by latency, of these k by energy in the last level's block: two launches where a second
-    // tournament over the gated scores took four (45 against 31 us on 2^20, 128 fastest, k = 64)
+    // tournament over the gated scores took four (45 us on 2^20, 128 fastest, k = 64; 31 with one, and 19.4 with blocks and lists
+    // as plan_for cuts them, sorted pools and tight bounds)
     a.k = m_latency;
     a.k_energy = k;
-    return run_tournament<PRED_RANK>(a, n_segments, vec, list_a, list_b, st);
+    return run_tournament<PRED_RANK>(a, n_segments, vec, roomy, list_a, list_b, st);
 }
 
 extern "C" int32_t topk_select(const float *energy, const float *latency, const uint8_t *legal, uint64_t n,
@@ -1179,11 +1258,11 @@ extern "C" int32_t topk_select_static(const float *energy, const float *latency,
                                       uint32_t *idx_out, float *energy_out, uint32_t *count_out, void *stream)
 {
     bool stage_a;
-    WsLayout w;
+    uint64_t need;
     const int32_t bad = check_arguments(energy, latency, n, n_segments, k, mode, alpha, m_latency, idx_out, energy_out,
-                                        count_out, &stage_a, &w);
+                                        count_out, &stage_a, &need);
     if (bad != ECK_OK) return bad;
-    if (w.total > ECK_TOPK_STATIC_BYTES) return ECK_EWORKSPACE;
+    if (need > ECK_TOPK_STATIC_BYTES) return ECK_EWORKSPACE;
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess) {
         (void)hipGetLastError();

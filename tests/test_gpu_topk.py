@@ -259,3 +259,28 @@ def test_candidates_listed_under_the_gate(G, segments, seg_len, k, kind):
     eck.topk_select(ed, ld, gd, segments, k, idx, eo, cnt, ws, alpha=alpha)
     torch.cuda.synchronize()
     _same((idx.cpu().numpy().view(np.uint32), eo.cpu().numpy(), cnt.cpu().numpy().view(np.uint32)), want)
+
+
+@pytest.mark.parametrize("segments,seg_len,k", [(1, 4096, 64), (1, 4096, 65), (1, 4097, 33), (2, 8192, 256), (2, 8193, 257), (1, 16385, 48),
+                                                (1, 16388, 49), (1, 300000, 100), (3, 70000, 250), (1, 200004, 513), (2, 150000, 1000),
+                                                (130, 16400, 3), (1, 1 << 20, 128), (1, (1 << 20) + 1, 129), (1, 16384, 1024), (4, 1030, 1025)])
+@pytest.mark.parametrize("order", ["random", "rising", "falling", "few"])
+def test_block_sizes_and_list_shares(G, segments, seg_len, k, order):
+    """Both sides of the lines between block sizes, lists that go into the threads of the next level evenly and not, and
+    pools of more entries than a block has threads.  In ascending or descending order one block holds the whole selection
+    and no bound is tight; few distinct values tie by the thousand."""
+    rng = np.random.default_rng(seg_len + k)
+    n = segments * seg_len
+    e = rng.standard_normal(n).astype(np.float32)
+    lat = (1.0 + rng.random(n)).astype(np.float32)
+    if order == "few":
+        e, lat = np.round(e).astype(np.float32), np.round(lat * 8).astype(np.float32)
+    elif order != "random":
+        step = 1 if order == "rising" else -1
+        e, lat = (np.sort(v.reshape(segments, -1), axis=1)[:, ::step].reshape(-1).copy() for v in (e, lat))
+    legal = (rng.random(n) < 0.5).astype(np.uint8)
+    _same(G.topk_gpu(e, None, legal, segments, k), oracle.topk(e, None, legal, segments, k))
+    _same(G.topk_gpu(e, lat, None, segments, k, alpha=1.2), oracle.topk(e, lat, None, segments, k, alpha=1.2))
+    if k <= 1000:
+        _same(G.topk_gpu(e, lat, legal, segments, max(1, k // 2), mode=eck.SELECT_RANK, m_latency=k),
+              oracle.topk(e, lat, legal, segments, max(1, k // 2), mode=oracle.SEL_RANK, m_latency=k))
