@@ -16,6 +16,7 @@
 #include <mutex>
 
 #include "eck_internal.h"
+#include "lanes.h"
 
 using namespace eck;
 
@@ -105,8 +106,7 @@ __global__ __launch_bounds__(256) void latmin_kernel(const float *__restrict__ l
             if (l == l) best = min(best, score_order_key(l));
         }
     }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) best = min(best, (uint32_t)__shfl_xor((int)best, off));
+    best = wave_least(best);
     __shared__ uint32_t wave_best[4];
     if ((threadIdx.x & 63) == 0) wave_best[threadIdx.x >> 6] = best;
     __syncthreads();
@@ -164,8 +164,7 @@ __global__ __launch_bounds__(256) void scan_kernel(const float *__restrict__ lat
     uint32_t best = 0xFFFFFFFFu;
 #pragma unroll
     for (int j = 0; j < PER; ++j) best = min(best, (on >> j) & 1u ? score_order_key(l[j]) : 0xFFFFFFFFu);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) best = min(best, (uint32_t)__shfl_xor((int)best, off));
+    best = wave_least(best);
     if ((threadIdx.x & 63) == 0) wave_best[threadIdx.x >> 6] = best;
     __syncthreads();
 #pragma unroll
@@ -179,12 +178,7 @@ __global__ __launch_bounds__(256) void scan_kernel(const float *__restrict__ lat
     // places by a prefix sum over the wavefront and one LDS atomic (an atomic per thread: 10 us more where a gate admits
     // everything); a wavefront that overflows the list alone writes nothing
     const uint32_t mine = (uint32_t)__popc(under);
-    uint32_t upto = mine;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t up = (uint32_t)__shfl_up((int)upto, off);
-        if ((threadIdx.x & 63) >= (uint32_t)off) upto += up;
-    }
+    const uint32_t upto = wave_prefix_sum(mine);
     const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
     uint32_t at = 0;
     if ((threadIdx.x & 63) == 0 && total) at = atomicAdd(&cursor, total);
@@ -235,48 +229,6 @@ struct Shared {
     uint64_t any_composite; // radix select: one of the block's composites, to find the leading bits all of them share
 };
 
-// The value of the lane whose number differs in bit `stride`: data-parallel moves up to 8, half-row and half-wavefront swaps
-// above.  (A shuffle through the LDS crossbar takes some 100 cycles of latency, and the exchanges of a sort wait for each
-// other.)
-__device__ __forceinline__ uint32_t exchange_word(uint32_t v, uint32_t stride)
-{
-    const int x = (int)v;
-    switch (stride) {
-    case 1: return (uint32_t)__builtin_amdgcn_mov_dpp(x, 0xB1, 0xF, 0xF, true);  // quad_perm 1 0 3 2
-    case 2: return (uint32_t)__builtin_amdgcn_mov_dpp(x, 0x4E, 0xF, 0xF, true);  // quad_perm 2 3 0 1
-    case 4: return (uint32_t)__builtin_amdgcn_mov_dpp(__builtin_amdgcn_mov_dpp(x, 0x141, 0xF, 0xF, true), 0x1B, 0xF, 0xF, true); // row_half_mirror, quad_perm 3 2 1 0
-    case 8: return (uint32_t)__builtin_amdgcn_mov_dpp(x, 0x128, 0xF, 0xF, true); // row_ror:8
-    case 16: {
-        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false); // even rows twice, odd rows twice
-        return threadIdx.x & 16 ? r[0] : r[1];
-    }
-    default: {
-        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false); // lower half twice, upper half twice
-        return threadIdx.x & 32 ? r[0] : r[1];
-    }
-    }
-}
-template <class V>
-__device__ __forceinline__ V lane_exchange(V v, uint32_t stride);
-template <>
-__device__ __forceinline__ uint32_t lane_exchange<uint32_t>(uint32_t v, uint32_t stride)
-{
-    return exchange_word(v, stride);
-}
-template <>
-__device__ __forceinline__ uint64_t lane_exchange<uint64_t>(uint64_t v, uint32_t stride)
-{
-    return ((uint64_t)exchange_word((uint32_t)(v >> 32), stride) << 32) | exchange_word((uint32_t)v, stride);
-}
-
-// the least of a wavefront's values, in every lane
-__device__ __forceinline__ uint32_t wave_least(uint32_t v)
-{
-#pragma unroll
-    for (uint32_t stride = 1; stride < 64; stride <<= 1) v = min(v, exchange_word(v, stride));
-    return v;
-}
-
 // the 64 values of a wavefront in ascending order over the lanes (bitonic sorting network)
 template <class V>
 __device__ __forceinline__ V wave_sort(V v)
@@ -286,26 +238,12 @@ __device__ __forceinline__ V wave_sort(V v)
     for (uint32_t size = 2; size <= 64; size <<= 1)
 #pragma unroll
         for (uint32_t stride = size >> 1; stride > 0; stride >>= 1) {
-            const V other = lane_exchange<V>(v, stride);
+            const V other = lane_exchange(v, stride);
             const bool keep_min = ((lane & stride) == 0) == ((lane & size) == 0);
             const V lo = v < other ? v : other, hi = v < other ? other : v;
             v = keep_min ? lo : hi;
         }
     return v;
-}
-
-template <int T>
-__device__ __forceinline__ uint32_t block_sum(uint32_t v, Shared<T> &sh)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += (uint32_t)__shfl_xor((int)v, off);
-    __syncthreads(); // wave_sum may still be read from an earlier use
-    if ((threadIdx.x & 63) == 0) sh.wave_sum[threadIdx.x >> 6] = v;
-    __syncthreads();
-    uint32_t total = 0;
-#pragma unroll
-    for (int w = 0; w < T / 64; ++w) total += sh.wave_sum[w];
-    return total;
 }
 
 // A bound on the block's k-th smallest value, from the least value of every thread (V = order key or composite,
@@ -326,7 +264,7 @@ __device__ __forceinline__ V block_bound(V least, uint32_t k, V none, Shared<T> 
         part = least;
 #pragma unroll
         for (uint32_t stride = 1; stride < 64; stride <<= 1) {
-            const V other = lane_exchange<V>(part, stride);
+            const V other = lane_exchange(part, stride);
             const V lo = part < other ? part : other, hi = part < other ? other : part;
             part = stride < lanes ? lo : hi;
         }
@@ -413,7 +351,7 @@ __device__ uint64_t radix_threshold(const uint64_t (&c)[ITEMS], uint32_t k, uint
 #pragma unroll
     for (int j = 0; j < ITEMS; ++j) differ |= c[j] != NONE ? c[j] ^ ref : 0;
 #pragma unroll
-    for (uint32_t stride = 32; stride > 0; stride >>= 1) differ |= lane_exchange<uint64_t>(differ, stride);
+    for (uint32_t stride = 32; stride > 0; stride >>= 1) differ |= lane_exchange(differ, stride);
     if ((threadIdx.x & 63) == 0) sh.wave_bound[threadIdx.x >> 6] = differ;
     __syncthreads();
     differ = 0;
@@ -445,12 +383,7 @@ __device__ uint64_t radix_threshold(const uint64_t (&c)[ITEMS], uint32_t k, uint
             local[j] = sh.hist[threadIdx.x * PER + j];
             sum += local[j];
         }
-        uint32_t incl = sum;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t up = (uint32_t)__shfl_up((int)incl, off);
-            if ((threadIdx.x & 63) >= (uint32_t)off) incl += up;
-        }
+        const uint32_t incl = wave_prefix_sum(sum);
         if ((threadIdx.x & 63) == 63) sh.wave_sum[threadIdx.x >> 6] = incl;
         __syncthreads();
         uint32_t below = incl - sum;
@@ -884,7 +817,7 @@ __device__ __forceinline__ void select_and_emit(const SelectArgs &a, uint32_t s,
             }
 #pragma unroll
             for (uint32_t stride = 32; stride > 0; stride >>= 1)
-                if (stride < size) merge(stride, lane_exchange<uint64_t>(v, stride));
+                if (stride < size) merge(stride, lane_exchange(v, stride));
         }
         if (i < k_out) emit(i, v);
         return;

@@ -14,6 +14,7 @@
 // so every histogram, and with it every split decision, is independent of the order of execution; gains are
 // evaluated in fp64 from those integers.
 #include "eck_internal.h"
+#include "lanes.h"
 
 #include <atomic>
 #include <new>
@@ -727,6 +728,20 @@ __device__ __forceinline__ bool better_split(double og, uint32_t orank, double g
     return og > g || (og == g && orank < rank);
 }
 
+// the best split of a wavefront's, in every lane
+__device__ __forceinline__ void best_of_wave(double &gain, uint32_t &rank)
+{
+#pragma unroll
+    for (uint32_t stride = 1; stride < 64; stride <<= 1) {
+        const double og = lane_exchange(gain, stride);
+        const uint32_t orank = lane_exchange(rank, stride);
+        if (better_split(og, orank, gain, rank)) {
+            gain = og;
+            rank = orank;
+        }
+    }
+}
+
 __global__ __launch_bounds__(SPLIT_FEATS * 64) void tree_split_kernel(unsigned long long *__restrict__ hist, int n_feat,
                                                                       double lam, SplitRecord *__restrict__ partial)
 {
@@ -754,17 +769,8 @@ __global__ __launch_bounds__(SPLIT_FEATS * 64) void tree_split_kernel(unsigned l
         }
         // inclusive prefix of the lanes' totals; its last lane holds the node's totals (every pair of the node is
         // in exactly one bin of every feature, so each feature's histogram sums to the same G, H, N)
-        long long pg = g[3], ph = hh[3], pc = c[3];
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const long long ug = __shfl_up(pg, off), uh = __shfl_up(ph, off), uc = __shfl_up(pc, off);
-            if (lane >= off) {
-                pg += ug;
-                ph += uh;
-                pc += uc;
-            }
-        }
-        const long long G = __shfl(pg, 63), H = __shfl(ph, 63), N = __shfl(pc, 63);
+        long long pg = wave_prefix_sum((int64_t)g[3]), ph = wave_prefix_sum((int64_t)hh[3]), pc = wave_prefix_sum((int64_t)c[3]);
+        const long long G = last_lane(pg), H = last_lane(ph), N = last_lane(pc);
         if (N > 1) {
             const double parent = (double)G * (double)G / ((double)H + lam);
             pg -= g[3];
@@ -786,15 +792,7 @@ __global__ __launch_bounds__(SPLIT_FEATS * 64) void tree_split_kernel(unsigned l
             }
         }
     }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const double og = __shfl_xor(best, off);
-        const uint32_t orank = __shfl_xor(best_rank, off);
-        if (better_split(og, orank, best, best_rank)) {
-            best = og;
-            best_rank = orank;
-        }
-    }
+    best_of_wave(best, best_rank);
     __shared__ double s_gain[SPLIT_FEATS];
     __shared__ uint32_t s_rank[SPLIT_FEATS];
     if (lane == 0) {
@@ -958,15 +956,7 @@ __device__ __forceinline__ void settle_level(const LevelArgs &a, int level_befor
                 best_rank = o.rank;
             }
         }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            const double og = __shfl_xor(best, off);
-            const uint32_t orank = __shfl_xor(best_rank, off);
-            if (better_split(og, orank, best, best_rank)) {
-                best = og;
-                best_rank = orank;
-            }
-        }
+        best_of_wave(best, best_rank);
         if (lane) continue;
         const bool split = !bad && best_rank != 0xFFFFFFFFu && best > 0.0;
         s.feat[node] = (uint16_t)(split ? best_rank / BINS : a.n_feat);
@@ -1100,11 +1090,8 @@ __global__ __launch_bounds__(LEVEL_THREADS) void tree_level_kernel(LevelArgs a, 
         total.g += g[q];
         total.h += h[q];
     }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        total.g += __shfl_xor(total.g, off);
-        total.h += __shfl_xor(total.h, off);
-    }
+    total.g = last_lane(wave_prefix_sum((int64_t)total.g));
+    total.h = last_lane(wave_prefix_sum((int64_t)total.h));
     double best = 0.0;
     uint32_t best_rank = 0xFFFFFFFFu;
     SideSums best_left = {0, 0}, before = {0, 0};
@@ -1112,18 +1099,10 @@ __global__ __launch_bounds__(LEVEL_THREADS) void tree_level_kernel(LevelArgs a, 
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         if (!__any(h[q] != 0)) continue;
-        long long pg = g[q], ph = h[q];
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const long long ug = __shfl_up(pg, off), uh = __shfl_up(ph, off);
-            if (lane >= off) {
-                pg += ug;
-                ph += uh;
-            }
-        }
+        const long long pg = wave_prefix_sum((int64_t)g[q]), ph = wave_prefix_sum((int64_t)h[q]);
         const SideSums left = {before.g + pg, before.h + ph};
-        before.g += __shfl(pg, 63);
-        before.h += __shfl(ph, 63);
+        before.g += last_lane(pg);
+        before.h += last_lane(ph);
         const int bin = 64 * q + lane;
         if (h[q] == 0 || bin >= 255 || left.h == total.h) continue;
         const SideSums right = {total.g - left.g, total.h - left.h};
@@ -1137,15 +1116,7 @@ __global__ __launch_bounds__(LEVEL_THREADS) void tree_level_kernel(LevelArgs a, 
         }
     }
     const uint32_t own_rank = best_rank;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const double og = __shfl_xor(best, off);
-        const uint32_t orank = __shfl_xor(best_rank, off);
-        if (better_split(og, orank, best, best_rank)) {
-            best = og;
-            best_rank = orank;
-        }
-    }
+    best_of_wave(best, best_rank);
     const uint64_t at = (uint64_t)(node0 + wave) * a.n_feat + f;
     if (best_rank != 0xFFFFFFFFu && own_rank == best_rank) a.left_out[at] = best_left; // (ranks are distinct: one lane)
     if (lane == 0) {
