@@ -43,12 +43,13 @@ __device__ __forceinline__ uint32_t wave_least(uint32_t v)
     return v;
 }
 
-// the value of lane 63, in every lane
-__device__ __forceinline__ int64_t last_lane(int64_t v)
+// the value of one lane (the same for all), in every lane
+__device__ __forceinline__ int64_t lane_value(int64_t v, int lane)
 {
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, 63), hi = (uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), 63);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane), hi = (uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), lane);
     return (int64_t)((uint64_t)hi << 32 | lo);
 }
+__device__ __forceinline__ int64_t last_lane(int64_t v) { return lane_value(v, 63); }
 
 // sums over the lanes up to and including each: within rows, then the last lane of a row to the next row, then of the first
 // two rows to the others

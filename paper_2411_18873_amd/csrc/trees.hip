@@ -940,44 +940,80 @@ struct Settled {
     float leaf[256];
 };
 
-// The level before (`level_before`, the last one of a tree when `leaves` is set): the test of every node, and its leaves
-__device__ __forceinline__ void settle_level(const LevelArgs &a, int level_before, bool leaves, bool write, Settled &s)
+// The level before (`level_before`, the last one of a tree when LEAVES is set): the test of every node, and its leaves.  N
+// nodes of a wavefront at a time, everything they need requested before anything waits: at the start of a launch every load
+// goes past the L2.
+template <bool LEAVES, int N>
+__device__ __forceinline__ void settle_nodes(const LevelArgs &a, int nodes, bool write, Settled &s)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+    const int lane = threadIdx.x & 63, waves = blockDim.x >> 6;
     const bool bad = a.sc->bad != 0;
-    for (int node = wave; node < 1 << level_before; node += waves) {
-        const SplitRecord *mine = a.rec_in + (uint64_t)node * a.n_feat;
-        double best = 0.0;
-        uint32_t best_rank = 0xFFFFFFFFu;
-        for (int f = lane; f < a.n_feat; f += 64) {
-            const SplitRecord o = mine[f];
-            if (better_split(o.gain, o.rank, best, best_rank)) {
-                best = o.gain;
-                best_rank = o.rank;
-            }
-        }
-        best_of_wave(best, best_rank);
-        if (lane) continue;
-        const bool split = !bad && best_rank != 0xFFFFFFFFu && best > 0.0;
-        s.feat[node] = (uint16_t)(split ? best_rank / BINS : a.n_feat);
-        s.bin[node] = (uint16_t)(split ? best_rank % BINS : 0);
-        if (write) {
-            a.nf[node] = (uint8_t)(split ? best_rank / BINS : 0);
-            a.nt[node] = split ? (float)((best_rank % BINS) + 1) * 0.25f : __builtin_inff();
-        }
-        if (leaves) {
-            const NodeTotals t = a.tot_in[node];
-            SideSums side[2];
-            side[0] = split ? a.left_in[(uint64_t)node * a.n_feat + best_rank / BINS] : SideSums{t.all.g - t.odd.g, t.all.h - t.odd.h};
-            side[1] = SideSums{t.all.g - side[0].g, t.all.h - side[0].h};
+    for (int first = threadIdx.x >> 6; first < nodes; first += N * waves) {
+        double best[N];
+        uint32_t best_rank[N];
+        SideSums left[N]; // of this lane's best
+        NodeTotals total[N];
 #pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const float v = side[k].h && !bad ? (float)(-a.eta * (double)side[k].g / ((double)side[k].h + a.lam)) : 0.0f;
-                s.leaf[2 * node + k] = v;
-                if (write) a.leaf[2 * node + k] = v;
+        for (int k = 0; k < N; ++k) {
+            best[k] = 0.0;
+            best_rank[k] = 0xFFFFFFFFu;
+            left[k] = {0, 0};
+            if (LEAVES) total[k] = a.tot_in[min(first + k * waves, nodes - 1)];
+        }
+        for (int f = lane; f < a.n_feat; f += 64) {
+            SplitRecord o[N];
+            SideSums l[N];
+#pragma unroll
+            for (int k = 0; k < N; ++k) {
+                const uint64_t at = (uint64_t)min(first + k * waves, nodes - 1) * a.n_feat + f;
+                o[k] = a.rec_in[at];
+                if (LEAVES) l[k] = a.left_in[at]; // (of a feature without a split: left over, not used)
+            }
+#pragma unroll
+            for (int k = 0; k < N; ++k)
+                if (better_split(o[k].gain, o[k].rank, best[k], best_rank[k])) {
+                    best[k] = o[k].gain;
+                    best_rank[k] = o[k].rank;
+                    if (LEAVES) left[k] = l[k];
+                }
+        }
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            const int node = first + k * waves;
+            best_of_wave(best[k], best_rank[k]);
+            const bool split = !bad && best_rank[k] != 0xFFFFFFFFu && best[k] > 0.0;
+            if (node < nodes && lane == 0) {
+                s.feat[node] = (uint16_t)(split ? best_rank[k] / BINS : a.n_feat);
+                s.bin[node] = (uint16_t)(split ? best_rank[k] % BINS : 0);
+                if (write) {
+                    a.nf[node] = (uint8_t)(split ? best_rank[k] / BINS : 0);
+                    a.nt[node] = split ? (float)((best_rank[k] % BINS) + 1) * 0.25f : __builtin_inff();
+                }
+            }
+            if (LEAVES) {
+                // the winner's sums from the lane that holds them; lane 0 works the left leaf out, lane 1 the right one
+                const int from = __builtin_amdgcn_readfirstlane((int)(best_rank[k] / BINS)) & 63;
+                const SideSums all = total[k].all, odd = total[k].odd;
+                SideSums side = split ? SideSums{lane_value(left[k].g, from), lane_value(left[k].h, from)}
+                                      : SideSums{all.g - odd.g, all.h - odd.h};
+                if (lane) side = SideSums{all.g - side.g, all.h - side.h};
+                const float v = side.h && !bad ? (float)(-a.eta * (double)side.g / ((double)side.h + a.lam)) : 0.0f;
+                if (node < nodes && lane < 2) {
+                    s.leaf[2 * node + lane] = v;
+                    if (write) a.leaf[2 * node + lane] = v;
+                }
             }
         }
     }
+}
+
+template <bool LEAVES>
+__device__ __forceinline__ void settle_level(const LevelArgs &a, int level_before, bool write, Settled &s)
+{
+    const int nodes = 1 << level_before, waves = blockDim.x >> 6;
+    if (nodes <= waves) settle_nodes<LEAVES, 1>(a, nodes, write, s);
+    else if (LEAVES || nodes <= 2 * waves) settle_nodes<LEAVES, 2>(a, nodes, write, s); // (four with their sums spill)
+    else settle_nodes<LEAVES, 4>(a, nodes, write, s);
 }
 
 // where pair i goes from node j of the level before
@@ -1011,58 +1047,74 @@ __global__ __launch_bounds__(LEVEL_THREADS) void tree_level_kernel(LevelArgs a, 
     const int level_before = ROOT ? a.depth - 1 : level - 1;
     const bool settles = !ROOT || !first_tree;
     const bool placed = settles && level_before > 0; // the level before had several nodes: at_in says which
-    if (settles) settle_level(a, level_before, ROOT, write, settled);
-    __syncthreads();
-    for (uint32_t base = tid; base < a.n; base += LEVEL_UNROLL * LEVEL_THREADS) {
+    struct Pairs {
         uint32_t i[LEVEL_UNROLL], r[LEVEL_UNROLL];
         long long g[LEVEL_UNROLL], h[LEVEL_UNROLL];
+        float p[LEVEL_UNROLL], y[LEVEL_UNROLL];
         uint8_t b[LEVEL_UNROLL], odd[LEVEL_UNROLL];
+    } v;
+    // (a wavefront past the last pair skips the group; its lanes past it take the last pair again, not counted)
+    const uint32_t wave_first = (uint32_t)__builtin_amdgcn_readfirstlane(tid);
+    auto past = [&](uint32_t base, int u) { return base - tid + wave_first + u * LEVEL_THREADS >= a.n; };
+    auto request = [&](uint32_t base) {
 #pragma unroll
         for (int u = 0; u < LEVEL_UNROLL; ++u) {
-            i[u] = min(base + u * LEVEL_THREADS, a.n - 1); // (past the end the last pair again, not counted)
-            b[u] = a.bins[(uint64_t)f * a.n + i[u]];
-            odd[u] = f == 0 ? a.bins[(uint64_t)a.n_feat * a.n + i[u]] : (uint8_t)0;
-            r[u] = placed ? a.at_in[i[u]] : 0;
-        }
-        if (ROOT) {
-            float p[LEVEL_UNROLL], y[LEVEL_UNROLL];
-#pragma unroll
-            for (int u = 0; u < LEVEL_UNROLL; ++u) {
-                p[u] = a.p_in[i[u]];
-                y[u] = a.y[i[u]];
+            if (past(base, u)) break;
+            v.i[u] = min(base + u * LEVEL_THREADS, a.n - 1);
+            v.b[u] = a.bins[(uint64_t)f * a.n + v.i[u]];
+            v.odd[u] = f == 0 ? a.bins[(uint64_t)a.n_feat * a.n + v.i[u]] : (uint8_t)0;
+            v.r[u] = placed ? a.at_in[v.i[u]] : 0;
+            if (ROOT) {
+                v.p[u] = a.p_in[v.i[u]];
+                v.y[u] = a.y[v.i[u]];
+            } else {
+                v.g[u] = a.gq[v.i[u]];
             }
+            if (settles) v.h[u] = a.hq[v.i[u]]; // (the second derivative is the same for every tree)
+        }
+    };
+    request(tid); // on their way while the level before is settled
+    __builtin_amdgcn_sched_barrier(0);
+    if (settles) settle_level<ROOT>(a, level_before, write, settled);
+    __syncthreads();
+    for (uint32_t base = tid; base - tid < a.n; base += LEVEL_UNROLL * LEVEL_THREADS) {
+        if (base != (uint32_t)tid) request(base);
+        uint8_t right[LEVEL_UNROLL]; // the bin that sends a pair to a child, all requested together
+        if (settles) {
 #pragma unroll
             for (int u = 0; u < LEVEL_UNROLL; ++u) {
-                if (settles) p[u] = p[u] + settled.leaf[child_of(a, settled, r[u], i[u])];
-                const double yi = (double)y[u], d = (double)p[u] - yi;
-                g[u] = quantise(2.0 * d / yi);
-                h[u] = quantise(2.0 / yi);
-                r[u] = 0;
+                if (past(base, u)) break;
+                right[u] = a.bins[(uint64_t)settled.feat[v.r[u]] * a.n + v.i[u]];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < LEVEL_UNROLL; ++u) {
+            if (past(base, u)) break;
+            const uint32_t child = settles ? 2 * v.r[u] + (right[u] <= settled.bin[v.r[u]] ? 0u : 1u) : 0u;
+            if (ROOT) {
+                if (settles) v.p[u] = v.p[u] + settled.leaf[child];
+                const double yi = (double)v.y[u], d = (double)v.p[u] - yi;
+                v.g[u] = quantise(2.0 * d / yi);
+                if (!settles) v.h[u] = quantise(2.0 / yi);
+                v.r[u] = 0;
                 if (write) {
-                    a.p_out[i[u]] = p[u];
-                    a.gq[i[u]] = g[u];
-                    a.hq[i[u]] = h[u];
+                    a.p_out[v.i[u]] = v.p[u];
+                    a.gq[v.i[u]] = v.g[u];
+                    if (!settles) a.hq[v.i[u]] = v.h[u];
                 }
+            } else {
+                v.r[u] = child;
+                if (write) a.at_out[v.i[u]] = (uint8_t)child;
             }
-        } else {
-#pragma unroll
-            for (int u = 0; u < LEVEL_UNROLL; ++u) {
-                g[u] = a.gq[i[u]];
-                h[u] = a.hq[i[u]];
-                r[u] = child_of(a, settled, r[u], i[u]);
-                if (write) a.at_out[i[u]] = (uint8_t)r[u];
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < LEVEL_UNROLL; ++u) {
-            const uint32_t rr = r[u] - (uint32_t)node0; // wraps for nodes below the group
-            if (rr >= (uint32_t)in_group || base + u * LEVEL_THREADS >= a.n) continue;
-            const uint32_t cell = (rr * copies + (lane & (copies - 1))) * LEVEL_STRIDE + b[u];
-            atomicAdd(&hg[cell], (unsigned long long)g[u]);
-            atomicAdd(&hh[cell], (unsigned long long)h[u]);
-            if (odd[u]) {
-                atomicAdd(&odd_g[rr], (unsigned long long)g[u]);
-                atomicAdd(&odd_h[rr], (unsigned long long)h[u]);
+            const uint32_t rr = v.r[u] - (uint32_t)node0; // wraps for nodes below the group
+            if (rr < (uint32_t)in_group && base + u * LEVEL_THREADS < a.n) {
+                const uint32_t cell = (rr * copies + (lane & (copies - 1))) * LEVEL_STRIDE + v.b[u];
+                atomicAdd(&hg[cell], (unsigned long long)v.g[u]);
+                atomicAdd(&hh[cell], (unsigned long long)v.h[u]);
+                if (v.odd[u]) {
+                    atomicAdd(&odd_g[rr], (unsigned long long)v.g[u]);
+                    atomicAdd(&odd_h[rr], (unsigned long long)v.h[u]);
+                }
             }
         }
     }
@@ -1130,7 +1182,7 @@ __global__ __launch_bounds__(1024) void tree_last_kernel(LevelArgs a, int any_tr
 {
     __shared__ Settled settled;
     __shared__ double scratch[1024];
-    if (any_tree) settle_level(a, a.depth - 1, true, true, settled);
+    if (any_tree) settle_level<true>(a, a.depth - 1, true, settled);
     __syncthreads();
     double sum = 0.0;
     for (uint32_t i = threadIdx.x; i < a.n; i += 1024) {
