@@ -43,6 +43,24 @@ __device__ __forceinline__ uint32_t wave_least(uint32_t v)
     return v;
 }
 
+// the largest of a wavefront's values, none of them a NaN, in every lane
+__device__ __forceinline__ double wave_most(double v)
+{
+    auto two = [](uint32_t hi, uint32_t lo) { return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo); };
+#pragma unroll
+    for (uint32_t stride = 1; stride < 16; stride <<= 1) v = __builtin_fmax(v, lane_exchange(v, stride));
+    {
+        const uint64_t u = __builtin_bit_cast(uint64_t, v); // (both sides of a pair arrive in both of its lanes)
+        const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+        const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)u, (uint32_t)u, false, false);
+        v = __builtin_fmax(two(hi[0], lo[0]), two(hi[1], lo[1]));
+    }
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)u, (uint32_t)u, false, false);
+    return __builtin_fmax(two(hi[0], lo[0]), two(hi[1], lo[1]));
+}
+
 // the value of one lane (the same for all), in every lane
 __device__ __forceinline__ int64_t lane_value(int64_t v, int lane)
 {

@@ -728,18 +728,15 @@ __device__ __forceinline__ bool better_split(double og, uint32_t orank, double g
     return og > g || (og == g && orank < rank);
 }
 
-// the best split of a wavefront's, in every lane
+// The best split of a wavefront's, in every lane: the largest gain, and the lowest rank of those that have it (ranks are
+// distinct but for the one of no split).  (Exchanging gain and rank together: a hundred instructions for forty.)
 __device__ __forceinline__ void best_of_wave(double &gain, uint32_t &rank)
 {
-#pragma unroll
-    for (uint32_t stride = 1; stride < 64; stride <<= 1) {
-        const double og = lane_exchange(gain, stride);
-        const uint32_t orank = lane_exchange(rank, stride);
-        if (better_split(og, orank, gain, rank)) {
-            gain = og;
-            rank = orank;
-        }
-    }
+    const double most = wave_most(gain);
+    const uint64_t have = __ballot(gain == most);
+    if (__popcll(have) == 1) rank = (uint32_t)__builtin_amdgcn_readlane((int)rank, (int)__ffsll((unsigned long long)have) - 1);
+    else rank = wave_least(gain == most ? rank : 0xFFFFFFFFu);
+    gain = most;
 }
 
 __global__ __launch_bounds__(SPLIT_FEATS * 64) void tree_split_kernel(unsigned long long *__restrict__ hist, int n_feat,
@@ -937,6 +934,7 @@ struct LevelArgs {
 struct Settled {
     uint16_t feat[128]; // of every node of the level before: a pair goes left when its bin of feat is at most bin
     uint16_t bin[128];
+    SideSums side[256]; // (a tree's last level)
     float leaf[256];
 };
 
@@ -991,17 +989,13 @@ __device__ __forceinline__ void settle_nodes(const LevelArgs &a, int nodes, bool
                 }
             }
             if (LEAVES) {
-                // the winner's sums from the lane that holds them; lane 0 works the left leaf out, lane 1 the right one
+                // the winner's sums from the lane that holds them
                 const int from = __builtin_amdgcn_readfirstlane((int)(best_rank[k] / BINS)) & 63;
                 const SideSums all = total[k].all, odd = total[k].odd;
                 SideSums side = split ? SideSums{lane_value(left[k].g, from), lane_value(left[k].h, from)}
                                       : SideSums{all.g - odd.g, all.h - odd.h};
                 if (lane) side = SideSums{all.g - side.g, all.h - side.h};
-                const float v = side.h && !bad ? (float)(-a.eta * (double)side.g / ((double)side.h + a.lam)) : 0.0f;
-                if (node < nodes && lane < 2) {
-                    s.leaf[2 * node + lane] = v;
-                    if (write) a.leaf[2 * node + lane] = v;
-                }
+                if (node < nodes && lane < 2) s.side[2 * node + lane] = side;
             }
         }
     }
@@ -1014,6 +1008,15 @@ __device__ __forceinline__ void settle_level(const LevelArgs &a, int level_befor
     if (nodes <= waves) settle_nodes<LEAVES, 1>(a, nodes, write, s);
     else if (LEAVES || nodes <= 2 * waves) settle_nodes<LEAVES, 2>(a, nodes, write, s); // (four with their sums spill)
     else settle_nodes<LEAVES, 4>(a, nodes, write, s);
+    if (LEAVES) { // (a thread per leaf: a wavefront that divides for two leaves of a node takes as long as for 64)
+        __syncthreads();
+        if ((int)threadIdx.x < 2 * nodes) {
+            const SideSums side = s.side[threadIdx.x];
+            const float v = side.h && a.sc->bad == 0 ? (float)(-a.eta * (double)side.g / ((double)side.h + a.lam)) : 0.0f;
+            s.leaf[threadIdx.x] = v;
+            if (write) a.leaf[threadIdx.x] = v;
+        }
+    }
 }
 
 // where pair i goes from node j of the level before
@@ -1132,31 +1135,20 @@ __global__ __launch_bounds__(LEVEL_THREADS) void tree_level_kernel(LevelArgs a, 
     // a wavefront per node, 64 bins at a time; gains and ties as in tree_split_kernel.  An empty bin splits like the bin
     // before it, which has the lower rank, so only bins with pairs are evaluated, and stretches without any are skipped.
     if (wave >= in_group) return;
+    const unsigned long long *node_g = hg + wave * copies * LEVEL_STRIDE, *node_h = hh + wave * copies * LEVEL_STRIDE;
     long long g[4], h[4];
-    SideSums total = {0, 0};
+    uint64_t filled[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const int cell = wave * copies * LEVEL_STRIDE + 64 * q + lane;
-        g[q] = (long long)hg[cell];
-        h[q] = (long long)hh[cell];
-        total.g += g[q];
-        total.h += h[q];
+        g[q] = (long long)node_g[64 * q + lane];
+        h[q] = (long long)node_h[64 * q + lane];
+        filled[q] = __ballot(h[q] != 0);
     }
-    total.g = last_lane(wave_prefix_sum((int64_t)total.g));
-    total.h = last_lane(wave_prefix_sum((int64_t)total.h));
-    double best = 0.0;
+    double best = 0.0, parent = 0.0;
     uint32_t best_rank = 0xFFFFFFFFu;
-    SideSums best_left = {0, 0}, before = {0, 0};
-    const double parent = (double)total.g * (double)total.g / ((double)total.h + a.lam);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        if (!__any(h[q] != 0)) continue;
-        const long long pg = wave_prefix_sum((int64_t)g[q]), ph = wave_prefix_sum((int64_t)h[q]);
-        const SideSums left = {before.g + pg, before.h + ph};
-        before.g += last_lane(pg);
-        before.h += last_lane(ph);
-        const int bin = 64 * q + lane;
-        if (h[q] == 0 || bin >= 255 || left.h == total.h) continue;
+    SideSums best_left = {0, 0}, total = {0, 0};
+    auto judge = [&](SideSums left, long long in_bin, int bin) {
+        if (in_bin == 0 || bin >= 255 || left.h == total.h) return;
         const SideSums right = {total.g - left.g, total.h - left.h};
         const double gain = (double)left.g * (double)left.g / ((double)left.h + a.lam) +
                             (double)right.g * (double)right.g / ((double)right.h + a.lam) - parent;
@@ -1165,6 +1157,38 @@ __global__ __launch_bounds__(LEVEL_THREADS) void tree_level_kernel(LevelArgs a, 
             best = gain;
             best_rank = rank;
             best_left = left;
+        }
+    };
+    auto parent_gain = [&] { return (double)total.g * (double)total.g / ((double)total.h + a.lam); };
+    // the first and the last bin with pairs (none at all: 0 and 0)
+    const int lowest = filled[0] ? __builtin_ctzll(filled[0]) : filled[1] ? 64 + __builtin_ctzll(filled[1]) :
+                       filled[2] ? 128 + __builtin_ctzll(filled[2]) : filled[3] ? 192 + __builtin_ctzll(filled[3]) : 0;
+    const int highest = filled[3] ? 255 - __builtin_clzll(filled[3]) : filled[2] ? 191 - __builtin_clzll(filled[2]) :
+                        filled[1] ? 127 - __builtin_clzll(filled[1]) : filled[0] ? 63 - __builtin_clzll(filled[0]) : 0;
+    if (highest - lowest < 64) {
+        // they fit one scan, from the first of them on: as a rule, for values that are logarithms of one operator's schedules
+        const int bin = lowest + lane;
+        const long long gb = bin < BINS ? (long long)node_g[bin] : 0, hb = bin < BINS ? (long long)node_h[bin] : 0;
+        const SideSums left = {wave_prefix_sum((int64_t)gb), wave_prefix_sum((int64_t)hb)};
+        total = {last_lane(left.g), last_lane(left.h)};
+        parent = parent_gain();
+        judge(left, hb, bin);
+    } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            total.g += g[q];
+            total.h += h[q];
+        }
+        total = {last_lane(wave_prefix_sum((int64_t)total.g)), last_lane(wave_prefix_sum((int64_t)total.h))};
+        parent = parent_gain();
+        SideSums before = {0, 0};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (!filled[q]) continue;
+            const long long pg = wave_prefix_sum((int64_t)g[q]), ph = wave_prefix_sum((int64_t)h[q]);
+            judge({before.g + pg, before.h + ph}, h[q], 64 * q + lane);
+            before.g += last_lane(pg);
+            before.h += last_lane(ph);
         }
     }
     const uint32_t own_rank = best_rank;
