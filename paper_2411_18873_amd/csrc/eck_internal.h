@@ -102,13 +102,24 @@ __device__ __forceinline__ float adam_one(float *theta, uint64_t P, uint64_t i, 
 // forward pass of an fp32 model (score_f32.hip); mn: also the minima, or NULL
 int32_t score_f32(const eck_model *m, const float *feat, uint64_t ld, uint64_t n, float *out, const MinArgs *mn,
                   hipStream_t stream);
-// re-derive the packed weights from theta (BF16 models); enqueued on stream
-int32_t model_repack(eck_model *m, hipStream_t stream);
+// What a refit's kernels pass on, device memory in the call's workspace
+struct RefitScalars {
+    float emax;
+    uint32_t bad; // data error found in the labels: leave the model alone
+    float snr, loss;
+};
+// The end of costmodel_update in one launch: the SNR of the predictions `pred` made on entry (NULL: already in *sc), the step
+// count, the call's results, and the packed weights of a BF16 model
+int32_t refit_finish(eck_model *m, const float *pred, const float *y, uint64_t n_pairs, int32_t n_steps, const RefitScalars *sc,
+                     float *snr_out, float *loss_out, hipStream_t stream);
 // Adam steps of a BF16 model in two launches per step (refit.hip): whether that path takes this call, the bytes it
 // needs behind the other buffers of costmodel_update's workspace, and the steps themselves (labels y and the
 // data-error flag come from the caller's kernels; the last step's mean loss goes to *loss_scalar, device memory)
 bool refit_applies(const eck_model *m, const void *feat, int32_t feat_dtype, uint64_t ld, int minibatch);
 uint64_t refit_workspace_bytes(const eck_model *m, int minibatch);
+// (refit_begin: labels y from the measured energies, and the weights' copies that the steps multiply with)
+int32_t refit_begin(const eck_model *m, const float *energy, uint64_t n_pairs, float *y, RefitScalars *sc, int32_t minibatch, void *ws,
+                    hipStream_t st);
 int32_t refit_steps(const eck_model *m, const void *feat, int32_t feat_dtype, uint64_t ld, const float *y, uint64_t n_pairs,
                     int32_t n_steps, int32_t minibatch, float lr, float beta1, float beta2, float eps,
                     const uint32_t *bad_flag, float *loss_scalar, void *ws, hipStream_t st);

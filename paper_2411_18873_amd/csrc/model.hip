@@ -7,6 +7,7 @@
 #include <type_traits>
 
 #include "eck_internal.h"
+#include "refit_labels.h"
 
 using namespace eck;
 
@@ -73,64 +74,111 @@ __device__ __forceinline__ uint16_t bf16_bits(float x)
     return (uint16_t)(u >> 16);
 }
 
-// theta (fp32 master) -> packed buffer.  One thread per packed element.
-__global__ void pack_kernel(const float *__restrict__ theta, int F, int H1, int H2, uint64_t off_w1, uint64_t off_b1,
-                            uint64_t off_w2, uint64_t off_b2, uint64_t off_w3, uint64_t off_b3,
-                            unsigned char *__restrict__ packed, PackedLayout L)
+// Shape and destination of a BF16 model's packed weights; total: elements of the packed buffer (0: an fp32 model, none)
+struct PackArgs {
+    int F, H1, H2;
+    uint64_t off_w1, off_b1, off_w2, off_b2, off_w3, off_b3;
+    unsigned char *packed;
+    PackedLayout L;
+    uint32_t total;
+};
+
+PackArgs pack_args(const eck_model *m)
 {
+    PackArgs a = {};
+    if (m->dtype != ECK_BF16) return a;
+    const int F = m->widths[0], H1 = m->widths[1], H2 = m->widths[2];
+    return {F, H1, H2, m->off_w[0], m->off_b[0], m->off_w[1], m->off_b[1], m->off_w[2], m->off_b[2], (unsigned char *)m->d_packed,
+            packed_layout(F, H1, H2), (uint32_t)(F * H1 + H1 + H1 * H2 + 2 * H2 + 1)};
+}
+
+// theta (fp32 master) -> element e of the packed buffer
+__device__ __forceinline__ void pack_element(const float *__restrict__ theta, const PackArgs &a, uint32_t e)
+{
+    const int F = a.F, H1 = a.H1, H2 = a.H2;
+    const uint64_t off_w1 = a.off_w1, off_b1 = a.off_b1, off_w2 = a.off_w2, off_b2 = a.off_b2, off_w3 = a.off_w3, off_b3 = a.off_b3;
+    unsigned char *packed = a.packed;
+    const PackedLayout &L = a.L;
     const uint32_t n_w1 = F * H1, n_w1b = H1, n_w2 = H1 * H2;
-    const uint32_t total = n_w1 + n_w1b + n_w2 + 2 * H2 + 1;
-    for (uint32_t e = blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gridDim.x * blockDim.x) {
-        if (e < n_w1) {
-            // [oc][ks][lane][t]
-            const uint32_t t = e & 7, lane = (e >> 3) & 63, frag = e >> 9;
-            const uint32_t ksteps = F / 16, ks = frag % ksteps, oc = frag / ksteps;
-            const uint32_t h = lane >> 5, r = lane & 31;
-            const uint32_t k = 16 * ks + 8 * h + t, unit = 32 * oc + r;
-            reinterpret_cast<uint16_t *>(packed + L.w1)[e] = bf16_bits(theta[off_w1 + (uint64_t)k * H1 + unit]);
-        } else if (e < n_w1 + n_w1b) {
-            const uint32_t x = e - n_w1;
+    if (e < n_w1) {
+        // [oc][ks][lane][t]
+        const uint32_t t = e & 7, lane = (e >> 3) & 63, frag = e >> 9;
+        const uint32_t ksteps = F / 16, ks = frag % ksteps, oc = frag / ksteps;
+        const uint32_t h = lane >> 5, r = lane & 31;
+        const uint32_t k = 16 * ks + 8 * h + t, unit = 32 * oc + r;
+        reinterpret_cast<uint16_t *>(packed + L.w1)[e] = bf16_bits(theta[off_w1 + (uint64_t)k * H1 + unit]);
+    } else if (e < n_w1 + n_w1b) {
+        const uint32_t x = e - n_w1;
+        const uint32_t q = x & 15, h = (x >> 4) & 1, chunk = x >> 5;
+        reinterpret_cast<float *>(packed + L.w1b)[x] = round_through_bf16(theta[off_b1 + unit_of_dreg(chunk, h, q)]);
+    } else if (e < n_w1 + n_w1b + n_w2) {
+        const uint32_t x = e - n_w1 - n_w1b;
+        const uint32_t t = x & 7, lane = (x >> 3) & 63, frag = x >> 9;
+        const uint32_t ksteps = H1 / 16, ks = frag % ksteps, oc = frag / ksteps;
+        const uint32_t h = lane >> 5, r = lane & 31;
+        const uint32_t k = unit_of_dreg(ks >> 1, h, 8 * (ks & 1) + t), unit = 32 * oc + r;
+        reinterpret_cast<uint16_t *>(packed + L.w2)[x] = bf16_bits(theta[off_w2 + (uint64_t)k * H2 + unit]);
+    } else {
+        uint32_t x = e - n_w1 - n_w1b - n_w2;
+        if (x < (uint32_t)H2) {
             const uint32_t q = x & 15, h = (x >> 4) & 1, chunk = x >> 5;
-            reinterpret_cast<float *>(packed + L.w1b)[x] = round_through_bf16(theta[off_b1 + unit_of_dreg(chunk, h, q)]);
-        } else if (e < n_w1 + n_w1b + n_w2) {
-            const uint32_t x = e - n_w1 - n_w1b;
-            const uint32_t t = x & 7, lane = (x >> 3) & 63, frag = x >> 9;
-            const uint32_t ksteps = H1 / 16, ks = frag % ksteps, oc = frag / ksteps;
-            const uint32_t h = lane >> 5, r = lane & 31;
-            const uint32_t k = unit_of_dreg(ks >> 1, h, 8 * (ks & 1) + t), unit = 32 * oc + r;
-            reinterpret_cast<uint16_t *>(packed + L.w2)[x] = bf16_bits(theta[off_w2 + (uint64_t)k * H2 + unit]);
+            reinterpret_cast<float *>(packed + L.b2)[x] = round_through_bf16(theta[off_b2 + unit_of_dreg(chunk, h, q)]);
+        } else if ((x -= H2) < (uint32_t)H2) {
+            const uint32_t q = x & 15, h = (x >> 4) & 1, chunk = x >> 5;
+            reinterpret_cast<float *>(packed + L.w3)[x] = round_through_bf16(theta[off_w3 + unit_of_dreg(chunk, h, q)]);
         } else {
-            uint32_t x = e - n_w1 - n_w1b - n_w2;
-            if (x < (uint32_t)H2) {
-                const uint32_t q = x & 15, h = (x >> 4) & 1, chunk = x >> 5;
-                reinterpret_cast<float *>(packed + L.b2)[x] = round_through_bf16(theta[off_b2 + unit_of_dreg(chunk, h, q)]);
-            } else if ((x -= H2) < (uint32_t)H2) {
-                const uint32_t q = x & 15, h = (x >> 4) & 1, chunk = x >> 5;
-                reinterpret_cast<float *>(packed + L.w3)[x] = round_through_bf16(theta[off_w3 + unit_of_dreg(chunk, h, q)]);
-            } else {
-                reinterpret_cast<float *>(packed + L.b3)[0] = round_through_bf16(theta[off_b3]);
-            }
+            reinterpret_cast<float *>(packed + L.b3)[0] = round_through_bf16(theta[off_b3]);
         }
     }
 }
 
-__global__ void fill_zero_kernel(float *p, uint64_t n)
+// A state handed over (n floats; zeros behind them) and the packed weights that go with it, in one launch
+__global__ __launch_bounds__(256) void set_state_kernel(const float *__restrict__ blob, uint64_t n, float *__restrict__ state,
+                                                        uint64_t floats, PackArgs pack)
 {
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
-        p[i] = 0.0f;
+    const uint64_t first = (uint64_t)blockIdx.x * 256 + threadIdx.x, step = (uint64_t)gridDim.x * 256;
+    for (uint64_t i = first; i < floats; i += step) state[i] = i < n ? blob[i] : 0.0f;
+    for (uint64_t e = first; e < pack.total; e += step) pack_element(blob, pack, (uint32_t)e);
 }
+
+__global__ __launch_bounds__(256) void get_state_kernel(const float *__restrict__ state, uint64_t floats, float *__restrict__ blob)
+{
+    const uint64_t step = (uint64_t)gridDim.x * 256;
+    for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < floats; i += step) blob[i] = state[i];
+}
+
+// Block 0: the SNR of the predictions on entry, the step count and the call's results; the others: the packed weights.  (One
+// launch for three: 8.6 us of kernels that hardly fill a compute unit, and two boundaries of 3.7 us.)
+__global__ __launch_bounds__(1024) void refit_finish_kernel(float *__restrict__ state, uint64_t P, const float *__restrict__ pred,
+                                                            const float *__restrict__ y, uint64_t n_pairs, int n_steps,
+                                                            const RefitScalars *sc, float *snr_out, float *loss_out, PackArgs pack)
+{
+    if (blockIdx.x == 0) {
+        const bool bad = sc->bad != 0;
+        float snr = sc->snr;
+        if (pred && !bad) snr = signal_to_noise(pred, y, n_pairs);
+        if (threadIdx.x == 0) {
+            if (!bad) state[3 * P] += (float)n_steps;
+            *snr_out = snr;
+            *loss_out = sc->loss;
+        }
+        return;
+    }
+    const uint32_t e = (blockIdx.x - 1) * 1024 + threadIdx.x;
+    if (e < pack.total) pack_element(state, pack, e);
+}
+
+// what a grid of 256 threads per block needs for so many floats, within reason
+unsigned state_blocks(uint64_t floats) { return (unsigned)(floats > 256 * 1024 ? 1024 : (floats + 255) / 256); }
 
 } // namespace
 
-int32_t eck::model_repack(eck_model *m, hipStream_t stream)
+int32_t eck::refit_finish(eck_model *m, const float *pred, const float *y, uint64_t n_pairs, int32_t n_steps, const RefitScalars *sc,
+                          float *snr_out, float *loss_out, hipStream_t stream)
 {
-    if (m->dtype != ECK_BF16) return ECK_OK;
-    const int F = m->widths[0], H1 = m->widths[1], H2 = m->widths[2];
-    const PackedLayout L = packed_layout(F, H1, H2);
-    const uint32_t total = F * H1 + (H1 / 32) * 512 + H1 * H2 + 2 * H2 + 1;
-    hipLaunchKernelGGL(pack_kernel, dim3((total + 255) / 256), dim3(256), 0, stream, m->d_state, F, H1, H2,
-                       m->off_w[0], m->off_b[0], m->off_w[1], m->off_b[1], m->off_w[2], m->off_b[2],
-                       (unsigned char *)m->d_packed, L);
+    const PackArgs pack = pack_args(m);
+    hipLaunchKernelGGL(refit_finish_kernel, dim3(1 + (pack.total + 1023) / 1024), dim3(1024), 0, stream, m->d_state, m->n_params, pred, y,
+                       n_pairs, n_steps, sc, snr_out, loss_out, pack);
     ECK_HIP_TRY(hipGetLastError());
     return ECK_OK;
 }
@@ -202,8 +250,13 @@ extern "C" int32_t eck_model_create(int32_t n_layers, const int32_t *widths, int
             return ECK_EDEVICE;
         }
     }
-    hipLaunchKernelGGL(fill_zero_kernel, dim3(256), dim3(256), 0, 0, m->d_state, 3 * off + 1);
-    if (hipGetLastError() != hipSuccess || model_repack(m, 0) != ECK_OK) {
+    // everything zero, the packed weights too
+    auto clear = [](void *p, uint64_t floats) {
+        hipLaunchKernelGGL(set_state_kernel, dim3(state_blocks(floats)), dim3(256), 0, 0, (const float *)nullptr, (uint64_t)0, (float *)p, floats, PackArgs{});
+    };
+    clear(m->d_state, 3 * off + 1);
+    if (m->d_packed) clear(m->d_packed, m->packed_bytes / 4);
+    if (hipGetLastError() != hipSuccess) {
         eck_model_destroy(m);
         return ECK_EDEVICE;
     }
@@ -226,19 +279,18 @@ extern "C" int32_t eck_model_set_state(eck_model *m, const float *blob, uint64_t
     const uint64_t P = m->n_params;
     if (n_floats != P && n_floats != 3 * P + 1) return ECK_ESHAPE;
     hipStream_t st = as_stream(stream);
-    ECK_HIP_TRY(hipMemcpyAsync(m->d_state, blob, n_floats * sizeof(float), hipMemcpyDeviceToDevice, st));
-    if (n_floats == P) {
-        hipLaunchKernelGGL(fill_zero_kernel, dim3(256), dim3(256), 0, st, m->d_state + P, 2 * P + 1);
-        ECK_HIP_TRY(hipGetLastError());
-    }
-    return model_repack(m, st);
+    hipLaunchKernelGGL(set_state_kernel, dim3(state_blocks(3 * P + 1)), dim3(256), 0, st, blob, n_floats, m->d_state, 3 * P + 1,
+                       pack_args(m));
+    ECK_HIP_TRY(hipGetLastError());
+    return ECK_OK;
 }
 
 extern "C" int32_t eck_model_get_state(const eck_model *m, float *blob, uint64_t n_floats, void *stream)
 {
     if (!m || !blob) return ECK_EINVAL;
     if (n_floats != 3 * m->n_params + 1) return ECK_ESHAPE;
-    ECK_HIP_TRY(hipMemcpyAsync(blob, m->d_state, n_floats * sizeof(float), hipMemcpyDeviceToDevice, as_stream(stream)));
+    hipLaunchKernelGGL(get_state_kernel, dim3(state_blocks(n_floats)), dim3(256), 0, as_stream(stream), m->d_state, n_floats, blob);
+    ECK_HIP_TRY(hipGetLastError());
     return ECK_OK;
 }
 

@@ -16,6 +16,7 @@
 // biases and the output weights rounded through bf16, the second hidden layer and the output layer in fp32.
 // Every reduction has a fixed order, so a run is reproducible bit for bit.
 #include "eck_internal.h"
+#include "refit_labels.h"
 
 using namespace eck;
 
@@ -433,12 +434,17 @@ __global__ __launch_bounds__(256) void step_weights_kernel(StepArgs a)
     }
 }
 
-// bf16 copies of W1 and W2 in the fragment order the rows kernel multiplies with
-__global__ void step_prepare_kernel(const float *theta, uint64_t off_w1, uint64_t off_w2, int F, int H1, int H2,
-                                    uint16_t *w1t, uint16_t *w2t, uint16_t *w2)
+// The last block: labels; the others: bf16 copies of W1 and W2 in the fragment order the rows kernel multiplies with
+__global__ __launch_bounds__(1024) void step_prepare_kernel(const float *theta, uint64_t off_w1, uint64_t off_w2, int F, int H1, int H2,
+                                                            uint16_t *w1t, uint16_t *w2t, uint16_t *w2, const float *energy,
+                                                            uint64_t n_pairs, float *y, RefitScalars *sc)
 {
+    if (blockIdx.x == gridDim.x - 1) {
+        make_labels(energy, n_pairs, y, sc);
+        return;
+    }
     const int n1 = F * H1, n2 = H1 * H2;
-    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < n1 + n2; e += gridDim.x * blockDim.x) {
+    for (int e = blockIdx.x * 1024 + threadIdx.x; e < n1 + n2; e += (gridDim.x - 1) * 1024) {
         if (e < n1) {
             const int f = e / H1, i = e % H1;
             w1t[frag_at(i, f, F)] = bf16_bits(theta[off_w1 + e]);
@@ -461,8 +467,6 @@ int32_t launch_steps(const eck_model *m, StepArgs a, int32_t feat_dtype, int32_t
     auto weights_kernel = feat_dtype == ECK_BF16 ? step_weights_kernel<F, H1, H2, true> : step_weights_kernel<F, H1, H2, false>;
     ECK_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(rows_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                     (int)lds));
-    hipLaunchKernelGGL(step_prepare_kernel, dim3(128), dim3(256), 0, st, a.theta, a.off_w1, a.off_w2, F, H1, H2, a.w1t, a.w2t,
-                       a.w2);
     const int B = a.rows;
     const uint64_t nb = n_pairs / (uint64_t)B;
     const unsigned weight_blocks = (H1 / 32) * (H2 / 32) + (F / 32) * (H1 / 32) + (H2 + 1 + 15) / 16;
@@ -498,9 +502,8 @@ bool eck::refit_applies(const eck_model *m, const void *feat, int32_t feat_dtype
     return m->widths[0] % 32 == 0; // tiles of W1 are 32 features tall
 }
 
-int32_t eck::refit_steps(const eck_model *m, const void *feat, int32_t feat_dtype, uint64_t ld, const float *y, uint64_t n_pairs,
-                         int32_t n_steps, int32_t minibatch, float lr, float beta1, float beta2, float eps,
-                         const uint32_t *bad_flag, float *loss_scalar, void *ws, hipStream_t st)
+// the buffers of a call's steps in its workspace, and the model's own
+static StepArgs step_buffers(const eck_model *m, int32_t minibatch, void *ws)
 {
     auto align = [](uint64_t v) { return (v + 255) & ~255ull; };
     const uint64_t F = m->widths[0], H1 = m->widths[1], H2 = m->widths[2], B = (uint64_t)minibatch;
@@ -511,8 +514,6 @@ int32_t eck::refit_steps(const eck_model *m, const void *feat, int32_t feat_dtyp
         return at;
     };
     StepArgs a = {};
-    a.feat = feat;
-    a.ld = ld;
     a.rows = minibatch;
     a.theta = m->d_state;
     a.P = m->n_params;
@@ -532,6 +533,28 @@ int32_t eck::refit_steps(const eck_model *m, const void *feat, int32_t feat_dtyp
     a.dy = reinterpret_cast<float *>(take(B * 4));
     a.lterm = reinterpret_cast<float *>(take(B * 4));
     a.corr = reinterpret_cast<float *>(take(2 * sizeof(float)));
+    return a;
+}
+
+int32_t eck::refit_begin(const eck_model *m, const float *energy, uint64_t n_pairs, float *y, RefitScalars *sc, int32_t minibatch, void *ws,
+                         hipStream_t st)
+{
+    const StepArgs a = step_buffers(m, minibatch, ws);
+    const int F = m->widths[0], H1 = m->widths[1], H2 = m->widths[2], blocks = (F * H1 + H1 * H2 + 1023) / 1024;
+    hipLaunchKernelGGL(step_prepare_kernel, dim3((blocks < 256 ? blocks : 256) + 1), dim3(1024), 0, st, a.theta, a.off_w1, a.off_w2, F, H1, H2,
+                       a.w1t, a.w2t, a.w2, energy, n_pairs, y, sc);
+    ECK_HIP_TRY(hipGetLastError());
+    return ECK_OK;
+}
+
+int32_t eck::refit_steps(const eck_model *m, const void *feat, int32_t feat_dtype, uint64_t ld, const float *y, uint64_t n_pairs,
+                         int32_t n_steps, int32_t minibatch, float lr, float beta1, float beta2, float eps,
+                         const uint32_t *bad_flag, float *loss_scalar, void *ws, hipStream_t st)
+{
+    const int F = m->widths[0], H1 = m->widths[1], H2 = m->widths[2];
+    StepArgs a = step_buffers(m, minibatch, ws);
+    a.feat = feat;
+    a.ld = ld;
     a.y = y;
     a.bad = bad_flag;
     a.lr = lr;

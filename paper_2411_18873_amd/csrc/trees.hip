@@ -15,6 +15,7 @@
 // evaluated in fp64 from those integers.
 #include "eck_internal.h"
 #include "lanes.h"
+#include "refit_labels.h"
 
 #include <atomic>
 #include <new>
@@ -93,6 +94,19 @@ __global__ void tree_set_kernel(const uint8_t *nf, const float *nt, const float 
         nt_out[from] = thr;
     }
     if (leaf_out) leaf_out[e] = leaf[e];
+}
+
+// An ensemble handed back: n_nodes nodes and n_leaves leaves, of which there are more
+__global__ __launch_bounds__(256) void tree_get_kernel(const uint8_t *nf, const float *nt, const float *leaf, uint64_t n_nodes, uint64_t n_leaves,
+                                                       uint8_t *nf_out, float *nt_out, float *leaf_out)
+{
+    const uint64_t step = (uint64_t)gridDim.x * 256;
+    for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < n_leaves; i += step) {
+        leaf_out[i] = leaf[i];
+        if (i >= n_nodes) continue;
+        nf_out[i] = nf[i];
+        nt_out[i] = nt[i];
+    }
 }
 
 // C candidates per block, its trees shared between S groups of C threads.
@@ -545,12 +559,6 @@ int32_t launch_score(const eck_trees *m, int n_trees, const void *feat, int32_t 
 
 // ----------------------------------------------------------------------------------------------- boosting
 
-struct BoostScalars {
-    float emax;
-    uint32_t bad;
-    float snr, loss;
-};
-
 // feature value -> histogram bin: 256 bins of width 1/4 on [0, 64); "bin(x) <= b" is "x < (b + 1) / 4"
 __device__ __forceinline__ uint32_t bin_of(float x)
 {
@@ -566,85 +574,48 @@ __device__ __forceinline__ long long quantise(double v)
     return __double2ll_rn(v * FIX);
 }
 
-__device__ double block_sum_f64(double v, double *scratch)
+// The last row of blocks: labels (its first block); the others: bins of every (feature, pair), computed once per call; row
+// n_feat of the bins is 1 where feature 0 is not below +inf (the pairs that go right at a node without a split, whose test
+// is "feature 0 < +inf").
+__global__ __launch_bounds__(1024) void tree_prepare_kernel(const void *__restrict__ feat, int is_bf16, uint64_t ld, uint64_t n_pairs, int n_feat,
+                                                            uint8_t *__restrict__ bins, const float *__restrict__ energy,
+                                                            float *__restrict__ y, RefitScalars *sc)
 {
-    scratch[threadIdx.x] = v;
-    __syncthreads();
-    for (int off = blockDim.x / 2; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off) scratch[threadIdx.x] += scratch[threadIdx.x + off];
-        __syncthreads();
-    }
-    const double r = scratch[0];
-    __syncthreads();
-    return r;
-}
-
-// one block: validate the measured energies and normalise them by their maximum (fp32 division)
-__global__ __launch_bounds__(1024) void tree_labels_kernel(const float *__restrict__ e, uint64_t n, float *__restrict__ y,
-                                                           BoostScalars *sc)
-{
-    __shared__ float smax[1024];
-    __shared__ uint32_t sbad[1024];
-    float mx = 0.0f;
-    uint32_t bad = 0;
-    for (uint64_t i = threadIdx.x; i < n; i += 1024) {
-        const float v = e[i];
-        if (!(v > 0.0f) || v == __builtin_inff()) bad = 1;
-        mx = fmaxf(mx, v);
-    }
-    smax[threadIdx.x] = mx;
-    sbad[threadIdx.x] = bad;
-    __syncthreads();
-    for (int off = 512; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off) {
-            smax[threadIdx.x] = fmaxf(smax[threadIdx.x], smax[threadIdx.x + off]);
-            sbad[threadIdx.x] |= sbad[threadIdx.x + off];
-        }
-        __syncthreads();
-    }
-    const float emax = smax[0];
-    for (uint64_t i = threadIdx.x; i < n; i += 1024) y[i] = e[i] / emax;
-    if (threadIdx.x == 0) {
-        sc->emax = emax;
-        sc->bad = sbad[0];
-        sc->snr = sc->loss = __builtin_nanf("");
-    }
-}
-
-// bins of every (feature, pair), computed once per call; row n_feat is 1 where feature 0 is not below +inf (the pairs
-// that go right at a node without a split, whose test is "feature 0 < +inf")
-__global__ void tree_bins_kernel(const void *__restrict__ feat, int is_bf16, uint64_t ld, uint64_t n_pairs, int n_feat,
-                                 uint8_t *__restrict__ bins)
-{
-    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint64_t i = (uint64_t)blockIdx.x * 1024 + threadIdx.x;
     const int f = blockIdx.y;
-    if (i >= n_pairs || f >= n_feat) return;
+    if (f == n_feat) {
+        if (blockIdx.x == 0) make_labels(energy, n_pairs, y, sc);
+        return;
+    }
+    if (i >= n_pairs) return;
     const float x = feature_value(feat, is_bf16, (uint64_t)f * ld + i);
     bins[(uint64_t)f * n_pairs + i] = (uint8_t)bin_of(x);
     if (f == 0) bins[(uint64_t)n_feat * n_pairs + i] = x < __builtin_inff() ? 0 : 1;
 }
 
-// SNR = sum y^2 / sum (p - y)^2 (which == 0: the ensemble on entry) or the mean Eq.-(1) loss (which == 1)
-__global__ __launch_bounds__(1024) void tree_quality_kernel(const float *__restrict__ p, const float *__restrict__ y,
-                                                            uint64_t n, int which, BoostScalars *sc)
+// SNR = sum y^2 / sum (p - y)^2 (the ensemble on entry)
+__device__ __forceinline__ void entry_quality(const float *__restrict__ p, const float *__restrict__ y, uint64_t n, RefitScalars *sc)
 {
-    __shared__ double scratch[1024];
-    double a = 0.0, b = 0.0;
+    const float snr = signal_to_noise(p, y, n);
+    if (threadIdx.x == 0 && !sc->bad) sc->snr = snr;
+}
+
+// the same, or the mean Eq.-(1) loss (which == 1)
+__global__ __launch_bounds__(1024) void tree_quality_kernel(const float *__restrict__ p, const float *__restrict__ y,
+                                                            uint64_t n, int which, RefitScalars *sc)
+{
+    if (which == 0) {
+        entry_quality(p, y, n, sc);
+        return;
+    }
+    __shared__ double scratch[512];
+    double loss = 0.0;
     for (uint64_t i = threadIdx.x; i < n; i += 1024) {
         const double yi = y[i], d = (double)p[i] - yi;
-        if (which == 0) {
-            a += yi * yi;
-            b += d * d;
-        } else {
-            a += d * d / yi;
-        }
+        loss += d * d / yi;
     }
-    a = block_sum_f64(a, scratch);
-    b = block_sum_f64(b, scratch);
-    if (threadIdx.x == 0 && !sc->bad) {
-        if (which == 0) sc->snr = (float)(a / b);
-        else sc->loss = (float)(a / (double)n);
-    }
+    loss = block_sum(loss, scratch);
+    if (threadIdx.x == 0 && !sc->bad) sc->loss = (float)(loss / (double)n);
 }
 
 // first and second derivative of Eq. (1) in the prediction, as integers of resolution 2^-20
@@ -817,7 +788,7 @@ __global__ __launch_bounds__(SPLIT_FEATS * 64) void tree_split_kernel(unsigned l
 // (equal values, so the order does not matter); nodes no pair stands on keep "does not split".
 __global__ void tree_partition_kernel(const void *__restrict__ feat, int is_bf16, uint64_t ld, uint64_t n_pairs,
                                       const SplitRecord *__restrict__ partial, uint32_t groups, uint32_t first_node,
-                                      const BoostScalars *sc, uint8_t *__restrict__ nf, float *__restrict__ nt,
+                                      const RefitScalars *sc, uint8_t *__restrict__ nf, float *__restrict__ nt,
                                       uint32_t *__restrict__ at)
 {
     const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -849,7 +820,7 @@ __global__ void tree_partition_kernel(const void *__restrict__ feat, int is_bf16
 __global__ __launch_bounds__(1024) void tree_leaf_kernel(const long long *__restrict__ gq, const long long *__restrict__ hq,
                                                          const uint32_t *__restrict__ at, uint64_t n_pairs,
                                                          uint32_t nodes, uint32_t leaves, double eta, double lam,
-                                                         float *__restrict__ leaf_out, const BoostScalars *sc)
+                                                         float *__restrict__ leaf_out, const RefitScalars *sc)
 {
     __shared__ unsigned long long sg[256], sh[256], sn[256];
     for (uint32_t l = threadIdx.x; l < leaves; l += 1024) sg[l] = sh[l] = sn[l] = 0;
@@ -876,7 +847,7 @@ __global__ void tree_advance_kernel(float *__restrict__ p, const uint32_t *__res
     if (i < n_pairs) p[i] = p[i] + lw[at[i] - nodes];
 }
 
-__global__ void tree_finish_kernel(const BoostScalars *sc, float *snr_out, float *loss_out)
+__global__ void tree_finish_kernel(const RefitScalars *sc, float *snr_out, float *loss_out)
 {
     if (threadIdx.x || blockIdx.x) return;
     *snr_out = sc->snr;
@@ -928,7 +899,7 @@ struct LevelArgs {
     uint8_t *nf; // the nodes of the level before, and (level 0) the leaves of the tree before
     float *nt, *leaf;
     double eta, lam;
-    const BoostScalars *sc;
+    RefitScalars *sc;
 };
 
 struct Settled {
@@ -1036,6 +1007,10 @@ __global__ __launch_bounds__(LEVEL_THREADS) void tree_level_kernel(LevelArgs a, 
     __shared__ Settled settled;
     __shared__ unsigned long long odd_g[LEVEL_SLOTS], odd_h[LEVEL_SLOTS];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (ROOT && (int)blockIdx.x == a.n_feat) { // the call's first launch has one more block
+        entry_quality(a.p_in, a.y, a.n, a.sc);
+        return;
+    }
     const int f = blockIdx.x, node0 = blockIdx.y * LEVEL_SLOTS;
     const int in_group = min(LEVEL_SLOTS, (1 << level) - node0);
     // Copies of each histogram while the level has few nodes, neighbouring lanes to different ones: features take few
@@ -1201,24 +1176,48 @@ __global__ __launch_bounds__(LEVEL_THREADS) void tree_level_kernel(LevelArgs a, 
     }
 }
 
-// one block: the last tree's last level, the pairs' final predictions, the mean Eq.-(1) loss, and the call's results
-__global__ __launch_bounds__(1024) void tree_last_kernel(LevelArgs a, int any_tree, BoostScalars *sc, float *snr_out, float *loss_out)
+// The words of nodes for the scoring kernel, from the arrays: slots first, first + step, ... of those of `trees` trees
+__device__ __forceinline__ void make_words(const uint8_t *nf, const float *nt, int n_feat, int depth, uint32_t trees, uint32_t *words,
+                                           uint32_t first, uint32_t step)
 {
+    const uint32_t nodes = (1u << depth) - 1u;
+    for (uint32_t e = first; e < trees << depth; e += step) {
+        const uint32_t t = e >> depth, i = e & nodes;
+        const uint64_t from = (uint64_t)t * nodes + (i ? i - 1 : 0); // word 0 is not read
+        words[(t << depth) + mirrored(i)] = bf16_node(nt[from], min((uint32_t)nf[from], (uint32_t)n_feat - 1u));
+    }
+}
+
+// Block 0: the last tree's last level, the pairs' final predictions, the mean Eq.-(1) loss, the call's results, and the words of
+// the last tree; the others: the words of the trees before it.  nf, nt, words: of the call's first tree.
+__global__ __launch_bounds__(1024) void tree_last_kernel(LevelArgs a, int n_rounds, const uint8_t *nf, const float *nt, uint32_t *words,
+                                                         float *snr_out, float *loss_out)
+{
+    if (blockIdx.x > 0) {
+        make_words(nf, nt, a.n_feat, a.depth, n_rounds - 1, words, (blockIdx.x - 1) * 1024 + threadIdx.x, (gridDim.x - 1) * 1024);
+        return;
+    }
     __shared__ Settled settled;
-    __shared__ double scratch[1024];
-    if (any_tree) settle_level<true>(a, a.depth - 1, true, settled);
+    __shared__ double scratch[512];
+    if (n_rounds) settle_level<true>(a, a.depth - 1, true, settled);
     __syncthreads();
     double sum = 0.0;
     for (uint32_t i = threadIdx.x; i < a.n; i += 1024) {
         float p = a.p_in[i];
-        if (any_tree) p = p + settled.leaf[child_of(a, settled, a.depth > 1 ? a.at_in[i] : 0u, i)];
+        if (n_rounds) p = p + settled.leaf[child_of(a, settled, a.depth > 1 ? a.at_in[i] : 0u, i)];
         const double yi = a.y[i], d = (double)p - yi;
         sum += d * d / yi;
     }
-    sum = block_sum_f64(sum, scratch);
+    if (n_rounds) { // (its last level was written by this block, before a barrier)
+        const uint32_t t = (uint32_t)n_rounds - 1, tree_nodes = (1u << a.depth) - 1u;
+        make_words(nf + (uint64_t)t * tree_nodes, nt + (uint64_t)t * tree_nodes, a.n_feat, a.depth, 1, words + ((uint64_t)t << a.depth), threadIdx.x, 1024);
+    } else {
+        entry_quality(a.p_in, a.y, a.n, a.sc);
+    }
+    sum = block_sum(sum, scratch);
     if (threadIdx.x == 0) {
-        *snr_out = sc->snr;
-        *loss_out = sc->bad ? sc->loss : (float)(sum / (double)a.n);
+        *snr_out = a.sc->snr;
+        *loss_out = a.sc->bad ? a.sc->loss : (float)(sum / (double)a.n);
     }
 }
 
@@ -1253,7 +1252,7 @@ BoostWs boost_layout(const eck_trees *m, uint64_t n_pairs)
     const uint64_t nodes = (uint64_t)1 << (m->depth - 1); // of the last level
     BoostWs w = {};
     uint64_t o = 0;
-    w.scalars = o; o = up(o + sizeof(BoostScalars));
+    w.scalars = o; o = up(o + sizeof(RefitScalars));
     w.y = o; o = up(o + n_pairs * 4);
     w.p = o; o = up(o + n_pairs * 4);
     w.gq = o; o = up(o + n_pairs * 8);
@@ -1283,7 +1282,7 @@ int32_t boost_levels(eck_trees *m, char *base, const BoostWs &w, uint64_t n_pair
                      float *snr_out, float *loss_out, hipStream_t st)
 {
     const size_t nodes = ((size_t)1 << m->depth) - 1, leaves = (size_t)1 << m->depth, last_nodes = (size_t)1 << (m->depth - 1);
-    BoostScalars *sc = reinterpret_cast<BoostScalars *>(base + w.scalars);
+    RefitScalars *sc = reinterpret_cast<RefitScalars *>(base + w.scalars);
     LevelArgs a = {};
     a.bins = reinterpret_cast<const uint8_t *>(base + w.bins);
     a.n = (uint32_t)n_pairs;
@@ -1332,7 +1331,7 @@ int32_t boost_levels(eck_trees *m, char *base, const BoostWs &w, uint64_t n_pair
             if (l == 0) {
                 a.p_in = p[p_side];
                 a.p_out = p[p_side ^ 1];
-                hipLaunchKernelGGL(tree_level_kernel<true>, grid, dim3(LEVEL_THREADS), LDS, st, a, l, r == 0 ? 1 : 0);
+                hipLaunchKernelGGL(tree_level_kernel<true>, dim3(grid.x + (r == 0 ? 1 : 0)), dim3(LEVEL_THREADS), LDS, st, a, l, r == 0 ? 1 : 0);
                 p_side ^= 1;
             } else {
                 hipLaunchKernelGGL(tree_level_kernel<false>, grid, dim3(LEVEL_THREADS), LDS, st, a, l, 0);
@@ -1342,7 +1341,10 @@ int32_t boost_levels(eck_trees *m, char *base, const BoostWs &w, uint64_t n_pair
     }
     if (n_rounds > 0) settle((size_t)m->n_trees + n_rounds - 1, m->depth - 1);
     a.p_in = p[p_side];
-    hipLaunchKernelGGL(tree_last_kernel, dim3(1), dim3(1024), 0, st, a, n_rounds > 0 ? 1 : 0, sc, snr_out, loss_out);
+    const size_t first = (size_t)m->n_trees;
+    const unsigned word_blocks = n_rounds > 1 ? (unsigned)(((((size_t)n_rounds - 1) << m->depth) + 1023) / 1024) : 0;
+    hipLaunchKernelGGL(tree_last_kernel, dim3(1 + (word_blocks < 64 ? word_blocks : 64)), dim3(1024), 0, st, a, n_rounds, m->d_feat + first * nodes,
+                       m->d_thr + first * nodes, m->d_word + first * leaves, snr_out, loss_out);
     ECK_HIP_TRY(hipGetLastError());
     return ECK_OK;
 }
@@ -1422,9 +1424,10 @@ extern "C" int32_t eck_trees_get(const eck_trees *m, uint8_t *node_feat, float *
     if (!node_feat || !node_thr || !leaf) return ECK_EINVAL;
     const size_t nodes = ((size_t)1 << m->depth) - 1, leaves = (size_t)1 << m->depth;
     hipStream_t st = as_stream(stream);
-    ECK_HIP_TRY(hipMemcpyAsync(node_feat, m->d_feat, m->n_trees * nodes, hipMemcpyDeviceToDevice, st));
-    ECK_HIP_TRY(hipMemcpyAsync(node_thr, m->d_thr, m->n_trees * nodes * 4, hipMemcpyDeviceToDevice, st));
-    ECK_HIP_TRY(hipMemcpyAsync(leaf, m->d_leaf, m->n_trees * leaves * 4, hipMemcpyDeviceToDevice, st));
+    const uint64_t slots = (uint64_t)m->n_trees * leaves;
+    hipLaunchKernelGGL(tree_get_kernel, dim3((unsigned)(slots < 1024 * 256 ? (slots + 255) / 256 : 1024)), dim3(256), 0, st, m->d_feat, m->d_thr,
+                       m->d_leaf, m->n_trees * nodes, slots, node_feat, node_thr, leaf);
+    ECK_HIP_TRY(hipGetLastError());
     return ECK_OK;
 }
 
@@ -1460,7 +1463,7 @@ extern "C" int32_t treemodel_update(eck_trees *m, const void *feat, int32_t feat
 
     hipStream_t st = as_stream(stream);
     char *base = static_cast<char *>(ws);
-    BoostScalars *sc = reinterpret_cast<BoostScalars *>(base + w.scalars);
+    RefitScalars *sc = reinterpret_cast<RefitScalars *>(base + w.scalars);
     float *y = reinterpret_cast<float *>(base + w.y), *p = reinterpret_cast<float *>(base + w.p);
     long long *gq = reinterpret_cast<long long *>(base + w.gq), *hq = reinterpret_cast<long long *>(base + w.hq);
     uint32_t *at = reinterpret_cast<uint32_t *>(base + w.at);
@@ -1473,26 +1476,18 @@ extern "C" int32_t treemodel_update(eck_trees *m, const void *feat, int32_t feat
     const unsigned pair_blocks = (unsigned)((n_pairs + 255) / 256);
     const double lam = (double)lambda * FIX;
 
-    hipLaunchKernelGGL(tree_labels_kernel, dim3(1), dim3(1024), 0, st, energy_measured, n_pairs, y, sc);
+    hipLaunchKernelGGL(tree_prepare_kernel, dim3((unsigned)((n_pairs + 1023) / 1024), m->n_feat + 1), dim3(1024), 0, st, feat, is_bf16, ld, n_pairs,
+                       m->n_feat, bins, energy_measured, y, sc);
     // predictions of the ensemble as it stands: the scoring kernel (fp32, base first, trees in order)
     int32_t rc = launch_score(m, m->n_trees, feat, feat_dtype, ld, n_pairs, p, st);
     if (rc != ECK_OK) return rc;
-    hipLaunchKernelGGL(tree_quality_kernel, dim3(1), dim3(1024), 0, st, p, y, n_pairs, 0, sc);
-    hipLaunchKernelGGL(tree_bins_kernel, dim3(pair_blocks, m->n_feat), dim3(256), 0, st, feat, is_bf16, ld, n_pairs,
-                       m->n_feat, bins);
     if (n_pairs <= level_max_pairs(m)) {
         rc = boost_levels(m, base, w, n_pairs, n_rounds, eta, lam, snr_out, loss_out, st);
         if (rc != ECK_OK) return rc;
-        if (n_rounds > 0) {
-            const size_t t = (size_t)m->n_trees;
-            hipLaunchKernelGGL(tree_set_kernel, dim3((unsigned)((((size_t)n_rounds << m->depth) + 255) / 256)), dim3(256), 0, st,
-                               m->d_feat + t * nodes, m->d_thr + t * nodes, nullptr, m->n_feat, m->depth, n_rounds, nullptr, nullptr,
-                               nullptr, m->d_word + t * leaves);
-            ECK_HIP_TRY(hipGetLastError());
-        }
         m->n_trees += n_rounds;
         return ECK_OK;
     }
+    hipLaunchKernelGGL(tree_quality_kernel, dim3(1), dim3(1024), 0, st, p, y, n_pairs, 0, sc);
     {
         // the histogram buffer starts clear; from then on the split kernel clears what it reads
         const uint64_t words = ((uint64_t)1 << (m->depth - 1)) * m->n_feat * BINS * 3;

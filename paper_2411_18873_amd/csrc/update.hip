@@ -16,6 +16,7 @@
 #include <cmath>
 
 #include "eck_internal.h"
+#include "refit_labels.h"
 
 using namespace eck;
 
@@ -176,76 +177,20 @@ __global__ __launch_bounds__(256 * KG) void gemm_mfma_kernel(GemmArgs first, Gem
     }
 }
 
-struct Scalars {
-    float emax;
-    uint32_t bad;
-    float snr, loss;
-};
-
-// one block: validate the measured energies, normalise them by their maximum
-__global__ __launch_bounds__(1024) void labels_kernel(const float *__restrict__ e, uint64_t n, float *__restrict__ y,
-                                                      Scalars *sc)
+__global__ __launch_bounds__(1024) void labels_kernel(const float *__restrict__ e, uint64_t n, float *__restrict__ y, RefitScalars *sc)
 {
-    __shared__ float smax[1024];
-    __shared__ uint32_t sbad[1024];
-    float mx = 0.0f;
-    uint32_t bad = 0;
-    for (uint64_t i = threadIdx.x; i < n; i += 1024) {
-        const float v = e[i];
-        if (!(v > 0.0f) || v == __builtin_inff()) bad = 1;
-        mx = fmaxf(mx, v);
-    }
-    smax[threadIdx.x] = mx;
-    sbad[threadIdx.x] = bad;
-    __syncthreads();
-    for (int off = 512; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off) {
-            smax[threadIdx.x] = fmaxf(smax[threadIdx.x], smax[threadIdx.x + off]);
-            sbad[threadIdx.x] |= sbad[threadIdx.x + off];
-        }
-        __syncthreads();
-    }
-    const float emax = smax[0];
-    for (uint64_t i = threadIdx.x; i < n; i += 1024) y[i] = e[i] / emax;
-    if (threadIdx.x == 0) {
-        sc->emax = emax;
-        sc->bad = sbad[0];
-        sc->snr = sc->loss = __builtin_nanf("");
-    }
-}
-
-// fixed-order block reduction in double
-__device__ double block_sum(double v, double *scratch)
-{
-    scratch[threadIdx.x] = v;
-    __syncthreads();
-    for (int off = blockDim.x / 2; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off) scratch[threadIdx.x] += scratch[threadIdx.x + off];
-        __syncthreads();
-    }
-    const double r = scratch[0];
-    __syncthreads();
-    return r;
+    make_labels(e, n, y, sc);
 }
 
 // SNR = sum y^2 / sum (pred - y)^2 over the whole buffer (one block)
-__global__ __launch_bounds__(1024) void snr_kernel(const float *__restrict__ pred, const float *__restrict__ y,
-                                                   uint64_t n, Scalars *sc)
+__global__ __launch_bounds__(1024) void snr_kernel(const float *__restrict__ pred, const float *__restrict__ y, uint64_t n, RefitScalars *sc)
 {
-    __shared__ double scratch[1024];
-    double sig = 0.0, noise = 0.0;
-    for (uint64_t i = threadIdx.x; i < n; i += 1024) {
-        const double yi = y[i], d = (double)pred[i] - yi;
-        sig += yi * yi;
-        noise += d * d;
-    }
-    sig = block_sum(sig, scratch);
-    noise = block_sum(noise, scratch);
-    if (threadIdx.x == 0 && !sc->bad) sc->snr = (float)(sig / noise);
+    const float snr = signal_to_noise(pred, y, n);
+    if (threadIdx.x == 0 && !sc->bad) sc->snr = snr;
 }
 
 __global__ void adam_kernel(float *__restrict__ state, const float *__restrict__ grad, uint64_t P, int step_in_call,
-                            float lr, float beta1, float beta2, float eps, const Scalars *sc)
+                            float lr, float beta1, float beta2, float eps, const RefitScalars *sc)
 {
     if (sc->bad) return;
     const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -253,14 +198,6 @@ __global__ void adam_kernel(float *__restrict__ state, const float *__restrict__
     const double t = (double)state[3 * P] + step_in_call + 1; // t itself is advanced once, after the last step
     const float c1 = (float)(1.0 - pow((double)beta1, t)), c2 = (float)(1.0 - pow((double)beta2, t));
     (void)adam_one(state, P, i, state[i], state[P + i], state[2 * P + i], grad[i], beta1, beta2, lr, eps, c1, c2);
-}
-
-__global__ void finish_kernel(float *state, uint64_t P, int n_steps, const Scalars *sc, float *snr_out, float *loss_out)
-{
-    if (threadIdx.x || blockIdx.x) return;
-    if (!sc->bad) state[3 * P] += (float)n_steps;
-    *snr_out = sc->snr;
-    *loss_out = sc->loss;
 }
 
 // Output layer, forward and backward, fused and row-local: one wavefront per minibatch row computes
@@ -303,7 +240,7 @@ __global__ __launch_bounds__(256) void output_layer_kernel(const float *__restri
 // (fixed order, double) when this is the step whose loss is reported.
 __global__ __launch_bounds__(1024) void output_grad_kernel(const float *__restrict__ h2, const float *__restrict__ dy,
                                                            int H2, int rows, float *__restrict__ grad_w3b3,
-                                                           const float *__restrict__ loss_terms, Scalars *sc, int is_last)
+                                                           const float *__restrict__ loss_terms, RefitScalars *sc, int is_last)
 {
     __shared__ float partial[16][64];
     const int cg = threadIdx.x & 63, rg = threadIdx.x >> 6;
@@ -352,7 +289,7 @@ UpdWs upd_layout(const eck_model *m, uint64_t n_pairs, int mb)
     auto align = [](uint64_t v) { return (v + 255) & ~255ull; };
     UpdWs w;
     uint64_t o = 0;
-    w.scalars = o; o = align(o + sizeof(Scalars));
+    w.scalars = o; o = align(o + sizeof(RefitScalars));
     w.y = o;       o = align(o + n_pairs * 4);
     w.pred = o;    o = align(o + n_pairs * 4);
     w.h1 = w.h2 = w.dy = w.lterm = w.d2 = w.d1 = w.grad = o;
@@ -411,7 +348,7 @@ extern "C" int32_t costmodel_update(eck_model *m, const void *feat, int32_t feat
 
     hipStream_t st = as_stream(stream);
     char *base = static_cast<char *>(ws);
-    Scalars *sc = reinterpret_cast<Scalars *>(base + w.scalars);
+    RefitScalars *sc = reinterpret_cast<RefitScalars *>(base + w.scalars);
     float *y = reinterpret_cast<float *>(base + w.y), *pred = reinterpret_cast<float *>(base + w.pred);
     float *h1 = reinterpret_cast<float *>(base + w.h1), *h2 = reinterpret_cast<float *>(base + w.h2);
     float *dy = reinterpret_cast<float *>(base + w.dy), *d2 = reinterpret_cast<float *>(base + w.d2);
@@ -422,29 +359,23 @@ extern "C" int32_t costmodel_update(eck_model *m, const void *feat, int32_t feat
     float *theta = m->d_state;
     const int elem = feat_dtype == ECK_BF16 ? 2 : 4;
 
-    hipLaunchKernelGGL(labels_kernel, dim3(1), dim3(1024), 0, st, energy_measured, n_pairs, y, sc);
-    // predictions of the model as it stands: the same forward pass that scores candidates
-    int32_t rc = costmodel_score(m, feat, feat_dtype, ld, n_pairs, pred, nullptr, 0, stream);
+    const bool two_launches = m->dtype == ECK_BF16 && refit_applies(m, feat, feat_dtype, ld, minibatch);
+    int32_t rc = ECK_OK;
+    if (two_launches) rc = refit_begin(m, energy_measured, n_pairs, y, sc, minibatch, base + w.refit, st);
+    else hipLaunchKernelGGL(labels_kernel, dim3(1), dim3(1024), 0, st, energy_measured, n_pairs, y, sc);
     if (rc != ECK_OK) return rc;
-    hipLaunchKernelGGL(snr_kernel, dim3(1), dim3(1024), 0, st, pred, y, n_pairs, sc);
-
-    if (refit_applies(m, feat, feat_dtype, ld, minibatch)) {
-        // BF16 model: two launches per step
-        rc = refit_steps(m, feat, feat_dtype, ld, y, n_pairs, n_steps, minibatch, lr, beta1, beta2, eps, &sc->bad, &sc->loss,
-                         base + w.refit, st);
+    // predictions of the model as it stands: the same forward pass that scores candidates
+    rc = costmodel_score(m, feat, feat_dtype, ld, n_pairs, pred, nullptr, 0, stream);
+    if (rc != ECK_OK) return rc;
+    if (two_launches || m->dtype == ECK_F32) {
+        rc = two_launches ? refit_steps(m, feat, feat_dtype, ld, y, n_pairs, n_steps, minibatch, lr, beta1, beta2, eps, &sc->bad,
+                                        &sc->loss, base + w.refit, st)
+                          : refit_f32_steps(m, static_cast<const float *>(feat), ld, y, n_pairs, n_steps, minibatch, lr, beta1, beta2,
+                                            eps, &sc->bad, &sc->loss, base + w.refit, st);
         if (rc != ECK_OK) return rc;
-        hipLaunchKernelGGL(finish_kernel, dim3(1), dim3(64), 0, st, theta, P, n_steps, sc, snr_out, loss_out);
-        ECK_HIP_TRY(hipGetLastError());
-        return model_repack(m, st);
+        return refit_finish(m, pred, y, n_pairs, n_steps, sc, snr_out, loss_out, st);
     }
-    if (m->dtype == ECK_F32) {
-        rc = refit_f32_steps(m, static_cast<const float *>(feat), ld, y, n_pairs, n_steps, minibatch, lr, beta1, beta2, eps,
-                             &sc->bad, &sc->loss, base + w.refit, st);
-        if (rc != ECK_OK) return rc;
-        hipLaunchKernelGGL(finish_kernel, dim3(1), dim3(64), 0, st, theta, P, n_steps, sc, snr_out, loss_out);
-        ECK_HIP_TRY(hipGetLastError());
-        return ECK_OK;
-    }
+    hipLaunchKernelGGL(snr_kernel, dim3(1), dim3(1024), 0, st, pred, y, n_pairs, sc); // (the steps reuse pred)
     const uint64_t nb = n_pairs / (uint64_t)B;
     for (int s = 0; s < n_steps; ++s) {
         const uint64_t row0 = ((uint64_t)s % nb) * (uint64_t)B;
@@ -474,9 +405,8 @@ extern "C" int32_t costmodel_update(eck_model *m, const void *feat, int32_t feat
         hipLaunchKernelGGL(adam_kernel, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, st, theta, grad, P, s, lr, beta1,
                            beta2, eps, sc);
     }
-    hipLaunchKernelGGL(finish_kernel, dim3(1), dim3(64), 0, st, theta, P, n_steps, sc, snr_out, loss_out);
     ECK_HIP_TRY(hipGetLastError());
-    return model_repack(m, st);
+    return refit_finish(m, nullptr, y, n_pairs, n_steps, sc, snr_out, loss_out, st);
 }
 
 extern "C" int32_t eck_k_count(double k, int64_t M, int64_t *count_out)

@@ -252,9 +252,9 @@ class Trees:
 
     def get(self):
         n = self.n_trees
-        node_feat = torch.zeros((n, (1 << self.depth) - 1), dtype=torch.uint8, device="cuda")
-        node_thr = torch.zeros((n, (1 << self.depth) - 1), dtype=torch.float32, device="cuda")
-        leaf = torch.zeros((n, 1 << self.depth), dtype=torch.float32, device="cuda")
+        node_feat = torch.empty((n, (1 << self.depth) - 1), dtype=torch.uint8, device="cuda")
+        node_thr = torch.empty((n, (1 << self.depth) - 1), dtype=torch.float32, device="cuda")
+        leaf = torch.empty((n, 1 << self.depth), dtype=torch.float32, device="cuda")
         _check("eck_trees_get", lib().eck_trees_get(self.h, _ptr(node_feat), _ptr(node_thr), _ptr(leaf), _stream()))
         return node_feat, node_thr, leaf
 
