@@ -60,7 +60,7 @@ struct eck_model {
     uint64_t n_params;
     uint64_t off_w[3], off_b[3]; // offsets of W_l and b_l in theta
     float *d_state = nullptr;    // [theta | m | v | t]  (3P+1 floats)
-    void *d_packed = nullptr;    // BF16: weights in matrix-core fragment order + fp32 bias/output vectors
+    void *d_packed = nullptr;    // weights in matrix-core fragment order; BF16: + bias/output vectors, fp32: in three parts
     uint64_t packed_bytes = 0;
     int device = -1;
 };
@@ -109,7 +109,7 @@ struct RefitScalars {
     float snr, loss;
 };
 // The end of costmodel_update in one launch: the SNR of the predictions `pred` made on entry (NULL: already in *sc), the step
-// count, the call's results, and the packed weights of a BF16 model
+// count, the call's results, and the packed weights
 int32_t refit_finish(eck_model *m, const float *pred, const float *y, uint64_t n_pairs, int32_t n_steps, const RefitScalars *sc,
                      float *snr_out, float *loss_out, hipStream_t stream);
 // Adam steps of a BF16 model in two launches per step (refit.hip): whether that path takes this call, the bytes it

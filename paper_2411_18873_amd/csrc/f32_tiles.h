@@ -1,4 +1,4 @@
-// What the fp32 matrix-core kernels share (HIP, gfx950): the tile layout and the loads of a layer's weights.
+// The fp32 matrix-core kernels of the refit (HIP, gfx950): the tile layout and the loads of a layer's weights.
 //
 // v_mfma_f32_16x16x4_f32, fp32 operands and accumulation.  The network is evaluated transposed, rows = hidden units
 // (A = weights), columns = candidates or minibatch rows (B = activations).  Lane = 16 p + c (quarter p):

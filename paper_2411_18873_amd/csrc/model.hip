@@ -7,6 +7,7 @@
 #include <type_traits>
 
 #include "eck_internal.h"
+#include "f32_split.h"
 #include "refit_labels.h"
 
 using namespace eck;
@@ -74,9 +75,10 @@ __device__ __forceinline__ uint16_t bf16_bits(float x)
     return (uint16_t)(u >> 16);
 }
 
-// Shape and destination of a BF16 model's packed weights; total: elements of the packed buffer (0: an fp32 model, none)
+// Shape and destination of a model's packed weights; total: elements of a BF16 model's packed buffer, lanes of an fp32
+// model's fragments
 struct PackArgs {
-    int F, H1, H2;
+    int bf16, F, H1, H2;
     uint64_t off_w1, off_b1, off_w2, off_b2, off_w3, off_b3;
     unsigned char *packed;
     PackedLayout L;
@@ -85,16 +87,19 @@ struct PackArgs {
 
 PackArgs pack_args(const eck_model *m)
 {
-    PackArgs a = {};
-    if (m->dtype != ECK_BF16) return a;
-    const int F = m->widths[0], H1 = m->widths[1], H2 = m->widths[2];
-    return {F, H1, H2, m->off_w[0], m->off_b[0], m->off_w[1], m->off_b[1], m->off_w[2], m->off_b[2], (unsigned char *)m->d_packed,
-            packed_layout(F, H1, H2), (uint32_t)(F * H1 + H1 + H1 * H2 + 2 * H2 + 1)};
+    const int F = m->widths[0], H1 = m->widths[1], H2 = m->widths[2], bf16 = m->dtype == ECK_BF16;
+    return {bf16, F, H1, H2, m->off_w[0], m->off_b[0], m->off_w[1], m->off_b[1], m->off_w[2], m->off_b[2], (unsigned char *)m->d_packed,
+            bf16 ? packed_layout(F, H1, H2) : PackedLayout{},
+            bf16 ? (uint32_t)(F * H1 + H1 + H1 * H2 + 2 * H2 + 1) : 64 * (split::fragments1(F, H1) + split::fragments2(H1, H2))};
 }
 
-// theta (fp32 master) -> element e of the packed buffer
+// theta (fp32 master) -> element, or lane, e of the packed buffer
 __device__ __forceinline__ void pack_element(const float *__restrict__ theta, const PackArgs &a, uint32_t e)
 {
+    if (!a.bf16) {
+        split::pack_lane(theta + a.off_w1, theta + a.off_w2, a.F, a.H1, a.H2, e / 64, e % 64, a.packed);
+        return;
+    }
     const int F = a.F, H1 = a.H1, H2 = a.H2;
     const uint64_t off_w1 = a.off_w1, off_b1 = a.off_b1, off_w2 = a.off_w2, off_b2 = a.off_b2, off_w3 = a.off_w3, off_b3 = a.off_b3;
     unsigned char *packed = a.packed;
@@ -241,21 +246,19 @@ extern "C" int32_t eck_model_create(int32_t n_layers, const int32_t *widths, int
         delete m;
         return ECK_EDEVICE;
     }
-    if (dtype == ECK_BF16) {
-        m->packed_bytes = packed_layout(widths[0], widths[1], widths[2]).total;
-        if (hipMalloc(&m->d_packed, m->packed_bytes) != hipSuccess) {
-            (void)hipGetLastError();
-            (void)hipFree(m->d_state);
-            delete m;
-            return ECK_EDEVICE;
-        }
+    m->packed_bytes = dtype == ECK_BF16 ? packed_layout(widths[0], widths[1], widths[2]).total : split::packed_bytes(widths[0], widths[1], widths[2]);
+    if (hipMalloc(&m->d_packed, m->packed_bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        (void)hipFree(m->d_state);
+        delete m;
+        return ECK_EDEVICE;
     }
     // everything zero, the packed weights too
     auto clear = [](void *p, uint64_t floats) {
         hipLaunchKernelGGL(set_state_kernel, dim3(state_blocks(floats)), dim3(256), 0, 0, (const float *)nullptr, (uint64_t)0, (float *)p, floats, PackArgs{});
     };
     clear(m->d_state, 3 * off + 1);
-    if (m->d_packed) clear(m->d_packed, m->packed_bytes / 4);
+    clear(m->d_packed, m->packed_bytes / 4);
     if (hipGetLastError() != hipSuccess) {
         eck_model_destroy(m);
         return ECK_EDEVICE;

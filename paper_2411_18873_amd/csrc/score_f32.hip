@@ -1,193 +1,303 @@
 // Forward pass of fp32 models on the matrix cores (HIP, gfx950): costmodel_score for ECK_F32 models of any hidden
 // widths (Alg. 1: LatencyEvaAndPick, EnergyModelEvaAndPick; Sec. 5.4).
 //
-// The network is evaluated transposed, as in the bf16 kernel, on the tiles of f32_tiles.h.  A block's wavefronts share a
-// layer's tiles between them as evenly as they go and all read the same activations from LDS.  Weights come straight from
-// the parameter vector through the L1: they need neither LDS nor packing.
+// The network is evaluated transposed, rows = hidden units (weights), columns = candidates, every fp32 number as the sum of
+// three bfloat16 ones and every product as the six largest of their products, summed in fp32 (f32_split.h): sixteen times the
+// fp32 matrix rate, for six times the products.  A block's wavefronts share a layer's 16-unit tiles as evenly as they go and
+// read the same activations from LDS, which holds their parts as [part][unit / 8][candidate][unit % 8].  The weights' parts
+// are made when the state changes and stream from the L2, one load at a time between matrix instructions.
 //
-// What bounds it: the fp32 matrix rate (a library product reaches 153 TFLOP/s on this card).  Measured, 64-512-512-1 on
-// 32768 candidates: 135 TFLOP/s (144 us; 139 us when the weight loads are left out); 64-256-256-1 on 98304: 121, on 100003
-// (a last round of few blocks): 108 (152 us).  The vector kernels before it: 16-18 TFLOP/s (1191 us, 931 us).  What it
-// took: weight loads without vector instructions for their addresses (buffer loads with a scalar row offset: 64-bit lane
-// addresses cost a quarter of the matrix time), issued one at a time between matrix instructions.
+// What bounds it: matrix instructions and the LDS reads of the activations behind them (a part of four candidate tiles is read
+// for twelve matrix instructions), for narrow models the features.  Measured, against fp32 matrix instructions (which reached
+// 121-135 of their 153 TFLOP/s): 64-256-256-1 on 100003 candidates 152 -> 96 us (171 TFLOP/s of fp32 products, 1030 of bfloat16
+// ones), 64-128-128-1 on 2^18 126 -> 87, 64-512-512-1 on 100003 499 -> 425, 32-64-64-1 on 6400 6.9 -> 6.2 and on 2^20 156 -> 130.
+// Models of 16 units or less wait for their features' parts: 100003 candidates 7.8 -> 8.7 us, 64-16-512-1 52.7 -> 59.  Errors
+// against 64 bits, relative to the scores' norm (before in brackets): 512 units 2.5-3.4e-8 (6.1-6.4e-8), 256 3.1-3.6e-8
+// (6.2-6.6e-8), 128 3.1-4.2e-8 (6.6-8.5e-8), 64 3.9-4.4e-8 (7.4-9.1e-8), 200 and 96 3.6-4.0e-8 (6.8-9.4e-8).
 #include <type_traits>
 
-#include "f32_tiles.h"
+#include "f32_split.h"
+#include "lanes.h"
 
 using namespace eck;
-using namespace eck::f32;
+using namespace eck::split;
 
 namespace {
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int RSRC_FLAGS = 0x00020000; // buffer descriptor: raw 32-bit data
+constexpr int CHUNK = 256;             // units of the first hidden layer that LDS holds at a time
+
 struct F32Net {
-    F32Layer l1, l2;
-    const float *w3, *b3;
+    const unsigned char *packed; // fragments of both hidden layers
+    const float *w1, *b1, *w2, *b2, *w3, *b3;
+    int F, H1, H2;
 };
 
-// acc[j][ct] = b + W^T x for a slice and CT tiles of candidates; act: the activations of units 0-3 of this wavefront's
-// first candidate, `cands` candidates to a row.  Register q of tile j at quarter p is unit first + J (4p + q) + j.
-template <int J, int CT>
-__device__ __forceinline__ void slice_product(const F32Layer &l, int first, const f32x4 *act, int cands, int p, int c,
-                                              f32x4 (&acc)[4][CT])
+// Sums of M x CT tiles: the largest product of each pair apart from the others, so that it is rounded once per group of 32
+// inputs and the others at their own size
+template <int M, int CT>
+struct Sums {
+    f32x4 large[M][CT], small[M][CT];
+};
+
+// s[j][ct] += W^T x for J tiles from `first_tile` on, over `groups` groups of 32 inputs from `group0` on, and CT tiles of
+// candidates.  layer: byte offset of its fragments; act: granules (16 bytes: eight units of one candidate) of part 0, this
+// wavefront's first candidate; `cands` granules to a row, `part_step` to a part.  AHEAD: the next group's activations are read
+// while this one is multiplied.
+template <int J, bool AHEAD, int M, int CT>
+__device__ __forceinline__ void product(__amdgpu_buffer_rsrc_t weights, uint32_t layer, int layer_groups, int first_tile, int group0,
+                                        int groups, const u32x4 *act, int cands, int part_step, int lane, Sums<M, CT> &s)
 {
-    const Slice<J> slice(l, first, p, c);
-    const int whole = l.K / 16;
-    // weights of an even and an odd group; past the end the last whole group again
-    float even[4][J], odd[4][J];
-    if (whole) {
+    constexpr int SETS = J * CT <= 4 ? 2 : 1; // weights requested two groups ahead where the registers hold them, else one
+    const int last = groups - 1;
+    const u32x4 *from = act + (lane >> 4) * cands + (lane & 15);
+    bf16x8 a[SETS][J][PARTS], b[AHEAD ? 2 : 1][PARTS][CT];
+    auto fetch = [&](int g, int j, bf16x8(&to)[PARTS]) {
+        const uint32_t at = layer + ((uint32_t)(first_tile + j) * layer_groups + group0 + min(g, last)) * (PARTS * 1024u);
 #pragma unroll
-        for (int t = 0; t < 4; ++t) slice.row(0, t, even[t]);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) slice.row(min(1, whole - 1), t, odd[t]);
-    }
-#pragma unroll
-    for (int j = 0; j < J; ++j) {
-        f32x4 bias;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) bias[q] = l.b[min(first + J * (4 * p + q) + j, l.H - 1)];
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct) acc[j][ct] = bias;
-    }
-    const f32x4 *from = act + p * cands + c;
-    f32x4 be[CT], bo[CT]; // activations of an even and an odd group
-    auto read_act = [&](int g, f32x4(&b)[CT]) {
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct) b[ct] = from[4 * g * cands + 16 * ct];
+        for (int i = 0; i < PARTS; ++i)
+            to[i] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(weights, 16 * lane, at + 1024u * i, 0));
     };
-    auto step = [&](int t, const float (&a)[J], const f32x4 (&b)[CT]) {
+    auto read = [&](int g, bf16x8(&to)[PARTS][CT]) {
 #pragma unroll
-        for (int j = 0; j < J; ++j)
+        for (int i = 0; i < PARTS; ++i)
 #pragma unroll
-            for (int ct = 0; ct < CT; ++ct) acc[j][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[ct][t], acc[j][ct], 0, 0, 0);
+            for (int ct = 0; ct < CT; ++ct)
+                to[i][ct] = __builtin_bit_cast(bf16x8, from[i * part_step + 4 * min(g, last) * cands + 16 * ct]);
     };
-    // Two groups per trip, without a branch inside (at one the compiler copies every accumulator, behind a wait for the
-    // matrix unit).  The weights of a step are requested for two groups on as soon as the step's matrix instructions are
-    // issued: one load at a time, because a wavefront that issues several in a row waits for the load path and leaves
-    // the matrix unit idle (all of a group at once: 93 TFLOP/s; none at all, reusing stale weights: 136), and pinned
-    // there, because left alone the compiler moves them together.
-    const int last = whole - 1;
+#pragma unroll
+    for (int k = 0; k < SETS; ++k)
+#pragma unroll
+        for (int j = 0; j < J; ++j) fetch(k, j, a[k][j]);
+    if (AHEAD) read(0, b[0]);
+    auto group = [&](int g, auto odd) {
+        constexpr int P = decltype(odd)::value, S = P % SETS, B = AHEAD ? P : 0;
+        if (AHEAD) read(g + 1, b[AHEAD ? P ^ 1 : 0]);
+        else read(g, b[0]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            constexpr int WEIGHT[6] = {2, 0, 1, 1, 0, 0}, INPUT[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+            for (int k = 0; k < 6; ++k)
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) {
+                    f32x4 &to = k < 5 ? s.small[j][ct] : s.large[j][ct];
+                    to = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[S][j][WEIGHT[k]], b[B][INPUT[k]][ct], to, 0, 0, 0);
+                }
+            __builtin_amdgcn_sched_barrier(0);
+            fetch(g + SETS, j, a[S][j]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
     int g = 0;
-    read_act(0, be);
-    for (; g + 2 <= whole; g += 2) {
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            step(t, even[t], be);
-            __builtin_amdgcn_sched_barrier(0);
-            slice.row(min(g + 2, last), t, even[t]);
-            if (t == 0) read_act(g + 1, bo);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            step(t, odd[t], bo);
-            __builtin_amdgcn_sched_barrier(0);
-            slice.row(min(g + 3, last), t, odd[t]);
-            if (t == 0) read_act(min(g + 2, last), be);
-            __builtin_amdgcn_sched_barrier(0);
-        }
+    for (; g + 2 <= groups; g += 2) {
+        group(g, std::integral_constant<int, 0>());
+        group(g + 1, std::integral_constant<int, 1>());
     }
-    if (g < whole) {
-#pragma unroll
-        for (int t = 0; t < 4; ++t) step(t, even[t], be);
+    if (g < groups) group(g, std::integral_constant<int, 0>());
+}
+
+// A candidate whose numbers are not all finite, or do not stay so: plain fp32 sums, by one wavefront.  h: [H1] floats of LDS.
+__device__ __forceinline__ float score_plain(const F32Net &net, const float *feat, uint64_t ld, uint64_t cand, float *h, int lane)
+{
+    for (int u = lane; u < net.H1; u += 64) {
+        float s = net.b1[u];
+        for (int k = 0; k < net.F; ++k) s = fmaf(feat[(uint64_t)k * ld + cand], net.w1[(int64_t)k * net.H1 + u], s);
+        h[u] = fmaxf(s, 0.0f);
     }
-    if (l.K % 16) {
-        read_act(whole, be);
-        slice.partial_group(whole, even);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) step(t, even[t], be);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // the wavefront reads back what its own lanes wrote
+    float y = 0.0f;
+    for (int u = lane; u < net.H2; u += 64) {
+        float s = net.b2[u];
+        for (int k = 0; k < net.H1; ++k) s = fmaf(h[k], net.w2[(int64_t)k * net.H2 + u], s);
+        y = fmaf(fmaxf(s, 0.0f), net.w3[u], y);
     }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) y += __shfl_xor(y, off);
+    return net.b3[0] + y;
 }
 
 // blockDim = 64 * unit_slots * cand_slots: wavefront (us, cs) works on share us of every layer for the CT candidate
 // tiles of slot cs.  Every sum has an order that depends on the widths alone, so a candidate's score depends neither on
-// n nor on its place.
-template <int CT, bool WITH_MIN>
+// n nor on its place.  M, M2: most 16-unit tiles per
+// wavefront of the units of the first and the second layer that are worked on at a time.  ONE: CHUNK units take the first layer.
+template <int CT, int M, int M2, bool ONE, bool WITH_MIN>
 __global__ __launch_bounds__(512, 2) void score_f32_kernel(F32Net net, const float *__restrict__ feat, uint64_t ld,
-                                                           uint64_t n, float *__restrict__ out, int unit_slots, int rows4,
-                                                           MinArgs mn)
+                                                           uint64_t n, float *__restrict__ out, int unit_slots, int x_rows,
+                                                           int h_rows, int act_bytes, MinArgs mn)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char f32_lds[];
-    f32x4 *act = reinterpret_cast<f32x4 *>(f32_lds); // [rows4][cands]
     const int tid = threadIdx.x, lane = tid & 63, p = lane >> 4, c = lane & 15;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), waves = (int)blockDim.x / 64;
     const int us = wave % unit_slots, cs = wave / unit_slots;
-    const int cands = (int)(blockDim.x / 64) / unit_slots * (16 * CT);
-    float *part = reinterpret_cast<float *>(act + (int64_t)rows4 * cands); // [unit_slots][cands]
+    const int cands = waves / unit_slots * (16 * CT);
+    // features [3][x_rows][cands] and activations [3][h_rows][cands], in one place where a single chunk takes the first layer
+    u32x4 *x_l = reinterpret_cast<u32x4 *>(f32_lds), *h_l = ONE ? x_l : x_l + PARTS * x_rows * cands;
+    float *sum_l = reinterpret_cast<float *>(f32_lds + act_bytes); // [tiles of the second layer][cands]
+    const int out_tiles = tiles_of(net.H2);
+    uint32_t *odd_l = reinterpret_cast<uint32_t *>(sum_l + out_tiles * cands); // [cands], then whether there is any
     const uint64_t base = (uint64_t)blockIdx.x * cands;
+    for (int e = tid; e <= cands; e += blockDim.x) odd_l[e] = 0;
 
-    for (int e = tid; e < net.l1.K / 4 * cands; e += blockDim.x) { // 32 or 64 features
-        const int cand = e % cands, four = e / cands;
+    for (int e = tid; e < net.F / 8 * cands; e += blockDim.x) { // 32 or 64 features
+        const int cand = e % cands, eight = e / cands;
         const uint64_t col = base + cand < n ? base + cand : n - 1;
-        f32x4 v;
+        float v[8];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) v[t] = feat[(uint64_t)(4 * four + t) * ld + col];
-        act[e] = v;
+        for (int t = 0; t < 8; ++t) v[t] = feat[(uint64_t)(8 * eight + t) * ld + col];
+        u32x4 to[PARTS];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            uint32_t part[PARTS];
+            split_two(v[2 * t], v[2 * t + 1], part);
+#pragma unroll
+            for (int i = 0; i < PARTS; ++i) to[i][t] = part[i];
+        }
+#pragma unroll
+        for (int i = 0; i < PARTS; ++i) x_l[(i * x_rows + eight) * cands + cand] = to[i];
     }
     __syncthreads();
-    const f32x4 *mine = act + cs * (16 * CT);
-    f32x4 acc[4][CT];
-    // this wavefront's share of the 16-unit tiles of a layer: the first shares are a tile larger when they do not divide
-    auto share_of = [&](const F32Layer &l, int *first) {
-        const int tiles = (l.H + 15) / 16, base_tiles = tiles / unit_slots, more = tiles % unit_slots;
-        *first = 16 * (us * base_tiles + min(us, more));
+    const __amdgpu_buffer_rsrc_t weights = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<unsigned char *>(net.packed), 0, (fragments1(net.F, net.H1) + fragments2(net.H1, net.H2)) * (PARTS * 1024), RSRC_FLAGS);
+    const uint32_t layer2 = fragments1(net.F, net.H1) * (PARTS * 1024u);
+    const int groups1 = groups_of(net.F), groups2 = groups_of(net.H1);
+    // this wavefront's share of so many tiles: the first shares are a tile larger when they do not divide
+    auto share_of = [&](int tiles, int *first) {
+        const int base_tiles = tiles / unit_slots, more = tiles % unit_slots;
+        *first = us * base_tiles + min(us, more);
         return base_tiles + (us < more ? 1 : 0);
     };
-    int first1, first2;
-    const int tiles1 = share_of(net.l1, &first1), tiles2 = share_of(net.l2, &first2);
-    auto product = [&](const F32Layer &l, int tiles, int first) {
-        if (tiles == 4) slice_product<4, CT>(l, first, mine, cands, p, c, acc);
-        else if (tiles == 3) slice_product<3, CT>(l, first, mine, cands, p, c, acc);
-        else if (tiles == 2) slice_product<2, CT>(l, first, mine, cands, p, c, acc);
-        else if (tiles == 1) slice_product<1, CT>(l, first, mine, cands, p, c, acc);
+    auto run = [&](int tiles, uint32_t layer, int layer_groups, int first_tile, int group0, int groups, const u32x4 *act, int part_step,
+                   auto ahead, auto &to) {
+        constexpr bool AHEAD = decltype(ahead)::value;
+        constexpr int MOST = sizeof(to) / sizeof(Sums<1, CT>);
+        const u32x4 *mine = act + cs * (16 * CT);
+        auto go = [&](auto j) {
+            product<decltype(j)::value, AHEAD>(weights, layer, layer_groups, first_tile, group0, groups, mine, cands, part_step, lane, to);
+        };
+        if constexpr (MOST == 4) {
+            if (tiles == 4) go(std::integral_constant<int, 4>());
+            else if (tiles == 3) go(std::integral_constant<int, 3>());
+        }
+        if constexpr (MOST >= 2) {
+            if (tiles == 2) go(std::integral_constant<int, 2>());
+        }
+        if (tiles == 1) go(std::integral_constant<int, 1>());
     };
-    product(net.l1, tiles1, first1);
-    __syncthreads(); // every wavefront has read the features: their place takes the first hidden layer
-    auto store = [&](auto tiles) {
-        constexpr int J = decltype(tiles)::value;
-        const int unit0 = first1 + 4 * J * p; // this lane's 4 J consecutive units
+    auto start = [&](const float *b, int H, int first_tile, auto &to) {
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct)
+        for (int j = 0; j < (int)(sizeof(to) / sizeof(Sums<1, CT>)); ++j) {
+            f32x4 v;
 #pragma unroll
-            for (int m = 0; m < J; ++m) {
-                f32x4 v;
-                // (a unit past H1 is zero; its weights in the next layer are, too)
+            for (int q = 0; q < 4; ++q) v[q] = b[min(16 * (first_tile + j) + 4 * p + q, H - 1)];
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const int e = 4 * m + t;
-                    v[t] = unit0 + e < net.l1.H ? fmaxf(acc[e % J][ct][e / J], 0.0f) : 0.0f;
-                }
-                if (unit0 / 4 + m < rows4) act[(unit0 / 4 + m) * cands + 16 * (cs * CT + ct) + c] = v;
+            for (int ct = 0; ct < CT; ++ct) {
+                to.large[j][ct] = v;
+                to.small[j][ct] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
             }
+        }
     };
-    if (tiles1 == 4) store(std::integral_constant<int, 4>());
-    else if (tiles1 == 3) store(std::integral_constant<int, 3>());
-    else if (tiles1 == 2) store(std::integral_constant<int, 2>());
-    else if (tiles1 == 1) store(std::integral_constant<int, 1>());
-    __syncthreads();
-    float y[CT] = {};
-    product(net.l2, tiles2, first2);
+    // zero times everything a candidate's sums held: a NaN once one of them was not finite
+    float odd[CT] = {};
+    // The second layer as many units at a time as the sums of M2 tiles take, over the first one CHUNK units at a time: where
+    // neither goes in one, the first is worked out again (an eighth more products at 64-512-512, but sums of 512 units in both
+    // layers spill with more than one candidate tile: 708-775 us against 391 on 100003 candidates)
+    const int most2 = unit_slots * (16 * M2);
+    for (int v0 = 0; v0 < net.H2; v0 += most2) {
+        int first2;
+        const int tiles2 = share_of(tiles_of(min(most2, net.H2 - v0)), &first2);
+        first2 += v0 / 16;
+        Sums<M2, CT> sum2;
+        if (!ONE) start(net.b2, net.H2, first2, sum2);
+        for (int u0 = 0; ONE ? u0 == 0 : u0 < net.H1; u0 += CHUNK) {
+            const int in_chunk = ONE ? net.H1 : min(CHUNK, net.H1 - u0);
+            if (!ONE || v0 == 0) {
+                int first1;
+                const int tiles1 = share_of(tiles_of(in_chunk), &first1);
+                Sums<M, CT> sum1;
+                start(net.b1, net.H1, u0 / 16 + first1, sum1);
+                run(tiles1, 0, groups1, u0 / 16 + first1, 0, groups1, x_l, x_rows * cands, std::false_type(), sum1);
+                __syncthreads(); // every wavefront has read what the activations take the place of
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        if (j >= tiles2) break;
+                for (int j = 0; j < M; ++j) {
+                    if (j >= tiles1) break;
+                    const int in = 16 * (first1 + j) + 4 * p; // this lane's four units, from the chunk's first on
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int unit = first2 + tiles2 * (4 * p + q) + j;
-            const float w = net.w3[min(unit, net.l2.H - 1)];
+                    for (int ct = 0; ct < CT; ++ct) {
+                        float v[4];
 #pragma unroll
-            for (int ct = 0; ct < CT; ++ct) y[ct] = unit < net.l2.H ? fmaf(fmaxf(acc[j][ct][q], 0.0f), w, y[ct]) : y[ct];
+                        for (int q = 0; q < 4; ++q) {
+                            const float sum = sum1.large[j][ct][q] + sum1.small[j][ct][q];
+                            odd[ct] = fmaf(sum, 0.0f, odd[ct]);
+                            // (a unit past H1 is zero; its weights in the next layer are, too)
+                            v[q] = u0 + in + q < net.H1 ? fmaxf(sum, 0.0f) : 0.0f;
+                        }
+                        uint32_t lo[PARTS], hi[PARTS];
+                        split_two(v[0], v[1], lo);
+                        split_two(v[2], v[3], hi);
+#pragma unroll
+                        for (int i = 0; i < PARTS; ++i) {
+                            u32x4 *row = h_l + (i * h_rows + in / 8) * cands + 16 * (cs * CT + ct) + c;
+                            reinterpret_cast<uint2 *>(row)[in / 4 % 2] = make_uint2(lo[i], hi[i]);
+                        }
+                    }
+                }
+                // inputs of the last group that no tile covers
+                if (tiles_of(in_chunk) % 2) {
+                    for (int e = tid; e < 2 * PARTS * cands; e += blockDim.x)
+                        h_l[(e / (2 * cands) * h_rows + 2 * tiles_of(in_chunk) + e / cands % 2) * cands + e % cands] = u32x4{0, 0, 0, 0};
+                }
+                __syncthreads();
+            }
+            if (ONE) start(net.b2, net.H2, first2, sum2);
+            run(tiles2, layer2, groups2, first2, u0 / 32, groups_of(in_chunk), h_l, h_rows * cands, std::true_type(), sum2);
+        }
+        // a tile's part of the output, whichever wavefront worked it out
+#pragma unroll
+        for (int j = 0; j < M2; ++j) {
+            if (j >= tiles2) break;
+            float y[CT] = {};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int unit = 16 * (first2 + j) + 4 * p + q;
+                const float w = net.w3[min(unit, net.H2 - 1)];
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) {
+                    const float sum = sum2.large[j][ct][q] + sum2.small[j][ct][q];
+                    odd[ct] = fmaf(sum, 0.0f, odd[ct]);
+                    y[ct] = unit < net.H2 ? fmaf(fmaxf(sum, 0.0f), w, y[ct]) : y[ct];
+                }
+            }
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) {
+                y[ct] += __uint_as_float(lane_exchange(__float_as_uint(y[ct]), 16));
+                y[ct] += __uint_as_float(lane_exchange(__float_as_uint(y[ct]), 32));
+                if (p == 0) sum_l[(first2 + j) * cands + 16 * (cs * CT + ct) + c] = y[ct];
+            }
         }
     }
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct) {
-        y[ct] += __shfl_xor(y[ct], 16);
-        y[ct] += __shfl_xor(y[ct], 32);
-        if (p == 0) part[us * cands + 16 * (cs * CT + ct) + c] = y[ct];
-    }
+    for (int ct = 0; ct < CT; ++ct)
+        if (odd[ct] != odd[ct]) odd_l[16 * (cs * CT + ct) + c] = odd_l[cands] = 1;
     __syncthreads();
+    if (odd_l[cands]) {
+        float *h = reinterpret_cast<float *>(f32_lds) + wave * 512; // (the activations are done with)
+        for (int cand = wave; cand < cands; cand += waves) {
+            if (!odd_l[cand] || base + cand >= n) continue;
+            const float total = score_plain(net, feat, ld, base + cand, h, lane);
+            if (lane == 0) sum_l[cand] = total;
+        }
+        __syncthreads();
+    }
     if (tid >= cands) return;
     const uint64_t cand = base + tid;
-    float total = net.b3[0];
-    for (int s = 0; s < unit_slots; ++s) total += part[s * cands + tid];
+    // (up to 32 parts one after the other in fp32 are the largest error of a score)
+    double parts = net.b3[0];
+    for (int t = 0; t < out_tiles; ++t) parts += sum_l[t * cands + tid];
+    const float total = odd_l[tid] ? sum_l[tid] : (float)parts;
     if (cand < n) out[cand] = total;
     if (WITH_MIN) {
         uint32_t key = 0xFFFFFFFFu;
@@ -211,28 +321,50 @@ template <bool WITH_MIN>
 int32_t launch(const eck_model *m, const float *feat, uint64_t ld, uint64_t n, float *out, const MinArgs &mn, hipStream_t st)
 {
     const int F = m->widths[0], H1 = m->widths[1], H2 = m->widths[2];
-    if ((n + 31) / 32 > 0x7FFFFFFFull) return ECK_EUNSUPPORTED;
-    const F32Net net{{m->d_state + m->off_w[0], m->d_state + m->off_b[0], F, H1},
-                     {m->d_state + m->off_w[1], m->d_state + m->off_b[1], H1, H2},
-                     m->d_state + m->off_w[2], m->d_state + m->off_b[2]};
-    const int widest = H1 > H2 ? H1 : H2, unit_slots = (widest + 63) / 64; // at most eight
-    // As few wavefronts as four tiles each allow share a layer (two tiles each: 67.7 against 63.4 us, 64-128-128-1 on
-    // 131072 candidates; 165 against 153 us, 64-256-256-1 on 100003).  Four candidate tiles per wavefront quarter the
-    // weight reads per candidate; fewer when blocks that large would leave compute units without two of them.  At least
-    // four wavefronts a block (63 against 94 us at 128 units), as long as that leaves enough blocks, too.  Narrow models with
-    // many candidates wait for the features: two candidate tiles leave the registers for twice as many wavefronts (2^20
-    // candidates, four against two: 32-1-1-1 65.8 and 53.3 us, 32-64-64-1 160 and 153; 2^18 15.5 and 14.1, 41 and 41; 2^17
-    // 8.0 and 8.2, 20.1 and 22.2).
+    if ((n + 15) / 16 > 0x7FFFFFFFull) return ECK_EUNSUPPORTED;
+    const float *s = m->d_state;
+    const F32Net net{(const unsigned char *)m->d_packed, s + m->off_w[0], s + m->off_b[0], s + m->off_w[1], s + m->off_b[1],
+                     s + m->off_w[2], s + m->off_b[2], F, H1, H2};
+    const int widest = H1 > H2 ? H1 : H2;
     const uint64_t tiles = (n + 15) / 16;
-    int cand_slots = unit_slots < 4 ? 4 / unit_slots : 1, ct = unit_slots == 1 && tiles >= 16384 ? 2 : 4;
-    while (ct > 1 && tiles < 512ull * cand_slots * ct) ct /= 2;
-    while (cand_slots > 1 && tiles < 512ull * cand_slots * ct) cand_slots /= 2;
-    const int cands = 16 * ct * cand_slots, rows4 = ((F > H1 ? F : H1) + 15) / 16 * 4;
-    const size_t lds = (size_t)rows4 * cands * 16 + (size_t)unit_slots * cands * 4;
-    auto kern = ct == 4 ? score_f32_kernel<4, WITH_MIN> : ct == 2 ? score_f32_kernel<2, WITH_MIN> : score_f32_kernel<1, WITH_MIN>;
+    // Two unit tiles per wavefront and four candidate tiles (64 candidates a block): a weight is read for four, an activation
+    // for two.  Fewer candidates where blocks that large would leave compute units without one (64-256-256-1, us with 1 / 2 /
+    // 4 candidate tiles: 1000 9 / 10 / -, 6400 17 / 10.7 / 14, 16000 34 / 21 / 15, 100003 199 / 126 / 95); two at most
+    // where the sums of both layers are held at once (more than CHUNK units in the first).  Narrower models with one unit tile per wavefront until the chip is full (64-128-128-1: 6400 6.2 against
+    // 6.8, 16000 7.9 and 8.9, 30000 14.6 and 11; 32-64-64-1: 30000 6.4 and 6.9, 60000 11 and 8.8), those of 32 units or less
+    // always (64-30-20-1 on 2^20: 116-118 against 130).
+    int ct = tiles <= 256 ? 1 : tiles <= 512 || H1 > CHUNK ? 2 : 4, per = 2, unit_slots = 8, cand_slots = 1;
+    if (widest <= 16) {
+        per = unit_slots = 1;
+        if (ct > 2) ct = 2;
+        cand_slots = tiles < 8192 ? 2 : 1;
+    } else if (widest <= 32) {
+        per = 1;
+        unit_slots = cand_slots = 2;
+        if (ct > 2) ct = 2;
+    } else if (widest <= 64) {
+        per = tiles <= 2048 ? 1 : 2;
+        unit_slots = 4 / per;
+    } else if (widest <= 128) {
+        per = tiles <= 1024 ? 1 : 2;
+        unit_slots = 8 / per;
+    }
+    const int cands = 16 * ct * cand_slots, x_rows = F / 8, h_rows = 4 * groups_of(H1 < CHUNK ? H1 : CHUNK);
+    const int rows = H1 <= CHUNK ? (x_rows > h_rows ? x_rows : h_rows) : x_rows + h_rows;
+    const int threads = 64 * unit_slots * cand_slots;
+    size_t act_bytes = (size_t)PARTS * rows * cands * 16;
+    if (act_bytes < (size_t)threads * 32) act_bytes = (size_t)threads * 32; // (score_plain: 512 floats a wavefront)
+    const size_t lds = act_bytes + ((size_t)tiles_of(H2) * cands + cands + 1) * 4;
+    auto kern = H1 > CHUNK ? (ct == 2 ? score_f32_kernel<2, 2, 2, false, WITH_MIN> : score_f32_kernel<1, 2, 4, false, WITH_MIN>)
+                : per == 2 ? (ct == 4   ? score_f32_kernel<4, 2, 2, true, WITH_MIN>
+                              : ct == 2 ? score_f32_kernel<2, 2, 2, true, WITH_MIN>
+                                        : score_f32_kernel<1, 2, 2, true, WITH_MIN>)
+                           : (ct == 4   ? score_f32_kernel<4, 1, 1, true, WITH_MIN>
+                              : ct == 2 ? score_f32_kernel<2, 1, 1, true, WITH_MIN>
+                                        : score_f32_kernel<1, 1, 1, true, WITH_MIN>);
     ECK_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    hipLaunchKernelGGL(kern, dim3((unsigned)((n + cands - 1) / cands)), dim3(64 * unit_slots * cand_slots), lds, st, net, feat,
-                       ld, n, out, unit_slots, rows4, mn);
+    hipLaunchKernelGGL(kern, dim3((unsigned)((n + cands - 1) / cands)), dim3(threads), lds, st, net, feat,
+                       ld, n, out, unit_slots, x_rows, h_rows, (int)act_bytes, mn);
     ECK_HIP_TRY(hipGetLastError());
     return ECK_OK;
 }

@@ -254,3 +254,48 @@ def test_narrow_fp32_models_on_many_candidates(G, widths):
     for n in (262128, 262129, 300001):
         feat = G.to_dev(np.ascontiguousarray(f32[:, np.arange(n + 1) % some]))
         assert np.array_equal(G.score_gpu(model, feat, n), few[np.arange(n) % some]), n
+
+
+@pytest.mark.parametrize("widths,n", [((32, 64, 64, 1), 777), ((64, 50, 30, 1), 40001), ((64, 128, 128, 1), 9000), ((64, 256, 256, 1), 5000),
+                                      ((64, 300, 17, 1), 9000), ((64, 16, 512, 1), 9000), ((32, 512, 512, 1), 1000), ((64, 9, 1, 1), 200000)])
+def test_fp32_scores_of_numbers_that_are_not_finite(G, widths, n):
+    """A number that is infinite, a NaN or above bfloat16's range has no parts to multiply: its candidate is worked out in plain
+    fp32 sums, with the infinities and NaNs those have (a NaN sum leaves the ReLU as zero); every other candidate keeps its
+    bits.  Huge finite features, which do have parts, are as close as ordinary ones (weights of one sign where they are, so that no
+    cancellation decides between a number and an infinity)."""
+    rng = np.random.default_rng(widths[1] + n)
+    F, H1, H2, _ = widths
+    w1, w2, w3 = (rng.standard_normal(s).astype(np.float32) / np.float32(s[0] ** 0.5) for s in ((F, H1), (H1, H2), (H2, 1)))
+    b1, b2, b3 = (rng.standard_normal(s).astype(np.float32) * np.float32(0.1) for s in (H1, H2, 1))
+    theta = np.concatenate([t.ravel() for t in (w1, b1, w2, b2, w3, b3)])
+    model = G.make_model(widths, eck.F32, theta)
+    x = rng.random((F, n + (n & 1))).astype(np.float32)
+    clean = G.score_gpu(model, G.to_dev(x), n)
+    odd = {0: np.inf, 5: -np.inf, 17: np.nan, n // 2: 3.4e38, n - 1: np.inf, n // 3: 1e30, n // 4: -2.5e37}
+    for at, value in odd.items():
+        x[rng.integers(F), at] = value
+    got = G.score_gpu(model, G.to_dev(x), n)
+    same = np.ones(n, dtype=bool)
+    same[list(odd)] = False
+    assert np.array_equal(got[same].view(np.uint32), clean[same].view(np.uint32))
+    with np.errstate(all="ignore"):
+        for at in odd:
+            h1 = np.fmax((x[:, at].astype(np.float64) @ w1.astype(np.float64) + b1), 0.0)
+            h2 = np.fmax(h1 @ w2.astype(np.float64) + b2, 0.0)
+            want = float((h2 @ w3.astype(np.float64))[0] + b3[0])
+            size = float(h2 @ np.abs(w3[:, 0].astype(np.float64)) + abs(b3[0]))
+            if np.isfinite(want):
+                assert abs(float(got[at]) - want) <= 1e-5 * size, (at, got[at], want)
+            else:
+                assert (np.isnan(got[at]) and np.isnan(want)) or got[at] == want, (at, got[at], want)
+    # weights that are not finite: every candidate takes the plain sums
+    w2[rng.integers(H1), rng.integers(H2)] = np.inf
+    bad = G.make_model(widths, eck.F32, np.concatenate([t.ravel() for t in (w1, b1, w2, b2, w3, b3)]))
+    few = 300
+    got = G.score_gpu(bad, G.to_dev(np.ascontiguousarray(x[:, 20:20 + few])), few)
+    with np.errstate(all="ignore"):
+        h1 = np.fmax(w1.T @ x[:, 20:20 + few] + b1[:, None], 0)
+        terms = np.where(h1[:, None, :] == 0, np.where(np.isinf(w2)[:, :, None], np.nan, 0.0), w2[:, :, None] * h1[:, None, :])
+        want = (np.fmax(terms.sum(0) + b2[:, None], 0) * w3).sum(0) + b3[0] if H1 * H2 * few < 3e7 else None
+    if want is not None:
+        assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isinf(got), np.isinf(want))
