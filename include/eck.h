@@ -191,8 +191,9 @@ int32_t eck_candidates_gather(const uint16_t *genes, uint64_t ld, uint64_t n, in
  *                   flags of features_compute, so that duplicates drop out of
  *                   topk_select)
  * genes: device uint16 [n_genes][ld]; flags: device uint8 [n]; ws: device, at
- * least eck_candidates_dedup_workspace_bytes(n) bytes (a hash table of candidate
- * indices, 4-byte aligned).  The result does not depend on execution order.
+ * least a hash table of candidate indices (4 bytes for each of the next power of
+ * two at or above 2n slots), 4-byte aligned; the query says what is fastest, which
+ * is more for 16384 to 2^20 candidates, and wants 16-byte alignment.  The result does not depend on execution order.
  * Errors: EINVAL, ESHAPE (ld < n), EUNSUPPORTED (n > 2^30), EWORKSPACE, EALIGN. */
 uint64_t eck_candidates_dedup_workspace_bytes(uint64_t n);
 int32_t eck_candidates_dedup(const uint16_t *genes, uint64_t ld, uint64_t n, int32_t n_genes, uint8_t *flags,

@@ -9,6 +9,7 @@
 #include <new>
 
 #include "eck_internal.h"
+#include "lanes.h"
 
 using namespace eck;
 
@@ -507,6 +508,186 @@ __global__ void dedup_insert_kernel(const uint16_t *__restrict__ genes, uint64_t
     }
 }
 
+// ---- the same for up to 2^20 candidates of up to eight genes without device-wide atomics: candidates that could be equal are
+// brought together by their hash, and each part's table is a block's own, in LDS.  us of the two launches, this way against the
+// one above, candidates drawn from themselves and from 100 kinds: 8192 10.2 / 13.5 and 10.2 / 8.8; 16384 10.3 / 15.4 and 10.5 /
+// 10.7; 260 001 16.7 / 29.4 and 30.7 / 60.7; 2^20 42.7 / 84 and 56 / 211; all alike, 2^20: 1779 / 12390.  A round of 260 001
+// children of 256 parents with crossover and features: 63.5 -> 44.7.
+
+constexpr int DEDUP_THREADS = 1024;
+constexpr int DEDUP_GENES = 8;          // genes in a 16-byte record
+constexpr uint32_t DEDUP_SLOTS = 8192;  // of a part's table, four times the candidates of a part
+constexpr uint32_t DEDUP_RECORDS = 2048; // records of a part that LDS holds
+constexpr uint32_t DEDUP_CHUNKS = 256;  // most blocks of the first launch: every block of the second looks all of them up
+constexpr uint64_t DEDUP_MOST = 1ull << 20, DEDUP_LEAST = 16384;
+constexpr uint64_t kEmptyEntry = ~0ull;
+
+// candidates per thread of the first launch, and parts (by the hash's top bits)
+inline int dedup_items(uint64_t n) { return n <= DEDUP_CHUNKS * DEDUP_THREADS * 2 ? 2 : 4; }
+inline uint32_t dedup_parts_log2(uint64_t n) { return n <= 1u << 19 ? 8 : 9; }
+
+// Clears the flags as dedup_clear_kernel does and sorts a chunk's candidates by part: [chunk][hash's lower half << 32 | index],
+// their genes as records, and where each part lies in the chunk, [part][chunk] first << 16 | number.  Bound by its chain of
+// phases for few candidates (260 001: 10.7 us), by the scattered records for many (2^20: 24).
+template <int ITEMS>
+__global__ __launch_bounds__(DEDUP_THREADS) void dedup_sort_kernel(const uint16_t *__restrict__ genes, uint64_t ld, uint32_t n, int n_genes,
+                                                                   uint8_t *__restrict__ flags, int overwrite, uint4 *__restrict__ records,
+                                                                   uint64_t *__restrict__ entries, uint32_t *__restrict__ bounds,
+                                                                   uint32_t parts_log2)
+{
+    __shared__ uint64_t sorted[DEDUP_THREADS * ITEMS];
+    __shared__ uint32_t count[DEDUP_THREADS], first[DEDUP_THREADS], wave_sum[DEDUP_THREADS / 64];
+    const int tid = threadIdx.x;
+    const uint32_t parts = 1u << parts_log2, shift = 64 - parts_log2;
+    count[tid] = 0;
+    const uint32_t start = blockIdx.x * (DEDUP_THREADS * ITEMS);
+    uint64_t h[ITEMS];
+    uint32_t rank[ITEMS], gene[ITEMS][DEDUP_GENES];
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+        const uint32_t i = min(start + j * DEDUP_THREADS + tid, n - 1);
+#pragma unroll
+        for (int g = 0; g < DEDUP_GENES; ++g) gene[j][g] = g < n_genes ? genes[(uint64_t)g * ld + i] : 0;
+    }
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+        h[j] = 0;
+#pragma unroll
+        for (int g = 0; g < DEDUP_GENES; ++g)
+            if (g < n_genes) h[j] = splitmix_finalise(h[j] + kGamma + gene[j][g]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+        const uint32_t i = start + j * DEDUP_THREADS + tid;
+        if (i >= n) continue;
+        flags[i] = overwrite || flags[i] ? 1 : 0;
+        rank[j] = atomicAdd(&count[h[j] >> shift], 1u);
+    }
+    __syncthreads();
+    const uint32_t mine = count[tid], upto = wave_prefix_sum(mine);
+    if ((tid & 63) == 63) wave_sum[tid >> 6] = upto;
+    __syncthreads();
+    if ((uint32_t)tid < parts) {
+        uint32_t at = upto - mine;
+        for (int w = 0; w < tid >> 6; ++w) at += wave_sum[w];
+        first[tid] = at;
+        bounds[(uint64_t)tid * gridDim.x + blockIdx.x] = at << 16 | mine;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+        const uint32_t i = start + j * DEDUP_THREADS + tid;
+        if (i >= n) continue;
+        const uint32_t to = first[h[j] >> shift] + rank[j];
+        sorted[to] = h[j] << 32 | i;
+        records[start + to] = make_uint4(gene[j][0] | gene[j][1] << 16, gene[j][2] | gene[j][3] << 16, gene[j][4] | gene[j][5] << 16,
+                                         gene[j][6] | gene[j][7] << 16);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+        const uint32_t e = j * DEDUP_THREADS + tid;
+        if (start + e < n) entries[start + e] = sorted[e];
+    }
+}
+
+// A block per part: its candidates into a table, where the lowest index of a tuple stays and every other one's flag is cleared, as
+// in dedup_insert_kernel.  Bound by the LDS: a compare-and-swap per probe (260 001 candidates 6.5 us, 2^20 19.5; with the genes
+// of possible equals gathered from their rows 14.6 and 72).
+__global__ __launch_bounds__(DEDUP_THREADS) void dedup_part_kernel(uint32_t chunks, uint32_t chunk, const uint4 *__restrict__ records,
+                                                                   const uint64_t *__restrict__ entries, const uint32_t *__restrict__ bounds,
+                                                                   uint8_t *flags)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char dedup_lds[];
+    uint4 *near = reinterpret_cast<uint4 *>(dedup_lds); // [DEDUP_RECORDS] of the part's first candidates
+    // [DEDUP_SLOTS] a zero (so that no candidate looks like an empty slot), 23 bits of hash, 20 of index, 20 of place in the part
+    unsigned long long *table = reinterpret_cast<unsigned long long *>(near + DEDUP_RECORDS);
+    __shared__ uint32_t before[DEDUP_CHUNKS], from[DEDUP_CHUNKS], wave_sum[DEDUP_CHUNKS / 64], full; // of every chunk: candidates in the chunks before it, and where they are
+    const int tid = threadIdx.x;
+    uint32_t w = 0, upto = 0;
+    if (tid < (int)DEDUP_CHUNKS) { // (whole wavefronts)
+        w = (uint32_t)tid < chunks ? bounds[(uint64_t)blockIdx.x * chunks + tid] : 0;
+        upto = wave_prefix_sum(w & 0xFFFFu);
+        if ((tid & 63) == 63) wave_sum[tid >> 6] = upto;
+    }
+    for (uint32_t s = tid; s < DEDUP_SLOTS; s += DEDUP_THREADS) table[s] = kEmptyEntry;
+    if (tid == 0) full = 0;
+    __syncthreads();
+    if (tid < (int)DEDUP_CHUNKS) {
+        uint32_t at = upto - (w & 0xFFFFu);
+        for (int v = 0; v < tid >> 6; ++v) at += wave_sum[v];
+        before[tid] = at;
+        from[tid] = tid * chunk + (w >> 16);
+    }
+    uint32_t total = 0;
+#pragma unroll
+    for (uint32_t v = 0; v < DEDUP_CHUNKS / 64; ++v) total += wave_sum[v];
+    __syncthreads();
+    auto place = [&](uint32_t e) { // of the part's candidate e in entries and records
+        uint32_t b = 0; // the last chunk with no more than e candidates before it
+#pragma unroll
+        for (uint32_t step = DEDUP_CHUNKS / 2; step > 0; step >>= 1) b += before[b + step] <= e ? step : 0;
+        return from[b] + e - before[b];
+    };
+    auto record = [&](uint32_t e) { return e < DEDUP_RECORDS ? near[e] : records[place(e)]; };
+    auto equal = [](uint4 a, uint4 b) { return ((a.x ^ b.x) | (a.y ^ b.y) | (a.z ^ b.z) | (a.w ^ b.w)) == 0; };
+    constexpr int KEEP = DEDUP_RECORDS / DEDUP_THREADS;
+    uint64_t kept[KEEP];
+#pragma unroll
+    for (int k = 0; k < KEEP; ++k) {
+        const uint32_t e = tid + k * DEDUP_THREADS;
+        if (e >= total) continue;
+        const uint32_t at = place(e);
+        kept[k] = entries[at];
+        near[e] = records[at];
+    }
+    __syncthreads();
+    auto insert = [&](uint32_t e, uint64_t entry) {
+        const uint32_t i = (uint32_t)entry;
+        const unsigned long long mine = (entry >> 32 & 0x7FFFFFu) << 40 | (uint64_t)i << 20 | e;
+        uint32_t slot = (uint32_t)(entry >> 32) % DEDUP_SLOTS, probe = 0;
+        for (; probe < DEDUP_SLOTS; ++probe) {
+            unsigned long long seen = atomicCAS(&table[slot], kEmptyEntry, mine);
+            if (seen == kEmptyEntry) break; // this candidate now stands for its tuple
+            if (seen >> 40 == mine >> 40 && equal(record((uint32_t)seen & 0xFFFFFu), record(e))) {
+                if (seen > mine) seen = atomicMin(&table[slot], mine);
+                const unsigned long long later = seen > mine ? seen : mine;
+                flags[(later >> 20) & 0xFFFFFu] = 0;
+                break;
+            }
+            slot = (slot + 1) % DEDUP_SLOTS;
+        }
+        if (probe == DEDUP_SLOTS) full = 1;
+    };
+#pragma unroll
+    for (int k = 0; k < KEEP; ++k)
+        if (tid + k * DEDUP_THREADS < total) insert(tid + k * DEDUP_THREADS, kept[k]);
+    for (uint32_t e = tid + DEDUP_RECORDS; e < total; e += DEDUP_THREADS) insert(e, entries[place(e)]);
+    __syncthreads();
+    if (!full) return;
+    // (more tuples in a part than its table holds: only genes chosen for that; every candidate against every other)
+    for (uint32_t e = tid; e < total; e += DEDUP_THREADS) {
+        const uint32_t at = place(e), i = (uint32_t)entries[at];
+        const uint4 own = records[at];
+        for (uint32_t o = 0; o < total; ++o) {
+            const uint32_t there = place(o);
+            if ((uint32_t)entries[there] < i && equal(records[there], own)) {
+                flags[i] = 0;
+                break;
+            }
+        }
+    }
+}
+
+// bytes of the parts' records, entries and bounds, or 0 where that path is not taken
+uint64_t dedup_part_bytes(uint64_t n)
+{
+    if (n < DEDUP_LEAST || n > DEDUP_MOST) return 0;
+    const uint64_t chunk = (uint64_t)DEDUP_THREADS * dedup_items(n);
+    return n * 24 + (((n + chunk - 1) / chunk) << dedup_parts_log2(n)) * 4;
+}
+
 uint64_t dedup_slots(uint64_t n)
 {
     uint64_t slots = 2;
@@ -518,7 +699,8 @@ uint64_t dedup_slots(uint64_t n)
 extern "C" uint64_t eck_candidates_dedup_workspace_bytes(uint64_t n)
 {
     if (n == 0 || n > (1ull << 30)) return 0;
-    return dedup_slots(n) * sizeof(uint32_t);
+    const uint64_t table = dedup_slots(n) * sizeof(uint32_t), parts = dedup_part_bytes(n);
+    return table > parts ? table : parts;
 }
 
 extern "C" int32_t eck_candidates_dedup(const uint16_t *genes, uint64_t ld, uint64_t n, int32_t n_genes, uint8_t *flags,
@@ -532,6 +714,20 @@ extern "C" int32_t eck_candidates_dedup(const uint16_t *genes, uint64_t ld, uint
     if ((uintptr_t)ws & 3) return ECK_EALIGN;
     uint32_t *table = static_cast<uint32_t *>(ws);
     hipStream_t st = as_stream(stream);
+    const uint64_t parts = dedup_part_bytes(n);
+    if (parts && n_genes <= DEDUP_GENES && ws_bytes >= parts && ((uintptr_t)ws & 15) == 0) {
+        const uint32_t chunk = DEDUP_THREADS * dedup_items(n), chunks = (uint32_t)((n + chunk - 1) / chunk), log2 = dedup_parts_log2(n);
+        uint4 *records = static_cast<uint4 *>(ws);
+        uint64_t *entries = reinterpret_cast<uint64_t *>(records + n);
+        uint32_t *bounds = reinterpret_cast<uint32_t *>(entries + n);
+        hipLaunchKernelGGL((dedup_items(n) == 2 ? dedup_sort_kernel<2> : dedup_sort_kernel<4>), dim3(chunks), dim3(DEDUP_THREADS), 0, st, genes, ld,
+                           (uint32_t)n, (int)n_genes, flags, (int)overwrite, records, entries, bounds, log2);
+        constexpr int LDS = DEDUP_SLOTS * 8 + DEDUP_RECORDS * 16;
+        ECK_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(dedup_part_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, LDS));
+        hipLaunchKernelGGL(dedup_part_kernel, dim3(1u << log2), dim3(DEDUP_THREADS), LDS, st, chunks, chunk, records, entries, bounds, flags);
+        ECK_HIP_TRY(hipGetLastError());
+        return ECK_OK;
+    }
     const uint32_t mask = (uint32_t)(slots - 1);
     hipLaunchKernelGGL(dedup_clear_kernel, dim3((unsigned)((slots + 255) / 256)), dim3(256), 0, st, table, slots, flags,
                        (uint32_t)n, (int)overwrite);

@@ -442,3 +442,37 @@ def test_dedup_clears_flags_of_many_and_few_occurrences(G, n, ld, kinds):
         torch.cuda.synchronize()
         expected = want if overwrite else (want != 0) & (before != 0)
         assert np.array_equal(flags.cpu().numpy(), np.asarray(expected, dtype=np.uint8))
+
+
+@pytest.mark.parametrize("n", [16383, 16384, 16385, 40001, 524288, 524289, (1 << 20) - 1, 1 << 20, (1 << 20) + 1])
+@pytest.mark.parametrize("kinds,n_genes", [(1, 3), (1500, 8), (1500, 9), (200000, 1), (1 << 30, 5)])
+def test_dedup_by_parts_and_by_one_table(G, n, kinds, n_genes):
+    """Candidates sorted by hash with a table per part (16384 to 2^20 candidates of up to eight genes, in the workspace of the
+    query) and one table for all: few tuples of many occurrences, whose part is far larger than the others, and nearly all
+    distinct; genes over all sixteen bits; rows longer than n; a workspace of the table's size only, and one that starts 4
+    bytes into a 16-byte line."""
+    import torch
+    if kinds == 1 and n not in (16384, 40001):
+        pytest.skip("one tuple: the sizes above say nothing more")
+    rng = np.random.default_rng(n + kinds)
+    ld = n + 3
+    base = rng.integers(0, 65536, size=(n_genes, min(kinds, n)), dtype=np.uint16)
+    genes = np.ascontiguousarray(base[:, rng.integers(0, base.shape[1], size=ld)])
+    # (the oracle compares every pair; numpy's first occurrences, which the oracle is pinned by, for more than a few thousand)
+    want = np.zeros(n, dtype=np.uint8)
+    want[np.unique(np.ascontiguousarray(genes[:, :n].T).view("V%d" % (2 * n_genes)).ravel(), return_index=True)[1]] = 1
+    assert np.array_equal(oracle.dedup(np.ascontiguousarray(genes[:, :3000])), want[:3000])
+    dev = G.to_dev(genes)
+    table = 4
+    while table < 8 * n:
+        table *= 2
+    full = eck.candidates_dedup_workspace_bytes(n)
+    ws = torch.full((max(full, table) + 32,), 255, dtype=torch.uint8, device="cuda")
+    for room in (ws[:full], ws[:table], ws[4:4 + full]):
+        for overwrite in (True, False):
+            flags = G.to_dev((rng.random(n) < 0.7).astype(np.uint8) * 2)
+            before = flags.cpu().numpy()
+            eck.candidates_dedup(dev, n, flags, overwrite=overwrite, ws=room)
+            torch.cuda.synchronize()
+            got = flags.cpu().numpy()
+            assert np.array_equal(got, want if overwrite else (want & (before != 0)).astype(np.uint8))
