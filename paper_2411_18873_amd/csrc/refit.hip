@@ -15,6 +15,10 @@
 // roundings as the launch-per-product path: features, weights, first hidden activations and both deltas in bf16,
 // biases and the output weights rounded through bf16, the second hidden layer and the output layer in fp32.
 // Every reduction has a fixed order, so a run is reproducible bit for bit.
+// What bounds a step is the latency of loads right after a launch and the chain of dependent phases, so both kernels
+// request all that they can name before they wait for any of it, and values become bfloat16 two at a time by the
+// hardware's conversion.  Measured, 64-256-256-1, a whole call: 8 steps of 512 rows 160.4 us where each value was loaded
+// and rounded at its use, 144.9 now; 4 steps of 16384 rows 482 and 305.
 #include "eck_internal.h"
 #include "refit_labels.h"
 
@@ -24,7 +28,6 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ uint16_t bf16_bits(float x)
 {
@@ -32,6 +35,14 @@ __device__ __forceinline__ uint16_t bf16_bits(float x)
     if ((u & 0x7F800000u) == 0x7F800000u) return (uint16_t)(u >> 16);
     u += 0x7FFFu + ((u >> 16) & 1u);
     return (uint16_t)(u >> 16);
+}
+
+// two values as bfloat16, rounded to nearest, in a word (one instruction; by the integer steps above, twelve)
+__device__ __forceinline__ uint32_t bf16_two(float a, float b)
+{
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    const bf16x2 two = {(__bf16)a, (__bf16)b};
+    return __builtin_bit_cast(uint32_t, two);
 }
 
 __device__ __forceinline__ float through_bf16(float x) { return __uint_as_float((uint32_t)bf16_bits(x) << 16); }
@@ -127,10 +138,19 @@ __device__ __forceinline__ f32x16 row_tile_product(const uint16_t *a_lds, const 
 
 // Registers 4g .. 4g+3 of a D tile -- rows 8g + 4h .. +3 of column c -- as bf16 into a fragment-ordered matrix with
 // n = column (unit), k = minibatch row: four consecutive k of one lane's fragment, one 8-byte store.
-__device__ __forceinline__ void store_rows4(uint16_t *t, int unit, int rows_total, int row, const uint16_t (&v)[4])
+__device__ __forceinline__ void store_rows4(uint16_t *t, int unit, int rows_total, int row, uint32_t lo, uint32_t hi)
 {
-    u16x4 packed = {v[0], v[1], v[2], v[3]};
-    *reinterpret_cast<u16x4 *>(t + frag_at(unit, row, rows_total)) = packed;
+    *reinterpret_cast<uint2 *>(t + frag_at(unit, row, rows_total)) = make_uint2(lo, hi);
+}
+
+// the same four values into a row-major LDS matrix: rows row .. row + 3 of column col
+__device__ __forceinline__ void put_rows4(uint16_t *lds, int ld, int row, int col, uint32_t lo, uint32_t hi)
+{
+    uint16_t *at = lds + row * ld + col;
+    at[0] = (uint16_t)lo;
+    at[ld] = (uint16_t)(lo >> 16);
+    at[2 * ld] = (uint16_t)hi;
+    at[3 * ld] = (uint16_t)(hi >> 16);
 }
 
 // One block = 32 minibatch rows; one wavefront per 32-column tile of the widest layer (H / 32 wavefronts), so every
@@ -164,45 +184,50 @@ __global__ __launch_bounds__((H1 > H2 ? H1 : H2) * 2) void step_rows_kernel(Step
     const bool has1 = wave < H1 / 32, has2 = wave < H2 / 32; // this wavefront owns a tile of the first / second layer
     const int col = 32 * wave + c;
 
+    // Everything the first two layers need is requested before anything is waited for, the features, which are needed first,
+    // in front: a load at the start of a launch goes past the L2 and takes more than a microsecond, and a bias rounded where
+    // it arrived held the features back by as much again.  refit_applies asks for the alignment of these loads: ld and the
+    // base are whole 16 bytes, row0 and r0 multiples of 32 rows.
+    constexpr int FOURS = 32 * F / 4; // four neighbouring rows of a feature
+    constexpr int PER = (FOURS + NT - 1) / NT;
+    uint2 x2[PER];
+    float4 x4[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int e = min(tid + k * NT, FOURS - 1);
+        const uint64_t at = (uint64_t)(e >> 3) * a.ld + a.row0 + r0 + 4 * (e & 7);
+        if (FEAT_BF16) x2[k] = *reinterpret_cast<const uint2 *>(reinterpret_cast<const uint16_t *>(a.feat) + at);
+        else x4[k] = *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(a.feat) + at);
+    }
     Fragments<F> w1f;
     Fragments<H1> w2f;
-    float bias1 = 0.0f, bias2 = 0.0f, w3 = 0.0f;
-    if (has1) {
-        fetch_fragments<F>(a.w1t + (int64_t)wave * 32 * F, lane, w1f); // tile `wave`: 32 * F elements
-        bias1 = through_bf16(a.theta[a.off_b1 + col]);
-    }
-    if (has2) {
-        fetch_fragments<H1>(a.w2t + (int64_t)wave * 32 * H1, lane, w2f);
-        bias2 = through_bf16(a.theta[a.off_b2 + col]);
-        w3 = through_bf16(a.theta[a.off_w3 + col]);
-    }
+    const int col1 = min(col, H1 - 1), col2 = min(col, H2 - 1);
+    const float bias1_raw = a.theta[a.off_b1 + col1], bias2_raw = a.theta[a.off_b2 + col2], w3_raw = a.theta[a.off_w3 + col2];
+    const float target = a.y[a.row0 + r0 + (tid & 31)], bias3_raw = a.theta[a.off_b3];
+    if (has1) fetch_fragments<F>(a.w1t + (int64_t)wave * 32 * F, lane, w1f); // tile `wave`: 32 * F elements
+    if (has2) fetch_fragments<H1>(a.w2t + (int64_t)wave * 32 * H1, lane, w2f);
+    __builtin_amdgcn_sched_barrier(0);
     // the block's 32 feature rows, as bf16, k-major
-    for (int e = tid; e < 32 * F; e += NT) {
-        const int r = e & 31, f = e >> 5;
-        const uint64_t at = (uint64_t)f * a.ld + a.row0 + r0 + r;
-        x_l[r * LDX + f] = FEAT_BF16 ? reinterpret_cast<const uint16_t *>(a.feat)[at]
-                                     : bf16_bits(reinterpret_cast<const float *>(a.feat)[at]);
-    }
-    // what the output layer will want from memory, requested now
-    float target = 1.0f, bias3 = 0.0f;
-    if (tid < 32) {
-        target = a.y[a.row0 + r0 + tid];
-        bias3 = through_bf16(a.theta[a.off_b3]);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int e = min(tid + k * NT, FOURS - 1);
+        const uint32_t lo = FEAT_BF16 ? x2[k].x : bf16_two(x4[k].x, x4[k].y), hi = FEAT_BF16 ? x2[k].y : bf16_two(x4[k].z, x4[k].w);
+        put_rows4(x_l, LDX, 4 * (e & 7), e >> 3, lo, hi);
     }
     lds_barrier();
+    const float bias1 = through_bf16(bias1_raw), bias2 = through_bf16(bias2_raw), w3 = through_bf16(w3_raw), bias3 = through_bf16(bias3_raw);
 
     // ---- h1 = relu(x W1 + b1), bf16
     if (has1) {
         const f32x16 acc = row_tile_product<F, LDX>(x_l, a.w1t + (int64_t)wave * 32 * F, w1f, lane);
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-            uint16_t v[4];
+            float v[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                v[e] = bf16_bits(fmaxf(acc[4 * g + e] + bias1, 0.0f));
-                h1_l[d_row(4 * g + e, h) * LD1 + col] = v[e];
-            }
-            store_rows4(a.h1t, col, a.rows, r0 + d_row(4 * g, h), v);
+            for (int e = 0; e < 4; ++e) v[e] = fmaxf(acc[4 * g + e] + bias1, 0.0f);
+            const uint32_t lo = bf16_two(v[0], v[1]), hi = bf16_two(v[2], v[3]);
+            put_rows4(h1_l, LD1, d_row(4 * g, h), col, lo, hi);
+            store_rows4(a.h1t, col, a.rows, r0 + d_row(4 * g, h), lo, hi);
         }
     }
     lds_barrier();
@@ -253,14 +278,14 @@ __global__ __launch_bounds__((H1 > H2 ? H1 : H2) * 2) void step_rows_kernel(Step
     if (has2) {
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-            uint16_t v[4];
+            const float4 dy = *reinterpret_cast<const float4 *>(dy_l + d_row(4 * g, h)); // four neighbouring rows
+            const float row_dy[4] = {dy.x, dy.y, dy.z, dy.w};
+            float v[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int row = d_row(4 * g + e, h);
-                v[e] = bf16_bits(h2v[4 * g + e] > 0.0f ? dy_l[row] * w3 : 0.0f);
-                d2_l[row * LD2 + col] = v[e];
-            }
-            store_rows4(a.d2t, col, a.rows, r0 + d_row(4 * g, h), v);
+            for (int e = 0; e < 4; ++e) v[e] = h2v[4 * g + e] > 0.0f ? row_dy[e] * w3 : 0.0f;
+            const uint32_t lo = bf16_two(v[0], v[1]), hi = bf16_two(v[2], v[3]);
+            put_rows4(d2_l, LD2, d_row(4 * g, h), col, lo, hi);
+            store_rows4(a.d2t, col, a.rows, r0 + d_row(4 * g, h), lo, hi);
         }
     }
     lds_barrier();
@@ -269,14 +294,11 @@ __global__ __launch_bounds__((H1 > H2 ? H1 : H2) * 2) void step_rows_kernel(Step
         const f32x16 acc = row_tile_product<H2, LD2>(d2_l, a.w2 + (int64_t)wave * 32 * H2, wbf, lane);
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-            uint16_t v[4];
+            float v[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int row = d_row(4 * g + e, h);
-                const bool active = h1_l[row * LD1 + col] != 0; // a ReLU output: positive unless its bits are zero
-                v[e] = active ? bf16_bits(acc[4 * g + e]) : (uint16_t)0;
-            }
-            store_rows4(a.d1t, col, a.rows, r0 + d_row(4 * g, h), v);
+            for (int e = 0; e < 4; ++e) // a ReLU output: positive unless its bits are zero
+                v[e] = h1_l[d_row(4 * g + e, h) * LD1 + col] != 0 ? acc[4 * g + e] : 0.0f;
+            store_rows4(a.d1t, col, a.rows, r0 + d_row(4 * g, h), bf16_two(v[0], v[1]), bf16_two(v[2], v[3]));
         }
     }
 }
@@ -316,6 +338,14 @@ __global__ __launch_bounds__(256) void step_weights_kernel(StepArgs a)
             w_old[e] = a.theta[at[e]];
             m_old[e] = a.theta[a.P + at[e]];
             v_old[e] = a.theta[2 * a.P + at[e]];
+        }
+        // ... and the bias that it updates, in the first tile row
+        const uint64_t bias_at = (second ? a.off_b2 : a.off_b1) + 32 * ntile + (tid & 31);
+        float bias_w = 0.0f, bias_m = 0.0f, bias_v = 0.0f;
+        if (mt == 0) {
+            bias_w = a.theta[bias_at];
+            bias_m = a.theta[a.P + bias_at];
+            bias_v = a.theta[2 * a.P + bias_at];
         }
         // A rows: hidden unit (W2) or feature (W1) 32 mt + m; B columns: unit 32 ntile + n
         const uint16_t *bsrc = (second ? a.d2t : a.d1t) + (int64_t)ntile * 32 * B + lane * 8; // fragments of tile ntile
@@ -369,7 +399,7 @@ __global__ __launch_bounds__(256) void step_weights_kernel(StepArgs a)
             const float g = ((part[0][q][lane] + part[1][q][lane]) + part[2][q][lane]) + part[3][q][lane];
             const int m = 32 * mt + d_row(q, h), n = 32 * ntile + c;
             const float w = adam_one(a.theta, a.P, at[e], w_old[e], m_old[e], v_old[e], g, a.beta1, a.beta2, a.lr, a.eps, c1, c2);
-            const uint16_t wb = bf16_bits(w);
+            const uint16_t wb = (uint16_t)bf16_two(w, w);
             if (second) {
                 a.w2[frag_at(m, n, H2)] = wb;
                 a.w2t[frag_at(n, m, H1)] = wb;
@@ -379,9 +409,7 @@ __global__ __launch_bounds__(256) void step_weights_kernel(StepArgs a)
         }
         if (mt == 0 && tid < 32) {
             const float g = ((colsum[0][tid] + colsum[1][tid]) + colsum[2][tid]) + colsum[3][tid];
-            const uint64_t i = (second ? a.off_b2 : a.off_b1) + 32 * ntile + tid;
-            (void)adam_one(a.theta, a.P, i, a.theta[i], a.theta[a.P + i], a.theta[2 * a.P + i], g, a.beta1, a.beta2, a.lr, a.eps,
-                           c1, c2);
+            (void)adam_one(a.theta, a.P, bias_at, bias_w, bias_m, bias_v, g, a.beta1, a.beta2, a.lr, a.eps, c1, c2);
         }
         return;
     }
@@ -392,21 +420,25 @@ __global__ __launch_bounds__(256) void step_weights_kernel(StepArgs a)
     const int cg = tid & 15, rg = tid >> 4;
     const int col = block * 16 + cg;
     float acc = 0.0f;
+    const uint64_t i_out = col < H2 ? a.off_w3 + col : a.off_b3;
+    const float w_out = a.theta[i_out], m_out = a.theta[a.P + i_out], v_out = a.theta[2 * a.P + i_out];
     {
+        // (up to 32 rows under way together: a block sums B / 16 rows a thread, and four at a time the loads' latency counts for
+        // every fourth row)
+        constexpr int AHEAD = 32;
         const int per = B / 16, rlo = rg * per, rhi = rlo + per; // B is a multiple of 64: per is a multiple of 4
-        if (col < H2) {
-            for (int r = rlo; r < rhi; r += 4) {
-                float v[4], d[4];
+        if (col <= H2) {
+            for (int r = rlo; r < rhi; r += AHEAD) {
+                float v[AHEAD], d[AHEAD];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    v[u] = a.h2[(int64_t)(r + u) * H2 + col];
-                    d[u] = a.dy[r + u];
+                for (int u = 0; u < AHEAD; ++u) {
+                    const int row = min(r + u, rhi - 1);
+                    v[u] = col < H2 ? a.h2[(int64_t)row * H2 + col] : 1.0f;
+                    d[u] = a.dy[row];
                 }
 #pragma unroll
-                for (int u = 0; u < 4; ++u) acc = fmaf(v[u], d[u], acc);
+                for (int u = 0; u < AHEAD; ++u) acc = r + u < rhi ? fmaf(v[u], d[u], acc) : acc;
             }
-        } else if (col == H2) {
-            for (int r = rlo; r < rhi; ++r) acc += a.dy[r];
         }
     }
     psum[rg * 16 + cg] = acc;
@@ -428,9 +460,7 @@ __global__ __launch_bounds__(256) void step_weights_kernel(StepArgs a)
         float g = psum[cg];
 #pragma unroll
         for (int r = 1; r < 16; ++r) g += psum[r * 16 + cg];
-        const uint64_t i = col < H2 ? a.off_w3 + col : a.off_b3;
-        (void)adam_one(a.theta, a.P, i, a.theta[i], a.theta[a.P + i], a.theta[2 * a.P + i], g, a.beta1, a.beta2, a.lr, a.eps,
-                       c1, c2);
+        (void)adam_one(a.theta, a.P, i_out, w_out, m_out, v_out, g, a.beta1, a.beta2, a.lr, a.eps, c1, c2);
     }
 }
 

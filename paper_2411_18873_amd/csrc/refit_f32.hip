@@ -10,8 +10,9 @@
 // each product's loads: weights are requested before the barrier or the product that precedes theirs, several groups of
 // sixteen rows of the reduction at a time.  Every sum has a fixed order.
 // Measured, 64-128-128-1 on minibatches of 250: 136 us per step launched one product at a time (a vector kernel of two
-// blocks for most of them, 30 us each), 16 us in two launches (rows 10.5, weights 5.4; a block of its own for the bias
-// corrections took 0.85 us a step off the rows kernel); 64-512-512-1, 512 rows: 290 and 70.
+// blocks for most of them, 30 us each), 15 us in two launches (a block of its own for the bias corrections took 0.85 us a
+// step off the rows kernel; the features requested first and the biases' moments with the tile's, 0.6); 64-512-512-1,
+// 512 rows: 290 and 70.
 #include "f32_tiles.h"
 
 using namespace eck;
@@ -187,32 +188,39 @@ __global__ __launch_bounds__(64 * WAVES, 2) void step_rows_f32_kernel(StepF32 a)
     const F32Layer l1{a.theta + a.off_w1, a.theta + a.off_b1, F, H1}, l2{a.theta + a.off_w2, a.theta + a.off_b2, H1, H2};
     const ForwardSlice<J> s1(l1, first, p, c), s2(l2, first, p, c);
     const BackSlice<J> back(l2, first, p, c);
-    float w1f[DEPTH][4][J], w2f[DEPTH][4][J];
-    if (has1) request<J, DEPTH>(s1, F, w1f);
-    if (has2) request<J, DEPTH>(s2, H1, w2f);
-    float b1[E], b2[E], w3[E];
+    // Everything the first two layers need is requested before anything is waited for, the features, which are needed first, in
+    // front
+    auto features = [&](int e) {
+        const int row = e % ROWS, four = e / ROWS;
+        const uint64_t col = a.row0 + min(r0 + row, a.rows - 1);
+        f32x4 v;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) v[t] = a.feat[(uint64_t)(4 * four + t) * a.ld + col];
+        return v;
+    };
+    auto keep = [&](int e, f32x4 v) {
+        const int row = e % ROWS, four = e / ROWS;
+        if (r0 + row >= a.rows) v = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        x_l[e] = v;
+        *reinterpret_cast<f32x4 *>(a.x + (int64_t)(r0 + row) * F + 4 * four) = v;
+    };
+    const int items = F / 4 * ROWS;
+    const f32x4 first_features = features(min(tid, items - 1));
+    float b1[E], b2[E], w3[E], w1f[DEPTH][4][J], w2f[DEPTH][4][J];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         b1[e] = l1.b[min(unit0 + e, H1 - 1)];
         b2[e] = l2.b[min(unit0 + e, H2 - 1)];
         w3[e] = a.theta[a.off_w3 + min(unit0 + e, H2 - 1)];
     }
-    float target = 1.0f, bias3 = 0.0f;
-    if (tid < ROWS) {
-        target = a.y[a.row0 + min(r0 + tid, a.rows - 1)];
-        bias3 = a.theta[a.off_b3];
-    }
-    for (int e = tid; e < F / 4 * ROWS; e += threads) {
-        const int row = e % ROWS, four = e / ROWS;
-        const uint64_t col = a.row0 + min(r0 + row, a.rows - 1);
-        f32x4 v;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) v[t] = a.feat[(uint64_t)(4 * four + t) * a.ld + col];
-        if (r0 + row >= a.rows) v = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        x_l[e] = v;
-        *reinterpret_cast<f32x4 *>(a.x + (int64_t)(r0 + row) * F + 4 * four) = v;
-    }
+    float target = a.y[a.row0 + min(r0 + c, a.rows - 1)], bias3 = a.theta[a.off_b3];
+    if (has1) request<J, DEPTH>(s1, F, w1f);
+    if (has2) request<J, DEPTH>(s2, H1, w2f);
+    __builtin_amdgcn_sched_barrier(0);
+    if (tid < items) keep(tid, first_features);
+    for (int e = tid + threads; e < items; e += threads) keep(e, features(e));
     lds_barrier();
+    asm volatile("" : "+v"(target), "+v"(bias3)); // (there by now; left to their use, they wait for all later loads, too)
 
     // ---- h1 = relu(x W1 + b1)
     float h1[E];
@@ -331,6 +339,10 @@ __global__ __launch_bounds__(64 * WAVES) void step_weights_f32_kernel(StepF32 a,
             const int m = m0 + tid / TILE + e * (TILE / PER), n = n0 + tid % TILE;
             state[e] = load_moments(a, off_w + (uint64_t)min(m, M - 1) * N + min(n, N - 1));
         }
+        // ... and the bias, in the first tile row
+        const uint64_t bias_at = off_b + min(n0 + tid % TILE, N - 1);
+        Moments bias_state = {0.0f, 0.0f, 0.0f};
+        if (m0 == 0) bias_state = load_moments(a, bias_at);
         const uint32_t a_lane = 4u * (uint32_t)(4 * p * M + m0 + 2 * c), d_lane = 4u * (uint32_t)(4 * p * N + n0 + 2 * c);
         f32x4 acc[2][2];
 #pragma unroll
@@ -398,7 +410,7 @@ __global__ __launch_bounds__(64 * WAVES) void step_weights_f32_kernel(StepF32 a,
             float g = colsum[0][tid];
 #pragma unroll
             for (int w = 1; w < WAVES; ++w) g += colsum[w][tid];
-            adam_one(a, off_b + n0 + tid, load_moments(a, off_b + n0 + tid), g, c1, c2);
+            adam_one(a, bias_at, bias_state, g, c1, c2);
         }
         return;
     }
@@ -409,6 +421,8 @@ __global__ __launch_bounds__(64 * WAVES) void step_weights_f32_kernel(StepF32 a,
     const int cg = tid & 15, rg = tid >> 4, col = block * 16 + cg;
     const int per = (a.padded + RG - 1) / RG, rlo = rg * per, rhi = min(rlo + per, a.padded);
     float sum = 0.0f;
+    const uint64_t i_out = col < a.H2 ? a.off_w3 + col : a.off_b3;
+    const Moments out_state = load_moments(a, i_out);
     if (col < a.H2) {
         int r = rlo;
         for (; r + 8 <= rhi; r += 8) {
@@ -445,8 +459,7 @@ __global__ __launch_bounds__(64 * WAVES) void step_weights_f32_kernel(StepF32 a,
         float g = psum[cg];
 #pragma unroll
         for (int r = 1; r < RG; ++r) g += psum[r * 16 + cg];
-        const uint64_t i = col < a.H2 ? a.off_w3 + col : a.off_b3;
-        adam_one(a, i, load_moments(a, i), g, c1, c2);
+        adam_one(a, i_out, out_state, g, c1, c2);
     }
 }
 
