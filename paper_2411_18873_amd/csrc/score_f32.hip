@@ -9,7 +9,7 @@
 //
 // What bounds it: matrix instructions and the LDS reads of the activations behind them (a part of four candidate tiles is read
 // for twelve matrix instructions), for narrow models the features.  Measured, against fp32 matrix instructions (which reached
-// 121-135 of their 153 TFLOP/s): 64-256-256-1 on 100003 candidates 152 -> 96 us (171 TFLOP/s of fp32 products, 1030 of bfloat16
+// 121-135 of their 153 TFLOP/s): 64-256-256-1 on 100003 candidates 152 -> 93 us (177 TFLOP/s of fp32 products, 1060 of bfloat16
 // ones), 64-128-128-1 on 2^18 126 -> 87, 64-512-512-1 on 100003 499 -> 425, 32-64-64-1 on 6400 6.9 -> 6.2 and on 2^20 156 -> 130.
 // Models of 16 units or less wait for their features' parts: 100003 candidates 7.8 -> 8.7 us, 64-16-512-1 52.7 -> 59.  Errors
 // against 64 bits, relative to the scores' norm (before in brackets): 512 units 2.5-3.4e-8 (6.1-6.4e-8), 256 3.1-3.6e-8
@@ -125,9 +125,9 @@ __device__ __forceinline__ float score_plain(const F32Net &net, const float *fea
 // n nor on its place.  M, M2: most 16-unit tiles per
 // wavefront of the units of the first and the second layer that are worked on at a time.  ONE: CHUNK units take the first layer.
 template <int CT, int M, int M2, bool ONE, bool WITH_MIN>
-__global__ __launch_bounds__(512, 2) void score_f32_kernel(F32Net net, const float *__restrict__ feat, uint64_t ld,
-                                                           uint64_t n, float *__restrict__ out, int unit_slots, int x_rows,
-                                                           int h_rows, int act_bytes, MinArgs mn)
+__device__ __forceinline__ void score_block(const F32Net &net, const float *__restrict__ feat, uint64_t ld, uint64_t n,
+                                            float *__restrict__ out, int unit_slots, int x_rows, int h_rows, int act_bytes,
+                                            const MinArgs &mn, uint64_t skip, uint32_t block)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char f32_lds[];
     const int tid = threadIdx.x, lane = tid & 63, p = lane >> 4, c = lane & 15;
@@ -139,7 +139,7 @@ __global__ __launch_bounds__(512, 2) void score_f32_kernel(F32Net net, const flo
     float *sum_l = reinterpret_cast<float *>(f32_lds + act_bytes); // [tiles of the second layer][cands]
     const int out_tiles = tiles_of(net.H2);
     uint32_t *odd_l = reinterpret_cast<uint32_t *>(sum_l + out_tiles * cands); // [cands], then whether there is any
-    const uint64_t base = (uint64_t)blockIdx.x * cands;
+    const uint64_t base = skip + (uint64_t)block * cands;
     for (int e = tid; e <= cands; e += blockDim.x) odd_l[e] = 0;
 
     for (int e = tid; e < net.F / 8 * cands; e += blockDim.x) { // 32 or 64 features
@@ -324,6 +324,20 @@ __global__ __launch_bounds__(512, 2) void score_f32_kernel(F32Net net, const flo
     }
 }
 
+// The first `whole` blocks take CT candidate tiles a slot, `skip` candidates together; the others, in the last round of blocks,
+// LAST_CT.
+template <int CT, int M, int M2, bool ONE, bool WITH_MIN, int LAST_CT = CT>
+__global__ __launch_bounds__(512, 2) void score_f32_kernel(F32Net net, const float *__restrict__ feat, uint64_t ld,
+                                                           uint64_t n, float *__restrict__ out, int unit_slots, int x_rows,
+                                                           int h_rows, int act_bytes, MinArgs mn, uint32_t whole, uint64_t skip)
+{
+    if (LAST_CT == CT || blockIdx.x < whole)
+        score_block<CT, M, M2, ONE, WITH_MIN>(net, feat, ld, n, out, unit_slots, x_rows, h_rows, act_bytes, mn, 0, blockIdx.x);
+    else
+        score_block<LAST_CT, M, M2, ONE, WITH_MIN>(net, feat, ld, n, out, unit_slots, x_rows, h_rows, act_bytes, mn, skip,
+                                                   blockIdx.x - whole);
+}
+
 template <bool WITH_MIN>
 int32_t launch(const eck_model *m, const float *feat, uint64_t ld, uint64_t n, float *out, const MinArgs &mn, hipStream_t st)
 {
@@ -337,9 +351,10 @@ int32_t launch(const eck_model *m, const float *feat, uint64_t ld, uint64_t n, f
     // Two unit tiles per wavefront and four candidate tiles (64 candidates a block): a weight is read for four, an activation
     // for two.  Fewer candidates where blocks that large would leave compute units without one (64-256-256-1, us with 1 / 2 /
     // 4 candidate tiles: 1000 9 / 10 / -, 6400 17 / 10.7 / 14, 16000 34 / 21 / 15, 100003 199 / 126 / 95); two at most
-    // where the sums of both layers are held at once (more than CHUNK units in the first).  Narrower models with one unit tile per wavefront until the chip is full (64-128-128-1: 6400 6.2 against
-    // 6.8, 16000 7.9 and 8.9, 30000 14.6 and 11; 32-64-64-1: 30000 6.4 and 6.9, 60000 11 and 8.8), those of 32 units or less
-    // always (64-30-20-1 on 2^20: 116-118 against 130).
+    // where the sums of both layers are held at once (more than CHUNK units in the first).  Narrower models with one unit
+    // tile per wavefront until the chip is full (64-128-128-1: 6400 6.2 against 6.8, 16000 7.9 and 8.9, 30000 14.6 and 11;
+    // 32-64-64-1: 30000 6.4 and 6.9, 60000 11 and 8.8), those of 32 units or less always (64-30-20-1 on 2^20: 116-118
+    // against 130).
     int ct = tiles <= 256 ? 1 : tiles <= 512 || H1 > CHUNK ? 2 : 4, per = 2, unit_slots = 8, cand_slots = 1;
     if (widest <= 16) {
         per = unit_slots = 1;
@@ -362,16 +377,40 @@ int32_t launch(const eck_model *m, const float *feat, uint64_t ld, uint64_t n, f
     size_t act_bytes = (size_t)PARTS * rows * cands * 16;
     if (act_bytes < (size_t)threads * 32) act_bytes = (size_t)threads * 32; // (score_plain: 512 floats a wavefront)
     const size_t lds = act_bytes + ((size_t)tiles_of(H2) * cands + cands + 1) * 4;
-    auto kern = H1 > CHUNK ? (ct == 2 ? score_f32_kernel<2, 2, 2, false, WITH_MIN> : score_f32_kernel<1, 2, 4, false, WITH_MIN>)
-                : per == 2 ? (ct == 4   ? score_f32_kernel<4, 2, 2, true, WITH_MIN>
+    // Eight wavefronts of blocks of 64 candidates fill a compute unit (their registers), so a launch takes whole rounds of
+    // them; what a last round short of blocks would do goes over the whole chip in blocks of 16 or 32 candidates.  Rounds
+    // and us with such blocks, without: 64-256-256-1 1.1 24.0, 28.7; 1.25 24.4, 28.3; 1.4 24.8, 28.2; 3.1 51.7, 55.5;
+    // 64-512-512-1, of 32 candidates before, 16 now: 1.1 59.4, 62.9; 3.4 124.6, 127.7; 64-128-128-1, two blocks a unit: 1.1
+    // 15.2, 18.0; 3.1 34.6, 36.9; from an eighth of a round on slower (1.25 18.2, 18.2; 2.2 29.3, 28.3), and for narrower
+    // models, with no rounds to speak of, from three rounds on.
+    const uint64_t blocks = (n + cands - 1) / cands;
+    uint64_t whole = blocks, grid = blocks;
+    int last_ct = ct;
+    if (unit_slots >= 4 && ct == (H1 > CHUNK ? 2 : 4)) {
+        int cus = 256;
+        (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, m->device);
+        const uint64_t round = (uint64_t)cus * (8 / unit_slots), left = blocks % round;
+        if (left && left <= (unit_slots == 8 ? round / 2 : round / 8)) {
+            last_ct = ct == 2 || left <= round / 4 ? 1 : 2;
+            whole = blocks - left;
+            const uint64_t few = 16 * (uint64_t)last_ct;
+            grid = whole + (n - whole * cands + few - 1) / few;
+        }
+    }
+    auto kern = H1 > CHUNK ? (last_ct < ct ? score_f32_kernel<2, 2, 2, false, WITH_MIN, 1>
+                              : ct == 2    ? score_f32_kernel<2, 2, 2, false, WITH_MIN>
+                                           : score_f32_kernel<1, 2, 4, false, WITH_MIN>)
+                : per == 2 ? (last_ct < ct ? (last_ct == 1 ? score_f32_kernel<4, 2, 2, true, WITH_MIN, 1>
+                                                           : score_f32_kernel<4, 2, 2, true, WITH_MIN, 2>)
+                              : ct == 4 ? score_f32_kernel<4, 2, 2, true, WITH_MIN>
                               : ct == 2 ? score_f32_kernel<2, 2, 2, true, WITH_MIN>
                                         : score_f32_kernel<1, 2, 2, true, WITH_MIN>)
                            : (ct == 4   ? score_f32_kernel<4, 1, 1, true, WITH_MIN>
                               : ct == 2 ? score_f32_kernel<2, 1, 1, true, WITH_MIN>
                                         : score_f32_kernel<1, 1, 1, true, WITH_MIN>);
     ECK_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    hipLaunchKernelGGL(kern, dim3((unsigned)((n + cands - 1) / cands)), dim3(threads), lds, st, net, feat,
-                       ld, n, out, unit_slots, x_rows, h_rows, (int)act_bytes, mn);
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(threads), lds, st, net, feat, ld, n, out, unit_slots, x_rows, h_rows,
+                       (int)act_bytes, mn, (uint32_t)whole, whole * cands);
     ECK_HIP_TRY(hipGetLastError());
     return ECK_OK;
 }

@@ -256,6 +256,33 @@ def test_narrow_fp32_models_on_many_candidates(G, widths):
         assert np.array_equal(G.score_gpu(model, feat, n), few[np.arange(n) % some]), n
 
 
+@pytest.mark.parametrize("widths,block,blocks_a_unit", [([64, 256, 256, 1], 64, 1), ([64, 130, 17, 1], 64, 1), ([64, 128, 100, 1], 64, 2),
+                                                        ([64, 300, 40, 1], 32, 1), ([32, 16, 512, 1], 64, 1)])
+def test_fp32_last_round_of_smaller_blocks(G, widths, block, blocks_a_unit):
+    """A launch whose last round of blocks would leave most of the chip idle gives that round's candidates to smaller blocks:
+    from no candidate over whole rounds to just past half a round, each has the bits it has in a call of few (checked against
+    the oracle), and every segment, blocks of both sizes in it or not, the least of its scores."""
+    some = 1009
+    f32, _ = _features("c1" if widths[0] == 32 else "c2", some + 1, widths[0])
+    theta = synth.mlp_theta(widths, 6, bias_scale=0.4)
+    model = G.make_model(widths, eck.F32, theta)
+    few = G.score_gpu(model, G.to_dev(f32), some)
+    assert G.within(few, oracle.score(widths, theta, f32, n=some), oracle.score_magnitude(widths, theta, f32, n=some), 1e-5) <= 1.0
+    units = torch.cuda.get_device_properties(0).multi_processor_count * blocks_a_unit
+    left = [0, 1, units // 8 * block, units // 8 * block + 1, units // 4 * block - 17, units // 4 * block + 1, units // 2 * block,
+            units // 2 * block + 1]
+    for n in [2 * units * block + more for more in left]:
+        feat = G.to_dev(np.ascontiguousarray(f32[:, np.arange(n + (n & 1)) % some]))
+        want = few[np.arange(n) % some]
+        assert np.array_equal(G.score_gpu(model, feat, n), want), n
+        segments = max(s for s in range(1, 60) if n % s == 0)
+        out, keys = torch.zeros(n, device="cuda"), torch.zeros(segments, dtype=torch.int32, device="cuda")
+        eck.costmodel_score_min(model, feat, n, out, None, segments, keys)
+        bits = want.reshape(segments, -1).min(axis=1).view(np.uint32)
+        order = np.where(bits >> 31, ~bits, bits | np.uint32(1 << 31))
+        assert np.array_equal(out.cpu().numpy(), want) and np.array_equal(keys.cpu().numpy().view(np.uint32), order), n
+
+
 @pytest.mark.parametrize("widths,n", [((32, 64, 64, 1), 777), ((64, 50, 30, 1), 40001), ((64, 128, 128, 1), 9000), ((64, 256, 256, 1), 5000),
                                       ((64, 300, 17, 1), 9000), ((64, 16, 512, 1), 9000), ((32, 512, 512, 1), 1000), ((64, 9, 1, 1), 200000)])
 def test_fp32_scores_of_numbers_that_are_not_finite(G, widths, n):
