@@ -322,6 +322,23 @@ def _boost_both(G, trees, x, bf16, e, rounds, eta, lam, arrays, have):
     return ref
 
 
+@pytest.mark.parametrize("n_pairs,n_feat,depth,bf16", [(1024, 6, 7, True), (1023, 70, 5, False), (2048, 7, 8, True), (3073, 5, 6, False)])
+def test_boosting_nodes_of_few_and_many_bins(G, n_pairs, n_feat, depth, bf16):
+    """Nodes whose bins lie within one wavefront's 64 (1, 2, 63 and 64 of them, at either end of the range) take one scan,
+    wider ones (65 and all) more; features of every such span in one tree, more than 64 features, sums of equal gain on both
+    sides.  A call appends to the last one's trees, none at all reports what they are worth: the oracle's, bit for bit."""
+    spans = [(0, 1), (100, 2), (192, 64), (7, 65), (0, 256), (190, 63), (64, 64)]
+    rng = np.random.default_rng(n_pairs)
+    x = np.empty((n_feat, n_pairs + (n_pairs & 1) + 2), dtype=np.float32)
+    for f in range(n_feat):
+        first, count = spans[f % len(spans)]
+        x[f] = 0.25 * (first + rng.integers(count, size=x.shape[1]))
+    e = np.exp(np.round(rng.standard_normal(n_pairs), 1)).astype(np.float32)
+    trees, arrays = eck.Trees(n_feat, depth, 3, 0.5), _empty(depth, 3)
+    for have, rounds in ((0, 0), (0, 1), (1, 2), (3, 0)):
+        _boost_both(G, trees, x, bf16, e, rounds, float(np.float32(0.3)), 1.0, arrays, have)
+
+
 @pytest.mark.parametrize("n_pairs,n_feat,depth,rounds,bf16", [(7168, 9, 8, 2, True), (7169, 9, 8, 2, True), (9217, 15, 7, 2, False),
                                                              (12288, 5, 6, 3, False), (12289, 5, 6, 3, True), (14337, 17, 6, 2, False),
                                                              (20480, 33, 6, 2, True), (20481, 33, 6, 2, True), (28673, 48, 5, 2, False),

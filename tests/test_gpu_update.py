@@ -268,6 +268,31 @@ def test_bf16_refit_every_model_shape_and_both_step_paths(G, widths, mb):
     assert np.array_equal(sa, b.get_state().cpu().numpy()) and np.array_equal(sa, c.get_state().cpu().numpy())
 
 
+@pytest.mark.parametrize("widths,mb,ld_extra", [([64, 128, 128, 1], 576, 8), ([32, 64, 64, 1], 1088, 16), ([64, 256, 256, 1], 64, 24)])
+def test_bf16_refit_rows_past_a_threads_32(G, widths, mb, ld_extra):
+    """The output layer's blocks have up to 32 rows of a thread under way: 36, 68 (a remainder after one and two times 32) and 4
+    of them, of features whose rows lie further apart than there are pairs; one step against the oracle at the bf16
+    tolerance, and the output layer's and the biases' first moments, which are plain sums: their terms carry bfloat16's
+    relative error of 2^-8 from h1 and the deltas, 2e-2 with the few activations that flip."""
+    F, P, n = widths[0], synth.param_count(widths), 2 * mb
+    _, b16, _ = _pairs(n + ld_extra)
+    b16 = np.ascontiguousarray(b16[:F, :n + ld_extra])
+    feat_o = oracle.bf16_bits_to_f32(b16)
+    e = synth.measured_energy(feat_o[:, :n], 5)
+    theta = synth.mlp_theta(widths, 6, bf16=True, bias_scale=0.2)
+    st = _oracle_state(theta)
+    model = G.make_model(widths, eck.BF16, theta)
+    snr_g, loss_g = G.update_gpu(model, G.bf16_dev(b16), e, 1, mb)
+    snr_o, loss_o = oracle.update(widths, st, feat_o, e, 1, mb, bf16_weights=True)
+    assert abs(snr_g - snr_o) <= 2e-2 * snr_o and abs(loss_g - loss_o) <= 2e-2 * loss_o
+    got = model.get_state().cpu().numpy().astype(np.float64)
+    H1, H2 = widths[1], widths[2]
+    b1, w2, b2, w3 = F * H1, F * H1 + H1, F * H1 + H1 + H1 * H2, F * H1 + H1 + H1 * H2 + H2
+    for lo, hi in ((b1, w2), (b2, w3), (w3, P)):
+        off = np.linalg.norm(got[P + lo:P + hi] - st[P + lo:P + hi]) / np.linalg.norm(st[P + lo:P + hi])
+        assert off <= 2e-2, (lo, hi, off)
+
+
 @pytest.mark.parametrize("widths,n_pairs,minibatch", [([64, 17, 48, 1], 45, 15), ([32, 33, 5, 1], 34, 17), ([64, 128, 128, 1], 500, 250),
                                                       ([64, 500, 497, 1], 66, 33), ([64, 300, 96, 1], 256, 128)])
 def test_fp32_later_minibatches(G, widths, n_pairs, minibatch):
