@@ -1224,19 +1224,21 @@ __global__ __launch_bounds__(1024) void tree_last_kernel(LevelArgs a, int n_roun
 // Most pairs the one-launch levels take.  Every block of such a level goes over all pairs, however few features there are;
 // the three launches share the pairs between blocks, and their histograms cost less with fewer features.  So the lines lie
 // lower with fewer features, and for deeper trees, whose lower levels spread a histogram's atomics over many nodes.  They
-// are where eight rounds took as long one way as the other, the least over features of some fifty values, of six values and
-// those of sampled convolution schedules.  us per call, one launch per level against three, on schedules' features:
-//   64 features, depth 6: 512 pairs 434 / 774, 16384 916 / 1246, 65536 2404 / 2805 (depth 8: 4519 / 6439)
-//   32 features, depth 6: 8192 pairs 1.36 times as fast, 16384 1.01 times, 32768 0.94 times, 65536 0.77 times
-//   8 features: depth 6, 8192 pairs 1.24 times, 16384 0.92 times; depth 3, 32768 pairs 1.03 times or more
-//   1 feature, depth 8: 8192 pairs 0.96 times, 16384 0.72 times, 65536 0.42 times
+// are where eight rounds took no longer with one launch a level than with three, the least over features of some fifty
+// values, of six values and those of sampled convolution schedules, and no higher than where a workspace for three launches
+// holds what one needs (fewer than 16 features at depths 3 and 4).  Three launches' time over one's, six values / schedules:
+//   48 features: depth 5 36864 pairs 1.19 / 1.30, 49152 1.00 / 1.22; depth 7 65536 1.33 / 1.02
+//   32 features: depth 6 28672 1.07 / 1.08, 36864 1.00 / 1.06, 49152 0.88 / 0.92; depth 8 36864 1.45 / 1.17, 49152 1.35 / 0.96
+//   16 features: depth 4 28672 1.05 / 1.34, 36864 0.98 / 1.33; depth 8 12288 1.35 / 1.13, 20480 1.15 / 0.92
+//   8 features: depth 3 65536 1.08 / 1.54; depth 5 20480 1.11 / 1.18, 28672 0.95 / 1.00; 1 feature, depth 8: 12288 1.28 / 0.89
+// 32 features, depth 6, 28672 pairs, eight rounds: 1164.8 us with three launches a level, 1056.2 with one (six values).
 uint64_t level_max_pairs(const eck_trees *m)
 {
     constexpr uint32_t MOST = 65536;
     // by depth from three on; fewer than 16, 32, 48 and 64 features
-    constexpr uint32_t most[ECK_MAX_TREE_DEPTH - 2][4] = {{32768, 32768, 49152, MOST},  {22528, 22528, 24576, 32768},
-                                                          {16384, 16384, 19456, 28672}, {12288, 14336, 20480, 49152},
-                                                          {9216, 12288, 24576, 49152},  {7168, 11264, 28672, MOST}};
+    constexpr uint32_t most[ECK_MAX_TREE_DEPTH - 2][4] = {{32768, 49152, MOST, MOST},   {22528, 28672, 36864, 36864},
+                                                          {20480, 20480, 28672, 36864}, {12288, 14336, 28672, 49152},
+                                                          {9216, 12288, 36864, 49152},  {7168, 12288, 36864, MOST}};
     if (m->depth < 3 || m->n_feat >= 64) return MOST;
     return most[m->depth - 3][m->n_feat / 16];
 }

@@ -352,6 +352,16 @@ def test_boosting_on_either_side_of_the_one_launch_levels(G, n_pairs, n_feat, de
     _boost_both(G, trees, x, bf16, e, rounds, float(np.float32(0.3)), 0.5, _empty(depth, rounds), 0)
 
 
+@pytest.mark.parametrize("n_pairs,n_feat,depth,bf16", [(20480, 1, 5, True), (20481, 1, 5, True), (28672, 17, 4, False), (28673, 17, 4, True),
+                                                       (36864, 33, 7, True), (36865, 33, 7, False), (36864, 48, 5, False), (12289, 16, 8, True)])
+def test_boosting_at_the_largest_one_launch_levels(G, n_pairs, n_feat, depth, bf16):
+    """The largest numbers of pairs whose levels are one launch each, and one pair more, by features and depth: the oracle's
+    trees, in a workspace of exactly the size asked for."""
+    x, rng = _odd_features(n_feat, n_pairs + (n_pairs & 1) + 2, n_pairs + n_feat)
+    e = np.exp(rng.standard_normal(n_pairs) * (4.0 if n_pairs % 2 else 0.3)).astype(np.float32)
+    _boost_both(G, eck.Trees(n_feat, depth, 2, 0.5), x, bf16, e, 2, float(np.float32(0.3)), 0.5, _empty(depth, 2), 0)
+
+
 def test_three_launch_levels_append_reject_and_report(G):
     """At a size whose levels are three launches: trees appended to those held, an energy that is no number (empty trees,
     predictions unchanged), and no rounds at all (the ensemble's quality, nothing appended)."""
