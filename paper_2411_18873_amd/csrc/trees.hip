@@ -863,6 +863,9 @@ __global__ void tree_finish_kernel(const RefitScalars *sc, float *snr_out, float
 // and finds its best splits.  At level 0 the level before is the last one of the tree before: the pairs get their leaf's
 // value, from the split's left and right sums, and their new derivatives.  So a round of depth d takes d launches.
 // Every sum is an integer sum and every decision the one the three-launch path takes, so the trees are the same bits.
+// What bounds it: the loads right after a launch, the LDS atomics and the scan, one after the other.  A level of 2048 pairs of 64
+// features at depth 6 takes 7.0 us, a root 8.8 (9.8 and 12.4 where the pairs were requested after settling, every scan went over
+// all bins and a split's sums were reduced along with its gain); eight rounds on 1536 pairs 490 and 324.
 
 // The pairs' counts are not needed: h = 2 / y is at least 2 for every valid label, so a side is empty exactly when its
 // sum of h is zero (and with an invalid label nothing splits).
