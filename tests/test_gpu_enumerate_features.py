@@ -476,3 +476,43 @@ def test_dedup_by_parts_and_by_one_table(G, n, kinds, n_genes):
             torch.cuda.synchronize()
             got = flags.cpu().numpy()
             assert np.array_equal(got, want if overwrite else (want & (before != 0)).astype(np.uint8))
+
+
+def genes_hash(genes):
+    """What candidates are sorted by: a SplitMix64 chain over the genes."""
+    gamma, h = np.uint64(0x9E3779B97F4A7C15), np.zeros(genes.shape[1], dtype=np.uint64)
+    for row in genes:
+        z = h + gamma + row.astype(np.uint64)
+        z = (z ^ (z >> np.uint64(30))) * np.uint64(0xBF58476D1CE4E5B9)
+        z = (z ^ (z >> np.uint64(27))) * np.uint64(0x94D049BB133111EB)
+        h = z ^ (z >> np.uint64(31))
+    return h
+
+
+@pytest.mark.parametrize("n,n_genes,distinct", [(20000, 8, 6000), (20000, 8, 8192), (20000, 8, 8193), (40001, 3, 9000), (600001, 3, 20000)])
+def test_dedup_of_genes_chosen_against_the_parts(G, n, n_genes, distinct):
+    """Parts of more tuples than a block's table in LDS has slots (8192), or nearly as many: half of the candidates' tuples hash into
+    one part, a third into another, the rest anywhere."""
+    import torch
+    rng = np.random.default_rng(n + distinct)
+    shift = np.uint64(64 - (8 if n <= 1 << 19 else 9))
+    pools = [[], []]
+    while any(sum(g.shape[1] for g in p) < distinct for p in pools):
+        draw = rng.integers(0, 65536, size=(n_genes, 1 << 19), dtype=np.uint16)
+        part = genes_hash(draw) >> shift
+        for p, which in zip(pools, (3, 200)):
+            p.append(draw[:, part == which])
+    pools = [np.concatenate(p, axis=1)[:, :distinct] for p in pools]
+    one, two = n // 2, n // 3
+    pick = lambda count: np.concatenate([np.arange(min(count, distinct)), rng.integers(0, distinct, size=max(0, count - distinct))])
+    genes = np.concatenate([pools[0][:, pick(one)], pools[1][:, pick(two)],
+                            rng.integers(0, 65536, size=(n_genes, n - one - two), dtype=np.uint16)], axis=1)
+    genes = np.ascontiguousarray(genes[:, rng.permutation(n)])
+    want = np.zeros(n, dtype=np.uint8)
+    want[np.unique(np.ascontiguousarray(genes.T).view("V%d" % (2 * n_genes)).ravel(), return_index=True)[1]] = 1
+    ws = torch.full((eck.candidates_dedup_workspace_bytes(n) + 256,), 255, dtype=torch.uint8, device="cuda")
+    flags = torch.zeros(n, dtype=torch.uint8, device="cuda")
+    eck.candidates_dedup(G.to_dev(genes), n, flags, overwrite=True, ws=ws[:-256])
+    torch.cuda.synchronize()
+    assert np.array_equal(flags.cpu().numpy(), want)
+    assert bool((ws[-256:] == 255).all())
