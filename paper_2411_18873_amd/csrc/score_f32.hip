@@ -9,9 +9,10 @@
 //
 // What bounds it: matrix instructions and the LDS reads of the activations behind them (a part of four candidate tiles is read
 // for twelve matrix instructions), for narrow models the features.  Measured, against fp32 matrix instructions (which reached
-// 121-135 of their 153 TFLOP/s): 64-256-256-1 on 100003 candidates 152 -> 93 us (177 TFLOP/s of fp32 products, 1060 of bfloat16
-// ones), 64-128-128-1 on 2^18 126 -> 87, 64-512-512-1 on 100003 499 -> 425, 32-64-64-1 on 6400 6.9 -> 6.2 and on 2^20 156 -> 130.
-// Models of 16 units or less wait for their features' parts: 100003 candidates 7.8 -> 8.7 us, 64-16-512-1 52.7 -> 59.  Errors
+// 121-135 of their 153 TFLOP/s): 64-256-256-1 on 100003 candidates 152 -> 95 us (172 TFLOP/s of fp32 products, 1030 of bfloat16
+// ones; 99 on cards that sustain a lower clock), 64-128-128-1 on 2^18 125 -> 82, 64-512-512-1 on 100003 500 -> 320 and on 1536
+// 22.6 -> 20.1, 32-64-64-1 on 6400 6.3 -> 4.3 and on 2^20 152 -> 119.  (64-512-512-1 took 423 and 22.5 with 256 units of the first
+// layer in LDS at a time and the second layer's sums of 256 units, for which the first was worked out twice.)  Errors
 // against 64 bits, relative to the scores' norm (before in brackets): 512 units 2.5-3.4e-8 (6.1-6.4e-8), 256 3.1-3.6e-8
 // (6.2-6.6e-8), 128 3.1-4.2e-8 (6.6-8.5e-8), 64 3.9-4.4e-8 (7.4-9.1e-8), 200 and 96 3.6-4.0e-8 (6.8-9.4e-8).
 #include <type_traits>
@@ -27,7 +28,6 @@ namespace {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int RSRC_FLAGS = 0x00020000; // buffer descriptor: raw 32-bit data
-constexpr int CHUNK = 256;             // units of the first hidden layer that LDS holds at a time
 
 struct F32Net {
     const unsigned char *packed; // fragments of both hidden layers
@@ -42,20 +42,20 @@ struct Sums {
     f32x4 large[M][CT], small[M][CT];
 };
 
-// s[j][ct] += W^T x for J tiles from `first_tile` on, over `groups` groups of 32 inputs from `group0` on, and CT tiles of
-// candidates.  layer: byte offset of its fragments; act: granules (16 bytes: eight units of one candidate) of part 0, this
-// wavefront's first candidate; `cands` granules to a row, `part_step` to a part.  AHEAD: the next group's activations are read
-// while this one is multiplied.
+// s[j][ct] += W^T x for J tiles from `first_tile` on, over `groups` groups of 32 inputs, and CT tiles of candidates.  layer:
+// byte offset of its fragments; act: granules (16 bytes: eight units of one candidate) of part 0, this wavefront's first
+// candidate; `cands` granules to a row, `part_step` to a part.  AHEAD: the next group's activations are read while this one is
+// multiplied.
 template <int J, bool AHEAD, int M, int CT>
-__device__ __forceinline__ void product(__amdgpu_buffer_rsrc_t weights, uint32_t layer, int layer_groups, int first_tile, int group0,
-                                        int groups, const u32x4 *act, int cands, int part_step, int lane, Sums<M, CT> &s)
+__device__ __forceinline__ void product(__amdgpu_buffer_rsrc_t weights, uint32_t layer, int groups, int first_tile, const u32x4 *act,
+                                        int cands, int part_step, int lane, Sums<M, CT> &s)
 {
     constexpr int SETS = J * CT <= 4 ? 2 : 1; // weights requested two groups ahead where the registers hold them, else one
     const int last = groups - 1;
     const u32x4 *from = act + (lane >> 4) * cands + (lane & 15);
     bf16x8 a[SETS][J][PARTS], b[AHEAD ? 2 : 1][PARTS][CT];
     auto fetch = [&](int g, int j, bf16x8(&to)[PARTS]) {
-        const uint32_t at = layer + ((uint32_t)(first_tile + j) * layer_groups + group0 + min(g, last)) * (PARTS * 1024u);
+        const uint32_t at = layer + ((uint32_t)(first_tile + j) * groups + min(g, last)) * (PARTS * 1024u);
 #pragma unroll
         for (int i = 0; i < PARTS; ++i)
             to[i] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(weights, 16 * lane, at + 1024u * i, 0));
@@ -122,9 +122,9 @@ __device__ __forceinline__ float score_plain(const F32Net &net, const float *fea
 
 // blockDim = 64 * unit_slots * cand_slots: wavefront (us, cs) works on share us of every layer for the CT candidate
 // tiles of slot cs.  Every sum has an order that depends on the widths alone, so a candidate's score depends neither on
-// n nor on its place.  M, M2: most 16-unit tiles per
-// wavefront of the units of the first and the second layer that are worked on at a time.  ONE: CHUNK units take the first layer.
-template <int CT, int M, int M2, bool ONE, bool WITH_MIN>
+// n nor on its place.  M: most 16-unit tiles per wavefront of the units that are worked on at a time, all of the first
+// layer's.
+template <int CT, int M, bool WITH_MIN>
 __device__ __forceinline__ void score_block(const F32Net &net, const float *__restrict__ feat, uint64_t ld, uint64_t n,
                                             float *__restrict__ out, int unit_slots, int x_rows, int h_rows, int act_bytes,
                                             const MinArgs &mn, uint64_t skip, uint32_t block)
@@ -134,97 +134,111 @@ __device__ __forceinline__ void score_block(const F32Net &net, const float *__re
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), waves = (int)blockDim.x / 64;
     const int us = wave % unit_slots, cs = wave / unit_slots;
     const int cands = waves / unit_slots * (16 * CT);
-    // features [3][x_rows][cands] and activations [3][h_rows][cands], in one place where a single chunk takes the first layer
-    u32x4 *x_l = reinterpret_cast<u32x4 *>(f32_lds), *h_l = ONE ? x_l : x_l + PARTS * x_rows * cands;
     float *sum_l = reinterpret_cast<float *>(f32_lds + act_bytes); // [tiles of the second layer][cands]
     const int out_tiles = tiles_of(net.H2);
     uint32_t *odd_l = reinterpret_cast<uint32_t *>(sum_l + out_tiles * cands); // [cands], then whether there is any
     const uint64_t base = skip + (uint64_t)block * cands;
-    for (int e = tid; e <= cands; e += blockDim.x) odd_l[e] = 0;
-
-    for (int e = tid; e < net.F / 8 * cands; e += blockDim.x) { // 32 or 64 features
-        const int cand = e % cands, eight = e / cands;
-        const uint64_t col = base + cand < n ? base + cand : n - 1;
-        float v[8];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) v[t] = feat[(uint64_t)(8 * eight + t) * ld + col];
-        u32x4 to[PARTS];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            uint32_t part[PARTS];
-            split_two(v[2 * t], v[2 * t + 1], part);
-#pragma unroll
-            for (int i = 0; i < PARTS; ++i) to[i][t] = part[i];
-        }
-#pragma unroll
-        for (int i = 0; i < PARTS; ++i) x_l[(i * x_rows + eight) * cands + cand] = to[i];
-    }
-    __syncthreads();
-    const __amdgpu_buffer_rsrc_t weights = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<unsigned char *>(net.packed), 0, (fragments1(net.F, net.H1) + fragments2(net.H1, net.H2)) * (PARTS * 1024), RSRC_FLAGS);
-    const uint32_t layer2 = fragments1(net.F, net.H1) * (PARTS * 1024u);
-    const int groups1 = groups_of(net.F), groups2 = groups_of(net.H1);
     // this wavefront's share of so many tiles: the first shares are a tile larger when they do not divide
     auto share_of = [&](int tiles, int *first) {
         const int base_tiles = tiles / unit_slots, more = tiles % unit_slots;
         *first = us * base_tiles + min(us, more);
         return base_tiles + (us < more ? 1 : 0);
     };
-    auto run = [&](int tiles, uint32_t layer, int layer_groups, int first_tile, int group0, int groups, const u32x4 *act, int part_step,
-                   auto ahead, auto &to) {
-        constexpr bool AHEAD = decltype(ahead)::value;
-        constexpr int MOST = sizeof(to) / sizeof(Sums<1, CT>);
-        const u32x4 *mine = act + cs * (16 * CT);
-        auto go = [&](auto j) {
-            product<decltype(j)::value, AHEAD>(weights, layer, layer_groups, first_tile, group0, groups, mine, cands, part_step, lane, to);
-        };
-        if constexpr (MOST == 4) {
+    auto for_tiles = [](int tiles, auto go) {
+        if constexpr (M == 4) {
             if (tiles == 4) go(std::integral_constant<int, 4>());
             else if (tiles == 3) go(std::integral_constant<int, 3>());
         }
-        if constexpr (MOST >= 2) {
+        if constexpr (M >= 2) {
             if (tiles == 2) go(std::integral_constant<int, 2>());
         }
         if (tiles == 1) go(std::integral_constant<int, 1>());
     };
-    auto start = [&](const float *b, int H, int first_tile, auto &to) {
+    // the output's weights of the units this lane holds of M tiles of the second layer (requested before the layer's product: a
+    // load behind it was waited for, 0.25 us a call)
+    auto output_weights = [&](int first, float(&w)[M][4]) {
 #pragma unroll
-        for (int j = 0; j < (int)(sizeof(to) / sizeof(Sums<1, CT>)); ++j) {
-            f32x4 v;
+        for (int j = 0; j < M; ++j)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = b[min(16 * (first_tile + j) + 4 * p + q, H - 1)];
+            for (int q = 0; q < 4; ++q) w[j][q] = net.w3[min(16 * (first + j) + 4 * p + q, net.H2 - 1)];
+    };
+    // the output's part of a tile, whichever wavefront worked it out; value(q, ct): the sums of its units 4p + q
+    auto tile_output = [&](int tile, const float(&w)[4], auto value) {
+        float y[CT] = {};
 #pragma unroll
-            for (int ct = 0; ct < CT; ++ct) {
-                to.large[j][ct] = v;
-                to.small[j][ct] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-            }
+        for (int q = 0; q < 4; ++q) {
+            const int unit = 16 * tile + 4 * p + q;
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) y[ct] = unit < net.H2 ? fmaf(fmaxf(value(q, ct), 0.0f), w[q], y[ct]) : y[ct];
+        }
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+            y[ct] += __uint_as_float(lane_exchange(__float_as_uint(y[ct]), 16));
+            y[ct] += __uint_as_float(lane_exchange(__float_as_uint(y[ct]), 32));
+            const int cand = 16 * (cs * CT + ct) + c;
+            if (p == 0) sum_l[tile * cands + cand] = y[ct];
         }
     };
-    // zero times everything a candidate's sums held: a NaN once one of them was not finite
-    float odd[CT] = {};
-    // The second layer as many units at a time as the sums of M2 tiles take, over the first one CHUNK units at a time: where
-    // neither goes in one, the first is worked out again (an eighth more products at 64-512-512, but sums of 512 units in both
-    // layers spill with more than one candidate tile: 708-775 us against 391 on 100003 candidates)
-    const int most2 = unit_slots * (16 * M2);
-    for (int v0 = 0; v0 < net.H2; v0 += most2) {
-        int first2;
-        const int tiles2 = share_of(tiles_of(min(most2, net.H2 - v0)), &first2);
-        first2 += v0 / 16;
-        Sums<M2, CT> sum2;
-        if (!ONE) start(net.b2, net.H2, first2, sum2);
-        for (int u0 = 0; ONE ? u0 == 0 : u0 < net.H1; u0 += CHUNK) {
-            const int in_chunk = ONE ? net.H1 : min(CHUNK, net.H1 - u0);
-            if (!ONE || v0 == 0) {
+    // The second layer as many units at a time as the sums of M tiles take
+    const int most2 = unit_slots * (16 * M);
+    {
+        u32x4 *x_l = reinterpret_cast<u32x4 *>(f32_lds); // features [3][x_rows][cands], then activations [3][h_rows][cands]
+        for (int e = tid; e <= cands; e += blockDim.x) odd_l[e] = 0;
+        for (int e = tid; e < net.F / 8 * cands; e += blockDim.x) { // 32 or 64 features
+            const int cand = e % cands, eight = e / cands;
+            const uint64_t col = base + cand < n ? base + cand : n - 1;
+            float v[8];
+#pragma unroll
+            for (int t = 0; t < 8; ++t) v[t] = feat[(uint64_t)(8 * eight + t) * ld + col];
+            u32x4 to[PARTS];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                uint32_t part[PARTS];
+                split_two(v[2 * t], v[2 * t + 1], part);
+#pragma unroll
+                for (int i = 0; i < PARTS; ++i) to[i][t] = part[i];
+            }
+#pragma unroll
+            for (int i = 0; i < PARTS; ++i) x_l[(i * x_rows + eight) * cands + cand] = to[i];
+        }
+        __syncthreads();
+        {
+            const __amdgpu_buffer_rsrc_t weights = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<unsigned char *>(net.packed), 0, (fragments1(net.F, net.H1) + fragments2(net.H1, net.H2)) * (PARTS * 1024), RSRC_FLAGS);
+            const uint32_t layer2 = fragments1(net.F, net.H1) * (PARTS * 1024u);
+            const int groups1 = groups_of(net.F), groups2 = groups_of(net.H1);
+            auto run = [&](int tiles, uint32_t layer, int groups, int first_tile, int part_step, auto ahead, auto &to) {
+                for_tiles(tiles, [&](auto j) {
+                    product<decltype(j)::value, decltype(ahead)::value>(weights, layer, groups, first_tile, x_l + cs * (16 * CT), cands, part_step,
+                                                                        lane, to);
+                });
+            };
+            auto start = [&](const float *b, int H, int first_tile, auto &to) {
+#pragma unroll
+                for (int j = 0; j < M; ++j) {
+                    f32x4 v;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) v[q] = b[min(16 * (first_tile + j) + 4 * p + q, H - 1)];
+#pragma unroll
+                    for (int ct = 0; ct < CT; ++ct) {
+                        to.large[j][ct] = v;
+                        to.small[j][ct] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                    }
+                }
+            };
+            // zero times everything a candidate's sums held: a NaN once one of them was not finite
+            float odd[CT] = {};
+            {
                 int first1;
-                const int tiles1 = share_of(tiles_of(in_chunk), &first1);
+                const int tiles1 = share_of(tiles_of(net.H1), &first1);
                 Sums<M, CT> sum1;
-                start(net.b1, net.H1, u0 / 16 + first1, sum1);
-                run(tiles1, 0, groups1, u0 / 16 + first1, 0, groups1, x_l, x_rows * cands, std::false_type(), sum1);
-                __syncthreads(); // every wavefront has read what the activations take the place of
+                start(net.b1, net.H1, first1, sum1);
+                run(tiles1, 0, groups1, first1, x_rows * cands, std::false_type(), sum1);
+                __syncthreads(); // every wavefront has read the features: their place takes the activations
 #pragma unroll
                 for (int j = 0; j < M; ++j) {
                     if (j >= tiles1) break;
-                    const int in = 16 * (first1 + j) + 4 * p; // this lane's four units, from the chunk's first on
+                    const int in = 16 * (first1 + j) + 4 * p; // this lane's four units
 #pragma unroll
                     for (int ct = 0; ct < CT; ++ct) {
                         float v[4];
@@ -233,56 +247,52 @@ __device__ __forceinline__ void score_block(const F32Net &net, const float *__re
                             const float sum = sum1.large[j][ct][q] + sum1.small[j][ct][q];
                             odd[ct] = fmaf(sum, 0.0f, odd[ct]);
                             // (a unit past H1 is zero; its weights in the next layer are, too)
-                            v[q] = u0 + in + q < net.H1 ? fmaxf(sum, 0.0f) : 0.0f;
+                            v[q] = in + q < net.H1 ? fmaxf(sum, 0.0f) : 0.0f;
                         }
                         uint32_t lo[PARTS], hi[PARTS];
                         split_two(v[0], v[1], lo);
                         split_two(v[2], v[3], hi);
 #pragma unroll
                         for (int i = 0; i < PARTS; ++i) {
-                            u32x4 *row = h_l + (i * h_rows + in / 8) * cands + 16 * (cs * CT + ct) + c;
+                            u32x4 *row = x_l + (i * h_rows + in / 8) * cands + 16 * (cs * CT + ct) + c;
                             reinterpret_cast<uint2 *>(row)[in / 4 % 2] = make_uint2(lo[i], hi[i]);
                         }
                     }
                 }
                 // inputs of the last group that no tile covers
-                if (tiles_of(in_chunk) % 2) {
+                if (tiles_of(net.H1) % 2) {
                     for (int e = tid; e < 2 * PARTS * cands; e += blockDim.x)
-                        h_l[(e / (2 * cands) * h_rows + 2 * tiles_of(in_chunk) + e / cands % 2) * cands + e % cands] = u32x4{0, 0, 0, 0};
+                        x_l[(e / (2 * cands) * h_rows + 2 * tiles_of(net.H1) + e / cands % 2) * cands + e % cands] = u32x4{0, 0, 0, 0};
                 }
                 __syncthreads();
             }
-            if (ONE) start(net.b2, net.H2, first2, sum2);
-            run(tiles2, layer2, groups2, first2, u0 / 32, groups_of(in_chunk), h_l, h_rows * cands, std::true_type(), sum2);
-        }
-        // a tile's part of the output, whichever wavefront worked it out
+            for (int v0 = 0; v0 < net.H2; v0 += most2) {
+                int first2;
+                const int tiles2 = share_of(tiles_of(min(most2, net.H2 - v0)), &first2);
+                first2 += v0 / 16;
+                Sums<M, CT> sum2;
+                float w3[M][4];
+                start(net.b2, net.H2, first2, sum2);
+                output_weights(first2, w3);
+                run(tiles2, layer2, groups2, first2, h_rows * cands, std::true_type(), sum2);
 #pragma unroll
-        for (int j = 0; j < M2; ++j) {
-            if (j >= tiles2) break;
-            float y[CT] = {};
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int unit = 16 * (first2 + j) + 4 * p + q;
-                const float w = net.w3[min(unit, net.H2 - 1)];
-#pragma unroll
-                for (int ct = 0; ct < CT; ++ct) {
-                    const float sum = sum2.large[j][ct][q] + sum2.small[j][ct][q];
-                    odd[ct] = fmaf(sum, 0.0f, odd[ct]);
-                    y[ct] = unit < net.H2 ? fmaf(fmaxf(sum, 0.0f), w, y[ct]) : y[ct];
+                for (int j = 0; j < M; ++j) {
+                    if (j >= tiles2) break;
+                    tile_output(
+                        first2 + j, w3[j],
+                        [&](int q, int ct) {
+                            const float sum = sum2.large[j][ct][q] + sum2.small[j][ct][q];
+                            odd[ct] = fmaf(sum, 0.0f, odd[ct]);
+                            return sum;
+                        });
                 }
             }
 #pragma unroll
-            for (int ct = 0; ct < CT; ++ct) {
-                y[ct] += __uint_as_float(lane_exchange(__float_as_uint(y[ct]), 16));
-                y[ct] += __uint_as_float(lane_exchange(__float_as_uint(y[ct]), 32));
-                if (p == 0) sum_l[(first2 + j) * cands + 16 * (cs * CT + ct) + c] = y[ct];
-            }
+            for (int ct = 0; ct < CT; ++ct)
+                if (odd[ct] != odd[ct]) odd_l[16 * (cs * CT + ct) + c] = odd_l[cands] = 1;
+            __syncthreads();
         }
     }
-#pragma unroll
-    for (int ct = 0; ct < CT; ++ct)
-        if (odd[ct] != odd[ct]) odd_l[16 * (cs * CT + ct) + c] = odd_l[cands] = 1;
-    __syncthreads();
     if (odd_l[cands]) {
         float *h = reinterpret_cast<float *>(f32_lds) + wave * 512; // (the activations are done with)
         for (int cand = wave; cand < cands; cand += waves) {
@@ -326,15 +336,15 @@ __device__ __forceinline__ void score_block(const F32Net &net, const float *__re
 
 // The first `whole` blocks take CT candidate tiles a slot, `skip` candidates together; the others, in the last round of blocks,
 // LAST_CT.
-template <int CT, int M, int M2, bool ONE, bool WITH_MIN, int LAST_CT = CT>
+template <int CT, int M, bool WITH_MIN, int LAST_CT = CT>
 __global__ __launch_bounds__(512, 2) void score_f32_kernel(F32Net net, const float *__restrict__ feat, uint64_t ld,
                                                            uint64_t n, float *__restrict__ out, int unit_slots, int x_rows,
                                                            int h_rows, int act_bytes, MinArgs mn, uint32_t whole, uint64_t skip)
 {
     if (LAST_CT == CT || blockIdx.x < whole)
-        score_block<CT, M, M2, ONE, WITH_MIN>(net, feat, ld, n, out, unit_slots, x_rows, h_rows, act_bytes, mn, 0, blockIdx.x);
+        score_block<CT, M, WITH_MIN>(net, feat, ld, n, out, unit_slots, x_rows, h_rows, act_bytes, mn, 0, blockIdx.x);
     else
-        score_block<LAST_CT, M, M2, ONE, WITH_MIN>(net, feat, ld, n, out, unit_slots, x_rows, h_rows, act_bytes, mn, skip,
+        score_block<LAST_CT, M, WITH_MIN>(net, feat, ld, n, out, unit_slots, x_rows, h_rows, act_bytes, mn, skip,
                                                    blockIdx.x - whole);
 }
 
@@ -350,12 +360,12 @@ int32_t launch(const eck_model *m, const float *feat, uint64_t ld, uint64_t n, f
     const uint64_t tiles = (n + 15) / 16;
     // Two unit tiles per wavefront and four candidate tiles (64 candidates a block): a weight is read for four, an activation
     // for two.  Fewer candidates where blocks that large would leave compute units without one (64-256-256-1, us with 1 / 2 /
-    // 4 candidate tiles: 1000 9 / 10 / -, 6400 17 / 10.7 / 14, 16000 34 / 21 / 15, 100003 199 / 126 / 95); two at most
-    // where the sums of both layers are held at once (more than CHUNK units in the first).  Narrower models with one unit
+    // 4 candidate tiles: 1000 9 / 10 / -, 6400 17 / 10.7 / 14, 16000 34 / 21 / 15, 100003 199 / 126 / 95); two at most, and
+    // four unit tiles, where the first layer has more than 256 units.  Narrower models with one unit
     // tile per wavefront until the chip is full (64-128-128-1: 6400 6.2 against 6.8, 16000 7.9 and 8.9, 30000 14.6 and 11;
     // 32-64-64-1: 30000 6.4 and 6.9, 60000 11 and 8.8), those of 32 units or less always (64-30-20-1 on 2^20: 116-118
     // against 130).
-    int ct = tiles <= 256 ? 1 : tiles <= 512 || H1 > CHUNK ? 2 : 4, per = 2, unit_slots = 8, cand_slots = 1;
+    int ct = tiles <= 256 ? 1 : tiles <= 512 || H1 > 256 ? 2 : 4, per = H1 > 256 ? 4 : 2, unit_slots = 8, cand_slots = 1;
     if (widest <= 16) {
         per = unit_slots = 1;
         if (ct > 2) ct = 2;
@@ -371,9 +381,9 @@ int32_t launch(const eck_model *m, const float *feat, uint64_t ld, uint64_t n, f
         per = tiles <= 1024 ? 1 : 2;
         unit_slots = 8 / per;
     }
-    const int cands = 16 * ct * cand_slots, x_rows = F / 8, h_rows = 4 * groups_of(H1 < CHUNK ? H1 : CHUNK);
-    const int rows = H1 <= CHUNK ? (x_rows > h_rows ? x_rows : h_rows) : x_rows + h_rows;
+    const int cands = 16 * ct * cand_slots, x_rows = F / 8, h_rows = 4 * groups_of(H1);
     const int threads = 64 * unit_slots * cand_slots;
+    const int rows = x_rows > h_rows ? x_rows : h_rows;
     size_t act_bytes = (size_t)PARTS * rows * cands * 16;
     if (act_bytes < (size_t)threads * 32) act_bytes = (size_t)threads * 32; // (score_plain: 512 floats a wavefront)
     const size_t lds = act_bytes + ((size_t)tiles_of(H2) * cands + cands + 1) * 4;
@@ -386,7 +396,7 @@ int32_t launch(const eck_model *m, const float *feat, uint64_t ld, uint64_t n, f
     const uint64_t blocks = (n + cands - 1) / cands;
     uint64_t whole = blocks, grid = blocks;
     int last_ct = ct;
-    if (unit_slots >= 4 && ct == (H1 > CHUNK ? 2 : 4)) {
+    if (unit_slots >= 4 && ct == (H1 > 256 ? 2 : 4)) {
         int cus = 256;
         (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, m->device);
         const uint64_t round = (uint64_t)cus * (8 / unit_slots), left = blocks % round;
@@ -397,17 +407,17 @@ int32_t launch(const eck_model *m, const float *feat, uint64_t ld, uint64_t n, f
             grid = whole + (n - whole * cands + few - 1) / few;
         }
     }
-    auto kern = H1 > CHUNK ? (last_ct < ct ? score_f32_kernel<2, 2, 2, false, WITH_MIN, 1>
-                              : ct == 2    ? score_f32_kernel<2, 2, 2, false, WITH_MIN>
-                                           : score_f32_kernel<1, 2, 4, false, WITH_MIN>)
-                : per == 2 ? (last_ct < ct ? (last_ct == 1 ? score_f32_kernel<4, 2, 2, true, WITH_MIN, 1>
-                                                           : score_f32_kernel<4, 2, 2, true, WITH_MIN, 2>)
-                              : ct == 4 ? score_f32_kernel<4, 2, 2, true, WITH_MIN>
-                              : ct == 2 ? score_f32_kernel<2, 2, 2, true, WITH_MIN>
-                                        : score_f32_kernel<1, 2, 2, true, WITH_MIN>)
-                           : (ct == 4   ? score_f32_kernel<4, 1, 1, true, WITH_MIN>
-                              : ct == 2 ? score_f32_kernel<2, 1, 1, true, WITH_MIN>
-                                        : score_f32_kernel<1, 1, 1, true, WITH_MIN>);
+    auto kern = per == 4 ? (last_ct < ct ? score_f32_kernel<2, 4, WITH_MIN, 1>
+                              : ct == 2    ? score_f32_kernel<2, 4, WITH_MIN>
+                                           : score_f32_kernel<1, 4, WITH_MIN>)
+                : per == 2 ? (last_ct < ct ? (last_ct == 1 ? score_f32_kernel<4, 2, WITH_MIN, 1>
+                                                           : score_f32_kernel<4, 2, WITH_MIN, 2>)
+                              : ct == 4 ? score_f32_kernel<4, 2, WITH_MIN>
+                              : ct == 2 ? score_f32_kernel<2, 2, WITH_MIN>
+                                        : score_f32_kernel<1, 2, WITH_MIN>)
+                           : (ct == 4   ? score_f32_kernel<4, 1, WITH_MIN>
+                              : ct == 2 ? score_f32_kernel<2, 1, WITH_MIN>
+                                        : score_f32_kernel<1, 1, WITH_MIN>);
     ECK_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(threads), lds, st, net, feat, ld, n, out, unit_slots, x_rows, h_rows,
                        (int)act_bytes, mn, (uint32_t)whole, whole * cands);
