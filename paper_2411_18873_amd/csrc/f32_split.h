@@ -24,7 +24,10 @@ __host__ __device__ inline uint32_t groups_of(int K) { return (uint32_t)(K + 31)
 // fragments (all parts) of the two hidden layers, 64 lanes each
 __host__ __device__ inline uint32_t fragments1(int F, int H1) { return tiles_of(H1) * groups_of(F); }
 __host__ __device__ inline uint32_t fragments2(int H1, int H2) { return tiles_of(H2) * groups_of(H1); }
-inline uint64_t packed_bytes(int F, int H1, int H2) { return (uint64_t)(fragments1(F, H1) + fragments2(H1, H2)) * PARTS * 1024; }
+__host__ __device__ inline uint32_t fragments(int F, int H1, int H2) { return fragments1(F, H1) + fragments2(H1, H2); }
+// behind the fragments a byte for each, not zero where it holds a weight without parts (or its unit's bias is not finite); whole words
+__host__ __device__ inline uint32_t flag_words(int F, int H1, int H2) { return (fragments(F, H1, H2) + 3) / 4; }
+inline uint64_t packed_bytes(int F, int H1, int H2) { return (uint64_t)fragments(F, H1, H2) * PARTS * 1024 + 4 * flag_words(F, H1, H2); }
 
 // the parts of two numbers, two to a word
 __device__ __forceinline__ void split_two(float a, float b, uint32_t (&part)[PARTS])
@@ -38,9 +41,10 @@ __device__ __forceinline__ void split_two(float a, float b, uint32_t (&part)[PAR
     }
 }
 
-// lane `lane` of fragment `frag` of a model's layers: eight weights, split
-__device__ __forceinline__ void pack_lane(const float *__restrict__ w1, const float *__restrict__ w2, int F, int H1, int H2, uint32_t frag,
-                                          uint32_t lane, unsigned char *__restrict__ packed)
+// lane `lane` of fragment `frag` of a model's layers: eight weights, split (all lanes of a wavefront)
+__device__ __forceinline__ void pack_lane(const float *__restrict__ w1, const float *__restrict__ b1, const float *__restrict__ w2,
+                                          const float *__restrict__ b2, int F, int H1, int H2, uint32_t frag, uint32_t lane,
+                                          unsigned char *__restrict__ packed)
 {
     const uint32_t n1 = fragments1(F, H1);
     const bool second = frag >= n1;
@@ -49,6 +53,7 @@ __device__ __forceinline__ void pack_lane(const float *__restrict__ w1, const fl
     const uint32_t f = second ? frag - n1 : frag, groups = groups_of(K), unit = 16 * (f / groups) + (lane & 15);
     const uint32_t k0 = 32 * (f % groups) + 8 * (lane >> 4);
     u32x4 out[PARTS];
+    bool outside = false;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         float two[2];
@@ -56,6 +61,7 @@ __device__ __forceinline__ void pack_lane(const float *__restrict__ w1, const fl
         for (int i = 0; i < 2; ++i) {
             const uint32_t k = k0 + 2 * e + i;
             two[i] = k < (uint32_t)K && unit < (uint32_t)H ? w[(uint64_t)k * H + unit] : 0.0f;
+            outside |= (__float_as_uint(two[i]) & 0x7FFFFFFFu) >= 0x7F7F8000u; // (from there on, infinity in bfloat16)
         }
         uint32_t part[PARTS];
         split_two(two[0], two[1], part);
@@ -64,6 +70,11 @@ __device__ __forceinline__ void pack_lane(const float *__restrict__ w1, const fl
     }
 #pragma unroll
     for (int i = 0; i < PARTS; ++i) reinterpret_cast<u32x4 *>(packed)[((uint64_t)frag * PARTS + i) * 64 + lane] = out[i];
+    if (k0 == 0 && unit < (uint32_t)H) {
+        outside |= (__float_as_uint((second ? b2 : b1)[unit]) & 0x7FFFFFFFu) >= 0x7F800000u;
+    }
+    const uint64_t any = __ballot(outside);
+    if (lane == 0) packed[(uint64_t)fragments(F, H1, H2) * PARTS * 1024 + frag] = any != 0;
 }
 
 } // namespace split

@@ -90,14 +90,14 @@ PackArgs pack_args(const eck_model *m)
     const int F = m->widths[0], H1 = m->widths[1], H2 = m->widths[2], bf16 = m->dtype == ECK_BF16;
     return {bf16, F, H1, H2, m->off_w[0], m->off_b[0], m->off_w[1], m->off_b[1], m->off_w[2], m->off_b[2], (unsigned char *)m->d_packed,
             bf16 ? packed_layout(F, H1, H2) : PackedLayout{},
-            bf16 ? (uint32_t)(F * H1 + H1 + H1 * H2 + 2 * H2 + 1) : 64 * (split::fragments1(F, H1) + split::fragments2(H1, H2))};
+            bf16 ? (uint32_t)(F * H1 + H1 + H1 * H2 + 2 * H2 + 1) : 64 * split::fragments(F, H1, H2)};
 }
 
 // theta (fp32 master) -> element, or lane, e of the packed buffer
 __device__ __forceinline__ void pack_element(const float *__restrict__ theta, const PackArgs &a, uint32_t e)
 {
     if (!a.bf16) {
-        split::pack_lane(theta + a.off_w1, theta + a.off_w2, a.F, a.H1, a.H2, e / 64, e % 64, a.packed);
+        split::pack_lane(theta + a.off_w1, theta + a.off_b1, theta + a.off_w2, theta + a.off_b2, a.F, a.H1, a.H2, e / 64, e % 64, a.packed);
         return;
     }
     const int F = a.F, H1 = a.H1, H2 = a.H2;

@@ -6,6 +6,8 @@
 // fp32 matrix rate, for six times the products.  A block's wavefronts share a layer's 16-unit tiles as evenly as they go and
 // read the same activations from LDS, which holds their parts as [part][unit / 8][candidate][unit % 8].  The weights' parts
 // are made when the state changes and stream from the L2, one load at a time between matrix instructions.
+// Models with weights that have no such parts, not finite ones above all, and candidates with such features are worked out in
+// fp32 products instead.
 //
 // What bounds it: matrix instructions and the LDS reads of the activations behind them (a part of four candidate tiles is read
 // for twelve matrix instructions), for narrow models the features.  Measured, against fp32 matrix instructions (which reached
@@ -18,6 +20,7 @@
 #include <type_traits>
 
 #include "f32_split.h"
+#include "f32_tiles.h"
 #include "lanes.h"
 
 using namespace eck;
@@ -25,12 +28,13 @@ using namespace eck::split;
 
 namespace {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-constexpr int RSRC_FLAGS = 0x00020000; // buffer descriptor: raw 32-bit data
+using f32::f32x4;
+using f32::RSRC_FLAGS;
 
 struct F32Net {
-    const unsigned char *packed; // fragments of both hidden layers
+    const unsigned char *packed; // fragments of both hidden layers ...
+    const uint32_t *flags;       // ... and in so many words (at most 144) whether they hold weights outside the parts' range
+    int words;
     const float *w1, *b1, *w2, *b2, *w3, *b3;
     int F, H1, H2;
 };
@@ -100,24 +104,83 @@ __device__ __forceinline__ void product(__amdgpu_buffer_rsrc_t weights, uint32_t
     if (g < groups) group(g, std::integral_constant<int, 0>());
 }
 
-// A candidate whose numbers are not all finite, or do not stay so: plain fp32 sums, by one wavefront.  h: [H1] floats of LDS.
-__device__ __forceinline__ float score_plain(const F32Net &net, const float *feat, uint64_t ld, uint64_t cand, float *h, int lane)
+// acc[j][ct] = b + W^T x in fp32 products, for J tiles of sixteen units from `first_tile` on and CT tiles of candidates.  act: the
+// activations of units 0-3 of this wavefront's first candidate, `cands` candidates to a row.  The weights come from the
+// parameters, requested two groups of sixteen inputs ahead, one load between matrix instructions.  (Rows of several
+// tiles interleaved would take one wide load for J, but give sums of an order that depends on J.)
+template <int J, int CT, int M>
+__device__ __forceinline__ void plain_product(const f32::F32Layer &l, int first_tile, const f32x4 *act, int cands, int p, int c,
+                                              f32x4 (&acc)[M][CT])
 {
-    for (int u = lane; u < net.H1; u += 64) {
-        float s = net.b1[u];
-        for (int k = 0; k < net.F; ++k) s = fmaf(feat[(uint64_t)k * ld + cand], net.w1[(int64_t)k * net.H1 + u], s);
-        h[u] = fmaxf(s, 0.0f);
-    }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // the wavefront reads back what its own lanes wrote
-    float y = 0.0f;
-    for (int u = lane; u < net.H2; u += 64) {
-        float s = net.b2[u];
-        for (int k = 0; k < net.H1; ++k) s = fmaf(h[k], net.w2[(int64_t)k * net.H2 + u], s);
-        y = fmaf(fmaxf(s, 0.0f), net.w3[u], y);
+    const int whole = l.K / 16, last = whole - 1;
+    auto slice = [&](int j) { return f32::Slice<1>(l, 16 * (first_tile + j), p, c); };
+    float even[4][J], odd[4][J]; // weights of an even and an odd group; past the end the last whole group again
+    auto fetch = [&](int g, int t, float(&a)[J]) {
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            float one[1];
+            slice(j).row(g, t, one);
+            a[j] = one[0];
+        }
+    };
+    if (whole) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) fetch(0, t, even[t]);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) fetch(min(1, last), t, odd[t]);
     }
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) y += __shfl_xor(y, off);
-    return net.b3[0] + y;
+    for (int j = 0; j < J; ++j) {
+        f32x4 bias;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) bias[q] = l.b[min(16 * (first_tile + j) + 4 * p + q, l.H - 1)];
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) acc[j][ct] = bias;
+    }
+    const f32x4 *from = act + p * cands + c;
+    f32x4 be[CT], bo[CT]; // activations of an even and an odd group
+    auto read = [&](int g, f32x4(&b)[CT]) {
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) b[ct] = from[4 * g * cands + 16 * ct];
+    };
+    auto step = [&](int t, const float(&a)[J], const f32x4(&b)[CT]) {
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) acc[j][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[ct][t], acc[j][ct], 0, 0, 0);
+    };
+    auto group = [&](int g, float(&a)[4][J], const f32x4(&b)[CT], f32x4(&next)[CT]) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            step(t, a[t], b);
+            __builtin_amdgcn_sched_barrier(0);
+            fetch(min(g + 2, last), t, a[t]);
+            if (t == 0) read(min(g + 1, last), next);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    int g = 0;
+    read(0, be);
+    for (; g + 2 <= whole; g += 2) {
+        group(g, even, be, bo);
+        group(g + 1, odd, bo, be);
+    }
+    if (g < whole) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) step(t, even[t], be);
+    }
+    if (l.K % 16) {
+        read(whole, be);
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            float tail[4][1];
+            slice(j).partial_group(whole, tail);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) even[t][j] = tail[t][0];
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) step(t, even[t], be);
+    }
 }
 
 // blockDim = 64 * unit_slots * cand_slots: wavefront (us, cs) works on share us of every layer for the CT candidate
@@ -163,7 +226,7 @@ __device__ __forceinline__ void score_block(const F32Net &net, const float *__re
             for (int q = 0; q < 4; ++q) w[j][q] = net.w3[min(16 * (first + j) + 4 * p + q, net.H2 - 1)];
     };
     // the output's part of a tile, whichever wavefront worked it out; value(q, ct): the sums of its units 4p + q
-    auto tile_output = [&](int tile, const float(&w)[4], auto value) {
+    auto tile_output = [&](int tile, const float(&w)[4], auto value, auto takes) {
         float y[CT] = {};
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -176,14 +239,18 @@ __device__ __forceinline__ void score_block(const F32Net &net, const float *__re
             y[ct] += __uint_as_float(lane_exchange(__float_as_uint(y[ct]), 16));
             y[ct] += __uint_as_float(lane_exchange(__float_as_uint(y[ct]), 32));
             const int cand = 16 * (cs * CT + ct) + c;
-            if (p == 0) sum_l[tile * cands + cand] = y[ct];
+            if (p == 0 && takes(cand)) sum_l[tile * cands + cand] = y[ct];
         }
     };
     // The second layer as many units at a time as the sums of M tiles take
     const int most2 = unit_slots * (16 * M);
+    bool outside; // the model's weights do not all have parts
     {
         u32x4 *x_l = reinterpret_cast<u32x4 *>(f32_lds); // features [3][x_rows][cands], then activations [3][h_rows][cands]
         for (int e = tid; e <= cands; e += blockDim.x) odd_l[e] = 0;
+        uint32_t flagged = net.flags[min(lane, net.words - 1)]; // (looked at behind the features, which are waited for in any case)
+        if (net.words > 64) flagged |= net.flags[min(lane + 64, net.words - 1)] | net.flags[min(lane + 128, net.words - 1)];
+
         for (int e = tid; e < net.F / 8 * cands; e += blockDim.x) { // 32 or 64 features
             const int cand = e % cands, eight = e / cands;
             const uint64_t col = base + cand < n ? base + cand : n - 1;
@@ -201,10 +268,11 @@ __device__ __forceinline__ void score_block(const F32Net &net, const float *__re
 #pragma unroll
             for (int i = 0; i < PARTS; ++i) x_l[(i * x_rows + eight) * cands + cand] = to[i];
         }
+        outside = __ballot(flagged != 0) != 0;
         __syncthreads();
-        {
+        if (!outside) {
             const __amdgpu_buffer_rsrc_t weights = __builtin_amdgcn_make_buffer_rsrc(
-                const_cast<unsigned char *>(net.packed), 0, (fragments1(net.F, net.H1) + fragments2(net.H1, net.H2)) * (PARTS * 1024), RSRC_FLAGS);
+                const_cast<unsigned char *>(net.packed), 0, fragments(net.F, net.H1, net.H2) * (PARTS * 1024), RSRC_FLAGS);
             const uint32_t layer2 = fragments1(net.F, net.H1) * (PARTS * 1024u);
             const int groups1 = groups_of(net.F), groups2 = groups_of(net.H1);
             auto run = [&](int tiles, uint32_t layer, int groups, int first_tile, int part_step, auto ahead, auto &to) {
@@ -284,7 +352,8 @@ __device__ __forceinline__ void score_block(const F32Net &net, const float *__re
                             const float sum = sum2.large[j][ct][q] + sum2.small[j][ct][q];
                             odd[ct] = fmaf(sum, 0.0f, odd[ct]);
                             return sum;
-                        });
+                        },
+                        [](int) { return true; });
                 }
             }
 #pragma unroll
@@ -293,12 +362,52 @@ __device__ __forceinline__ void score_block(const F32Net &net, const float *__re
             __syncthreads();
         }
     }
-    if (odd_l[cands]) {
-        float *h = reinterpret_cast<float *>(f32_lds) + wave * 512; // (the activations are done with)
-        for (int cand = wave; cand < cands; cand += waves) {
-            if (!odd_l[cand] || base + cand >= n) continue;
-            const float total = score_plain(net, feat, ld, base + cand, h, lane);
-            if (lane == 0) sum_l[cand] = total;
+    // The same in fp32 products: for the block, if the model needs them, else for its candidates whose numbers do
+    if (outside || odd_l[cands]) {
+        f32x4 *act = reinterpret_cast<f32x4 *>(f32_lds); // [unit / 4][cands][unit % 4], features and then activations
+        const f32x4 *mine = act + cs * (16 * CT);
+        for (int e = tid; e < net.F / 4 * cands; e += blockDim.x) {
+            const int cand = e % cands, four = e / cands;
+            const uint64_t col = base + cand < n ? base + cand : n - 1;
+            f32x4 v;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) v[t] = feat[(uint64_t)(4 * four + t) * ld + col];
+            act[e] = v;
+        }
+        __syncthreads();
+        auto run = [&](int tiles, const f32::F32Layer &l, int first_tile, f32x4(&acc)[M][CT]) {
+            for_tiles(tiles, [&](auto j) { plain_product<decltype(j)::value>(l, first_tile, mine, cands, p, c, acc); });
+        };
+        f32x4 acc[M][CT];
+        int first1;
+        const int tiles1 = share_of(tiles_of(net.H1), &first1);
+        run(tiles1, {net.w1, net.b1, net.F, net.H1}, first1, acc);
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < M; ++j) {
+            if (j >= tiles1) break;
+            const int in = 16 * (first1 + j) + 4 * p;
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) {
+                f32x4 v;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) v[q] = in + q < net.H1 ? fmaxf(acc[j][ct][q], 0.0f) : 0.0f;
+                act[in / 4 * cands + 16 * (cs * CT + ct) + c] = v;
+            }
+        }
+        __syncthreads();
+        for (int v0 = 0; v0 < net.H2; v0 += most2) {
+            int first2;
+            const int tiles2 = share_of(tiles_of(min(most2, net.H2 - v0)), &first2);
+            first2 += v0 / 16;
+            float w3[M][4];
+            output_weights(first2, w3);
+            run(tiles2, {net.w2, net.b2, net.H1, net.H2}, first2, acc);
+#pragma unroll
+            for (int j = 0; j < M; ++j) {
+                if (j >= tiles2) break;
+                tile_output(first2 + j, w3[j], [&](int q, int ct) { return acc[j][ct][q]; }, [&](int cand) { return outside || odd_l[cand]; });
+            }
         }
         __syncthreads();
     }
@@ -309,7 +418,7 @@ __device__ __forceinline__ void score_block(const F32Net &net, const float *__re
     // (up to 32 parts one after the other in fp32 are the largest error of a score)
     double parts = net.b3[0];
     for (int t = 0; t < out_tiles; ++t) parts += sum_l[t * cands + at];
-    const float total = odd_l[at] ? sum_l[at] : (float)parts;
+    const float total = (float)parts;
     if (mine) out[cand] = total;
     if (WITH_MIN) {
         uint32_t key = 0xFFFFFFFFu;
@@ -354,7 +463,9 @@ int32_t launch(const eck_model *m, const float *feat, uint64_t ld, uint64_t n, f
     const int F = m->widths[0], H1 = m->widths[1], H2 = m->widths[2];
     if ((n + 15) / 16 > 0x7FFFFFFFull) return ECK_EUNSUPPORTED;
     const float *s = m->d_state;
-    const F32Net net{(const unsigned char *)m->d_packed, s + m->off_w[0], s + m->off_b[0], s + m->off_w[1], s + m->off_b[1],
+    const unsigned char *packed = (const unsigned char *)m->d_packed;
+    const F32Net net{packed, reinterpret_cast<const uint32_t *>(packed + (uint64_t)fragments(F, H1, H2) * (PARTS * 1024)),
+                     (int)flag_words(F, H1, H2), s + m->off_w[0], s + m->off_b[0], s + m->off_w[1], s + m->off_b[1],
                      s + m->off_w[2], s + m->off_b[2], F, H1, H2};
     const int widest = H1 > H2 ? H1 : H2;
     const uint64_t tiles = (n + 15) / 16;
@@ -383,9 +494,8 @@ int32_t launch(const eck_model *m, const float *feat, uint64_t ld, uint64_t n, f
     }
     const int cands = 16 * ct * cand_slots, x_rows = F / 8, h_rows = 4 * groups_of(H1);
     const int threads = 64 * unit_slots * cand_slots;
-    const int rows = x_rows > h_rows ? x_rows : h_rows;
-    size_t act_bytes = (size_t)PARTS * rows * cands * 16;
-    if (act_bytes < (size_t)threads * 32) act_bytes = (size_t)threads * 32; // (score_plain: 512 floats a wavefront)
+    const int part_rows = PARTS * (x_rows > h_rows ? x_rows : h_rows), plain_rows = (F > H1 ? F : H1 + 15) / 16 * 4;
+    const size_t act_bytes = (size_t)(part_rows > plain_rows ? part_rows : plain_rows) * cands * 16;
     const size_t lds = act_bytes + ((size_t)tiles_of(H2) * cands + cands + 1) * 4;
     // Eight wavefronts of blocks of 64 candidates fill a compute unit (their registers), so a launch takes whole rounds of
     // them; what a last round short of blocks would do goes over the whole chip in blocks of 16 or 32 candidates.  Rounds

@@ -326,3 +326,49 @@ def test_fp32_scores_of_numbers_that_are_not_finite(G, widths, n):
         want = (np.fmax(terms.sum(0) + b2[:, None], 0) * w3).sum(0) + b3[0] if H1 * H2 * few < 3e7 else None
     if want is not None:
         assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isinf(got), np.isinf(want))
+
+
+@pytest.mark.parametrize("widths,n", [((64, 512, 512, 1), 1 << 14), ((64, 256, 256, 1), 1 << 15), ((32, 64, 64, 1), 1 << 17)])
+@pytest.mark.parametrize("where", ["first", "second", "bias", "all"])
+def test_fp32_models_that_are_not_finite_take_no_path_of_their_own_per_candidate(G, widths, n, where):
+    """A refit that diverged leaves NaNs and infinities in the weights, so that every candidate's sums hold some: they are worked
+    out in fp32 matrix instructions, at a sixth of the rate or more, not candidate by candidate (a hundredth and less)."""
+    F, H1, H2, _ = widths
+    rng = np.random.default_rng(H1)
+    theta = synth.mlp_theta(list(widths), 6, bias_scale=0.4)
+    bad = theta.copy()
+    first, second = F * H1, F * H1 + H1 + H1 * H2
+    if where == "first":
+        bad[rng.integers(first)] = np.nan
+    elif where == "second":
+        bad[first + H1 + rng.integers(H1 * H2)] = np.inf
+    elif where == "bias":
+        bad[first + rng.integers(H1)] = -np.inf
+    else:
+        bad[:] = np.nan
+    x = (rng.random((F, n)) * 8).astype(np.float32)
+    feat, out = G.to_dev(x), torch.zeros(n, device="cuda")
+    took = []
+    for th in (theta, bad):
+        model = G.make_model(list(widths), eck.F32, th)
+        start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        eck.costmodel_score(model, feat, n, out)
+        start.record()
+        for _ in range(8):
+            eck.costmodel_score(model, feat, n, out)
+        end.record()
+        torch.cuda.synchronize()
+        took.append(start.elapsed_time(end))
+    assert took[1] < 6 * took[0], took
+    some = 64
+    with np.errstate(all="ignore"):
+        w1, b1 = bad[:first].reshape(F, H1).astype(np.float64), bad[first:first + H1]
+        w2, b2 = bad[first + H1:second].reshape(H1, H2).astype(np.float64), bad[second:second + H2]
+        w3, b3 = bad[second + H2:-1].astype(np.float64), bad[-1]
+        h1 = np.fmax((x[:, :some, None] * w1[:, None, :]).sum(0) + b1, 0)
+        want = np.stack([np.fmax((h[:, None] * w2).sum(0) + b2, 0) @ w3 + b3 for h in h1])
+        size = np.stack([np.fmax((h[:, None] * w2).sum(0) + b2, 0) @ np.abs(w3) + abs(b3) for h in h1])
+    got = out[:some].cpu().numpy()
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isinf(got), np.isinf(want))
+    fine = np.isfinite(want)
+    assert np.all(np.abs(got[fine] - want[fine]) <= 1e-5 * size[fine])
