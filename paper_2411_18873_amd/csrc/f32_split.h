@@ -1,8 +1,14 @@
 // fp32 numbers as sums of three bfloat16 ones (HIP, gfx950), for products of fp32 matrices on the bfloat16 matrix cores.
 //
-// Rounded to nearest, x = x0 + x1 + x2 exactly, with |x1| <= 2^-9 |x| and |x2| <= 2^-18 |x|.  Of the nine products of two such
-// sums the six largest are kept; the others are below 2^-25 of the product together, less than the rounding of an fp32 product.
-// A number that is not finite, or rounds to infinity, has a NaN among its parts.
+// Rounded to nearest, x = x0 + x1 + x2 exactly, with |x1| <= 2^-9 |x| and |x2| <= 2^-18 |x|, for |x| >= 2^-110 and zero: below
+// that the last part falls under the least bfloat16, and what is lost grows from 2^-22 of the number at 2^-112 to 2^-10 at 2^-124.
+// Of the nine products of two such sums the six largest are kept; the others are below 2^-25 of the product together, less than
+// the rounding of an fp32 product.  A number that is not finite, or rounds to infinity, has a NaN among its parts.
+//
+// What keeps a layer's sums as good as fp32 ones: no input below 2^-40 and no weight below 2^-50 but zeros.  Then no product
+// is below 2^-90, so the rounding of a sum of them (2^-114) hides what the parts of a small output lose (2^-134), and an output
+// that is a bias alone has its parts if the bias is not below 2^-100.  Models with other weights, and candidates with other
+// features, are worked out in fp32 products.
 //
 // Weights of a layer ([K][H], row-major) as operands of v_mfma_f32_16x16x32_bf16, rows = units (lane = 16 p + c holds A[c][8p ..
 // 8p + 7], B[8p .. 8p + 7][c], D[4p + q][c] in register q): fragments [unit tile][group of 32 inputs][part][lane][8], zeros past K
@@ -25,9 +31,14 @@ __host__ __device__ inline uint32_t groups_of(int K) { return (uint32_t)(K + 31)
 __host__ __device__ inline uint32_t fragments1(int F, int H1) { return tiles_of(H1) * groups_of(F); }
 __host__ __device__ inline uint32_t fragments2(int H1, int H2) { return tiles_of(H2) * groups_of(H1); }
 __host__ __device__ inline uint32_t fragments(int F, int H1, int H2) { return fragments1(F, H1) + fragments2(H1, H2); }
-// behind the fragments a byte for each, not zero where it holds a weight without parts (or its unit's bias is not finite); whole words
+// behind the fragments a byte for each, not zero where it holds a weight outside the range (or its unit's bias is); whole words
 __host__ __device__ inline uint32_t flag_words(int F, int H1, int H2) { return (fragments(F, H1, H2) + 3) / 4; }
 inline uint64_t packed_bytes(int F, int H1, int H2) { return (uint64_t)fragments(F, H1, H2) * PARTS * 1024 + 4 * flag_words(F, H1, H2); }
+
+constexpr uint32_t LEAST_INPUT = 0x2B800000, LEAST_WEIGHT = 0x26800000, LEAST_BIAS = 0x0D800000; // 2^-40, 2^-50, 2^-100
+// the order of magnitudes as numbers, zero last; x lies below `least` (a float's bits) and is no zero if this is below
+// magnitude_order(least)
+__host__ __device__ inline uint32_t magnitude_order(uint32_t bits) { return (bits << 1) - 1; }
 
 // the parts of two numbers, two to a word
 __device__ __forceinline__ void split_two(float a, float b, uint32_t (&part)[PARTS])
@@ -61,7 +72,9 @@ __device__ __forceinline__ void pack_lane(const float *__restrict__ w1, const fl
         for (int i = 0; i < 2; ++i) {
             const uint32_t k = k0 + 2 * e + i;
             two[i] = k < (uint32_t)K && unit < (uint32_t)H ? w[(uint64_t)k * H + unit] : 0.0f;
-            outside |= (__float_as_uint(two[i]) & 0x7FFFFFFFu) >= 0x7F7F8000u; // (from there on, infinity in bfloat16)
+            const uint32_t order = magnitude_order(__float_as_uint(two[i]));
+            // (from the second bound on, infinity in bfloat16)
+            outside |= order < magnitude_order(LEAST_WEIGHT) || (order >= magnitude_order(0x7F7F8000) && order != 0xFFFFFFFFu);
         }
         uint32_t part[PARTS];
         split_two(two[0], two[1], part);
@@ -71,7 +84,8 @@ __device__ __forceinline__ void pack_lane(const float *__restrict__ w1, const fl
 #pragma unroll
     for (int i = 0; i < PARTS; ++i) reinterpret_cast<u32x4 *>(packed)[((uint64_t)frag * PARTS + i) * 64 + lane] = out[i];
     if (k0 == 0 && unit < (uint32_t)H) {
-        outside |= (__float_as_uint((second ? b2 : b1)[unit]) & 0x7FFFFFFFu) >= 0x7F800000u;
+        const uint32_t order = magnitude_order(__float_as_uint((second ? b2 : b1)[unit]));
+        outside |= (!second && order < magnitude_order(LEAST_BIAS)) || (order >= magnitude_order(0x7F800000) && order != 0xFFFFFFFFu);
     }
     const uint64_t any = __ballot(outside);
     if (lane == 0) packed[(uint64_t)fragments(F, H1, H2) * PARTS * 1024 + frag] = any != 0;

@@ -6,8 +6,8 @@
 // fp32 matrix rate, for six times the products.  A block's wavefronts share a layer's 16-unit tiles as evenly as they go and
 // read the same activations from LDS, which holds their parts as [part][unit / 8][candidate][unit % 8].  The weights' parts
 // are made when the state changes and stream from the L2, one load at a time between matrix instructions.
-// Models with weights that have no such parts, not finite ones above all, and candidates with such features are worked out in
-// fp32 products instead.
+// Models with weights that have no such parts and candidates with features that have none are worked out in fp32 products
+// instead.
 //
 // What bounds it: matrix instructions and the LDS reads of the activations behind them (a part of four candidate tiles is read
 // for twelve matrix instructions), for narrow models the features.  Measured, against fp32 matrix instructions (which reached
@@ -257,6 +257,9 @@ __device__ __forceinline__ void score_block(const F32Net &net, const float *__re
             float v[8];
 #pragma unroll
             for (int t = 0; t < 8; ++t) v[t] = feat[(uint64_t)(8 * eight + t) * ld + col];
+            uint32_t least = 0xFFFFFFFFu;
+#pragma unroll
+            for (int t = 0; t < 8; ++t) least = min(least, magnitude_order(__float_as_uint(v[t])));
             u32x4 to[PARTS];
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
@@ -265,6 +268,7 @@ __device__ __forceinline__ void score_block(const F32Net &net, const float *__re
 #pragma unroll
                 for (int i = 0; i < PARTS; ++i) to[i][t] = part[i];
             }
+            if (least < magnitude_order(LEAST_INPUT)) to[2][0] = 0x7FC07FC0u; // (its sums become NaNs, as with infinities)
 #pragma unroll
             for (int i = 0; i < PARTS; ++i) x_l[(i * x_rows + eight) * cands + cand] = to[i];
         }

@@ -372,3 +372,34 @@ def test_fp32_models_that_are_not_finite_take_no_path_of_their_own_per_candidate
     assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isinf(got), np.isinf(want))
     fine = np.isfinite(want)
     assert np.all(np.abs(got[fine] - want[fine]) <= 1e-5 * size[fine])
+
+
+@pytest.mark.parametrize("widths", [(64, 256, 256, 1), (32, 64, 64, 1), (64, 300, 40, 1), (64, 20, 100, 1)])
+@pytest.mark.parametrize("inputs,first,bias,second", [(-122, 100, None, 0), (-124, 90, None, 30), (8, -124, None, 120), (8, 40, None, -122),
+                                                      (None, 0, -124, 110), (-62, -62, None, 110), (-39, -49, -99, 90)])
+def test_fp32_scores_of_small_numbers(G, widths, inputs, first, bias, second):
+    """Numbers below 2^-110 are no sums of three bfloat16 ones.  Features, weights, biases and, from products of small ones,
+    activations of such sizes (powers of two; None: zeros), scaled up again behind, are as close as ordinary ones; candidates with
+    ordinary features beside small ones keep the bits they have alone."""
+    F, H1, H2, _ = widths
+    n = 777
+    number = np.float32(1 + 0.45 / 512) # (at 2^-124 the parts miss 9e-4 of it, at 2^-122 1e-4)
+    sized = lambda shape, power: np.full(shape, 0 if power is None else number * 2.0 ** power, dtype=np.float32)
+    x, w1, b1, w2, w3 = sized((F, n), inputs), sized((F, H1), first), sized(H1, bias), sized((H1, H2), second), sized((H2, 1), 0)
+    x[2:] = 0
+    theta = np.concatenate([t.ravel() for t in (w1, b1, w2, np.zeros(H2, np.float32), w3, np.zeros(1, np.float32))])
+    model = G.make_model(list(widths), eck.F32, theta)
+    got = G.score_gpu(model, G.to_dev(np.ascontiguousarray(np.pad(x, ((0, 0), (0, 1))))), n)
+    d = np.float64
+    want = (w3.T.astype(d) @ (w2.T.astype(d) @ (w1.T.astype(d) @ x.astype(d) + b1[:, None].astype(d))))[0]
+    # sums of positive terms: a rounding for each addition and each product
+    assert np.all(np.abs(got - want) <= (F + H1 + H2 + 4) * 2.0 ** -24 * want), float(np.max(np.abs(got / want - 1)))
+    if inputs is not None:
+        plain = np.random.default_rng(H1).random((F, n + 1)).astype(np.float32)
+        alone = G.score_gpu(model, G.to_dev(plain), n)
+        mixed = plain.copy()
+        mixed[:, 5::7] = np.pad(x, ((0, 0), (0, 1)))[:, 5::7]
+        both = G.score_gpu(model, G.to_dev(mixed), n)
+        ordinary = np.ones(n, dtype=bool)
+        ordinary[5::7] = False
+        assert np.array_equal(both[ordinary], alone[ordinary]) and np.array_equal(both[5::7], got[5::7])
