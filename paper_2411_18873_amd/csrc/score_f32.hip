@@ -6,8 +6,8 @@
 // fp32 matrix rate, for six times the products.  A block's wavefronts share a layer's 16-unit tiles as evenly as they go and
 // read the same activations from LDS, which holds their parts as [part][unit / 8][candidate][unit % 8].  The weights' parts
 // are made when the state changes and stream from the L2, one load at a time between matrix instructions.
-// Models with weights that have no such parts and candidates with features that have none are worked out in fp32 products
-// instead.
+// Models with weights that have no such parts, candidates with features that have none, and models whose first layer has no
+// more than sixteen units are worked out in fp32 products instead.
 //
 // What bounds it: matrix instructions and the LDS reads of the activations behind them (a part of four candidate tiles is read
 // for twelve matrix instructions), for narrow models the features.  Measured, against fp32 matrix instructions (which reached
@@ -186,8 +186,8 @@ __device__ __forceinline__ void plain_product(const f32::F32Layer &l, int first_
 // blockDim = 64 * unit_slots * cand_slots: wavefront (us, cs) works on share us of every layer for the CT candidate
 // tiles of slot cs.  Every sum has an order that depends on the widths alone, so a candidate's score depends neither on
 // n nor on its place.  M: most 16-unit tiles per wavefront of the units that are worked on at a time, all of the first
-// layer's.
-template <int CT, int M, bool WITH_MIN>
+// layer's.  BY_PARTS: products of parts, and fp32 ones where a model or a candidate needs them; else fp32 ones alone.
+template <int CT, int M, bool BY_PARTS, bool WITH_MIN>
 __device__ __forceinline__ void score_block(const F32Net &net, const float *__restrict__ feat, uint64_t ld, uint64_t n,
                                             float *__restrict__ out, int unit_slots, int x_rows, int h_rows, int act_bytes,
                                             const MinArgs &mn, uint64_t skip, uint32_t block)
@@ -244,8 +244,8 @@ __device__ __forceinline__ void score_block(const F32Net &net, const float *__re
     };
     // The second layer as many units at a time as the sums of M tiles take
     const int most2 = unit_slots * (16 * M);
-    bool outside; // the model's weights do not all have parts
-    {
+    bool outside = !BY_PARTS; // the model's weights do not all have parts
+    if constexpr (BY_PARTS) {
         u32x4 *x_l = reinterpret_cast<u32x4 *>(f32_lds); // features [3][x_rows][cands], then activations [3][h_rows][cands]
         for (int e = tid; e <= cands; e += blockDim.x) odd_l[e] = 0;
         uint32_t flagged = net.flags[min(lane, net.words - 1)]; // (looked at behind the features, which are waited for in any case)
@@ -449,15 +449,15 @@ __device__ __forceinline__ void score_block(const F32Net &net, const float *__re
 
 // The first `whole` blocks take CT candidate tiles a slot, `skip` candidates together; the others, in the last round of blocks,
 // LAST_CT.
-template <int CT, int M, bool WITH_MIN, int LAST_CT = CT>
+template <int CT, int M, bool BY_PARTS, bool WITH_MIN, int LAST_CT = CT>
 __global__ __launch_bounds__(512, 2) void score_f32_kernel(F32Net net, const float *__restrict__ feat, uint64_t ld,
                                                            uint64_t n, float *__restrict__ out, int unit_slots, int x_rows,
                                                            int h_rows, int act_bytes, MinArgs mn, uint32_t whole, uint64_t skip)
 {
     if (LAST_CT == CT || blockIdx.x < whole)
-        score_block<CT, M, WITH_MIN>(net, feat, ld, n, out, unit_slots, x_rows, h_rows, act_bytes, mn, 0, blockIdx.x);
+        score_block<CT, M, BY_PARTS, WITH_MIN>(net, feat, ld, n, out, unit_slots, x_rows, h_rows, act_bytes, mn, 0, blockIdx.x);
     else
-        score_block<LAST_CT, M, WITH_MIN>(net, feat, ld, n, out, unit_slots, x_rows, h_rows, act_bytes, mn, skip,
+        score_block<LAST_CT, M, BY_PARTS, WITH_MIN>(net, feat, ld, n, out, unit_slots, x_rows, h_rows, act_bytes, mn, skip,
                                                    blockIdx.x - whole);
 }
 
@@ -473,6 +473,7 @@ int32_t launch(const eck_model *m, const float *feat, uint64_t ld, uint64_t n, f
                      s + m->off_w[2], s + m->off_b[2], F, H1, H2};
     const int widest = H1 > H2 ? H1 : H2;
     const uint64_t tiles = (n + 15) / 16;
+    const bool by_parts = H1 > 16;
     // Two unit tiles per wavefront and four candidate tiles (64 candidates a block): a weight is read for four, an activation
     // for two.  Fewer candidates where blocks that large would leave compute units without one (64-256-256-1, us with 1 / 2 /
     // 4 candidate tiles: 1000 9 / 10 / -, 6400 17 / 10.7 / 14, 16000 34 / 21 / 15, 100003 199 / 126 / 95); two at most, and
@@ -481,10 +482,26 @@ int32_t launch(const eck_model *m, const float *feat, uint64_t ld, uint64_t n, f
     // 32-64-64-1: 30000 6.4 and 6.9, 60000 11 and 8.8), those of 32 units or less always (64-30-20-1 on 2^20: 116-118
     // against 130).
     int ct = tiles <= 256 ? 1 : tiles <= 512 || H1 > 256 ? 2 : 4, per = H1 > 256 ? 4 : 2, unit_slots = 8, cand_slots = 1;
-    if (widest <= 16) {
-        per = unit_slots = 1;
-        if (ct > 2) ct = 2;
-        cand_slots = tiles < 8192 ? 2 : 1;
+    if (!by_parts) {
+        // In fp32 products, which need no pass over parts: a group of 32 inputs would be half zeros in the second layer, and a
+        // first layer of one tile is its features' parts.  us, former fp32 instructions / products of parts / these: 32-16-16-1
+        // 6400 3.6 / 4.5 / 3.5, 100003 7.2 / 8.3 / 7.4, 2^20 51 / 53 / 41; 64-16-16-1 30000 5.2 / 6.8 / 5.3, 100003 10.2 / 12.8 / 10.3;
+        // 64-16-64-1 4096 5.3 / 4.2 / 3.8, 2^18 28 / 38 / 28; 64-16-512-1 4096 5.7 / 6.4 / 5.8, 100003 52 / 57 / 41.  Errors as fp32
+        // instructions have (64-16-512-1 0.7-1.0e-7 of the scores' norm; of parts 0.4-0.5e-7).  One wavefront a tile of the
+        // second layer until the chip is full, then fewer of more tiles; the lines lie where measured times cross.
+        per = widest > 256 && tiles <= 256 ? 4 : 1;
+        if (widest <= 16) {
+            unit_slots = 1;
+            cand_slots = tiles <= 1024 ? 1 : 4;
+            ct = tiles <= 3072 || (F == 64 && tiles > 8192) ? 1 : 2;
+        } else if (widest <= 64) {
+            unit_slots = tiles <= 5632 ? 4 : 2;
+            cand_slots = 4 / unit_slots;
+            ct = tiles <= 512 ? 1 : tiles <= 1536 || (F == 64 && tiles > 8192) ? 2 : 4;
+        } else {
+            unit_slots = tiles <= 512 || (widest > 128 && tiles <= 3072) ? 8 : 4;
+            ct = tiles <= 256 ? 1 : tiles <= 512 || (widest <= 128 && tiles <= 1536) ? 2 : 4;
+        }
     } else if (widest <= 32) {
         per = 1;
         unit_slots = cand_slots = 2;
@@ -498,7 +515,7 @@ int32_t launch(const eck_model *m, const float *feat, uint64_t ld, uint64_t n, f
     }
     const int cands = 16 * ct * cand_slots, x_rows = F / 8, h_rows = 4 * groups_of(H1);
     const int threads = 64 * unit_slots * cand_slots;
-    const int part_rows = PARTS * (x_rows > h_rows ? x_rows : h_rows), plain_rows = (F > H1 ? F : H1 + 15) / 16 * 4;
+    const int part_rows = by_parts ? PARTS * (x_rows > h_rows ? x_rows : h_rows) : 0, plain_rows = (F > H1 ? F : H1 + 15) / 16 * 4;
     const size_t act_bytes = (size_t)(part_rows > plain_rows ? part_rows : plain_rows) * cands * 16;
     const size_t lds = act_bytes + ((size_t)tiles_of(H2) * cands + cands + 1) * 4;
     // Eight wavefronts of blocks of 64 candidates fill a compute unit (their registers), so a launch takes whole rounds of
@@ -510,7 +527,7 @@ int32_t launch(const eck_model *m, const float *feat, uint64_t ld, uint64_t n, f
     const uint64_t blocks = (n + cands - 1) / cands;
     uint64_t whole = blocks, grid = blocks;
     int last_ct = ct;
-    if (unit_slots >= 4 && ct == (H1 > 256 ? 2 : 4)) {
+    if (by_parts && unit_slots >= 4 && ct == (H1 > 256 ? 2 : 4)) {
         int cus = 256;
         (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, m->device);
         const uint64_t round = (uint64_t)cus * (8 / unit_slots), left = blocks % round;
@@ -521,17 +538,21 @@ int32_t launch(const eck_model *m, const float *feat, uint64_t ld, uint64_t n, f
             grid = whole + (n - whole * cands + few - 1) / few;
         }
     }
-    auto kern = per == 4 ? (last_ct < ct ? score_f32_kernel<2, 4, WITH_MIN, 1>
-                              : ct == 2    ? score_f32_kernel<2, 4, WITH_MIN>
-                                           : score_f32_kernel<1, 4, WITH_MIN>)
-                : per == 2 ? (last_ct < ct ? (last_ct == 1 ? score_f32_kernel<4, 2, WITH_MIN, 1>
-                                                           : score_f32_kernel<4, 2, WITH_MIN, 2>)
-                              : ct == 4 ? score_f32_kernel<4, 2, WITH_MIN>
-                              : ct == 2 ? score_f32_kernel<2, 2, WITH_MIN>
-                                        : score_f32_kernel<1, 2, WITH_MIN>)
-                           : (ct == 4   ? score_f32_kernel<4, 1, WITH_MIN>
-                              : ct == 2 ? score_f32_kernel<2, 1, WITH_MIN>
-                                        : score_f32_kernel<1, 1, WITH_MIN>);
+    auto kern = !by_parts ? (per == 4   ? score_f32_kernel<1, 4, false, WITH_MIN>
+                             : ct == 4 ? score_f32_kernel<4, 1, false, WITH_MIN>
+                             : ct == 2 ? score_f32_kernel<2, 1, false, WITH_MIN>
+                                       : score_f32_kernel<1, 1, false, WITH_MIN>)
+                : per == 4 ? (last_ct < ct ? score_f32_kernel<2, 4, true, WITH_MIN, 1>
+                              : ct == 2    ? score_f32_kernel<2, 4, true, WITH_MIN>
+                                           : score_f32_kernel<1, 4, true, WITH_MIN>)
+                : per == 2 ? (last_ct < ct ? (last_ct == 1 ? score_f32_kernel<4, 2, true, WITH_MIN, 1>
+                                                           : score_f32_kernel<4, 2, true, WITH_MIN, 2>)
+                              : ct == 4 ? score_f32_kernel<4, 2, true, WITH_MIN>
+                              : ct == 2 ? score_f32_kernel<2, 2, true, WITH_MIN>
+                                        : score_f32_kernel<1, 2, true, WITH_MIN>)
+                           : (ct == 4   ? score_f32_kernel<4, 1, true, WITH_MIN>
+                              : ct == 2 ? score_f32_kernel<2, 1, true, WITH_MIN>
+                                        : score_f32_kernel<1, 1, true, WITH_MIN>);
     ECK_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(threads), lds, st, net, feat, ld, n, out, unit_slots, x_rows, h_rows,
                        (int)act_bytes, mn, (uint32_t)whole, whole * cands);

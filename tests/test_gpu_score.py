@@ -403,3 +403,29 @@ def test_fp32_scores_of_small_numbers(G, widths, inputs, first, bias, second):
         ordinary = np.ones(n, dtype=bool)
         ordinary[5::7] = False
         assert np.array_equal(both[ordinary], alone[ordinary]) and np.array_equal(both[5::7], got[5::7])
+
+
+@pytest.mark.parametrize("widths", [(32, 1, 1, 1), (64, 16, 16, 1), (64, 9, 17, 1), (32, 16, 64, 1), (64, 5, 128, 1), (64, 16, 130, 1),
+                                    (32, 12, 257, 1), (64, 16, 512, 1)])
+def test_fp32_models_of_a_first_layer_of_one_tile(G, widths):
+    """First layers of up to sixteen units are worked out in fp32 products, in blocks whose form depends on the candidates, the
+    features and the second layer: on both sides of every line each candidate has the bits it has in a call of few, checked
+    against the oracle, and every segment the least of its scores."""
+    widths = list(widths)
+    some = 1009
+    f32, _ = _features("c1" if widths[0] == 32 else "c2", some + 1, widths[0])
+    theta = synth.mlp_theta(widths, 6, bias_scale=0.4)
+    model = G.make_model(widths, eck.F32, theta)
+    few = G.score_gpu(model, G.to_dev(f32), some)
+    assert G.within(few, oracle.score(widths, theta, f32, n=some), oracle.score_magnitude(widths, theta, f32, n=some), 1e-5) <= 1.0
+    for tiles in (1, 4, 256, 512, 1024, 1536, 3072, 5632, 8192):
+        for n in (16 * tiles - 15, 16 * tiles, 16 * tiles + 1):
+            feat = G.to_dev(np.ascontiguousarray(f32[:, np.arange(n + (n & 1)) % some]))
+            want = few[np.arange(n) % some]
+            assert np.array_equal(G.score_gpu(model, feat, n), want), n
+            segments = max(s for s in range(1, 60) if n % s == 0)
+            out, keys = torch.zeros(n, device="cuda"), torch.zeros(segments, dtype=torch.int32, device="cuda")
+            eck.costmodel_score_min(model, feat, n, out, None, segments, keys)
+            bits = want.reshape(segments, -1).min(axis=1).view(np.uint32)
+            order = np.where(bits >> 31, ~bits, bits | np.uint32(1 << 31))
+            assert np.array_equal(out.cpu().numpy(), want) and np.array_equal(keys.cpu().numpy().view(np.uint32), order), n
