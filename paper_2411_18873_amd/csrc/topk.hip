@@ -543,7 +543,7 @@ __device__ __forceinline__ uint32_t block_least(uint32_t best, Shared<T> &sh)
 
 // The block's chunk of T * ITEMS candidates of segment s (four consecutive candidates per load where VEC allows
 // it): order keys of the feasible ones, bounded, the survivors turned into composites (held in c and compacted into
-// the pool).  `known`: the least of the segment's minima that this thread has looked at, or null: not looked yet.
+// the pool).  `known`: the least of the segment's minima, or null: not looked yet.
 template <int T, int SRC, int PRED>
 __device__ __forceinline__ void gather_scores(const SelectArgs &a, uint32_t s, Shared<T> &sh, uint64_t (&c)[ITEMS],
                                               uint32_t *kept, bool *bounded, const uint32_t *known)
@@ -577,7 +577,7 @@ __device__ __forceinline__ void gather_scores(const SelectArgs &a, uint32_t s, S
         if (a.alpha_inf) {
             tau = __builtin_inff();
         } else {
-            uint32_t best = known ? *known : 0xFFFFFFFFu;
+            uint32_t best = 0xFFFFFFFFu;
             for (uint32_t p = threadIdx.x; !known && p < a.lat_parts_n; p += T) best = min(best, a.lat_parts[(uint64_t)s * a.lat_parts_n + p]);
             if (a.lat_parts_n == 0) { // the segment is this block's chunk
                 if (SRC == SRC_SCORES_VEC) {
@@ -600,7 +600,7 @@ __device__ __forceinline__ void gather_scores(const SelectArgs &a, uint32_t s, S
                     }
                 }
             }
-            tau = gate_above(block_least<T>(best, sh), a.slack_factor);
+            tau = gate_above(known ? *known : block_least<T>(best, sh), a.slack_factor);
         }
     }
     // order keys of the feasible candidates (32 bits each: the index is implied by the position), their least
@@ -675,33 +675,46 @@ __device__ __forceinline__ void gather_scores(const SelectArgs &a, uint32_t s, S
 
 // The same from what scan_kernel listed of the chunk, one list entry per thread: false when the lists do not tell (one
 // overflowed, or the segment's gate lies above the one that a list was made under), the same answer in every thread.
-// *best: the least of the segment's minima among those that this thread looked at.
+// *best: the least of the segment's minima.
 template <int T>
 __device__ __forceinline__ bool gather_scanned(const SelectArgs &a, uint32_t s, Shared<T> &sh, uint64_t (&c)[ITEMS],
                                                uint32_t *kept, bool *bounded, uint32_t *best)
 {
     constexpr uint32_t LISTS = (uint32_t)(T * ITEMS) / SCAN_CHUNK; // of this block's chunk; at most SMALL entries
     static_assert(LISTS * SCAN_LIST <= SMALL && LISTS * SCAN_LIST <= (uint32_t)T, "");
-    const uint32_t *least = a.lat_parts + (uint64_t)s * a.lat_parts_n;
-    const uint32_t mine = threadIdx.x / SCAN_LIST, list = blockIdx.x * LISTS + mine;
-    const bool have = mine < LISTS && list < a.lat_parts_n;
-    uint32_t count = 0, own = 0xFFFFFFFFu;
-    uint64_t entry = 0; // (past the list's end: left over from earlier calls, not looked at)
-    if (have) {
-        count = a.listed[(uint64_t)s * a.lat_parts_n + list];
-        own = least[list];
-        entry = a.scan_lists[((uint64_t)s * a.lat_parts_n + list) * SCAN_LIST + threadIdx.x % SCAN_LIST];
+    const uint32_t *least = a.lat_parts + (uint64_t)s * a.lat_parts_n, *listed = a.listed + (uint64_t)s * a.lat_parts_n;
+    const uint32_t first = blockIdx.x * LISTS, mine = threadIdx.x / SCAN_LIST;
+    // every thread looks at all of the block's lists, so that no barrier has to bring their answers together
+    uint32_t count[LISTS], own[LISTS];
+#pragma unroll
+    for (uint32_t k = 0; k < LISTS; ++k) {
+        const uint32_t at = min(first + k, a.lat_parts_n - 1);
+        count[k] = listed[at];
+        own[k] = least[at];
     }
-    *best = 0xFFFFFFFFu;
-    for (uint32_t p = threadIdx.x; p < a.lat_parts_n; p += T) *best = min(*best, least[p]);
-    // (where the gate admits much, the chunk's loads go out before the minima are reduced)
-    if (__syncthreads_or(count > SCAN_LIST)) return false;
-    const float tau = gate_above(block_least<T>(*best, sh), a.slack_factor);
-    // (a gate that is no number admits nothing, but compares with nothing either: read the chunk)
-    if (__syncthreads_or(have && !(tau <= gate_above(own, a.slack_factor)))) return false;
+    uint64_t entry = 0; // (past the list's end: left over from earlier calls, not looked at)
+    if (mine < LISTS && first + mine < a.lat_parts_n) entry = a.scan_lists[((uint64_t)s * a.lat_parts_n + first + mine) * SCAN_LIST + threadIdx.x % SCAN_LIST];
+    uint32_t lowest = 0xFFFFFFFFu;
+    for (uint32_t p = threadIdx.x; p < a.lat_parts_n; p += T) lowest = min(lowest, least[p]);
+    lowest = wave_least(lowest);
+    if ((threadIdx.x & 63) == 0) sh.wave_sum[threadIdx.x >> 6] = lowest;
+    __syncthreads();
+#pragma unroll
+    for (uint32_t w = 0; w < T / 64; ++w) lowest = min(lowest, sh.wave_sum[w]);
+    *best = lowest;
+    const float tau = gate_above(lowest, a.slack_factor);
+    uint32_t from = 0; // entries of this thread's list that may be feasible
+#pragma unroll
+    for (uint32_t k = 0; k < LISTS; ++k) {
+        // A list whose least latency lies above the gate has nothing to give, however long it is (one of a sorted array; nothing
+        // legal and a gate that is no number do the same)
+        if (first + k >= a.lat_parts_n || !(key_to_float(own[k]) <= tau)) continue;
+        if (count[k] > SCAN_LIST || !(tau <= gate_above(own[k], a.slack_factor))) return false;
+        if (mine == k) from = count[k];
+    }
 #pragma unroll
     for (int j = 0; j < ITEMS; ++j) c[j] = NONE;
-    if (threadIdx.x % SCAN_LIST < count && __uint_as_float((uint32_t)(entry >> 32)) <= tau) {
+    if (threadIdx.x % SCAN_LIST < from && __uint_as_float((uint32_t)(entry >> 32)) <= tau) {
         const float e = a.energy[(uint64_t)s * a.seg_len + (uint32_t)entry];
         if (e == e) {
             c[0] = ((uint64_t)score_order_key(e) << a.idx_bits) | (uint32_t)entry;
@@ -846,8 +859,8 @@ __device__ __forceinline__ void select_and_emit(const SelectArgs &a, uint32_t s,
 // launch was tried: on this chip blocks of one launch sit on eight dies with separate L2 caches, so lists and
 // tickets have to be written through to memory -- device-scope stores and atomics, or a release fence, which
 // writes the whole L2 back -- and that costs far more than the second launch: 73 us and 400 us against 32.)
-template <int T, int SRC, int PRED>
-__global__ __launch_bounds__(T) void select_kernel(SelectArgs a)
+template <int T, int SRC, int PRED, bool CROWDED = false>
+__global__ __launch_bounds__(T, CROWDED ? 8 : 1) void select_kernel(SelectArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     Shared<T> &sh = *reinterpret_cast<Shared<T> *>(lds_raw);
@@ -975,7 +988,7 @@ bool sizes_ok(uint64_t n, uint32_t n_seg, uint32_t k)
            n_seg <= 65535;
 }
 
-template <int T, int SRC, int PRED>
+template <int T, int SRC, int PRED, bool CROWDED = false>
 void launch_select(const SelectArgs &a, uint32_t blocks, uint32_t n_seg, hipStream_t st)
 {
     size_t lds = (sizeof(Shared<T>) + 15) & ~(size_t)15;
@@ -984,7 +997,7 @@ void launch_select(const SelectArgs &a, uint32_t blocks, uint32_t n_seg, hipStre
         while (pow2 < (a.k_energy ? a.k_energy : a.k)) pow2 <<= 1;
         lds += (size_t)pow2 * sizeof(uint64_t);
     }
-    hipLaunchKernelGGL((select_kernel<T, SRC, PRED>), dim3(blocks, n_seg), dim3(T), lds, st, a);
+    hipLaunchKernelGGL((select_kernel<T, SRC, PRED, CROWDED>), dim3(blocks, n_seg), dim3(T), lds, st, a);
 }
 
 template <int T, int PRED>
@@ -992,7 +1005,11 @@ void launch_level0(const SelectArgs &a, uint32_t blocks, uint32_t n_seg, bool ve
 {
     if constexpr (PRED == PRED_THRESHOLD) {
         if (a.listed) {
-            if (vec) launch_select<T, SRC_SCANNED_VEC, PRED>(a, blocks, n_seg, st);
+            // Blocks of 1024 threads: two to a compute unit, for a few spilled registers, where a launch has more blocks than
+            // units; what a block waits for before it knows whether its lists tell is then hidden (64 segments of 2^18,
+            // everything admitted: k = 512 95.8 -> 82 us, 1024 114 -> 101; one segment of 2^18, 16 blocks, 27.7 and 28.8)
+            if (T == 1024 && vec && (uint64_t)blocks * n_seg > 256) launch_select<1024, SRC_SCANNED_VEC, PRED, true>(a, blocks, n_seg, st);
+            else if (vec) launch_select<T, SRC_SCANNED_VEC, PRED>(a, blocks, n_seg, st);
             else launch_select<T, SRC_SCANNED, PRED>(a, blocks, n_seg, st);
             return;
         }

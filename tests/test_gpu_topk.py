@@ -284,3 +284,32 @@ def test_block_sizes_and_list_shares(G, segments, seg_len, k, order):
     if k <= 1000:
         _same(G.topk_gpu(e, lat, legal, segments, max(1, k // 2), mode=eck.SELECT_RANK, m_latency=k),
               oracle.topk(e, lat, legal, segments, max(1, k // 2), mode=oracle.SEL_RANK, m_latency=k))
+
+
+@pytest.mark.parametrize("segments,seg_len", [(131, 16388), (131, 16385), (20, 16388), (1, 70000), (300, 4100), (2, 1500000)])
+@pytest.mark.parametrize("k", [5, 300, 1100])
+@pytest.mark.parametrize("alpha", [1.0, 1.1, 3.5])
+def test_long_lists_above_the_gate(G, segments, seg_len, k, alpha):
+    """Chunks whose own minimum admits more than a list holds, but which lie above the segment's gate; next to them segments that
+    admit everything, little, nothing legal, or have no gate (an infinite least latency, negative ones); launches of more blocks
+    than compute units, where those of 1024 threads share one, and of fewer."""
+    rng = np.random.default_rng(seg_len + k)
+    n = segments * seg_len
+    e = rng.standard_normal(n).astype(np.float32)
+    lat = (1.0 + rng.random((segments, seg_len))).astype(np.float32)
+    legal = (rng.random((segments, seg_len)) < 0.3).astype(np.uint8)
+    for s in range(segments):
+        kind = (s + seg_len) % 7
+        if kind < 2:
+            lat[s] = np.sort(lat[s])[::1 if kind == 0 else -1]
+        elif kind == 2:
+            lat[s] = 10 + lat[s] / 100
+        elif kind == 3:
+            lat[s] -= 3
+        elif kind == 4:
+            lat[s, rng.random(seg_len) < 0.9] = np.inf
+            lat[s, rng.random(seg_len) < 0.5] = np.nan
+        elif kind == 5:
+            (lat if s % 2 else legal)[s] = np.inf if s % 2 else 0
+    lat, legal = lat.reshape(-1), legal.reshape(-1)
+    _same(G.topk_gpu(e, lat, legal, segments, k, alpha=alpha), oracle.topk(e, lat, legal, segments, k, alpha=alpha))
