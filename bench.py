@@ -470,7 +470,8 @@ def main():
     }
     # the other calls of the step, each between HIP events: median milliseconds per call, and for the two calls that
     # only move data the algorithmic bytes per second against the 8 TB/s of HBM (features: genes in, 64 bf16 features
-    # and a flag out; top-k: energy, latency and flag of every candidate once)
+    # and a flag out; top-k: latency and flag of every candidate once, and energies, 4 B more, where the gate admits
+    # everything -- under a finite gate only those of the few that it admits are read)
     calls_ms = {name: T.median(name) for name in ("enumerate", "features", "score", "score_min", "topk", "update")}
     calls_ms["topk_alpha_inf"] = topk_inf_ms
     calls_ms["topk_two_pass"] = topk_two_pass_ms
@@ -481,10 +482,10 @@ def main():
                 "frac": nbytes / (ms * 1e-3) / PEAK_HBM, "ms": ms}
 
     result["hbm"] = {"features": hbm(N * (2 * G + 2 * F + 1), calls_ms["features"]),
-                     "topk": dict(hbm(N * 9, calls_ms["topk"]), input="alpha = 1.1, least latencies from the scoring "
+                     "topk": dict(hbm(N * 5, calls_ms["topk"]), input="alpha = 1.1, least latencies from the scoring "
                                   "launch: %d of %d slots filled" % (feasible_alpha, S * K)),
-                     "topk_two_pass": dict(hbm(N * 13, topk_two_pass_ms), input="alpha = 1.1, least latencies found by "
-                                           "the selection (latencies read twice)"),
+                     "topk_two_pass": dict(hbm(N * 5, topk_two_pass_ms), input="alpha = 1.1, least latencies found by "
+                                           "the selection, in the pass that lists what its gate may admit"),
                      "topk_alpha_inf": dict(hbm(N * 9, topk_inf_ms), input="alpha = inf: every segment selects k")}
     if not args.no_other_configs:
         result["other_configs"] = other_configs(torch, np, eck, synth, max(8, args.steps))

@@ -681,7 +681,7 @@ __global__ __launch_bounds__(BLOCK) void tree_hist_lds_kernel(const uint8_t *__r
 }
 
 // The split of largest gain, in two parts.  tree_split_kernel: one block per (node of the level, group of four
-// features), a wavefront per feature, a lane per four consecutive bins; prefix sums over the bins by shuffles.
+// features), a wavefront per feature, a lane per four consecutive bins; prefix sums over the bins by data-parallel moves.
 // gain(f, b) = GL^2/(HL+lam) + GR^2/(HR+lam) - G^2/(H+lam) in fp64; the largest gain > 0 wins, ties to the
 // lower feature, then the lower bin (the candidate's rank f * 256 + b breaks ties in every comparison).  The
 // block leaves its best (gain, rank) in `partial`; the kernel that moves the pairs to their children compares

@@ -444,16 +444,15 @@ def test_dedup_clears_flags_of_many_and_few_occurrences(G, n, ld, kinds):
         assert np.array_equal(flags.cpu().numpy(), np.asarray(expected, dtype=np.uint8))
 
 
-@pytest.mark.parametrize("n", [16383, 16384, 16385, 40001, 524288, 524289, (1 << 20) - 1, 1 << 20, (1 << 20) + 1])
-@pytest.mark.parametrize("kinds,n_genes", [(1, 3), (1500, 8), (1500, 9), (200000, 1), (1 << 30, 5)])
+@pytest.mark.parametrize("n,kinds,n_genes", [(16384, 1, 3), (40001, 1, 3)] + [  # (one tuple: other sizes say nothing more)
+    (n, *form) for n in (16383, 16384, 16385, 40001, 524288, 524289, (1 << 20) - 1, 1 << 20, (1 << 20) + 1)
+    for form in ((1500, 8), (1500, 9), (200000, 1), (1 << 30, 5))])
 def test_dedup_by_parts_and_by_one_table(G, n, kinds, n_genes):
     """Candidates sorted by hash with a table per part (16384 to 2^20 candidates of up to eight genes, in the workspace of the
     query) and one table for all: few tuples of many occurrences, whose part is far larger than the others, and nearly all
     distinct; genes over all sixteen bits; rows longer than n; a workspace of the table's size only, and one that starts 4
     bytes into a 16-byte line."""
     import torch
-    if kinds == 1 and n not in (16384, 40001):
-        pytest.skip("one tuple: the sizes above say nothing more")
     rng = np.random.default_rng(n + kinds)
     ld = n + 3
     base = rng.integers(0, 65536, size=(n_genes, min(kinds, n)), dtype=np.uint16)
