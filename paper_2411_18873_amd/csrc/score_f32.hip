@@ -11,8 +11,8 @@
 //
 // What bounds it: matrix instructions and the LDS reads of the activations behind them (a part of four candidate tiles is read
 // for twelve matrix instructions), for narrow models the features.  Measured, against fp32 matrix instructions (which reached
-// 121-135 of their 153 TFLOP/s): 64-256-256-1 on 100003 candidates 152 -> 95 us (172 TFLOP/s of fp32 products, 1030 of bfloat16
-// ones; 99 on cards that sustain a lower clock), 64-128-128-1 on 2^18 125 -> 82, 64-512-512-1 on 100003 500 -> 320 and on 1536
+// 121-135 of their 153 TFLOP/s): 64-256-256-1 on 100003 candidates 152 -> 92 us (179 TFLOP/s of fp32 products, 1070 of bfloat16
+// ones; 90-100 by the clock a card sustains), 64-128-128-1 on 2^18 125 -> 82, 64-512-512-1 on 100003 500 -> 320 and on 1536
 // 22.6 -> 20.1, 32-64-64-1 on 6400 6.3 -> 4.3 and on 2^20 152 -> 119.  (64-512-512-1 took 423 and 22.5 with 256 units of the first
 // layer in LDS at a time and the second layer's sums of 256 units, for which the first was worked out twice.)  Errors
 // against 64 bits, relative to the scores' norm (before in brackets): 512 units 2.5-3.4e-8 (6.1-6.4e-8), 256 3.1-3.6e-8
@@ -520,9 +520,9 @@ int32_t launch(const eck_model *m, const float *feat, uint64_t ld, uint64_t n, f
     const size_t lds = act_bytes + ((size_t)tiles_of(H2) * cands + cands + 1) * 4;
     // Eight wavefronts of blocks of 64 candidates fill a compute unit (their registers), so a launch takes whole rounds of
     // them; what a last round short of blocks would do goes over the whole chip in blocks of 16 or 32 candidates.  Rounds
-    // and us with such blocks, without: 64-256-256-1 1.1 24.0, 28.7; 1.25 24.4, 28.3; 1.4 24.8, 28.2; 3.1 51.7, 55.5;
-    // 64-512-512-1, of 32 candidates before, 16 now: 1.1 59.4, 62.9; 3.4 124.6, 127.7; 64-128-128-1, two blocks a unit: 1.1
-    // 15.2, 18.0; 3.1 34.6, 36.9; from an eighth of a round on slower (1.25 18.2, 18.2; 2.2 29.3, 28.3), and for narrower
+    // and us with such blocks, without: 64-256-256-1 1.1 23.5, 28.0; 1.4 24.7, 27.9; 3.1 52.0, 55.8; 64-512-512-1, of 32
+    // candidates before, 16 now: 1.1 45.0, 46.3; 1.4 47.2, 47.4; 3.1 95.6, 96.8; 64-128-128-1, two blocks a unit: 1.1
+    // 15.4, 18.1; 3.1 36.4, 38.4; from an eighth of a round on slower (1.25 18.2, 18.2; 2.2 29.3, 28.3), and for narrower
     // models, with no rounds to speak of, from three rounds on.
     const uint64_t blocks = (n + cands - 1) / cands;
     uint64_t whole = blocks, grid = blocks;

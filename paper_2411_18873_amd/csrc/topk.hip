@@ -121,8 +121,8 @@ __global__ __launch_bounds__(256) void latmin_kernel(const float *__restrict__ l
 // open: a superset of the chunk's feasible candidates as long as the segment's gate lies no higher, which the next launch
 // checks, as it does that the list has not overflowed (it reads the chunk again otherwise).  Where a gate admits few,
 // the latencies are thus read once and energies only for the listed.  Bound by the stream of latencies and flags.  64
-// segments of 2^18, alpha = 1.1: 14.5 us here and 10.2 in the next launch, where a pass for the minima alone takes 14.2 and the
-// next one, reading the latencies again, 21.2; where the gate admits everything, 15 and 35 against 14 and 33.
+// segments of 2^18, alpha = 1.1: 14.5-16 us here and 9 in the next launch, where a pass for the minima alone takes 14.2 and the
+// next one, reading the latencies again, 21.2; where the gate admits everything, 15 and 31 against 14 and 33.
 template <bool VEC>
 __global__ __launch_bounds__(256) void scan_kernel(const float *__restrict__ latency, const uint8_t *__restrict__ legal,
                                                    uint64_t seg_len, float slack_factor, uint32_t *__restrict__ least,

@@ -116,8 +116,8 @@ __global__ __launch_bounds__(256) void tree_get_kernel(const uint8_t *nf, const 
 //     adds them up.  Features are kept as floats.
 // What bounds it: vector instructions, then the two dependent LDS reads of a visit (node, feature value).  A visit takes
 // four: the node's address, the feature value's (mask and join), the difference to the threshold, and the step, which
-// shifts the difference's sign into the node's number.  Measured, 100 trees of depth 6 on 2^20 candidates: 136-138 us (two
-// thirds of the cycles issue vector instructions, two fifths move LDS data; no bank conflicts); with eight-byte nodes, a
+// shifts the difference's sign into the node's number.  Measured, 100 trees of depth 6 on 2^20 candidates: 136-138 us (62 %
+// of the cycles issue vector instructions, 69 % of those a unit is busy, two fifths move LDS data; no bank conflicts); with eight-byte nodes, a
 // compare into a mask and an add with carry 156 us.  Without effect: more wavefronts (trees shared by two groups over
 // 256 or 384 candidates, 158-165 us), the first two levels' nodes through the scalar cache; nodes gathered from the L1
 // instead of the LDS: 184 us for a quarter of them.
