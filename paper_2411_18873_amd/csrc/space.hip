@@ -490,14 +490,15 @@ __global__ void dedup_clear_kernel(uint32_t *table, uint64_t slots, uint8_t *__r
 // What bounds it: one device-wide atomic to a random line per candidate.  Crossover, features and de-duplication of a round
 // of 260 001 children: 61 us, of which this kernel 28; 76 with a second pass that probed for every candidate again (15 us) and a
 // minimum sent also by those that had met a lower index.  Reading the slot before the atomic costs a round trip: 66 us.
-__device__ __forceinline__ void dedup_insert(const uint16_t *__restrict__ genes, uint64_t ld, int n_genes, uint32_t *table,
-                                             uint32_t slots, uint32_t slot, uint32_t i, uint8_t *flags)
+template <class At> // at(slot): where it is
+__device__ __forceinline__ void dedup_insert(const uint16_t *__restrict__ genes, uint64_t ld, int n_genes, At at, uint32_t slots,
+                                             uint32_t slot, uint32_t i, uint8_t *flags)
 {
     for (uint32_t probe = 0; probe < slots; ++probe) {
-        uint32_t seen = atomicCAS(&table[slot], kEmptySlot, i);
+        uint32_t *here = at(slot), seen = atomicCAS(here, kEmptySlot, i);
         if (seen == kEmptySlot) return; // this candidate now stands for its tuple
         if (same_genes(genes, ld, n_genes, seen, i)) {
-            if (seen > i) seen = atomicMin(&table[slot], i);
+            if (seen > i) seen = atomicMin(here, i);
             flags[seen > i ? seen : i] = 0;
             return;
         }
@@ -509,7 +510,9 @@ __global__ void dedup_insert_kernel(const uint16_t *__restrict__ genes, uint64_t
                                     uint32_t *table, uint32_t slots, uint8_t *flags)
 {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) dedup_insert(genes, ld, n_genes, table, slots, (uint32_t)genes_hash(genes, ld, n_genes, i) & (slots - 1), i, flags);
+    if (i >= n) return;
+    dedup_insert(genes, ld, n_genes, [&](uint32_t slot) { return table + slot; }, slots,
+                 (uint32_t)genes_hash(genes, ld, n_genes, i) & (slots - 1), i, flags);
 }
 
 // ---- the same for up to 2^20 candidates of up to eight genes without device-wide atomics: candidates that could be equal are
@@ -600,17 +603,16 @@ __global__ __launch_bounds__(DEDUP_THREADS) void dedup_sort_kernel(const uint16_
 // A block per part: its candidates into a table, where the lowest index of a tuple stays and every other one's flag is cleared, as
 // in dedup_insert_kernel.  Bound by the LDS: a compare-and-swap per probe (260 001 candidates 6.5 us, 2^20 19.5; with the genes
 // of possible equals gathered from their rows 14.6 and 72).  A part of more tuples than its table takes goes through one in
-// memory instead: `spill`, two slots for each of the call's candidates, in the order of the parts.
-__global__ __launch_bounds__(DEDUP_THREADS) void dedup_part_kernel(uint32_t chunks, uint32_t chunk, const uint4 *__restrict__ records,
+// memory instead, where its records were: four slots for each of its candidates.
+__global__ __launch_bounds__(DEDUP_THREADS) void dedup_part_kernel(uint32_t chunks, uint32_t chunk, uint4 *records,
                                                                    const uint64_t *__restrict__ entries, const uint32_t *__restrict__ bounds,
-                                                                   uint8_t *flags, const uint16_t *__restrict__ genes, uint64_t ld, int n_genes,
-                                                                   uint32_t *spill)
+                                                                   uint8_t *flags, const uint16_t *__restrict__ genes, uint64_t ld, int n_genes)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char dedup_lds[];
     uint4 *near = reinterpret_cast<uint4 *>(dedup_lds); // [DEDUP_RECORDS] of the part's first candidates
     // [DEDUP_SLOTS] a zero (so that no candidate looks like an empty slot), 23 bits of hash, 20 of index, 20 of place in the part
     unsigned long long *table = reinterpret_cast<unsigned long long *>(near + DEDUP_RECORDS);
-    __shared__ uint32_t before[DEDUP_CHUNKS], from[DEDUP_CHUNKS], wave_sum[DEDUP_CHUNKS / 64], full, ahead; // of every chunk: candidates in the chunks before it, and where they are
+    __shared__ uint32_t before[DEDUP_CHUNKS], from[DEDUP_CHUNKS], wave_sum[DEDUP_CHUNKS / 64], full; // of every chunk: candidates in the chunks before it, and where they are
     const int tid = threadIdx.x;
     uint32_t w = 0, upto = 0;
     if (tid < (int)DEDUP_CHUNKS) { // (whole wavefronts)
@@ -619,7 +621,7 @@ __global__ __launch_bounds__(DEDUP_THREADS) void dedup_part_kernel(uint32_t chun
         if ((tid & 63) == 63) wave_sum[tid >> 6] = upto;
     }
     for (uint32_t s = tid; s < DEDUP_SLOTS; s += DEDUP_THREADS) table[s] = kEmptyEntry;
-    if (tid == 0) full = ahead = 0;
+    if (tid == 0) full = 0;
     __syncthreads();
     if (tid < (int)DEDUP_CHUNKS) {
         uint32_t at = upto - (w & 0xFFFFu);
@@ -678,27 +680,22 @@ __global__ __launch_bounds__(DEDUP_THREADS) void dedup_part_kernel(uint32_t chun
     if (!full) return;
     // Only genes chosen for it come here: as many steps as dedup_insert_kernel takes, if by one block.  (The flags cleared so
     // far are right: each was of a candidate that met a lower one of its tuple.)
-    uint32_t others = 0; // candidates of the parts before this one
-    for (uint32_t e = tid; e < blockIdx.x * chunks; e += DEDUP_THREADS) others += bounds[e] & 0xFFFFu;
-    atomicAdd(&ahead, others);
-    __syncthreads();
-    uint32_t *own = spill + 2 * (uint64_t)ahead;
-    const uint32_t slots = 2 * total;
-    for (uint32_t s = tid; s < slots; s += DEDUP_THREADS) own[s] = kEmptySlot;
+    for (uint32_t e = tid; e < total; e += DEDUP_THREADS) records[place(e)] = make_uint4(kEmptySlot, kEmptySlot, kEmptySlot, kEmptySlot);
     __threadfence();
     __syncthreads();
     for (uint32_t e = tid; e < total; e += DEDUP_THREADS) {
         const uint64_t entry = entries[place(e)];
-        dedup_insert(genes, ld, n_genes, own, slots, (uint32_t)(entry >> 32) % slots, (uint32_t)entry, flags);
+        dedup_insert(genes, ld, n_genes, [&](uint32_t slot) { return reinterpret_cast<uint32_t *>(records + place(slot / 4)) + slot % 4; },
+                     4 * total, (uint32_t)(entry >> 32) % (4 * total), (uint32_t)entry, flags);
     }
 }
 
-// bytes of the parts' records, entries, tables in memory and bounds, or 0 where that path is not taken
+// bytes of the parts' records, entries and bounds, or 0 where that path is not taken
 uint64_t dedup_part_bytes(uint64_t n)
 {
     if (n < DEDUP_LEAST || n > DEDUP_MOST) return 0;
     const uint64_t chunk = (uint64_t)DEDUP_THREADS * dedup_items(n);
-    return n * 32 + (((n + chunk - 1) / chunk) << dedup_parts_log2(n)) * 4;
+    return n * 24 + (((n + chunk - 1) / chunk) << dedup_parts_log2(n)) * 4;
 }
 
 uint64_t dedup_slots(uint64_t n)
@@ -732,13 +729,13 @@ extern "C" int32_t eck_candidates_dedup(const uint16_t *genes, uint64_t ld, uint
         const uint32_t chunk = DEDUP_THREADS * dedup_items(n), chunks = (uint32_t)((n + chunk - 1) / chunk), log2 = dedup_parts_log2(n);
         uint4 *records = static_cast<uint4 *>(ws);
         uint64_t *entries = reinterpret_cast<uint64_t *>(records + n);
-        uint32_t *spill = reinterpret_cast<uint32_t *>(entries + n), *bounds = spill + 2 * n;
+        uint32_t *bounds = reinterpret_cast<uint32_t *>(entries + n);
         hipLaunchKernelGGL((dedup_items(n) == 2 ? dedup_sort_kernel<2> : dedup_sort_kernel<4>), dim3(chunks), dim3(DEDUP_THREADS), 0, st, genes, ld,
                            (uint32_t)n, (int)n_genes, flags, (int)overwrite, records, entries, bounds, log2);
         constexpr int LDS = DEDUP_SLOTS * 8 + DEDUP_RECORDS * 16;
         ECK_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(dedup_part_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, LDS));
         hipLaunchKernelGGL(dedup_part_kernel, dim3(1u << log2), dim3(DEDUP_THREADS), LDS, st, chunks, chunk, records, entries, bounds, flags, genes,
-                           ld, (int)n_genes, spill);
+                           ld, (int)n_genes);
         ECK_HIP_TRY(hipGetLastError());
         return ECK_OK;
     }
