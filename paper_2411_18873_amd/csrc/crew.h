@@ -1,0 +1,140 @@
+// A crew: blocks of one launch that run on one die and meet in its L2 (HIP, gfx950).
+//
+// A chain of small dependent steps launched one by one pays a kernel boundary and cold caches for each: 3.7 us between two
+// empty launches.  A barrier over the whole chip costs more (9 us with a block on each of its 256 units), because the L2s of
+// the eight dies meet in memory.  On one die a store goes through the L1 into the L2 that the other units read, so a
+// hand-over is a store that has arrived, a flag and a poll: 0.73 us for 32 blocks that each write 2 KB, meet and read a
+// neighbour's.  A chain whose steps are small enough for a die therefore runs as one launch.
+//
+// A launch of 8 N blocks puts every eighth on the same die; those with blockIdx % 8 == pick are the candidates, the others
+// end at once.  Candidates that run on the die of the first of them sign the roll; the first one there closes it when all N
+// have, or after a while, and whoever comes later ends, too.  So the members of a crew all run already, and a barrier
+// between them ends whatever else the chip is doing and whichever blocks it still holds back; with fewer members each has
+// more to do.  The work's cut, and so every sum, does not depend on their number.
+//
+// What members write for each other: plain stores, which pass the L1.  What they read of each other: loads that miss the L1
+// (fresh_*; ordinary ones may find an older line in it, and the scalar cache is not looked at either).
+#pragma once
+#include "eck_internal.h"
+
+namespace eck {
+
+constexpr unsigned CREW_DIES = 8;
+constexpr unsigned CREW_MOST = 32;                      // members, one per compute unit of a die
+constexpr unsigned CREW_GRID = CREW_DIES * CREW_MOST;   // blocks of the launch
+
+struct CrewState { // device memory, zero before the launch: two lines
+    uint32_t home;      // the members' die + 1, 0: none yet
+    uint32_t size;      // members, 0: roll still open
+    uint32_t roll[16];  // by die: candidates that signed; top bit: closed
+    uint32_t pad[14];
+    uint32_t met[CREW_MOST]; // by member: barriers it has reached
+};
+static_assert(sizeof(CrewState) == 256, "fits the place behind a workspace's last buffer");
+
+// which of every eight blocks are candidates: crews of different workspaces on different dies
+inline unsigned crew_pick(const void *state) { return (unsigned)(((uintptr_t)state >> 8) * 0x9E3779B1u >> 16) % CREW_DIES; }
+
+__device__ __forceinline__ void crew_clear(CrewState *s) // by one wavefront of an earlier launch
+{
+    if (threadIdx.x < 64) reinterpret_cast<uint32_t *>(s)[threadIdx.x] = 0;
+}
+
+struct Crew {
+    CrewState *s;
+    uint32_t rank, size, barriers;
+
+    // Called by every thread of a candidate block; false: not a member.  slot: two words of LDS.
+    __device__ __forceinline__ bool join(CrewState *state, uint32_t *slot)
+    {
+        s = state;
+        barriers = 0;
+        if (threadIdx.x == 0) {
+            constexpr uint32_t CLOSED = 0x80000000u;
+            const uint32_t die = __builtin_amdgcn_s_getreg((31 << 11) | 20) & 15; // HW_REG_XCC_ID
+            const uint32_t place = __hip_atomic_fetch_add(&s->roll[die], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            uint32_t home = 0, members = 0;
+            const bool first = __hip_atomic_compare_exchange_strong(&s->home, &home, die + 1, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                                    __HIP_MEMORY_SCOPE_AGENT);
+            if ((first || home == die + 1) && place < CLOSED) {
+                if (place == 0) {
+                    constexpr int PATIENCE = 128; // polls, some 50 us
+                    for (int i = 0; i < PATIENCE && relaxed(&s->roll[die]) < gridDim.x / CREW_DIES; ++i) {
+                    }
+                    members = __hip_atomic_fetch_or(&s->roll[die], CLOSED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_store(&s->size, members, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                } else {
+                    while ((members = relaxed(&s->size)) == 0) { // the block that closes the roll is running
+                    }
+                }
+            }
+            slot[0] = place;
+            slot[1] = members;
+        }
+        __syncthreads();
+        rank = __builtin_amdgcn_readfirstlane(slot[0]);
+        size = __builtin_amdgcn_readfirstlane(slot[1]);
+        return size != 0;
+    }
+
+    // The block's stores have arrived and its flag says so.  Every thread; first half of a barrier.
+    __device__ __forceinline__ void arrive()
+    {
+        ++barriers;
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if (threadIdx.x == 0) __hip_atomic_store(&s->met[rank], barriers, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+
+    // Every member has arrived.  Second half; loads requested between the two stay on their way.
+    __device__ __forceinline__ void meet() const
+    {
+        if (threadIdx.x < 64) {
+            const uint32_t *theirs = &s->met[threadIdx.x < size ? threadIdx.x : rank];
+            while (__ballot((int32_t)(relaxed(theirs) - barriers) < 0)) {
+            }
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    }
+
+    static __device__ __forceinline__ uint32_t relaxed(const uint32_t *p)
+    {
+        return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+};
+
+// The thread's index, worked out anew wherever it is asked for: what follows from it stays inside its phase, and the registers of
+// one phase are the next one's (hoisted out of the loop over the steps, the addresses of all phases spilled a hundred registers).
+__device__ __forceinline__ int crew_thread()
+{
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    return tid;
+}
+
+// Loads of what other members wrote (FRESH: past the L1), or ordinary ones: `at` bytes behind a base that all lanes share, which
+// `shared` is added to (a scalar, so that a row of loads needs one address)
+constexpr int CREW_RSRC_FLAGS = 0x00020000; // buffer descriptor: raw 32-bit data
+constexpr int CREW_SC1 = 16;                // cache policy: device scope
+typedef int crew_i32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t crew_buffer(const void *base)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, -1, CREW_RSRC_FLAGS);
+}
+
+template <bool FRESH>
+__device__ __forceinline__ crew_i32x4 fresh_16(const void *base, uint32_t at, uint32_t shared)
+{
+    if (!FRESH) return *reinterpret_cast<const crew_i32x4 *>(static_cast<const char *>(base) + at + shared);
+    return __builtin_amdgcn_raw_buffer_load_b128(crew_buffer(base), at, shared, CREW_SC1);
+}
+
+// (at and shared in bytes)
+template <bool FRESH>
+__device__ __forceinline__ float fresh_float(const float *base, uint32_t at, uint32_t shared)
+{
+    if (!FRESH) return *reinterpret_cast<const float *>(reinterpret_cast<const char *>(base) + shared + at);
+    return __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(crew_buffer(base), at, shared, CREW_SC1));
+}
+
+} // namespace eck

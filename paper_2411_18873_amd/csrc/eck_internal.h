@@ -85,18 +85,47 @@ __device__ __forceinline__ uint32_t score_order_key(float x)
 // later phase stay on their way across it (__syncthreads() would wait for them).
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// Adam on parameter i of a state [theta | m | v | t] (bias-corrected, no weight decay) from its values as fetched earlier:
-// writes all three, returns the new weight.  c1, c2: 1 - beta^t of the step.
-__device__ __forceinline__ float adam_one(float *theta, uint64_t P, uint64_t i, float w, float m, float v, float g,
-                                          float beta1, float beta2, float lr, float eps, float c1, float c2)
+// Adam on a parameter (bias-corrected, no weight decay).  The corrections' divisions are worked out once a step: a division or
+// square root is a dozen instructions, and three and one of them a parameter were most of what a weights phase does once its
+// sums are there.
+struct AdamScales {
+    float m, v; // lr / (1 - beta1^t), 1 / sqrt(1 - beta2^t)
+};
+// of step t, which takes the powers by squaring (a dozen multiplications for two double-precision pow() of most of a microsecond;
+// a few units in the last place of a double)
+__device__ __forceinline__ AdamScales adam_scales(float lr, float beta1, float beta2, uint32_t t)
+{
+    double power1 = 1.0, power2 = 1.0, square1 = beta1, square2 = beta2;
+    for (; t; t >>= 1) {
+        if (t & 1) {
+            power1 *= square1;
+            power2 *= square2;
+        }
+        square1 *= square1;
+        square2 *= square2;
+    }
+    return {(float)((double)lr / (1.0 - power1)), (float)(1.0 / sqrt(1.0 - power2))};
+}
+struct AdamNext {
+    float w, m, v;
+};
+__device__ __forceinline__ AdamNext adam_next(float w, float m, float v, float g, float beta1, float beta2, float eps, AdamScales scales)
 {
     m = beta1 * m + (1.0f - beta1) * g;
     v = beta2 * v + (1.0f - beta2) * g * g;
-    theta[P + i] = m;
-    theta[2 * P + i] = v;
-    const float next = w - lr * (m / c1) / (sqrtf(v / c2) + eps);
-    theta[i] = next;
-    return next;
+    return {w - m * scales.m / (sqrtf(v) * scales.v + eps), m, v};
+}
+
+// the same on parameter i of a state [theta | m | v | t] from its values as fetched earlier: writes all three, returns the new
+// weight
+__device__ __forceinline__ float adam_one(float *theta, uint64_t P, uint64_t i, float w, float m, float v, float g,
+                                          float beta1, float beta2, float eps, AdamScales scales)
+{
+    const AdamNext next = adam_next(w, m, v, g, beta1, beta2, eps, scales);
+    theta[P + i] = next.m;
+    theta[2 * P + i] = next.v;
+    theta[i] = next.w;
+    return next.w;
 }
 
 // forward pass of an fp32 model (score_f32.hip); mn: also the minima, or NULL
@@ -114,7 +143,8 @@ int32_t refit_finish(eck_model *m, const float *pred, const float *y, uint64_t n
                      float *snr_out, float *loss_out, hipStream_t stream);
 // Adam steps of a BF16 model in two launches per step (refit.hip): whether that path takes this call, the bytes it
 // needs behind the other buffers of costmodel_update's workspace, and the steps themselves (labels y and the
-// data-error flag come from the caller's kernels; the last step's mean loss goes to *loss_scalar, device memory)
+// data-error flag come from the caller's kernels; the last step's mean loss goes to *loss_scalar, device memory; spare:
+// device memory of 4 F minibatch bytes, 256-byte aligned)
 bool refit_applies(const eck_model *m, const void *feat, int32_t feat_dtype, uint64_t ld, int minibatch);
 uint64_t refit_workspace_bytes(const eck_model *m, int minibatch);
 // (refit_begin: labels y from the measured energies, and the weights' copies that the steps multiply with)
@@ -122,7 +152,7 @@ int32_t refit_begin(const eck_model *m, const float *energy, uint64_t n_pairs, f
                     hipStream_t st);
 int32_t refit_steps(const eck_model *m, const void *feat, int32_t feat_dtype, uint64_t ld, const float *y, uint64_t n_pairs,
                     int32_t n_steps, int32_t minibatch, float lr, float beta1, float beta2, float eps,
-                    const uint32_t *bad_flag, float *loss_scalar, void *ws, hipStream_t st);
+                    const uint32_t *bad_flag, float *loss_scalar, void *spare, void *ws, hipStream_t st);
 // the same for fp32 models of any hidden widths and minibatches of any size (refit_f32.hip)
 uint64_t refit_f32_workspace_bytes(const eck_model *m, int minibatch);
 int32_t refit_f32_steps(const eck_model *m, const float *feat, uint64_t ld, const float *y, uint64_t n_pairs, int32_t n_steps,

@@ -38,7 +38,7 @@ struct StepF32 {
     float *lterm;      // [padded] Eq.-(1) terms of the rows
     const uint32_t *bad; // data error found in the labels: leave the model alone
     float *loss_out;   // mean of the Eq.-(1) terms, written in the step with report_loss set
-    float *corr;       // [2] Adam's bias corrections 1 - beta^t of the step (rows kernel -> weights kernel)
+    AdamScales *scales; // of the step (rows kernel -> weights kernel)
     int step_in_call, report_loss;
     float lr, beta1, beta2, eps;
 };
@@ -164,11 +164,9 @@ template <int J>
 __global__ __launch_bounds__(64 * WAVES, 2) void step_rows_f32_kernel(StepF32 a)
 {
     constexpr int DEPTH = J <= 2 ? 8 : 4, E = 4 * J;
-    if (blockIdx.x == gridDim.x - 1) { // the block of Adam's bias corrections, one lane each
-        if (threadIdx.x < 2) {
-            const double t = (double)a.theta[3 * a.P] + a.step_in_call + 1; // t itself is advanced once, after the last step
-            a.corr[threadIdx.x] = (float)(1.0 - pow((double)(threadIdx.x ? a.beta2 : a.beta1), t));
-        }
+    if (blockIdx.x == gridDim.x - 1) { // the block of Adam's bias corrections
+        // (t itself is advanced once, after the last step)
+        if (threadIdx.x == 0) *a.scales = adam_scales(a.lr, a.beta1, a.beta2, (uint32_t)a.theta[3 * a.P] + a.step_in_call + 1);
         return;
     }
     extern __shared__ __attribute__((aligned(16))) unsigned char rows_lds[];
@@ -303,9 +301,9 @@ struct Moments {
 
 __device__ __forceinline__ Moments load_moments(const StepF32 &a, uint64_t i) { return {a.theta[i], a.theta[a.P + i], a.theta[2 * a.P + i]}; }
 
-__device__ __forceinline__ void adam_one(const StepF32 &a, uint64_t i, Moments s, float g, float c1, float c2)
+__device__ __forceinline__ void adam_one(const StepF32 &a, uint64_t i, Moments s, float g, AdamScales scales)
 {
-    (void)eck::adam_one(a.theta, a.P, i, s.w, s.m, s.v, g, a.beta1, a.beta2, a.lr, a.eps, c1, c2);
+    (void)eck::adam_one(a.theta, a.P, i, s.w, s.m, s.v, g, a.beta1, a.beta2, a.eps, scales);
 }
 
 // Blocks, in order: the 32 x 32 tiles of W2, those of W1, then blocks of 16 columns of the output layer.  A tile block:
@@ -322,7 +320,7 @@ __global__ __launch_bounds__(64 * WAVES) void step_weights_f32_kernel(StepF32 a,
     const int tid = threadIdx.x, lane = tid & 63, p = lane >> 4, c = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bool bad = *a.bad != 0;
-    const float c1 = a.corr[0], c2 = a.corr[1];
+    const AdamScales scales = *a.scales;
     int block = blockIdx.x;
     if (block < blocks2 + blocks1) {
         const bool second = block < blocks2; // a tile of W2, else of W1
@@ -404,13 +402,13 @@ __global__ __launch_bounds__(64 * WAVES) void step_weights_f32_kernel(StepF32 a,
             float g = part[0][lm][ln];
 #pragma unroll
             for (int w = 1; w < WAVES; ++w) g += part[w][lm][ln];
-            if (m0 + lm < M && n0 + ln < N) adam_one(a, off_w + (uint64_t)(m0 + lm) * N + n0 + ln, state[e], g, c1, c2);
+            if (m0 + lm < M && n0 + ln < N) adam_one(a, off_w + (uint64_t)(m0 + lm) * N + n0 + ln, state[e], g, scales);
         }
         if (m0 == 0 && tid < TILE && n0 + tid < N) {
             float g = colsum[0][tid];
 #pragma unroll
             for (int w = 1; w < WAVES; ++w) g += colsum[w][tid];
-            adam_one(a, bias_at, bias_state, g, c1, c2);
+            adam_one(a, bias_at, bias_state, g, scales);
         }
         return;
     }
@@ -459,14 +457,14 @@ __global__ __launch_bounds__(64 * WAVES) void step_weights_f32_kernel(StepF32 a,
         float g = psum[cg];
 #pragma unroll
         for (int r = 1; r < RG; ++r) g += psum[r * 16 + cg];
-        adam_one(a, i_out, out_state, g, c1, c2);
+        adam_one(a, i_out, out_state, g, scales);
     }
 }
 
 // the buffers behind the others in costmodel_update's workspace; every matrix is padded by one tile width, because a
 // weights kernel's lane may read that far past the last row
 struct Buffers {
-    uint64_t x, h1, h2, d1, d2, dy, lterm, corr, total;
+    uint64_t x, h1, h2, d1, d2, dy, lterm, scales, total;
 };
 
 Buffers buffers_for(const eck_model *m, int minibatch)
@@ -487,7 +485,7 @@ Buffers buffers_for(const eck_model *m, int minibatch)
     w.d2 = take(B * H2);
     w.dy = take(B);
     w.lterm = take(B);
-    w.corr = take(2);
+    w.scales = take(2);
     w.total = o;
     return w;
 }
@@ -526,7 +524,7 @@ int32_t eck::refit_f32_steps(const eck_model *m, const float *feat, uint64_t ld,
     a.d2 = reinterpret_cast<float *>(base + w.d2);
     a.dy = reinterpret_cast<float *>(base + w.dy);
     a.lterm = reinterpret_cast<float *>(base + w.lterm);
-    a.corr = reinterpret_cast<float *>(base + w.corr);
+    a.scales = reinterpret_cast<AdamScales *>(base + w.scales);
     a.bad = bad_flag;
     a.loss_out = loss_scalar;
     a.lr = lr;

@@ -195,9 +195,9 @@ __global__ void adam_kernel(float *__restrict__ state, const float *__restrict__
     if (sc->bad) return;
     const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= P) return;
-    const double t = (double)state[3 * P] + step_in_call + 1; // t itself is advanced once, after the last step
-    const float c1 = (float)(1.0 - pow((double)beta1, t)), c2 = (float)(1.0 - pow((double)beta2, t));
-    (void)adam_one(state, P, i, state[i], state[P + i], state[2 * P + i], grad[i], beta1, beta2, lr, eps, c1, c2);
+    // (t itself is advanced once, after the last step)
+    const AdamScales scales = adam_scales(lr, beta1, beta2, (uint32_t)state[3 * P] + step_in_call + 1);
+    (void)adam_one(state, P, i, state[i], state[P + i], state[2 * P + i], grad[i], beta1, beta2, eps, scales);
 }
 
 // Output layer, forward and backward, fused and row-local: one wavefront per minibatch row computes
@@ -369,7 +369,7 @@ extern "C" int32_t costmodel_update(eck_model *m, const void *feat, int32_t feat
     if (rc != ECK_OK) return rc;
     if (two_launches || m->dtype == ECK_F32) {
         rc = two_launches ? refit_steps(m, feat, feat_dtype, ld, y, n_pairs, n_steps, minibatch, lr, beta1, beta2, eps, &sc->bad,
-                                        &sc->loss, base + w.refit, st)
+                                        &sc->loss, h1, base + w.refit, st)
                           : refit_f32_steps(m, static_cast<const float *>(feat), ld, y, n_pairs, n_steps, minibatch, lr, beta1, beta2,
                                             eps, &sc->bad, &sc->loss, base + w.refit, st);
         if (rc != ECK_OK) return rc;

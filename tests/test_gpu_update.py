@@ -338,3 +338,48 @@ def test_data_error_leaves_an_fp32_model_alone(G, widths, minibatch):
         snr, loss = G.update_gpu(model, feat, bad, 3, minibatch)
         assert math.isnan(snr) and math.isnan(loss)
         assert np.array_equal(model.get_state().cpu().numpy().view(np.uint32), before.view(np.uint32))
+
+
+@pytest.mark.parametrize("widths,mb,n_pairs,feat", [
+    ([64, 256, 256, 1], 64, 64, "bf16"), ([64, 256, 256, 1], 1024, 1024, "f32"), ([64, 256, 256, 1], 192, 576, "bf16"),
+    ([64, 128, 128, 1], 2048, 2048, "bf16"), ([64, 128, 128, 1], 448, 896, "f32"), ([32, 64, 64, 1], 320, 640, "bf16"),
+    ([32, 64, 64, 1], 2048, 2048, "f32")])
+def test_bf16_steps_of_a_crew_are_those_of_two_launches(G, widths, mb, n_pairs, feat):
+    """Calls of a few steps launch each step by itself, longer ones run all steps in one launch on one die: the same bits,
+    with one block of rows and with two a member, and with minibatches that come round again."""
+    f32, b16, e = _pairs(n_pairs)
+    F, epoch = widths[0], n_pairs // mb
+    x = G.bf16_dev(b16[:F].copy()) if feat == "bf16" else G.to_dev(np.ascontiguousarray(f32[:F]))
+    theta = synth.mlp_theta(widths, 4, bf16=True)
+    a, b = G.make_model(widths, eck.BF16, theta), G.make_model(widths, eck.BF16, theta)
+    steps = 6 if epoch < 3 else 9
+    _, loss = G.update_gpu(a, x, e, steps, mb)
+    for _ in range(steps // epoch):  # (a call starts with the first minibatch again)
+        _, loss_b = G.update_gpu(b, x, e, epoch, mb)
+    assert np.array_equal(a.get_state().cpu().numpy(), b.get_state().cpu().numpy())
+    assert loss == loss_b
+
+
+def test_bf16_refits_on_two_streams_at_once(G):
+    """Two crews may share the chip, and a die: each refit ends as it does alone."""
+    import torch
+    widths, n, mb, steps = [64, 256, 256, 1], 1024, 512, 24
+    _, b16, e = _pairs(n)
+    x, energy = G.bf16_dev(b16), G.to_dev(e.astype(np.float32))
+    thetas = [synth.mlp_theta(widths, 4 + i, bf16=True) for i in range(4)]
+    want = []
+    for t in thetas:
+        m = G.make_model(widths, eck.BF16, t)
+        G.update_gpu(m, x, e, steps, mb)
+        want.append(m.get_state().cpu().numpy())
+    models = [G.make_model(widths, eck.BF16, t) for t in thetas]
+    streams = [torch.cuda.Stream() for _ in thetas]
+    ws = [torch.empty(eck.costmodel_update_workspace_bytes(m, n, mb), dtype=torch.uint8, device="cuda") for m in models]
+    out = torch.zeros(8, device="cuda")
+    torch.cuda.synchronize()
+    for i, s in enumerate(streams):
+        with torch.cuda.stream(s):
+            eck.costmodel_update(models[i], x, energy, steps, mb, out[2 * i:2 * i + 1], out[2 * i + 1:2 * i + 2], ws[i])
+    torch.cuda.synchronize()
+    for m, w in zip(models, want):
+        assert np.array_equal(m.get_state().cpu().numpy(), w)
