@@ -62,6 +62,7 @@ struct eck_model {
     float *d_state = nullptr;    // [theta | m | v | t]  (3P+1 floats)
     void *d_packed = nullptr;    // weights in matrix-core fragment order; BF16: + bias/output vectors, fp32: in three parts
     uint64_t packed_bytes = 0;
+    float *d_copies = nullptr;   // fp32 models whose refits run by a crew: the weights as its steps read them (behind d_packed)
     int device = -1;
 };
 
@@ -155,6 +156,9 @@ int32_t refit_steps(const eck_model *m, const void *feat, int32_t feat_dtype, ui
                     const uint32_t *bad_flag, float *loss_scalar, void *spare, void *ws, hipStream_t st);
 // the same for fp32 models of any hidden widths and minibatches of any size (refit_f32.hip)
 uint64_t refit_f32_workspace_bytes(const eck_model *m, int minibatch);
+uint64_t refit_f32_copies_bytes(const eck_model *m); // of the weights, beside the model's state
+int32_t refit_f32_begin(const eck_model *m, const float *energy, uint64_t n_pairs, float *y, RefitScalars *sc, int32_t n_steps,
+                        int32_t minibatch, void *ws, hipStream_t st);
 int32_t refit_f32_steps(const eck_model *m, const float *feat, uint64_t ld, const float *y, uint64_t n_pairs, int32_t n_steps,
                         int32_t minibatch, float lr, float beta1, float beta2, float eps, const uint32_t *bad_flag,
                         float *loss_scalar, void *ws, hipStream_t st);

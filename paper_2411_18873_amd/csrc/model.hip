@@ -247,12 +247,14 @@ extern "C" int32_t eck_model_create(int32_t n_layers, const int32_t *widths, int
         return ECK_EDEVICE;
     }
     m->packed_bytes = dtype == ECK_BF16 ? packed_layout(widths[0], widths[1], widths[2]).total : split::packed_bytes(widths[0], widths[1], widths[2]);
-    if (hipMalloc(&m->d_packed, m->packed_bytes) != hipSuccess) {
+    const uint64_t copies_at = (m->packed_bytes + 255) & ~255ull, copies = refit_f32_copies_bytes(m);
+    if (hipMalloc(&m->d_packed, copies_at + copies) != hipSuccess) {
         (void)hipGetLastError();
         (void)hipFree(m->d_state);
         delete m;
         return ECK_EDEVICE;
     }
+    if (copies) m->d_copies = reinterpret_cast<float *>(static_cast<char *>(m->d_packed) + copies_at);
     // everything zero, the packed weights too
     auto clear = [](void *p, uint64_t floats) {
         hipLaunchKernelGGL(set_state_kernel, dim3(state_blocks(floats)), dim3(256), 0, 0, (const float *)nullptr, (uint64_t)0, (float *)p, floats, PackArgs{});

@@ -362,6 +362,7 @@ extern "C" int32_t costmodel_update(eck_model *m, const void *feat, int32_t feat
     const bool two_launches = m->dtype == ECK_BF16 && refit_applies(m, feat, feat_dtype, ld, minibatch);
     int32_t rc = ECK_OK;
     if (two_launches) rc = refit_begin(m, energy_measured, n_pairs, y, sc, minibatch, base + w.refit, st);
+    else if (m->dtype == ECK_F32) rc = refit_f32_begin(m, energy_measured, n_pairs, y, sc, n_steps, minibatch, base + w.refit, st);
     else hipLaunchKernelGGL(labels_kernel, dim3(1), dim3(1024), 0, st, energy_measured, n_pairs, y, sc);
     if (rc != ECK_OK) return rc;
     // predictions of the model as it stands: the same forward pass that scores candidates

@@ -383,3 +383,18 @@ def test_bf16_refits_on_two_streams_at_once(G):
     torch.cuda.synchronize()
     for m, w in zip(models, want):
         assert np.array_equal(m.get_state().cpu().numpy(), w)
+
+
+@pytest.mark.parametrize("widths,mb,epoch", [([64, 128, 128, 1], 250, 2), ([64, 128, 128, 1], 512, 1), ([64, 17, 48, 1], 15, 2), ([32, 1, 1, 1], 1, 2),
+                                             ([32, 50, 30, 1], 497, 1), ([64, 113, 127, 1], 33, 2), ([32, 64, 64, 1], 16, 1)])
+def test_fp32_steps_of_a_crew_are_those_of_two_launches(G, widths, mb, epoch):
+    """The same for an fp32 model of up to 128 units: calls of one or two steps launch each by itself, longer ones run by a crew."""
+    f32, _, e = _pairs(mb * epoch)
+    x = G.to_dev(np.ascontiguousarray(f32[:widths[0]]))
+    theta = synth.mlp_theta(widths, 4, bias_scale=0.1)
+    a, b = G.make_model(widths, eck.F32, theta), G.make_model(widths, eck.F32, theta)
+    _, loss = G.update_gpu(a, x, e, 6, mb)
+    for _ in range(6 // epoch):
+        _, loss_b = G.update_gpu(b, x, e, epoch, mb)
+    assert np.array_equal(a.get_state().cpu().numpy(), b.get_state().cpu().numpy())
+    assert loss == loss_b
