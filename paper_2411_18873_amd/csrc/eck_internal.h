@@ -142,18 +142,17 @@ struct RefitScalars {
 // count, the call's results, and the packed weights
 int32_t refit_finish(eck_model *m, const float *pred, const float *y, uint64_t n_pairs, int32_t n_steps, const RefitScalars *sc,
                      float *snr_out, float *loss_out, hipStream_t stream);
-// Adam steps of a BF16 model in two launches per step (refit.hip): whether that path takes this call, the bytes it
-// needs behind the other buffers of costmodel_update's workspace, and the steps themselves (labels y and the
-// data-error flag come from the caller's kernels; the last step's mean loss goes to *loss_scalar, device memory; spare:
-// device memory of 4 F minibatch bytes, 256-byte aligned)
-bool refit_applies(const eck_model *m, const void *feat, int32_t feat_dtype, uint64_t ld, int minibatch);
+// Adam steps of a BF16 model in two launches per step, or all in one (refit.hip): the bytes it needs in costmodel_update's
+// workspace, those of the minibatch's features apart, and the steps themselves (labels y and the data-error flag come from
+// the caller's kernels; the last step's mean loss goes to *loss_scalar, device memory; features, ws: 256-byte aligned)
+uint64_t refit_features_bytes(const eck_model *m, int minibatch);
 uint64_t refit_workspace_bytes(const eck_model *m, int minibatch);
 // (refit_begin: labels y from the measured energies, and the weights' copies that the steps multiply with)
 int32_t refit_begin(const eck_model *m, const float *energy, uint64_t n_pairs, float *y, RefitScalars *sc, int32_t minibatch, void *ws,
                     hipStream_t st);
 int32_t refit_steps(const eck_model *m, const void *feat, int32_t feat_dtype, uint64_t ld, const float *y, uint64_t n_pairs,
                     int32_t n_steps, int32_t minibatch, float lr, float beta1, float beta2, float eps,
-                    const uint32_t *bad_flag, float *loss_scalar, void *spare, void *ws, hipStream_t st);
+                    const uint32_t *bad_flag, float *loss_scalar, void *features, void *ws, hipStream_t st);
 // the same for fp32 models of any hidden widths and minibatches of any size (refit_f32.hip)
 uint64_t refit_f32_workspace_bytes(const eck_model *m, int minibatch);
 uint64_t refit_f32_copies_bytes(const eck_model *m); // of the weights, beside the model's state

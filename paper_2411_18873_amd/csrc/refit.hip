@@ -71,7 +71,8 @@ __device__ __forceinline__ int64_t frag_at(int n, int k, int K)
 struct StepArgs {
     const void *feat;   // [F][ld] bf16 or fp32, minibatch row r = column row0 + r
     uint64_t ld, row0;
-    int rows;           // minibatch size B (a multiple of 64)
+    int rows, padded;   // minibatch size B, and the same rounded up to 64: the rows behind it are zeros
+    bool aligned;       // no such rows, and the features of four neighbouring ones are whole 8 or 16 bytes
     float *theta;       // fp32 master [theta | m | v | t], n_params = P
     uint64_t P;
     uint64_t off_w1, off_b1, off_w2, off_b2, off_w3, off_b3;
@@ -84,7 +85,7 @@ struct StepArgs {
     uint16_t *h1t;      // first hidden layer
     uint16_t *d2t;      // delta of the second hidden layer
     uint16_t *d1t;      // delta of the first hidden layer
-    uint16_t *xt;       // features (a crew's steps only)
+    uint16_t *xt;       // features
     float *h2;          // fp32 [B][H2]
     float *dy;          // fp32 [B]
     float *lterm;       // fp32 [B]  Eq.-(1) terms of the rows
@@ -179,8 +180,7 @@ constexpr size_t rows_lds_bytes()
     return (size_t)32 * ((H1 + 8) + (H2 + 8)) * sizeof(uint16_t) + (NW * 32 + 32 + NW * 32 * 33) * sizeof(float);
 }
 
-// The features and labels of 32 minibatch rows, from column `from`, by NT threads: four neighbouring rows of a feature each.
-// refit_applies asks for the alignment of these loads: ld and the base are whole 16 bytes, `from` a multiple of 32 rows.
+// The features and labels of 32 minibatch rows, from row r0, by NT threads: four neighbouring rows of a feature each.
 template <int F, bool FEAT_BF16, int NT>
 struct RowInputs {
     static constexpr int FOURS = 32 * F / 4, PER = (FOURS + NT - 1) / NT, LDX = F + 8; // LDS row stride: no conflicts
@@ -190,19 +190,40 @@ struct RowInputs {
 
     static __device__ __forceinline__ int item(int t, int k) { return min(t + k * NT, FOURS - 1); }
 
-    __device__ __forceinline__ void request(const StepArgs &a, uint64_t from, int t)
+    __device__ __forceinline__ void request(const StepArgs &a, uint64_t row0, int r0, int t) // row0: the minibatch's first column
     {
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
-            const int e = item(t, k);
-            const uint64_t at = (uint64_t)(e >> 3) * a.ld + from + 4 * (e & 7);
-            if constexpr (FEAT_BF16) x2[k] = *reinterpret_cast<const uint2 *>(reinterpret_cast<const uint16_t *>(a.feat) + at);
-            else x4[k] = *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(a.feat) + at);
+            const int e = item(t, k), row = r0 + 4 * (e & 7);
+            const uint64_t at = (uint64_t)(e >> 3) * a.ld + row0;
+            const uint16_t *f2 = reinterpret_cast<const uint16_t *>(a.feat) + at;
+            const float *f4 = reinterpret_cast<const float *>(a.feat) + at;
+            if (a.aligned) {
+                if constexpr (FEAT_BF16) x2[k] = *reinterpret_cast<const uint2 *>(f2 + row);
+                else x4[k] = *reinterpret_cast<const float4 *>(f4 + row);
+            } else { // one by one, the rows behind the minibatch from its last
+                const int last = a.rows - 1;
+                if constexpr (FEAT_BF16) {
+                    uint32_t v[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) v[u] = f2[min(row + u, last)];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) v[u] = row + u <= last ? v[u] : 0;
+                    x2[k] = make_uint2(v[0] | v[1] << 16, v[2] | v[3] << 16);
+                } else {
+                    float v[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) v[u] = f4[min(row + u, last)];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) v[u] = row + u <= last ? v[u] : 0.0f;
+                    x4[k] = make_float4(v[0], v[1], v[2], v[3]);
+                }
+            }
         }
-        y = a.y[from + (t & 31)];
+        y = a.y[row0 + min(r0 + (t & 31), a.rows - 1)];
     }
 
-    // x: [32][LDX], the rows as bf16; xt, or null: the minibatch's features in fragment order, its rows from r0
+    // x: [32][LDX], the rows as bf16; xt: the minibatch's features in fragment order, its rows from r0
     __device__ __forceinline__ void keep(const StepArgs &a, int t, uint16_t *x, uint16_t *xt, int r0) const
     {
 #pragma unroll
@@ -212,7 +233,7 @@ struct RowInputs {
             if constexpr (FEAT_BF16) two = x2[k];
             else two = make_uint2(bf16_two(x4[k].x, x4[k].y), bf16_two(x4[k].z, x4[k].w));
             put_rows4(x, LDX, 4 * (e & 7), e >> 3, two.x, two.y);
-            if (xt) store_rows4(xt, e >> 3, a.rows, r0 + 4 * (e & 7), two.x, two.y);
+            store_rows4(xt, e >> 3, a.padded, r0 + 4 * (e & 7), two.x, two.y);
         }
     }
 };
@@ -270,7 +291,7 @@ __device__ __forceinline__ void step_rows(const StepArgs &a, const uint16_t *x_l
             for (int e = 0; e < 4; ++e) v[e] = fmaxf(acc[4 * g + e] + bias1, 0.0f);
             const uint32_t lo = bf16_two(v[0], v[1]), hi = bf16_two(v[2], v[3]);
             put_rows4(h1_l, LD1, d_row(4 * g, h), col, lo, hi);
-            store_rows4(a.h1t, col, a.rows, r0 + d_row(4 * g, h), lo, hi);
+            store_rows4(a.h1t, col, a.padded, r0 + d_row(4 * g, h), lo, hi);
         }
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -313,9 +334,10 @@ __device__ __forceinline__ void step_rows(const StepArgs &a, const uint16_t *x_l
         for (int w = 1; w < H2 / 32; ++w) pred += part_l[w * 32 + tid];
         pred += bias3;
         const float d = pred - target;
-        const float g = 2.0f * d / (target * (float)a.rows);
+        const bool counts = r0 + tid < a.rows;
+        const float g = counts ? 2.0f * d / (target * (float)a.rows) : 0.0f;
         a.dy[r0 + tid] = g;
-        a.lterm[r0 + tid] = d * d / target;
+        a.lterm[r0 + tid] = counts ? d * d / target : 0.0f;
         dy_l[tid] = g;
     }
     if (FRESH && has1) fetch_fragments<H2, FRESH>(a.w2, wave, lane, wbf, 0, Fragments<H2>::EARLY / 2);
@@ -331,7 +353,7 @@ __device__ __forceinline__ void step_rows(const StepArgs &a, const uint16_t *x_l
             for (int e = 0; e < 4; ++e) v[e] = h2v[4 * g + e] > 0.0f ? row_dy[e] * w3 : 0.0f;
             const uint32_t lo = bf16_two(v[0], v[1]), hi = bf16_two(v[2], v[3]);
             put_rows4(d2_l, LD2, d_row(4 * g, h), col, lo, hi);
-            store_rows4(a.d2t, col, a.rows, r0 + d_row(4 * g, h), lo, hi);
+            store_rows4(a.d2t, col, a.padded, r0 + d_row(4 * g, h), lo, hi);
         }
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -346,7 +368,7 @@ __device__ __forceinline__ void step_rows(const StepArgs &a, const uint16_t *x_l
 #pragma unroll
             for (int e = 0; e < 4; ++e) // a ReLU output: positive unless its bits are zero
                 v[e] = h1_l[d_row(4 * g + e, h) * LD1 + col] != 0 ? acc[4 * g + e] : 0.0f;
-            store_rows4(a.d1t, col, a.rows, r0 + d_row(4 * g, h), bf16_two(v[0], v[1]), bf16_two(v[2], v[3]));
+            store_rows4(a.d1t, col, a.padded, r0 + d_row(4 * g, h), bf16_two(v[0], v[1]), bf16_two(v[2], v[3]));
         }
     }
 }
@@ -363,9 +385,9 @@ __global__ __launch_bounds__((H1 > H2 ? H1 : H2) * 2) void step_rows_kernel(Step
     }
     uint16_t *x_l = reinterpret_cast<uint16_t *>(rows_lds + rows_lds_bytes<F, H1, H2>());
     RowInputs<F, FEAT_BF16, NT> inputs;
-    inputs.request(a, a.row0 + r0, threadIdx.x);
+    inputs.request(a, a.row0, r0, threadIdx.x);
     step_rows<F, H1, H2, false>(a, x_l, r0, rows_lds, [&](int tid) {
-        inputs.keep(a, tid, x_l, nullptr, 0);
+        inputs.keep(a, tid, x_l, a.xt, r0);
         lds_barrier();
         return inputs.y;
     });
@@ -398,7 +420,7 @@ struct OutputBlock {
     __device__ __forceinline__ void sum(float *psum) // [4 wavefronts][17]
     {
         constexpr int AHEAD = FRESH ? 8 : 16; // rows under way together
-        const int lane = tid & 63, per = a.rows / 64; // the minibatch is a multiple of 64
+        const int lane = tid & 63, per = a.padded / 64;
         const uint32_t first = (uint32_t)((tid >> 2) * per), at = 4u * (first * H2 + (uint32_t)(block * 16 + 4 * (lane & 3)));
         float sums[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
         for (int r = 0; r < per; r += AHEAD) {
@@ -458,7 +480,7 @@ __device__ __forceinline__ void report_loss(const StepArgs &a, int lane)
 // eight k-steps at a time, and the Adam state of the four parameters each thread will update fetched before that --
 // the four partial tiles are added in wavefront order through LDS, then 256 threads update four parameters each.
 // The blocks of the first tile row also sum the columns of B: the bias gradient.
-template <int F, int H1, int H2, bool FEAT_BF16>
+template <int F, int H1, int H2>
 __global__ __launch_bounds__(256) void step_weights_kernel(StepArgs a)
 {
     __shared__ float part[4][16][64];   // partial tiles of the four wavefronts
@@ -466,7 +488,7 @@ __global__ __launch_bounds__(256) void step_weights_kernel(StepArgs a)
     const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, c = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     constexpr int TILES_W2 = (H1 / 32) * (H2 / 32), TILES_W1 = (F / 32) * (H1 / 32);
-    const int B = a.rows;
+    const int B = a.padded;
     const bool bad = *a.bad != 0;
     const AdamScales scales = *a.scales;
     int block = blockIdx.x;
@@ -496,9 +518,8 @@ __global__ __launch_bounds__(256) void step_weights_kernel(StepArgs a)
         }
         // A rows: hidden unit (W2) or feature (W1) 32 mt + m; B columns: unit 32 ntile + n
         const uint16_t *bsrc = (second ? a.d2t : a.d1t) + (int64_t)ntile * 32 * B + lane * 8; // fragments of tile ntile
-        const uint16_t *asrc = a.h1t + (int64_t)mt * 32 * B + lane * 8;
-        const uint64_t feat_row = (uint64_t)(32 * mt + c) * a.ld + a.row0 + 8 * h;
-        const int k0 = wave * (B / 64), k1 = k0 + B / 64; // k-steps of 16 rows; B / 64 is a multiple of... at least 1
+        const uint16_t *asrc = (second ? a.h1t : a.xt) + (int64_t)mt * 32 * B + lane * 8;
+        const int k0 = wave * (B / 64), k1 = k0 + B / 64; // k-steps of 16 rows
         f32x16 acc;
 #pragma unroll
         for (int q = 0; q < 16; ++q) acc[q] = 0.0f;
@@ -509,17 +530,7 @@ __global__ __launch_bounds__(256) void step_weights_kernel(StepArgs a)
             for (int u = 0; u < 8; ++u) {
                 const int ks = kb + u < k1 ? kb + u : k1 - 1; // clamped: every load stays inside the operands
                 bv[u] = *reinterpret_cast<const bf16x8 *>(bsrc + 512 * place(ntile, ks, B));
-                if (second) {
-                    av[u] = *reinterpret_cast<const bf16x8 *>(asrc + 512 * place(mt, ks, B));
-                } else if (FEAT_BF16) {
-                    av[u] = *reinterpret_cast<const bf16x8 *>(reinterpret_cast<const uint16_t *>(a.feat) + feat_row + 16 * ks);
-                } else {
-                    const float4 lo = *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(a.feat) + feat_row + 16 * ks);
-                    const float4 hi = *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(a.feat) + feat_row + 16 * ks + 4);
-                    const float f8[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) av[u][e] = __builtin_bit_cast(__bf16, bf16_bits(f8[e]));
-                }
+                av[u] = *reinterpret_cast<const bf16x8 *>(asrc + 512 * place(mt, ks, B));
             }
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
@@ -597,7 +608,7 @@ __device__ __forceinline__ void crew_sums(const StepArgs &a, const uint16_t *inp
                                           float *parts, float *sums)
 {
     constexpr int AHEAD = 8; // k-steps of 16 rows under way together
-    const int B = a.rows, k0 = quarter * (B / 64), k1 = k0 + B / 64;
+    const int B = a.padded, k0 = quarter * (B / 64), k1 = k0 + B / 64;
     f32x16 acc;
     float bsum = 0.0f;
 #pragma unroll
@@ -717,7 +728,7 @@ __global__ __launch_bounds__(CREW_THREADS) void steps_crew_kernel(StepArgs a, Cr
     Crew crew;
     if (!crew.join(state, reinterpret_cast<uint32_t *>(crew_lds))) return;
     __syncthreads(); // (the words are read)
-    const int rank = (int)crew.rank, members = (int)crew.size, row_blocks = a.rows / 32;
+    const int rank = (int)crew.rank, members = (int)crew.size, row_blocks = a.padded / 32;
     // The rows' features and labels come from memory, some 2 us: the wavefronts that have no tile of a layer fetch those of a
     // member's first rows of a step during the step before, into the other half of the buffers.
     constexpr int STAGERS = CREW_THREADS - CREW_MAIN;
@@ -725,17 +736,17 @@ __global__ __launch_bounds__(CREW_THREADS) void steps_crew_kernel(StepArgs a, Cr
     auto x_of = [&](int step) { return reinterpret_cast<uint16_t *>(crew_lds + Cut::PHASE_LDS) + (step & 1) * (32 * Inputs::LDX); };
     AdamScales *scales_of = reinterpret_cast<AdamScales *>(crew_lds + Cut::LDS - sizeof(AdamScales)); // of the step, in its weights' phase
     auto y_of = [&](int step) { return reinterpret_cast<float *>(crew_lds + Cut::PHASE_LDS + 2 * 32 * Inputs::LDX * sizeof(uint16_t)) + (step & 1) * 32; };
-    auto xt_of = [&](int step) { return a.xt + (step & 1) * ((uint64_t)F * a.rows); };
-    auto stage = [&](int step, uint64_t from, int r0, int t) { // by threads t = 0 .. STAGERS - 1
+    auto xt_of = [&](int step) { return a.xt + (step & 1) * ((uint64_t)F * a.padded); };
+    auto stage = [&](int step, uint64_t row0, int r0, int t) { // by threads t = 0 .. STAGERS - 1
         Inputs inputs;
-        inputs.request(a, from, t);
+        inputs.request(a, row0, r0, t);
         inputs.keep(a, t, x_of(step), xt_of(step), r0);
         if (t < 32) y_of(step)[t] = inputs.y;
     };
     uint64_t row0 = 0;
     if (rank < row_blocks) {
         const int t = crew_thread() - CREW_MAIN;
-        if (t >= 0) stage(0, 32 * rank, 32 * rank, t);
+        if (t >= 0) stage(0, 0, 32 * rank, t);
         lds_barrier();
     }
     for (int step = 0; step < n_steps; ++step) {
@@ -745,13 +756,13 @@ __global__ __launch_bounds__(CREW_THREADS) void steps_crew_kernel(StepArgs a, Cr
             const int tid = crew_thread(), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
             if (i != rank) { // (a small crew)
                 lds_barrier();
-                if (wave >= CREW_MAIN / 64) stage(step, row0 + 32 * i, 32 * i, tid - CREW_MAIN);
+                if (wave >= CREW_MAIN / 64) stage(step, row0, 32 * i, tid - CREW_MAIN);
                 lds_barrier();
             }
             if (wave < Cut::ROW_WAVES) {
                 step_rows<F, H1, H2, true>(a, x_of(step), 32 * i, crew_lds, [&](int tid) { return y_of(step)[tid & 31]; });
             } else {
-                if (wave >= CREW_MAIN / 64 && i == rank && step + 1 < n_steps) stage(step + 1, next_row0 + 32 * i, 32 * i, tid - CREW_MAIN);
+                if (wave >= CREW_MAIN / 64 && i == rank && step + 1 < n_steps) stage(step + 1, next_row0, 32 * i, tid - CREW_MAIN);
                 for (int barrier = 0; barrier < ROWS_BARRIERS; ++barrier) lds_barrier();
             }
         }
@@ -852,12 +863,12 @@ int32_t launch_steps(const eck_model *m, StepArgs a, int32_t feat_dtype, int32_t
     constexpr int NW = (H1 > H2 ? H1 : H2) / 32;
     constexpr size_t lds = rows_lds_bytes<F, H1, H2>() + 32 * (F + 8) * sizeof(uint16_t);
     auto rows_kernel = feat_dtype == ECK_BF16 ? step_rows_kernel<F, H1, H2, true> : step_rows_kernel<F, H1, H2, false>;
-    auto weights_kernel = feat_dtype == ECK_BF16 ? step_weights_kernel<F, H1, H2, true> : step_weights_kernel<F, H1, H2, false>;
+    auto weights_kernel = step_weights_kernel<F, H1, H2>;
     ECK_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(rows_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                     (int)lds));
     const int B = a.rows;
     if constexpr (H1 <= 256 && H2 <= 256) {
-        if (crew_takes(B, n_steps, H1 > H2 ? H1 : H2)) {
+        if (crew_takes(a.padded, n_steps, H1 > H2 ? H1 : H2)) {
             constexpr size_t crew_lds = CrewCut<F, H1, H2>::LDS;
             auto crew_kernel = feat_dtype == ECK_BF16 ? steps_crew_kernel<F, H1, H2, true> : steps_crew_kernel<F, H1, H2, false>;
             ECK_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(crew_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)crew_lds));
@@ -875,7 +886,7 @@ int32_t launch_steps(const eck_model *m, StepArgs a, int32_t feat_dtype, int32_t
         a.step_in_call = s;
         a.report_loss = s == n_steps - 1;
         a.loss_out = loss_scalar;
-        hipLaunchKernelGGL(rows_kernel, dim3(B / 32 + 1), dim3(NW * 64), lds, st, a);
+        hipLaunchKernelGGL(rows_kernel, dim3(a.padded / 32 + 1), dim3(NW * 64), lds, st, a);
         hipLaunchKernelGGL(weights_kernel, dim3(weight_blocks), dim3(256), 0, st, a);
     }
     (void)m;
@@ -885,28 +896,23 @@ int32_t launch_steps(const eck_model *m, StepArgs a, int32_t feat_dtype, int32_t
 
 } // namespace
 
+static int padded_rows(int minibatch) { return (minibatch + 63) / 64 * 64; }
+
+uint64_t eck::refit_features_bytes(const eck_model *m, int minibatch) { return 4ull * m->widths[0] * padded_rows(minibatch); }
+
 uint64_t eck::refit_workspace_bytes(const eck_model *m, int minibatch)
 {
     auto align = [](uint64_t v) { return (v + 255) & ~255ull; };
-    const uint64_t F = m->widths[0], H1 = m->widths[1], H2 = m->widths[2], B = (uint64_t)minibatch;
+    const uint64_t F = m->widths[0], H1 = m->widths[1], H2 = m->widths[2], B = (uint64_t)padded_rows(minibatch);
     return align(F * H1 * 2) + align(H1 * H2 * 2) * 2 + align(H1 * B * 2) * 2 + align(H2 * B * 2) + align(B * H2 * 4) +
            align(B * 4) * 2 + 256;
-}
-
-bool eck::refit_applies(const eck_model *m, const void *feat, int32_t feat_dtype, uint64_t ld, int minibatch)
-{
-    if (m->dtype != ECK_BF16 || minibatch % 64) return false;
-    // the weights kernel reads eight consecutive rows of a feature with 16-byte loads
-    const uint64_t elem = feat_dtype == ECK_BF16 ? 2 : 4;
-    if ((ld * elem) % 16 || ((uintptr_t)feat & 15)) return false;
-    return m->widths[0] % 32 == 0; // tiles of W1 are 32 features tall
 }
 
 // the buffers of a call's steps in its workspace, and the model's own
 static StepArgs step_buffers(const eck_model *m, int32_t minibatch, void *ws)
 {
     auto align = [](uint64_t v) { return (v + 255) & ~255ull; };
-    const uint64_t F = m->widths[0], H1 = m->widths[1], H2 = m->widths[2], B = (uint64_t)minibatch;
+    const uint64_t F = m->widths[0], H1 = m->widths[1], H2 = m->widths[2], B = (uint64_t)padded_rows(minibatch);
     char *p = static_cast<char *>(ws);
     auto take = [&](uint64_t bytes) {
         char *at = p;
@@ -915,6 +921,7 @@ static StepArgs step_buffers(const eck_model *m, int32_t minibatch, void *ws)
     };
     StepArgs a = {};
     a.rows = minibatch;
+    a.padded = padded_rows(minibatch);
     a.theta = m->d_state;
     a.P = m->n_params;
     a.off_w1 = m->off_w[0];
@@ -952,11 +959,13 @@ int32_t eck::refit_begin(const eck_model *m, const float *energy, uint64_t n_pai
 
 int32_t eck::refit_steps(const eck_model *m, const void *feat, int32_t feat_dtype, uint64_t ld, const float *y, uint64_t n_pairs,
                          int32_t n_steps, int32_t minibatch, float lr, float beta1, float beta2, float eps,
-                         const uint32_t *bad_flag, float *loss_scalar, void *spare, void *ws, hipStream_t st)
+                         const uint32_t *bad_flag, float *loss_scalar, void *features, void *ws, hipStream_t st)
 {
     const int F = m->widths[0], H1 = m->widths[1], H2 = m->widths[2];
     StepArgs a = step_buffers(m, minibatch, ws);
-    a.xt = static_cast<uint16_t *>(spare);
+    a.xt = static_cast<uint16_t *>(features);
+    const uint64_t elem = feat_dtype == ECK_BF16 ? 2 : 4;
+    a.aligned = a.padded == minibatch && ld * elem % 16 == 0 && ((uintptr_t)feat & 15) == 0;
     a.feat = feat;
     a.ld = ld;
     a.y = y;

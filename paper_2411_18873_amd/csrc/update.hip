@@ -2,10 +2,11 @@
 // Adam on the weighted squared error of Eq. (1)  (Alg. 1: ModelUpdate, SNR;
 // Sec. 6.4).  HIP, gfx950.
 //
-// The steps of fp32 models, and of BF16 models whose minibatch is a multiple of
-// 64 rows, take two launches each (refit_f32.hip, refit.hip).  Here are the
-// labels, the SNR, and the steps of the other BF16 minibatches: a short chain of
-// launches of one strided tile GEMM on the matrix cores (forward, the three
+// The steps of fp32 models, and of BF16 models but for the smallest ragged
+// minibatches, take two launches each or all run in one (refit_f32.hip,
+// refit.hip).  Here are the labels, the SNR, and the steps of those minibatches,
+// whose workspace has no room for the others' buffers (some of up to 139 rows that
+// are no multiple of 64): a short chain of launches of one strided tile GEMM on the matrix cores (forward, the three
 // weight-gradient products with the bias gradient folded in as an extra all-ones
 // row, the two back-propagated deltas; bf16 operands, weights, activations and
 // back-propagated deltas rounded as they are staged, fp32 accumulation), a
@@ -305,10 +306,23 @@ UpdWs upd_layout(const eck_model *m, uint64_t n_pairs, int mb)
     w.d2 = o;      o = align(o + (uint64_t)mb * m->widths[2] * 4);
     w.d1 = o;      o = align(o + (uint64_t)mb * m->widths[1] * 4);
     w.grad = o;    o = align(o + m->n_params * 4);
-    w.refit = o;   // the two-launch step of BF16 models keeps its own buffers behind the others
+    w.refit = o;   // refit.hip's steps of minibatches of 64s keep their own buffers behind the others
     if (mb % 64 == 0) o += refit_workspace_bytes(m, mb);
     w.total = o;
     return w;
+}
+
+struct RefitPlace {
+    bool applies;
+    uint64_t ws, features;
+};
+
+RefitPlace refit_place(const eck_model *m, const UpdWs &w, int mb)
+{
+    if (m->dtype != ECK_BF16) return {false, 0, 0};
+    if (mb % 64 == 0) return {true, w.refit, w.h1};
+    const uint64_t features = w.h1 + refit_workspace_bytes(m, mb);
+    return {features + refit_features_bytes(m, mb) <= w.total, w.h1, features};
 }
 
 // One launch for one product, or for two products that do not depend on each other (grid.z = 2).
@@ -359,9 +373,13 @@ extern "C" int32_t costmodel_update(eck_model *m, const void *feat, int32_t feat
     float *theta = m->d_state;
     const int elem = feat_dtype == ECK_BF16 ? 2 : 4;
 
-    const bool two_launches = m->dtype == ECK_BF16 && refit_applies(m, feat, feat_dtype, ld, minibatch);
+    // Steps by refit.hip: minibatches of 64s have a place for its buffers, the features' where a launch-per-product step would
+    // keep the first layer; others where all that such a step keeps is enough, all from 80 rows of 256 units or 140 of 64 on.  8 steps
+    // of 250 rows (replayed graphs), product by product and so: 64-256-256 553 and 108.7 us, 32-64-64 460 and 67.0.
+    const RefitPlace place = refit_place(m, w, minibatch);
+    const bool two_launches = place.applies;
     int32_t rc = ECK_OK;
-    if (two_launches) rc = refit_begin(m, energy_measured, n_pairs, y, sc, minibatch, base + w.refit, st);
+    if (two_launches) rc = refit_begin(m, energy_measured, n_pairs, y, sc, minibatch, base + place.ws, st);
     else if (m->dtype == ECK_F32) rc = refit_f32_begin(m, energy_measured, n_pairs, y, sc, n_steps, minibatch, base + w.refit, st);
     else hipLaunchKernelGGL(labels_kernel, dim3(1), dim3(1024), 0, st, energy_measured, n_pairs, y, sc);
     if (rc != ECK_OK) return rc;
@@ -370,7 +388,7 @@ extern "C" int32_t costmodel_update(eck_model *m, const void *feat, int32_t feat
     if (rc != ECK_OK) return rc;
     if (two_launches || m->dtype == ECK_F32) {
         rc = two_launches ? refit_steps(m, feat, feat_dtype, ld, y, n_pairs, n_steps, minibatch, lr, beta1, beta2, eps, &sc->bad,
-                                        &sc->loss, h1, base + w.refit, st)
+                                        &sc->loss, base + place.features, base + place.ws, st)
                           : refit_f32_steps(m, static_cast<const float *>(feat), ld, y, n_pairs, n_steps, minibatch, lr, beta1, beta2,
                                             eps, &sc->bad, &sc->loss, base + w.refit, st);
         if (rc != ECK_OK) return rc;

@@ -343,6 +343,7 @@ def test_data_error_leaves_an_fp32_model_alone(G, widths, minibatch):
 @pytest.mark.parametrize("widths,mb,n_pairs,feat", [
     ([64, 256, 256, 1], 64, 64, "bf16"), ([64, 256, 256, 1], 1024, 1024, "f32"), ([64, 256, 256, 1], 192, 576, "bf16"),
     ([64, 128, 128, 1], 2048, 2048, "bf16"), ([64, 128, 128, 1], 448, 896, "f32"), ([32, 64, 64, 1], 320, 640, "bf16"),
+    ([64, 256, 256, 1], 250, 500, "bf16"), ([64, 128, 128, 1], 333, 666, "f32"), ([32, 64, 64, 1], 201, 402, "bf16"),
     ([32, 64, 64, 1], 2048, 2048, "f32")])
 def test_bf16_steps_of_a_crew_are_those_of_two_launches(G, widths, mb, n_pairs, feat):
     """Calls of a few steps launch each step by itself, longer ones run all steps in one launch on one die: the same bits,
@@ -358,6 +359,15 @@ def test_bf16_steps_of_a_crew_are_those_of_two_launches(G, widths, mb, n_pairs, 
         _, loss_b = G.update_gpu(b, x, e, epoch, mb)
     assert np.array_equal(a.get_state().cpu().numpy(), b.get_state().cpu().numpy())
     assert loss == loss_b
+
+
+@pytest.mark.parametrize("widths,mb,ld_extra", [([64, 256, 256, 1], 250, 2), ([64, 128, 128, 1], 333, 4), ([32, 64, 64, 1], 201, 2),
+                                                ([64, 512, 512, 1], 129, 0), ([64, 256, 256, 1], 65, 6), ([64, 128, 128, 1], 128, 2),
+                                                ([64, 256, 256, 1], 20, 2)])
+def test_bf16_refit_of_ragged_minibatches(G, widths, mb, ld_extra):
+    """Minibatches that are no multiple of 64, and features that are not whole 16 bytes apart: rows past the minibatch count
+    for nothing.  The last is so small that its steps run product by product."""
+    test_bf16_refit_rows_past_a_threads_32(G, widths, mb, ld_extra)
 
 
 def test_bf16_refits_on_two_streams_at_once(G):
