@@ -811,7 +811,8 @@ __device__ __forceinline__ uint64_t floor_div_f64(uint64_t a, uint64_t b)
 constexpr uint32_t kFeatBlock = 1024;
 
 // WANT_X: the transformed features are wanted (feat_out is not NULL; without them OUT_DTYPE means nothing).
-template <int OUT_DTYPE, bool TABLES_IN_LDS, int N_FEAT, bool WANT_RAW, bool XRED, bool WANT_X>
+// STREAM: they are stored past the caches (streams_features).
+template <int OUT_DTYPE, bool TABLES_IN_LDS, int N_FEAT, bool WANT_RAW, bool XRED, bool WANT_X, bool STREAM>
 __global__ __launch_bounds__(kFeatBlock) void features_kernel(SpaceBatch spaces, const uint16_t *__restrict__ genes,
                                                        uint64_t ld, uint64_t n, void *__restrict__ feat_out,
                                                        uint64_t *__restrict__ raw_out,
@@ -933,15 +934,18 @@ __global__ __launch_bounds__(kFeatBlock) void features_kernel(SpaceBatch spaces,
         row += stride;
         asm volatile("" : "+s"(row));
     };
-    // (a scalar base plus a 32-bit lane offset: the store's address costs no vector instruction; the stores are
-    // marked non-temporal: the matrix is far larger than the caches and is read by a later kernel, and streaming
-    // writes that need no place in the L2 take the kernel from 0.49 to 0.39 ms per 2^24 candidates)
+    // (a scalar base plus a 32-bit lane offset: the store's address costs no vector instruction)
     auto at = [&](uint64_t row, uint32_t lane_bytes) { return reinterpret_cast<global_byte *>(row) + lane_bytes; };
+    auto put = [&](uint64_t row, auto v) {
+        auto *to = reinterpret_cast<__attribute__((address_space(1))) decltype(v) *>(at(row, lane_x));
+        if constexpr (STREAM) __builtin_nontemporal_store(v, to);
+        else *to = v;
+    };
     auto store_x = [&](int f, float x) {
         if (!WANT_X) return;
         uint64_t &row = f < 32 ? feat_row : feat_row_upper;
         if (OUT_DTYPE == ECK_F32) {
-            __builtin_nontemporal_store(x, reinterpret_cast<__attribute__((address_space(1))) float *>(at(row, lane_x)));
+            put(row, x);
             next_row(row, feat_stride);
         } else if (!(f & 1)) {
             held = x;
@@ -950,9 +954,9 @@ __global__ __launch_bounds__(kFeatBlock) void features_kernel(SpaceBatch spaces,
             typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
             const float2_t both = {held, x};
             const uint32_t packed = __builtin_bit_cast(uint32_t, __builtin_convertvector(both, bf16x2_t));
-            __builtin_nontemporal_store((uint16_t)packed, reinterpret_cast<__attribute__((address_space(1))) uint16_t *>(at(row, lane_x)));
+            put(row, (uint16_t)packed);
             next_row(row, feat_stride);
-            __builtin_nontemporal_store((uint16_t)(packed >> 16), reinterpret_cast<__attribute__((address_space(1))) uint16_t *>(at(row, lane_x)));
+            put(row, (uint16_t)(packed >> 16));
             next_row(row, feat_stride);
         }
     };
@@ -1162,6 +1166,20 @@ __global__ __launch_bounds__(kFeatBlock) void features_kernel(SpaceBatch spaces,
 } // namespace
 
 namespace {
+// Whether features are stored past the caches.  Such stores leave the caches at once, a wavefront's 128 or 256 bytes of a row by
+// themselves, so where they do not start on 64 bytes, their ends are written to memory as pieces, twice: every column a
+// wavefront starts at has to lie there in every row.  Whole pieces of bfloat16 stream as they come; of fp32 a matrix of some 50 MB
+// and more goes through the caches in better order.  us, streamed / through the caches, one space, 64 features:
+//   rows on 128 bytes: fp32 131072 candidates 10.4 / 10.8, 229376 11.9 / 12.4, 262144 14.4 / 13.8, 524288 26.7 / 22.8, 2^20 58 / 45;
+//     bfloat16 262144 10.1 / 11.2, 2^20 26.1 / 28.3, 2^22 109 / 148
+//   8 bytes beside them: fp32 20482 9.05 / 8.54, 260001 23.5 / 14.2, 2^20 + 2 143 / 52; bfloat16 (4 bytes) 524290 34.8 / 17.8, 2^20 + 2 87 / 31
+bool streams_features(const void *feat_out, uint64_t ld, uint64_t n, uint32_t n_spaces, int32_t n_feat, uint64_t elem)
+{
+    constexpr uint64_t PIECE = 64, MOST_F32 = 49ull << 20;
+    if (((uintptr_t)feat_out | (ld * elem) | (n_spaces > 1 ? n * elem : 0)) % PIECE) return false;
+    return elem == 2 || n * n_spaces * n_feat * elem < MOST_F32;
+}
+
 int32_t features_launch(const eck_space *const *spaces, uint32_t n_spaces, const uint16_t *genes, uint64_t ld,
                         uint64_t n, int32_t n_feat, int32_t out_dtype, void *feat_out, uint64_t *raw_out,
                         uint8_t *legal_out, void *stream)
@@ -1188,14 +1206,18 @@ int32_t features_launch(const eck_space *const *spaces, uint32_t n_spaces, const
     const dim3 block(kFeatBlock), grid((unsigned)((n + kFeatBlock - 1) / kFeatBlock), n_spaces);
     hipStream_t st = as_stream(stream);
     const bool raw = raw_out != nullptr;
+    const bool stream_out = streams_features(feat_out, ld, n, n_spaces, n_feat, out_dtype == ECK_F32 ? 4 : 2);
 #define ECK_LAUNCH_FEATURES(DT, INLDS, NF, RAW, XR)                                                                 \
     do {                                                                                                           \
-        if (feat_out)                                                                                              \
-            hipLaunchKernelGGL((features_kernel<DT, INLDS, NF, RAW, XR, true>), grid, block, lds, st, batch, genes, ld, \
-                               n, feat_out, raw_out, legal_out, spaces[0]->prm.n_genes);                           \
-        else                                                                                                       \
-            hipLaunchKernelGGL((features_kernel<ECK_F32, INLDS, NF, RAW, XR, false>), grid, block, lds, st, batch,   \
+        if (feat_out && stream_out)                                                                                \
+            hipLaunchKernelGGL((features_kernel<DT, INLDS, NF, RAW, XR, true, true>), grid, block, lds, st, batch,  \
                                genes, ld, n, feat_out, raw_out, legal_out, spaces[0]->prm.n_genes);                \
+        else if (feat_out)                                                                                         \
+            hipLaunchKernelGGL((features_kernel<DT, INLDS, NF, RAW, XR, true, false>), grid, block, lds, st, batch, \
+                               genes, ld, n, feat_out, raw_out, legal_out, spaces[0]->prm.n_genes);                \
+        else                                                                                                       \
+            hipLaunchKernelGGL((features_kernel<ECK_F32, INLDS, NF, RAW, XR, false, false>), grid, block, lds, st,  \
+                               batch, genes, ld, n, feat_out, raw_out, legal_out, spaces[0]->prm.n_genes);         \
     } while (0)
 #define ECK_PICK_RAW(DT, INLDS, NF)                    \
     do {                                               \

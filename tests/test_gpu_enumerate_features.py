@@ -515,3 +515,29 @@ def test_dedup_of_genes_chosen_against_the_parts(G, n, n_genes, distinct):
     torch.cuda.synchronize()
     assert np.array_equal(flags.cpu().numpy(), want)
     assert bool((ws[-256:] == 255).all())
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_features_streamed_and_through_the_caches(G, dtype):
+    """Rows that start on 64 bytes are stored past the caches (of fp32 as long as the matrix is small), others through them:
+    the same values, nothing beside the columns asked for, and the oracle's at both ends."""
+    import torch
+    mine, ref = _spaces("c2", eck.SPACE_SPLIT)
+    code, kind = (eck.F32, torch.float32) if dtype == "f32" else (eck.BF16, torch.bfloat16)
+    n = 201600  # fp32: past the line; rows of either type a multiple of 64 bytes
+    genes = torch.zeros((mine.n_genes, n), dtype=torch.int16, device="cuda")
+    eck.candidate_enumerate(mine, eck.MODE_SAMPLE, n, genes, seed=7)
+    whole = torch.full((64, n), -1.0, dtype=kind, device="cuda")
+    eck.features_compute(mine, genes, n, 64, code, feat_out=whole)
+    for col0, part in ((0, 1000), (0, 190001), (2, n - 2), (33, 4097)):
+        got = torch.full((64, n), -1.0, dtype=kind, device="cuda")
+        eck.features_compute(mine, genes, part, 64, code, feat_out=got, col0=col0)
+        assert torch.equal(got[:, col0:col0 + part], whole[:, col0:col0 + part])
+        assert bool((got[:, :col0] == -1.0).all()) and bool((got[:, col0 + part:] == -1.0).all())
+    for at in (0, n - 1500):
+        _, want, bits, _ = oracle.features(ref, np.ascontiguousarray(genes[:, at:at + 1500].cpu().numpy().view(np.uint16)), 64)
+        mine_bits = whole[:, at:at + 1500].contiguous().cpu()
+        if dtype == "f32":
+            assert np.array_equal(mine_bits.numpy(), want)
+        else:
+            assert np.array_equal(mine_bits.view(torch.int16).numpy().view(np.uint16), bits)
