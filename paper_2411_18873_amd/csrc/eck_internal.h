@@ -33,7 +33,7 @@ struct SpaceParams {
     uint32_t hw_num_cu, hw_wave, hw_lds_bytes, hw_max_threads_cu, hw_max_blocks_cu;
     int32_t vec_axis;          // spatial axis whose innermost level is contiguous in memory
     uint64_t true_out, true_red, flop_useful, compulsory_bytes, compulsory_in_bytes;
-    uint32_t const_q10[6];     // transformed per-space constants: features 0, 22, 60, 61, 62, 63
+    float const_x[6];          // transformed per-space constants: features 0, 22, 60, 61, 62, 63
 };
 
 // bytes before the tables in a space's device copy

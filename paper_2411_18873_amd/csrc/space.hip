@@ -181,7 +181,7 @@ extern "C" int32_t eck_space_create(const eck_problem *pb, int32_t kind, eck_spa
     {
         const uint64_t constants[6] = {p.flop_useful, p.compulsory_bytes, p.elem_bytes, (uint64_t)p.op, p.true_out,
                                        p.true_red};
-        for (int c = 0; c < 6; ++c) p.const_q10[c] = log2_q10(constants[c] + 1);
+        for (int c = 0; c < 6; ++c) p.const_x[c] = (float)log2_q10(constants[c] + 1) * (1.0f / 1024.0f); // exact: below 2^16
     }
 
     eck_space *sp = new (std::nothrow) eck_space();
@@ -796,15 +796,20 @@ __device__ __forceinline__ float log2_fixed(double v, float bias)
     return __builtin_fmaf(biased, 1.0f / 1024.0f, bias);
 }
 
-// floor(a / b) for a < 2^53, 0 < b < 2^53 through one IEEE double division: both conversions are exact
-// and the correctly rounded quotient can exceed the true one only by rounding up across an integer, so
-// one downward correction suffices.  (A 64-bit integer division costs several times more instructions.)
-__device__ __forceinline__ uint64_t floor_div_f64(uint64_t a, uint64_t b)
+// Whole numbers below 2^53 are kept as doubles where they may pass 2^32: sums, products and scalings by powers of two of
+// them are exact, one instruction each, and the logarithm wants a double anyway (64-bit integer products take three
+// instructions, their conversions four; as integers these features' kernel issued a fifth more vector instructions).
+
+// floor(a / b) through one IEEE division: the correctly rounded quotient can exceed the true one only by rounding up across a
+// whole number, so one downward correction suffices.
+__device__ __forceinline__ double floor_div(double a, double b)
 {
-    uint64_t q = (uint64_t)((double)a / (double)b);
-    if (q * b > a) --q;
-    return q;
+    const double q = __builtin_floor(a / b);
+    return __builtin_fma(-q, b, a) < 0.0 ? q - 1.0 : q;
 }
+
+// ceil(a / 2^k)
+__device__ __forceinline__ double ceil_shift(double a, int k) { return __builtin_ceil(__builtin_ldexp(a, -k)); }
 
 // Threads, and candidates, per block of the feature kernel.  1024 measured 9 % faster than 256 on the
 // benchmark workload (the tables are staged once per 1024 candidates and a block writes 2 KB of every row).
@@ -929,7 +934,7 @@ __global__ __launch_bounds__(kFeatBlock) void features_kernel(SpaceBatch spaces,
     // instead of all coming in its last third.
     uint64_t feat_row_upper = feat_row + 32 * feat_stride;
     uint64_t raw_row_upper = raw_row + 32 * (ld * 8);
-    const uint32_t lane_x = threadIdx.x * (OUT_DTYPE == ECK_F32 ? 4 : 2), lane_raw = threadIdx.x * 8;
+    uint32_t lane_x = threadIdx.x * (OUT_DTYPE == ECK_F32 ? 4 : 2), lane_raw = threadIdx.x * 8;
     auto next_row = [&](uint64_t &row, uint64_t stride) {
         row += stride;
         asm volatile("" : "+s"(row));
@@ -970,17 +975,17 @@ __global__ __launch_bounds__(kFeatBlock) void features_kernel(SpaceBatch spaces,
     auto emit_const = [&](int f, int slot, uint64_t raw) {
         if (f >= N_FEAT) return;
         store_raw(f, raw);
-        store_x(f, (float)p.const_q10[slot] * (1.0f / 1024.0f)); // exact: below 2^16
+        store_x(f, p.const_x[slot]);
     };
     auto emit32 = [&](int f, uint32_t raw) {
         if (f >= N_FEAT) return;
         store_raw(f, raw);
         store_x(f, log2_fixed((double)(raw + 1), bias)); // raw <= 2^32 - 2 by the limits checked at space creation
     };
-    auto emit64 = [&](int f, uint64_t raw) {
+    auto emit_whole = [&](int f, double raw) {
         if (f >= N_FEAT) return;
-        store_raw(f, raw);
-        store_x(f, log2_fixed(__builtin_fma((double)(uint32_t)(raw >> 32), 4294967296.0, (double)(uint32_t)raw + 1.0), bias));
+        if (WANT_RAW) store_raw(f, (uint64_t)raw);
+        store_x(f, log2_fixed(raw + 1.0, bias));
     };
 
     // ---- derived quantities
@@ -1003,7 +1008,7 @@ __global__ __launch_bounds__(kFeatBlock) void features_kernel(SpaceBatch spaces,
     const bool conv = p.op == ECK_OP_CONV2D;
 
     uint32_t fp_a, fp_b, thr_a, thr_b;
-    uint64_t halo_q8;
+    double halo_q8;
     if (conv) {
         const uint32_t in_h = (tile[2] - 1) * p.stride + p.R, in_w = (tile[3] - 1) * p.stride + p.S;
         const uint32_t patch = in_h * in_w;
@@ -1011,13 +1016,13 @@ __global__ __launch_bounds__(kFeatBlock) void features_kernel(SpaceBatch spaces,
         fp_b = tile[1] * tile[4] * rs;
         thr_a = per_thread[0] * per_thread[2] * per_thread[3];
         thr_b = per_thread[1];
-        halo_q8 = floor_div_f64((uint64_t)patch << 8, tile[2] * tile[3]); // numerator < 2^40
+        halo_q8 = floor_div((double)patch * 256.0, (double)(tile[2] * tile[3]));
     } else {
         fp_a = tile[0] * tile[1] * tile[4];
         fp_b = tile[0] * tile[2] * tile[4];
         thr_a = per_thread[0] * per_thread[1];
         thr_b = per_thread[0] * per_thread[2];
-        halo_q8 = 256;
+        halo_q8 = 256.0;
     }
     const uint32_t fp = fp_a + fp_b;
 
@@ -1031,19 +1036,19 @@ __global__ __launch_bounds__(kFeatBlock) void features_kernel(SpaceBatch spaces,
         for (int a = 0; a < NAX; ++a) emit32(52 + a, tile[a]);
         emit32(57, fp_a);
         emit32(58, fp_b);
-        emit64(59, halo_q8);
+        emit_whole(59, halo_q8);
         emit_const(60, 2, p.elem_bytes);
         emit_const(61, 3, (uint64_t)p.op);
         emit_const(62, 4, p.true_out);
         emit_const(63, 5, p.true_red);
     }
 
-    const uint64_t padded_out = (uint64_t)grid_threads * outs_thread;
-    const uint64_t st_sectors = (padded_out * p.elem_bytes + 31) >> 5;
+    const double outs = (double)outs_thread, all_blocks_threads = (double)grid_threads, elem_bytes = (double)p.elem_bytes;
+    const double padded_out = all_blocks_threads * outs;
+    const double st_sectors = ceil_shift(padded_out * elem_bytes, 5);
 
     // ---- what depends on where the reduction runs
-    uint64_t block_threads, smem_bytes, ld_bytes, flop_exec, fma_thread, int_ops, ld_instr, shared_st_tx, shared_ld;
-    uint64_t waves_block;
+    double block_threads, smem_bytes, ld_bytes, flop_exec, fma_thread, int_ops, ld_instr, shared_st_tx, shared_ld, waves_block;
     uint32_t blocks_cu;
     if (XRED) {
         // the reduction axis's second level is spread over threads; nothing is staged, every thread loads its
@@ -1059,44 +1064,45 @@ __global__ __launch_bounds__(kFeatBlock) void features_kernel(SpaceBatch spaces,
             elems_a = thr_a * kser;
             elems_b = thr_b * kser;
         }
-        const uint64_t elems = (uint64_t)elems_a + elems_b;
-        const uint64_t loads_thread_stage = (elems + vec - 1) >> lvv;
-        const uint64_t all_threads = (uint64_t)grid_threads * kt; // grid * block
+        const uint32_t elems = elems_a + elems_b;
+        const double loads_thread_stage = ceil_shift((double)elems, (int)lvv);
+        const double all_threads = all_blocks_threads * (double)kt; // grid * block
+        const double all_stages = all_threads * (double)stages;
         const uint32_t tree_steps = kt > 1 ? 32u - (uint32_t)__clz((int)(kt - 1)) : 0u;
-        block_threads = (uint64_t)threads * kt;
-        smem_bytes = kt > 1 ? block_threads * outs_thread * 4 : 0; // fp32 partial sums
-        ld_bytes = all_threads * stages * elems * p.elem_bytes;
-        flop_exec = 2 * all_threads * outs_thread * red_thread + padded_out * (kt - 1);
-        fma_thread = (uint64_t)outs_thread * red_thread;
-        int_ops = all_threads * ((uint64_t)stages * (4 * loads_thread_stage + 2) +
-                                 2ull * ((red_thread + unroll - 1) >> lu) + 2ull * tree_steps);
-        ld_instr = all_threads * stages * loads_thread_stage;
-        shared_st_tx = kt > 1 ? (padded_out * (2ull * kt - 1) * 4 + 127) >> 7 : 0;
-        shared_ld = padded_out * 2 * (kt - 1);
-        waves_block = floor_div_f64(block_threads + p.hw_wave - 1, p.hw_wave); // block_threads < 2^48
-        blocks_cu = block_threads > p.hw_max_threads_cu ? 0u : p.hw_max_threads_cu / (uint32_t)block_threads;
+        block_threads = (double)threads * (double)kt;
+        smem_bytes = kt > 1 ? block_threads * (4.0 * outs) : 0.0; // fp32 partial sums
+        ld_bytes = all_stages * (double)elems * elem_bytes;
+        fma_thread = outs * (double)red_thread;
+        flop_exec = 2.0 * all_threads * fma_thread + padded_out * (double)(kt - 1);
+        // (twice the steps of the loop and of the tree, below 2^32)
+        int_ops = all_threads * ((double)stages * (4.0 * loads_thread_stage + 2.0) +
+                                 (double)(2 * (((red_thread + unroll - 1) >> lu) + tree_steps)));
+        ld_instr = all_stages * loads_thread_stage;
+        shared_st_tx = kt > 1 ? ceil_shift(padded_out * (double)(4 * (2 * kt - 1)), 7) : 0.0;
+        shared_ld = padded_out * (double)(2 * (kt - 1));
+        waves_block = floor_div(block_threads + (double)(p.hw_wave - 1), (double)p.hw_wave);
+        blocks_cu = block_threads > (double)p.hw_max_threads_cu ? 0u : p.hw_max_threads_cu / (uint32_t)block_threads;
     } else {
         // the reduction is staged through shared memory, stage by stage, by the whole block
         const uint32_t red = stages * stage_red;
         // vector loads per thread per stage: ceil(fp / (threads * vec)) == ceil(ceil(fp / threads) / vec)
-        const uint32_t loads_thread_stage = (ceil_div_u32(fp, threads) + vec - 1) >> lvv;
-        block_threads = threads;
-        smem_bytes = (uint64_t)fp * p.elem_bytes;
-        ld_bytes = (uint64_t)grid * stages * fp * p.elem_bytes;
-        flop_exec = 2 * padded_out * red;
-        fma_thread = (uint64_t)outs_thread * red;
-        int_ops = (uint64_t)grid_threads *
-                  ((uint64_t)stages * (4ull * loads_thread_stage + 2) + 2ull * ((red + unroll - 1) >> lu));
-        ld_instr = (uint64_t)grid_threads * stages * loads_thread_stage;
-        shared_st_tx = (ld_bytes + 127) >> 7;
-        shared_ld = (uint64_t)grid_threads * ((uint64_t)thr_a + thr_b) * red;
-        waves_block = ceil_div_u32(threads, p.hw_wave);
+        const double loads_thread_stage = (double)((ceil_div_u32(fp, threads) + vec - 1) >> lvv);
+        block_threads = (double)threads;
+        smem_bytes = (double)fp * elem_bytes;
+        ld_bytes = (double)grid * (double)stages * smem_bytes;
+        fma_thread = outs * (double)red;
+        flop_exec = 2.0 * all_blocks_threads * fma_thread;
+        int_ops = all_blocks_threads * ((double)stages * (4.0 * loads_thread_stage + 2.0) + (double)(2 * ((red + unroll - 1) >> lu)));
+        ld_instr = all_blocks_threads * (double)stages * loads_thread_stage;
+        shared_st_tx = ceil_shift(ld_bytes, 7);
+        shared_ld = all_blocks_threads * ((double)thr_a + (double)thr_b) * (double)red;
+        waves_block = (double)ceil_div_u32(threads, p.hw_wave);
         blocks_cu = p.hw_max_threads_cu / threads;
     }
-    const uint64_t ld_sectors = (ld_bytes + 31) >> 5;
+    const double ld_sectors = ceil_shift(ld_bytes, 5);
 
-    if (smem_bytes > p.hw_lds_bytes) blocks_cu = 0;
-    else if (smem_bytes > 0) blocks_cu = min(blocks_cu, p.hw_lds_bytes / (uint32_t)smem_bytes);
+    if (smem_bytes > (double)p.hw_lds_bytes) blocks_cu = 0;
+    else if (smem_bytes > 0.0) blocks_cu = min(blocks_cu, p.hw_lds_bytes / (uint32_t)smem_bytes);
     blocks_cu = min(blocks_cu, p.hw_max_blocks_cu);
     const uint32_t slots = p.hw_num_cu * (blocks_cu ? blocks_cu : 1);
     const uint32_t waves = grid / slots;
@@ -1117,47 +1123,48 @@ __global__ __launch_bounds__(kFeatBlock) void features_kernel(SpaceBatch spaces,
     const uint32_t low_bit = contiguous & (0u - contiguous);
     const uint32_t vec_contig = low_bit < vec ? low_bit : vec;
 
-    const bool legal = block_threads >= 32 && block_threads <= 1024 && lv.shape_ok && smem_bytes <= p.hw_lds_bytes &&
+    const bool legal = block_threads >= 32.0 && block_threads <= 1024.0 && lv.shape_ok && smem_bytes <= (double)p.hw_lds_bytes &&
                        vec * p.elem_bytes <= 16 && (contiguous & (vec - 1)) == 0;
     if (legal_out) legal_out[i] = legal ? 1 : 0;
+    // (known to be 32 bits wide only in the stretch of code that says so: else each store below has an addition of 64 bits)
+    asm("" : "+v"(lane_x));
+    if (WANT_RAW) asm("" : "+v"(lane_raw));
 
     emit_const(0, 0, p.flop_useful);
-    emit64(1, flop_exec);
-    emit64(2, fma_thread);
-    emit64(3, int_ops);
-    emit32(4, outs_thread);
-    emit64(5, (uint64_t)outs_thread + thr_a + thr_b);
+    emit_whole(1, flop_exec);
+    emit_whole(2, fma_thread);
+    emit_whole(3, int_ops);
+    emit_whole(4, outs);
+    emit_whole(5, outs + ((double)thr_a + (double)thr_b));
     emit32(6, grid);
-    if (XRED) emit64(7, block_threads);
-    else emit32(7, threads);
-    if (XRED) emit64(8, waves_block);
-    else emit32(8, (uint32_t)waves_block);
+    emit_whole(7, block_threads);
+    emit_whole(8, waves_block);
     emit32(9, blocks_cu);
     emit32(10, active);
     emit32(11, p.hw_num_cu - active);
     emit32(12, waves + (tail != 0));
     emit32(13, tail);
-    emit64(14, ld_instr);
-    emit64(15, ld_sectors);
-    emit64(16, st_sectors);
-    emit64(17, (uint64_t)grid_threads * ((outs_thread + vec - 1) >> lvv));
-    emit64(18, smem_bytes);
-    emit64(19, shared_st_tx);
-    emit64(20, shared_ld);
-    emit64(21, floor_div_f64(flop_exec << 3, ld_sectors + st_sectors)); // numerator < 2^52
+    emit_whole(14, ld_instr);
+    emit_whole(15, ld_sectors);
+    emit_whole(16, st_sectors);
+    emit_whole(17, all_blocks_threads * (double)((outs_thread + vec - 1) >> lvv));
+    emit_whole(18, smem_bytes);
+    emit_whole(19, shared_st_tx);
+    emit_whole(20, shared_ld);
+    emit_whole(21, floor_div(flop_exec * 8.0, ld_sectors + st_sectors));
     emit_const(22, 1, p.compulsory_bytes);
     {
         // (ld_bytes * 256) / c with ld_bytes < 2^50 and c < 2^34, as two exact steps
-        const uint64_t c = p.compulsory_in_bytes;
-        const uint64_t q1 = floor_div_f64(ld_bytes, c);
-        const uint64_t r1 = ld_bytes - q1 * c;
-        emit64(23, (q1 << 8) + floor_div_f64(r1 << 8, c));
+        const double c = (double)p.compulsory_in_bytes;
+        const double q1 = floor_div(ld_bytes, c);
+        const double r1 = __builtin_fma(-q1, c, ld_bytes);
+        emit_whole(23, q1 * 256.0 + floor_div(r1 * 256.0, c));
     }
     emit32(24, stages);
     emit32(25, stage_red);
     emit32(26, inner_trip);
     emit32(27, unroll);
-    emit64(28, (uint64_t)(unroll < inner_trip ? unroll : inner_trip) * outs_thread);
+    emit_whole(28, (double)(unroll < inner_trip ? unroll : inner_trip) * outs);
     emit32(29, depth);
     emit32(30, vec);
     emit32(31, vec_contig);
