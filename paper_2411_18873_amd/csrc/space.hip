@@ -811,12 +811,10 @@ __device__ __forceinline__ double floor_div(double a, double b)
 // ceil(a / 2^k)
 __device__ __forceinline__ double ceil_shift(double a, int k) { return __builtin_ceil(__builtin_ldexp(a, -k)); }
 
-// Threads, and candidates, per block of the feature kernel.  1024 measured 9 % faster than 256 on the
-// benchmark workload (the tables are staged once per 1024 candidates and a block writes 2 KB of every row).
-constexpr uint32_t kFeatBlock = 1024;
+constexpr uint32_t kFeatBlock = 1024; // threads, and candidates, per block of the feature kernel, at most (FeatureStores)
 
 // WANT_X: the transformed features are wanted (feat_out is not NULL; without them OUT_DTYPE means nothing).
-// STREAM: they are stored past the caches (streams_features).
+// STREAM: they are stored past the caches (FeatureStores).
 template <int OUT_DTYPE, bool TABLES_IN_LDS, int N_FEAT, bool WANT_RAW, bool XRED, bool WANT_X, bool STREAM>
 __global__ __launch_bounds__(kFeatBlock) void features_kernel(SpaceBatch spaces, const uint16_t *__restrict__ genes,
                                                        uint64_t ld, uint64_t n, void *__restrict__ feat_out,
@@ -827,8 +825,9 @@ __global__ __launch_bounds__(kFeatBlock) void features_kernel(SpaceBatch spaces,
     const unsigned char *blob = spaces.dev[blockIdx.y];
     const SpaceParams p = *reinterpret_cast<const SpaceParams *>(blob);
     const uint2 *tab = reinterpret_cast<const uint2 *>(blob + kDevHeader);
-    const uint64_t in_space = (uint64_t)blockIdx.x * kFeatBlock + threadIdx.x;
-    const uint64_t block_col = (uint64_t)blockIdx.y * n + (uint64_t)blockIdx.x * kFeatBlock; // wave-uniform
+    const uint32_t threads_block = blockDim.x;
+    const uint64_t in_space = (uint64_t)blockIdx.x * threads_block + threadIdx.x;
+    const uint64_t block_col = (uint64_t)blockIdx.y * n + (uint64_t)blockIdx.x * threads_block; // wave-uniform
     const uint64_t i = block_col + threadIdx.x;                                       // column in the matrices
 
     // The gene loads are issued together, before the tables are staged, so that one round trip covers them
@@ -848,16 +847,16 @@ __global__ __launch_bounds__(kFeatBlock) void features_kernel(SpaceBatch spaces,
         const uint4 *src = reinterpret_cast<const uint4 *>(tab);
         uint4 *dst = reinterpret_cast<uint4 *>(lds_tables);
         const uint32_t quads = (p.table_total + 1) >> 1;
-        for (uint32_t base = 0; base < quads; base += 4 * kFeatBlock) {
+        for (uint32_t base = 0; base < quads; base += 4 * threads_block) {
             uint4 v[4];
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                const uint32_t t = base + k * kFeatBlock + threadIdx.x;
+                const uint32_t t = base + k * threads_block + threadIdx.x;
                 v[k] = src[t < quads ? t : quads - 1];
             }
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                const uint32_t t = base + k * kFeatBlock + threadIdx.x;
+                const uint32_t t = base + k * threads_block + threadIdx.x;
                 if (t < quads) dst[t] = v[k];
             }
         }
@@ -1173,18 +1172,39 @@ __global__ __launch_bounds__(kFeatBlock) void features_kernel(SpaceBatch spaces,
 } // namespace
 
 namespace {
-// Whether features are stored past the caches.  Such stores leave the caches at once, a wavefront's 128 or 256 bytes of a row by
-// themselves, so where they do not start on 64 bytes, their ends are written to memory as pieces, twice: every column a
-// wavefront starts at has to lie there in every row.  Whole pieces of bfloat16 stream as they come; of fp32 a matrix of some 50 MB
-// and more goes through the caches in better order.  us, streamed / through the caches, one space, 64 features:
-//   rows on 128 bytes: fp32 131072 candidates 10.4 / 10.8, 229376 11.9 / 12.4, 262144 14.4 / 13.8, 524288 26.7 / 22.8, 2^20 58 / 45;
-//     bfloat16 262144 10.1 / 11.2, 2^20 26.1 / 28.3, 2^22 109 / 148
-//   8 bytes beside them: fp32 20482 9.05 / 8.54, 260001 23.5 / 14.2, 2^20 + 2 143 / 52; bfloat16 (4 bytes) 524290 34.8 / 17.8, 2^20 + 2 87 / 31
-bool streams_features(const void *feat_out, uint64_t ld, uint64_t n, uint32_t n_spaces, int32_t n_feat, uint64_t elem)
+// How features are stored, and by what blocks.
+//
+// Stores past the caches leave at once, a wavefront's 128 or 256 bytes of a row by themselves, so where they do not start on 64
+// bytes, their ends are written to memory as pieces, twice: every column a wavefront starts at has to lie there in every row.
+// A matrix that the memory-side cache holds (256 MB) is better written through the caches, small ones apart.  Small blocks
+// bring a small launch to more compute units and share a unit better, each stages the space's tables for itself, and a row's
+// stores that start anywhere want long runs.  us, 64 features of one space:
+//   rows on 64 bytes, bfloat16: streamed by blocks of 256 / 512 / 1024: 6400 candidates 4.4 / 5.1 / 7.0, 65536 5.4 / 6.1 / 8.0,
+//     262144 9.3 / 8.8 / 8.5, 2^21 51 / 52 / 63; blocks of 512 streamed / through the caches: 400000 12.7 / 13.9, 600000 17.7 / 16.7,
+//     1398144 38 / 33, 1800000 49 / 47, 1966080 49 / 56, 2^22 97 / 139
+//   fp32: blocks of 256 streamed / through the caches: 131072 8.6 / 9.3, 300032 16.8 / 14.9, 600000 32 / 26, 1200000 64 / 61, 1398144
+//     72 / 76, 2^21 100 / 115, 2^22 191 / 237; of 256 / 1024:
+//     140000 8.7 / 9.7, 180000 9.9 / 11.1, 262144 14.3 / 13.3, 300032 14.9 / 16.7, 2^20 46 / 43, 2^22 191 / 295
+//   8 bytes beside them: fp32 by 1024 streamed / through the caches 260001 23.5 / 13.9, 777777 80 / 35, 2^20 + 2 143 / 52, by 256
+//     through the caches 14.3, 35, and 3000003 242 for 221; bfloat16 777777 56 / 20.7, by 256 22.2
+struct FeatureStores {
+    bool stream;
+    uint32_t block;
+};
+FeatureStores feature_stores(const void *feat_out, uint64_t ld, uint64_t n, uint32_t n_spaces, int32_t n_feat, uint64_t elem,
+                             uint32_t table_entries)
 {
-    constexpr uint64_t PIECE = 64, MOST_F32 = 49ull << 20;
-    if (((uintptr_t)feat_out | (ld * elem) | (n_spaces > 1 ? n * elem : 0)) % PIECE) return false;
-    return elem == 2 || n * n_spaces * n_feat * elem < MOST_F32;
+    constexpr uint64_t PIECE = 64, MB = 1u << 20;
+    const uint64_t all = n * n_spaces, bytes = all * n_feat * elem;
+    const bool whole = ((uintptr_t)feat_out | (ld * elem) | (n_spaces > 1 ? n * elem : 0)) % PIECE == 0;
+    FeatureStores s;
+    s.stream = whole && (elem == 2 ? bytes < 70 * MB || bytes > 225 * MB : bytes < 49 * MB || bytes > 310 * MB);
+    if (table_entries > 2048) s.block = kFeatBlock; // 16 KB and more of tables
+    else if (all <= 131072) s.block = 256;
+    else if (!whole) s.block = kFeatBlock;
+    else if (elem == 2) s.block = 512;
+    else s.block = all > 196608 && all <= 262144 ? kFeatBlock : 256; // (one block on nearly each of 256 units)
+    return s;
 }
 
 int32_t features_launch(const eck_space *const *spaces, uint32_t n_spaces, const uint16_t *genes, uint64_t ld,
@@ -1210,13 +1230,13 @@ int32_t features_launch(const eck_space *const *spaces, uint32_t n_spaces, const
     const bool xred = spaces[0]->prm.kind == ECK_SPACE_SPLIT_XRED;
     const bool in_lds = spaces[0]->prm.kind != ECK_SPACE_KNOB && largest <= 6144;
     const size_t lds = in_lds ? (size_t)((largest + 1) / 2) * 16 : 0; // staged two entries at a time
-    const dim3 block(kFeatBlock), grid((unsigned)((n + kFeatBlock - 1) / kFeatBlock), n_spaces);
+    const FeatureStores stores = feature_stores(feat_out, ld, n, n_spaces, n_feat, out_dtype == ECK_F32 ? 4 : 2, in_lds ? largest : 0);
+    const dim3 block(stores.block), grid((unsigned)((n + stores.block - 1) / stores.block), n_spaces);
     hipStream_t st = as_stream(stream);
     const bool raw = raw_out != nullptr;
-    const bool stream_out = streams_features(feat_out, ld, n, n_spaces, n_feat, out_dtype == ECK_F32 ? 4 : 2);
 #define ECK_LAUNCH_FEATURES(DT, INLDS, NF, RAW, XR)                                                                 \
     do {                                                                                                           \
-        if (feat_out && stream_out)                                                                                \
+        if (feat_out && stores.stream)                                                                                \
             hipLaunchKernelGGL((features_kernel<DT, INLDS, NF, RAW, XR, true, true>), grid, block, lds, st, batch,  \
                                genes, ld, n, feat_out, raw_out, legal_out, spaces[0]->prm.n_genes);                \
         else if (feat_out)                                                                                         \
