@@ -1,5 +1,5 @@
-// Minibatch Adam steps on the weighted squared error of Eq. (1) for fp32 models of any hidden widths, two launches per
-// step (Alg. 1: ModelUpdate; Sec. 6.4).  HIP, gfx950.
+// Minibatch Adam steps on the weighted squared error of Eq. (1) for fp32 models of any hidden widths, two launches a
+// step or, where a step is small enough for one die, all steps in one (Alg. 1: ModelUpdate; Sec. 6.4).  HIP, gfx950.
 //
 // The same cut as for BF16 models, with fp32 operands throughout (v_mfma_f32_16x16x4_f32, tiles of f32_tiles.h):
 //   rows kernel:     both hidden layers, the output layer, the Eq.-(1) term and its derivative and the deltas of both
@@ -8,11 +8,11 @@
 //                    the block that completes its gradient.
 // A step is a chain of dependent products too small to fill the chip, so it is bound by launches and by the latency of
 // each product's loads: weights are requested before the barrier or the product that precedes theirs, several groups of
-// sixteen rows of the reduction at a time.  Every sum has a fixed order.
-// Measured, 64-128-128-1 on minibatches of 250: 136 us per step launched one product at a time (a vector kernel of two
-// blocks for most of them, 30 us each), 15 us in two launches (a block of its own for the bias corrections took 0.85 us a
-// step off the rows kernel; the features requested first and the biases' moments with the tile's, 0.6); 64-512-512-1,
-// 512 rows: 290 and 70.
+// sixteen rows of the reduction at a time.  Every sum has a fixed order, the same in both forms.
+// Measured, 64-128-128-1, 16 steps of 250 rows, a whole call with the state in and out: 252.4 us with two launches a step
+// (a block of its own for the bias corrections took 0.85 us a step off the rows kernel; the features requested first and
+// the biases' moments with the tile's, 0.6), 192.4 by a crew (crew.h).  One product at a time: 136 us a step.
+// 64-512-512-1, 512 rows, two launches: 70 us a step.
 #include "crew.h"
 #include "f32_tiles.h"
 #include "refit_labels.h"
@@ -618,7 +618,8 @@ __global__ __launch_bounds__(64 * WAVES) void step_weights_f32_kernel(StepF32 a,
 // ------------------------------------------------------------------------------------- all steps in one launch
 //
 // The same steps by a crew (crew.h): rows, a barrier, weights, a barrier, twelve wavefronts a member (so that a lane has 168
-// registers).  Eight take a tile of W2 or W1, the other four 16 columns of the output layer.  All sums are those of the two launches, in their order: the same bits.
+// registers).  Eight take a tile of W2 or W1, the other four 16 columns of the output layer.  All sums are those of
+// the two launches, in their order: the same bits.
 constexpr int CREW_THREADS = 768, CREW_MAIN = 64 * WAVES, CREW_SIDE = CREW_THREADS - CREW_MAIN;
 
 struct CrewLds { // byte offsets: either part's buffers from 0, behind them what outlives a part

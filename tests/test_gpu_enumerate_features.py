@@ -524,12 +524,12 @@ def test_features_streamed_and_through_the_caches(G, dtype):
     import torch
     mine, ref = _spaces("c2", eck.SPACE_SPLIT)
     code, kind = (eck.F32, torch.float32) if dtype == "f32" else (eck.BF16, torch.bfloat16)
-    n = 201600  # fp32: past the line; rows of either type a multiple of 64 bytes
+    n = 268800  # fp32: past the line; rows of either type a multiple of 64 bytes; with the parts, every size of block
     genes = torch.zeros((mine.n_genes, n), dtype=torch.int16, device="cuda")
     eck.candidate_enumerate(mine, eck.MODE_SAMPLE, n, genes, seed=7)
     whole = torch.full((64, n), -1.0, dtype=kind, device="cuda")
     eck.features_compute(mine, genes, n, 64, code, feat_out=whole)
-    for col0, part in ((0, 1000), (0, 190001), (2, n - 2), (33, 4097)):
+    for col0, part in ((0, 1000), (0, 190001), (0, 201600), (2, n - 2), (33, 4097)):
         got = torch.full((64, n), -1.0, dtype=kind, device="cuda")
         eck.features_compute(mine, genes, part, 64, code, feat_out=got, col0=col0)
         assert torch.equal(got[:, col0:col0 + part], whole[:, col0:col0 + part])
