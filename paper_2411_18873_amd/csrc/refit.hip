@@ -421,7 +421,11 @@ struct OutputBlock {
     {
         constexpr int AHEAD = FRESH ? 8 : 16; // rows under way together
         const int lane = tid & 63, per = a.padded / 64;
-        const uint32_t first = (uint32_t)((tid >> 2) * per), at = 4u * (first * H2 + (uint32_t)(block * 16 + 4 * (lane & 3)));
+        // a thread's first row: in the offset where the rows are a crew's few, else in the base (2^21 rows of 512 units are 2^32 bytes;
+        // a 64th of what fits the memory is less)
+        const uint32_t first = (uint32_t)((tid >> 2) * per), in_offset = FRESH ? first : 0, in_base = first - in_offset;
+        const float *h2 = a.h2 + (uint64_t)in_base * H2, *dy = a.dy + in_base;
+        const uint32_t at = 4u * (in_offset * H2 + (uint32_t)(block * 16 + 4 * (lane & 3)));
         float sums[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
         for (int r = 0; r < per; r += AHEAD) {
             float4 h[AHEAD];
@@ -429,8 +433,8 @@ struct OutputBlock {
 #pragma unroll
             for (int u = 0; u < AHEAD; ++u) {
                 const uint32_t row = min(r + u, per - 1);
-                h[u] = __builtin_bit_cast(float4, fresh_16<FRESH>(a.h2, at, 4u * H2 * row));
-                d[u] = fresh_float<FRESH>(a.dy, 4u * first, 4u * row);
+                h[u] = __builtin_bit_cast(float4, fresh_16<FRESH>(h2, at, 4u * H2 * row));
+                d[u] = fresh_float<FRESH>(dy, 4u * in_offset, 4u * row);
             }
 #pragma unroll
             for (int u = 0; u < AHEAD; ++u) {
@@ -468,7 +472,7 @@ template <bool FRESH>
 __device__ __forceinline__ void report_loss(const StepArgs &a, int lane)
 {
     double s = 0.0;
-    for (int r = lane; r < a.rows; r += 64) s += (double)fresh_float<FRESH>(a.lterm, 4 * r, 0);
+    for (int r = lane; r < a.rows; r += 64) s += (double)fresh_float<FRESH>(a.lterm, 4u * r, 0);
 #pragma unroll
     for (uint32_t off = 32; off > 0; off >>= 1) s += lane_exchange(s, off);
     if (lane == 0) *a.loss_out = (float)(s / a.rows);
@@ -529,8 +533,8 @@ __global__ __launch_bounds__(256) void step_weights_kernel(StepArgs a)
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 const int ks = kb + u < k1 ? kb + u : k1 - 1; // clamped: every load stays inside the operands
-                bv[u] = *reinterpret_cast<const bf16x8 *>(bsrc + 512 * place(ntile, ks, B));
-                av[u] = *reinterpret_cast<const bf16x8 *>(asrc + 512 * place(mt, ks, B));
+                bv[u] = *reinterpret_cast<const bf16x8 *>(bsrc + (int64_t)512 * place(ntile, ks, B));
+                av[u] = *reinterpret_cast<const bf16x8 *>(asrc + (int64_t)512 * place(mt, ks, B));
             }
 #pragma unroll
             for (int u = 0; u < 8; ++u) {

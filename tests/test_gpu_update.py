@@ -408,3 +408,50 @@ def test_fp32_steps_of_a_crew_are_those_of_two_launches(G, widths, mb, epoch):
         _, loss_b = G.update_gpu(b, x, e, epoch, mb)
     assert np.array_equal(a.get_state().cpu().numpy(), b.get_state().cpu().numpy())
     assert loss == loss_b
+
+
+@pytest.mark.parametrize("dtype,tol", [("bf16", 2e-2)])
+def test_steps_of_minibatches_past_4_gib(G, dtype, tol):
+    """2.4 million rows of 512 units: a matrix of activations is 4.9 GB, and what lies behind 2^32 bytes of it counts most (the
+    last 300 000 labels are a hundredth of the others, so their derivatives a hundred times theirs).  One step from zero moments
+    leaves 0.1 g in the first one, compared layer by layer with the gradient in 64 bits; bfloat16's operands as in the tests
+    above."""
+    import torch
+    widths, rows, late = [64, 512, 512, 1], 2400000, 300000
+    P, F = synth.param_count(widths), widths[0]
+    theta = synth.mlp_theta(widths, 6, bf16=True, bias_scale=0.2)
+    model = G.make_model(widths, eck.BF16 if dtype == "bf16" else eck.F32, theta)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.rand((F, rows), generator=gen, device="cuda") * 4.0
+    e = torch.rand(rows, generator=gen, device="cuda") + 1.0
+    e[rows - late:] *= 0.01
+    if dtype == "bf16":
+        x = x.to(torch.bfloat16)
+    out = torch.zeros(2, device="cuda")
+    ws = torch.empty(eck.costmodel_update_workspace_bytes(model, rows, rows), dtype=torch.uint8, device="cuda")
+    eck.costmodel_update(model, x, e, 1, rows, out[0:1], out[1:2], ws)
+    del ws
+    got = model.get_state()[P:2 * P].double() / (1.0 - float(np.float32(0.9)))
+    y = (e / e.max()).double()
+    layers, at = [], 0
+    t = G.to_dev(theta).double()
+    for fi, fo in zip(widths[:-1], widths[1:]):
+        layers += [t[at:at + fi * fo].view(fi, fo), t[at + fi * fo:at + fi * fo + fo]]
+        at += fi * fo + fo
+    w1, b1, w2, b2, w3, b3 = layers
+    want = [torch.zeros_like(v) for v in layers]
+    for lo in range(0, rows, 1 << 17):
+        xs, ys = x[:, lo:lo + (1 << 17)].double(), y[lo:lo + (1 << 17), None]
+        h1 = torch.relu(xs.t() @ w1 + b1)
+        h2 = torch.relu(h1 @ w2 + b2)
+        dy = 2.0 * (h2 @ w3 + b3 - ys) / (ys * rows)
+        d2 = (dy @ w3.t()) * (h2 > 0)
+        d1 = (d2 @ w2.t()) * (h1 > 0)
+        for g, v in zip(want, (xs @ d1, d1.sum(0), h1.t() @ d2, d2.sum(0), h2.t() @ dy, dy.sum(0))):
+            g += v
+    at = 0
+    for g in want:
+        part = got[at:at + g.numel()]
+        at += g.numel()
+        off = float((part - g.flatten()).norm() / g.norm())
+        assert off <= tol, (tuple(g.shape), off)
