@@ -391,7 +391,12 @@ __device__ __forceinline__ void tile_part(const float *A, const float *D, int M,
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     float bsum[2] = {0.0f, 0.0f};
-    const __amdgpu_buffer_rsrc_t ar = crew_buffer(A), dr = crew_buffer(D);
+    // A group of sixteen rows: at an offset where the rows are a crew's few, else by a descriptor of its own, which ends with the
+    // columns that it may read (2^21 rows of 512 units are 2^32 bytes)
+    auto rows_of = [](const float *matrix, int width, int g) {
+        if (FRESH) return crew_buffer(matrix);
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(matrix + (int64_t)16 * g * width), 0, (16 * width + TILE) * 4, RSRC_FLAGS);
+    };
     constexpr int BATCH = 4; // groups requested together
     for (int g0 = w; g0 < groups; g0 += BATCH * WAVES) {
         i32x2 av[BATCH][4], dv[BATCH][4];
@@ -399,10 +404,12 @@ __device__ __forceinline__ void tile_part(const float *A, const float *D, int M,
         for (int u = 0; u < BATCH; ++u) {
             const int g = g0 + u * WAVES;
             if (g >= groups) break;
+            const __amdgpu_buffer_rsrc_t ar = rows_of(A, M, g), dr = rows_of(D, N, g);
+            const int row = FRESH ? 16 * g : 0;
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
-                av[u][t] = __builtin_amdgcn_raw_buffer_load_b64(ar, a_lane, (16 * g + t) * M * 4, POLICY);
-                dv[u][t] = __builtin_amdgcn_raw_buffer_load_b64(dr, d_lane, (16 * g + t) * N * 4, POLICY);
+                av[u][t] = __builtin_amdgcn_raw_buffer_load_b64(ar, a_lane, (row + t) * M * 4, POLICY);
+                dv[u][t] = __builtin_amdgcn_raw_buffer_load_b64(dr, d_lane, (row + t) * N * 4, POLICY);
             }
         }
 #pragma unroll
@@ -526,6 +533,9 @@ struct OutputBlock {
     {
         constexpr int AHEAD = 8;
         const int per = (a.padded + OUT_GROUPS - 1) / OUT_GROUPS;
+        // (a group's first row in the offset where the rows are a crew's few, else in the base; a 32nd of what fits the memory is
+        // less than 2^32 bytes)
+        const float *h2[SETS], *dy[SETS];
         uint32_t at[SETS], dy_at[SETS];
         int rows[SETS]; // none for groups behind the minibatch, whose loads, and a last group's, end in the buffers behind h2 and dy
         float sum[SETS];
@@ -533,8 +543,11 @@ struct OutputBlock {
         for (int s = 0; s < SETS; ++s) {
             const int group = (tid >> 4) + s * (THREADS / 16), first = min(group * per, a.padded - 1);
             rows[s] = a.padded - group * per;
-            at[s] = 4u * (uint32_t)(first * a.H2 + min(col, a.H2 - 1));
-            dy_at[s] = 4u * (uint32_t)first;
+            const int in_offset = FRESH ? first : 0, in_base = first - in_offset;
+            h2[s] = a.h2 + (int64_t)in_base * a.H2;
+            dy[s] = a.dy + in_base;
+            at[s] = 4u * (uint32_t)(in_offset * a.H2 + min(col, a.H2 - 1));
+            dy_at[s] = 4u * (uint32_t)in_offset;
             sum[s] = 0.0f;
         }
         for (int r = 0; r < per; r += AHEAD) {
@@ -544,8 +557,8 @@ struct OutputBlock {
 #pragma unroll
                 for (int u = 0; u < AHEAD; ++u) {
                     const uint32_t row = min(r + u, per - 1);
-                    h[s][u] = fresh_float<FRESH>(a.h2, at[s], 4u * row * (uint32_t)a.H2);
-                    d[s][u] = fresh_float<FRESH>(a.dy, dy_at[s], 4u * row);
+                    h[s][u] = fresh_float<FRESH>(h2[s], at[s], 4u * row * (uint32_t)a.H2);
+                    d[s][u] = fresh_float<FRESH>(dy[s], dy_at[s], 4u * row);
                 }
 #pragma unroll
             for (int s = 0; s < SETS; ++s)
@@ -579,7 +592,7 @@ __device__ __forceinline__ void report_loss(const StepF32 &a, int lane)
 {
     double s = 0.0;
 #pragma unroll 8
-    for (int r = lane; r < a.rows; r += 64) s += (double)fresh_float<FRESH>(a.lterm, 4 * r, 0);
+    for (int r = lane; r < a.rows; r += 64) s += (double)fresh_float<FRESH>(a.lterm, 4u * r, 0);
 #pragma unroll
     for (uint32_t off = 32; off > 0; off >>= 1) s += lane_exchange(s, off);
     if (lane == 0) *a.loss_out = (float)(s / a.rows);
