@@ -92,10 +92,12 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 struct AdamScales {
     float m, v; // lr / (1 - beta1^t), 1 / sqrt(1 - beta2^t)
 };
-// of step t, which takes the powers by squaring (a dozen multiplications for two double-precision pow() of most of a microsecond;
-// a few units in the last place of a double)
-__device__ __forceinline__ AdamScales adam_scales(float lr, float beta1, float beta2, uint32_t t)
+// of the step behind `done` ones (whole, any number a float holds) and step_in_call more: the powers by squaring (a dozen
+// multiplications for two double-precision pow() of most of a microsecond; a few units in the last place of a double).  Of 2^32 steps
+// and more, the powers of every beta below 1 that a float holds are nothing beside 1.
+__device__ __forceinline__ AdamScales adam_scales(float lr, float beta1, float beta2, float done, int step_in_call)
 {
+    uint32_t t = (uint32_t)fmin((double)done + step_in_call + 1, 4294967295.0);
     double power1 = 1.0, power2 = 1.0, square1 = beta1, square2 = beta2;
     for (; t; t >>= 1) {
         if (t & 1) {

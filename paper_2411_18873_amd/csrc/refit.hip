@@ -169,7 +169,7 @@ __device__ __forceinline__ void put_rows4(uint16_t *lds, int ld, int row, int co
 
 __device__ __forceinline__ AdamScales step_scales(const StepArgs &a, int step_in_call)
 {
-    return adam_scales(a.lr, a.beta1, a.beta2, (uint32_t)a.theta[3 * a.P] + step_in_call + 1); // (t itself is advanced once, after the last step)
+    return adam_scales(a.lr, a.beta1, a.beta2, a.theta[3 * a.P], step_in_call); // (the count itself is advanced once, after the last step)
 }
 
 // LDS of a block that takes 32 rows, and of their features

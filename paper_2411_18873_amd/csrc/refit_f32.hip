@@ -171,7 +171,7 @@ __device__ __forceinline__ void product(const S &slice, int K, const f32x4 *act,
 
 __device__ __forceinline__ AdamScales step_scales(const StepF32 &a, int step_in_call)
 {
-    return adam_scales(a.lr, a.beta1, a.beta2, (uint32_t)a.theta[3 * a.P] + step_in_call + 1); // (t itself is advanced once, after the last step)
+    return adam_scales(a.lr, a.beta1, a.beta2, a.theta[3 * a.P], step_in_call); // (the count itself is advanced once, after the last step)
 }
 
 // ------------------------------------------------------------------------------------------------ rows kernel

@@ -196,8 +196,8 @@ __global__ void adam_kernel(float *__restrict__ state, const float *__restrict__
     if (sc->bad) return;
     const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= P) return;
-    // (t itself is advanced once, after the last step)
-    const AdamScales scales = adam_scales(lr, beta1, beta2, (uint32_t)state[3 * P] + step_in_call + 1);
+    // (the count itself is advanced once, after the last step)
+    const AdamScales scales = adam_scales(lr, beta1, beta2, state[3 * P], step_in_call);
     (void)adam_one(state, P, i, state[i], state[P + i], state[2 * P + i], grad[i], beta1, beta2, eps, scales);
 }
 

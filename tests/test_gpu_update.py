@@ -455,3 +455,26 @@ def test_steps_of_minibatches_past_4_gib(G, dtype, tol):
         at += g.numel()
         off = float((part - g.flatten()).norm() / g.norm())
         assert off <= tol, (tuple(g.shape), off)
+
+
+@pytest.mark.parametrize("widths,dtype,mb,steps", [([64, 256, 256, 1], "bf16", 64, 1), ([64, 256, 256, 1], "bf16", 64, 4), ([64, 256, 256, 1], "bf16", 20, 2),
+                                                   ([64, 128, 128, 1], "f32", 64, 2), ([64, 128, 128, 1], "f32", 64, 3)])
+@pytest.mark.parametrize("done", [4294967040.0, 1e10])
+def test_a_state_of_many_steps(G, widths, dtype, mb, steps, done):
+    """A step count around 2^32 and past it, which a caller may set: Adam's corrections are 1.  With lr = 1e-6 the gradients stay what they
+    are, and a weight moves by some 3 lr a step (0.1 g over sqrt(0.001) |g|, then more) whatever their size; bfloat16 rounds
+    them by 2^-8 and flips a few activations, so that one weight in a hundred, whose gradient vanishes, may be further off than 0.1 lr a step
+    and the weight's own rounding."""
+    P = synth.param_count(widths)
+    _, b16, e = _pairs(mb)
+    x = oracle.bf16_bits_to_f32(b16)
+    theta = synth.mlp_theta(widths, 4, bf16=True, bias_scale=0.1)
+    st = _oracle_state(theta)
+    st[3 * P] = done
+    model = eck.Model(widths, eck.BF16 if dtype == "bf16" else eck.F32)
+    model.set_state(G.to_dev(st.astype(np.float32)))
+    G.update_gpu(model, G.bf16_dev(b16) if dtype == "bf16" else G.to_dev(x), e, steps, mb, lr=1e-6)
+    oracle.update(widths, st, x, e, steps, mb, lr=1e-6, bf16_weights=dtype == "bf16")
+    got = model.get_state().cpu().numpy().astype(np.float64)
+    assert np.isfinite(got).all()
+    assert np.quantile(np.abs(got[:P] - st[:P]), 0.99) <= (1e-7 + 2.0 ** -24 * np.abs(theta).max()) * steps
