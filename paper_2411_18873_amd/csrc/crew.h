@@ -116,6 +116,7 @@ __device__ __forceinline__ int crew_thread()
 constexpr int CREW_RSRC_FLAGS = 0x00020000; // buffer descriptor: raw 32-bit data
 constexpr int CREW_SC1 = 16;                // cache policy: device scope
 typedef int crew_i32x4 __attribute__((ext_vector_type(4)));
+typedef crew_i32x4 crew_i32x4_any __attribute__((aligned(4))); // (a vector of an fp32 model of any widths starts on four bytes)
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t crew_buffer(const void *base)
 {
@@ -125,7 +126,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t crew_buffer(const void *base)
 template <bool FRESH>
 __device__ __forceinline__ crew_i32x4 fresh_16(const void *base, uint32_t at, uint32_t shared)
 {
-    if (!FRESH) return *reinterpret_cast<const crew_i32x4 *>(static_cast<const char *>(base) + at + shared);
+    if (!FRESH) return *reinterpret_cast<const crew_i32x4_any *>(static_cast<const char *>(base) + at + shared);
     return __builtin_amdgcn_raw_buffer_load_b128(crew_buffer(base), at, shared, CREW_SC1);
 }
 
