@@ -7,10 +7,11 @@
 // neighbour's.  A chain whose steps are small enough for a die therefore runs as one launch.
 //
 // A launch of 8 N blocks puts every eighth on the same die; those with blockIdx % 8 == pick are the candidates, the others
-// end at once.  Candidates that run on the die of the first of them sign the roll; the first one there closes it when all N
-// have, or after a while, and whoever comes later ends, too.  So the members of a crew all run already, and a barrier
-// between them ends whatever else the chip is doing and whichever blocks it still holds back; with fewer members each has
-// more to do.  The work's cut, and so every sum, does not depend on their number.
+// end at once.  Candidates that run on the die of the first of them sign the roll.  The first one there, the founder, begins
+// when all N have, or after a while, with those that have; who signs later waits and is taken on with the next step.  So the
+// members of a crew all run already, and a barrier between them ends whatever else the chip is doing and whichever blocks it
+// still holds back; with fewer members each has more to do, until the units that others held come free.  The work's cut, and
+// so every sum, does not depend on their number.
 //
 // What members write for each other: plain stores, which pass the L1.  What they read of each other: loads that miss the L1
 // (fresh_*; ordinary ones may find an older line in it, and the scalar cache is not looked at either).
@@ -20,14 +21,14 @@
 namespace eck {
 
 constexpr unsigned CREW_DIES = 8;
-constexpr unsigned CREW_MOST = 32;                      // members, one per compute unit of a die
-constexpr unsigned CREW_GRID = CREW_DIES * CREW_MOST;   // blocks of the launch
+constexpr unsigned CREW_MOST = 32; // members, one per compute unit of a die
 
 struct CrewState { // device memory, zero before the launch: two lines
     uint32_t home;      // the members' die + 1, 0: none yet
-    uint32_t size;      // members, 0: roll still open
-    uint32_t roll[16];  // by die: candidates that signed; top bit: closed
-    uint32_t pad[14];
+    uint32_t over;      // nobody is taken on any more
+    uint64_t muster;    // the founder's: who belongs to the crew and since which step (Crew::call)
+    uint32_t roll[16];  // by die: candidates that signed
+    uint32_t pad[12];
     uint32_t met[CREW_MOST]; // by member: barriers it has reached
 };
 static_assert(sizeof(CrewState) == 256, "fits the place behind a workspace's last buffer");
@@ -40,42 +41,89 @@ __device__ __forceinline__ void crew_clear(CrewState *s) // by one wavefront of 
     if (threadIdx.x < 64) reinterpret_cast<uint32_t *>(s)[threadIdx.x] = 0;
 }
 
+// Work in steps with two barriers each
 struct Crew {
     CrewState *s;
     uint32_t rank, size, barriers;
 
-    // Called by every thread of a candidate block; false: not a member.  slot: two words of LDS.
-    __device__ __forceinline__ bool join(CrewState *state, uint32_t *slot)
+    // `members` belong to the crew from `step` on, `before` of them already did; at_once: so many may be taken on together
+    static __device__ __forceinline__ uint64_t call(uint32_t step, uint32_t at_once, uint32_t before, uint32_t members)
+    {
+        return (uint64_t)step << 32 | at_once << 16 | before << 8 | members;
+    }
+    static __device__ __forceinline__ uint32_t part(uint64_t muster, int byte) { return (uint32_t)muster >> 8 * byte & 255; }
+    static __device__ __forceinline__ uint32_t members(uint64_t muster) { return part(muster, 0); }
+
+    static __device__ __forceinline__ uint32_t this_die() { return __builtin_amdgcn_s_getreg((31 << 11) | 20) & 15; } // HW_REG_XCC_ID
+
+    // Called by every thread of a candidate block: the step that it begins with, or -1: not a member.  slot: four words of LDS.
+    __device__ __forceinline__ int join(CrewState *state, uint32_t at_once, uint32_t *slot)
     {
         s = state;
-        barriers = 0;
         if (threadIdx.x == 0) {
-            constexpr uint32_t CLOSED = 0x80000000u;
-            const uint32_t die = __builtin_amdgcn_s_getreg((31 << 11) | 20) & 15; // HW_REG_XCC_ID
+            const uint32_t die = this_die();
             const uint32_t place = __hip_atomic_fetch_add(&s->roll[die], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            uint32_t home = 0, members = 0;
+            uint32_t home = 0;
+            uint64_t muster = 0;
             const bool first = __hip_atomic_compare_exchange_strong(&s->home, &home, die + 1, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                                     __HIP_MEMORY_SCOPE_AGENT);
-            if ((first || home == die + 1) && place < CLOSED) {
+            if (first || home == die + 1) {
                 if (place == 0) {
                     constexpr int PATIENCE = 128; // polls, some 50 us
-                    for (int i = 0; i < PATIENCE && relaxed(&s->roll[die]) < gridDim.x / CREW_DIES; ++i) {
+                    uint32_t there = 1;
+                    for (int i = 0; i < PATIENCE && (there = relaxed(&s->roll[die])) < gridDim.x / CREW_DIES; ++i) {
                     }
-                    members = __hip_atomic_fetch_or(&s->roll[die], CLOSED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    __hip_atomic_store(&s->size, members, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    muster = call(0, at_once, 0, min(there, at_once));
+                    __hip_atomic_store(&s->muster, muster, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 } else {
-                    while ((members = relaxed(&s->size)) == 0) { // the block that closes the roll is running
-                    }
+                    // (The founder runs.  `over` is read behind a muster without this block, and set when all of the last one's
+                    // members have reached a barrier.)
+                    do {
+                        muster = relaxed(&s->muster);
+                        asm volatile("" ::: "memory");
+                    } while (members(muster) <= place && !relaxed(&s->over));
                 }
             }
             slot[0] = place;
-            slot[1] = members;
+            slot[1] = members(muster);
+            slot[2] = part(muster, 1);
+            slot[3] = (uint32_t)(muster >> 32);
         }
         __syncthreads();
         rank = __builtin_amdgcn_readfirstlane(slot[0]);
-        size = __builtin_amdgcn_readfirstlane(slot[1]);
-        return size != 0;
+        const uint32_t all = __builtin_amdgcn_readfirstlane(slot[1]), before = __builtin_amdgcn_readfirstlane(slot[2]);
+        const uint32_t step = __builtin_amdgcn_readfirstlane(slot[3]);
+        if (rank >= all) return -1;
+        barriers = 2 * step;
+        size = before;
+        if (step > 0) meet(); // the others are through with the step before
+        size = all;
+        return (int)step;
     }
+
+    // Between a step's first barrier and its second, by every thread: who has signed belongs to the crew from the next step on.
+    // (The second barrier is the old members'; the next muster is written when all have met at the next first one.)
+    __device__ __forceinline__ void summon(int next_step) const
+    {
+        if (full() || !founder()) return;
+        const uint32_t there = relaxed(&s->roll[this_die()]), at_once = part(relaxed(&s->muster), 2);
+        if (there > size)
+            __hip_atomic_store(&s->muster, call(next_step, at_once, size, min(there, size + at_once)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __device__ __forceinline__ bool grown() // behind the second barrier
+    {
+        if (full()) return false;
+        const uint32_t all = __builtin_amdgcn_readfirstlane(members(relaxed(&s->muster)));
+        if (all == size) return false;
+        size = all;
+        return true;
+    }
+    __device__ __forceinline__ void dismiss() const // behind the last step's first barrier
+    {
+        if (founder()) __hip_atomic_store(&s->over, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __device__ __forceinline__ bool full() const { return __builtin_expect(size == CREW_MOST, true); }
+    __device__ __forceinline__ bool founder() const { return rank == 0 && threadIdx.x == 0; } // its first thread
 
     // The block's stores have arrived and its flag says so.  Every thread; first half of a barrier.
     __device__ __forceinline__ void arrive()
@@ -89,14 +137,15 @@ struct Crew {
     __device__ __forceinline__ void meet() const
     {
         if (threadIdx.x < 64) {
-            const uint32_t *theirs = &s->met[threadIdx.x < size ? threadIdx.x : rank];
+            const uint32_t *theirs = &s->met[threadIdx.x < size ? threadIdx.x : 0]; // (the founder; a block that joins has no flag yet)
             while (__ballot((int32_t)(relaxed(theirs) - barriers) < 0)) {
             }
         }
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     }
 
-    static __device__ __forceinline__ uint32_t relaxed(const uint32_t *p)
+    template <class T>
+    static __device__ __forceinline__ T relaxed(const T *p)
     {
         return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }

@@ -144,6 +144,10 @@ struct RefitScalars {
 // count, the call's results, and the packed weights
 int32_t refit_finish(eck_model *m, const float *pred, const float *y, uint64_t n_pairs, int32_t n_steps, const RefitScalars *sc,
                      float *snr_out, float *loss_out, hipStream_t stream);
+// How many blocks may be members of a refit's crew (crew.h), and how many of them are taken on at once
+struct CrewSize {
+    unsigned candidates, at_once;
+};
 // Adam steps of a BF16 model in two launches per step, or all in one (refit.hip): the bytes it needs in costmodel_update's
 // workspace, those of the minibatch's features apart, and the steps themselves (labels y and the data-error flag come from
 // the caller's kernels; the last step's mean loss goes to *loss_scalar, device memory; features, ws: 256-byte aligned)
@@ -154,7 +158,7 @@ int32_t refit_begin(const eck_model *m, const float *energy, uint64_t n_pairs, f
                     hipStream_t st);
 int32_t refit_steps(const eck_model *m, const void *feat, int32_t feat_dtype, uint64_t ld, const float *y, uint64_t n_pairs,
                     int32_t n_steps, int32_t minibatch, float lr, float beta1, float beta2, float eps,
-                    const uint32_t *bad_flag, float *loss_scalar, void *features, void *ws, hipStream_t st);
+                    const uint32_t *bad_flag, float *loss_scalar, void *features, void *ws, CrewSize crew, hipStream_t st);
 // the same for fp32 models of any hidden widths and minibatches of any size (refit_f32.hip)
 uint64_t refit_f32_workspace_bytes(const eck_model *m, int minibatch);
 uint64_t refit_f32_copies_bytes(const eck_model *m); // of the weights, beside the model's state
@@ -162,7 +166,7 @@ int32_t refit_f32_begin(const eck_model *m, const float *energy, uint64_t n_pair
                         int32_t minibatch, void *ws, hipStream_t st);
 int32_t refit_f32_steps(const eck_model *m, const float *feat, uint64_t ld, const float *y, uint64_t n_pairs, int32_t n_steps,
                         int32_t minibatch, float lr, float beta1, float beta2, float eps, const uint32_t *bad_flag,
-                        float *loss_scalar, void *ws, hipStream_t st);
+                        float *loss_scalar, void *ws, CrewSize crew, hipStream_t st);
 // topk_select on a workspace of the caller's or of the library's; known_min: THRESHOLD mode with the least latency
 // of every segment already known (device, one order key per segment), else NULL
 int32_t topk_select_impl(const float *energy, const float *latency, const uint8_t *legal, uint64_t n, uint32_t n_segments,

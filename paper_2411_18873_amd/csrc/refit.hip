@@ -411,10 +411,10 @@ struct OutputBlock {
 
     __device__ __forceinline__ void request()
     {
-        const uint64_t i = parameter();
-        w = a.theta[i];
-        m = a.theta[a.P + i];
-        v = a.theta[2 * a.P + i];
+        const uint32_t at = 4u * (uint32_t)parameter(), P4 = 4u * (uint32_t)a.P;
+        w = fresh_float<FRESH>(a.theta, at, 0);
+        m = fresh_float<FRESH>(a.theta, at, P4);
+        v = fresh_float<FRESH>(a.theta, at, 2 * P4);
     }
 
     __device__ __forceinline__ void sum(float *psum) // [4 wavefronts][17]
@@ -666,17 +666,17 @@ struct CrewTile {
     __device__ __forceinline__ int col() const { return 32 * nt + 4 * (lane & 7); }
     __device__ __forceinline__ bool has_bias() const { return mt == 0 && eight == 0; }
 
-    __device__ __forceinline__ void request() // the parameters' state: nobody but the member that owns the tile writes it
+    __device__ __forceinline__ void request() // (past the L1: as the crew grows, a tile passes from member to member)
     {
         const uint32_t P4 = 4u * (uint32_t)a.P;
         const __amdgpu_buffer_rsrc_t theta = crew_buffer(a.theta);
-        w = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(theta, mine, 0, 0));
-        m = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(theta, mine, P4, 0));
-        v = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(theta, mine, 2 * P4, 0));
+        w = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(theta, mine, 0, CREW_SC1));
+        m = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(theta, mine, P4, CREW_SC1));
+        v = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(theta, mine, 2 * P4, CREW_SC1));
         if (has_bias()) {
-            bias_w = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(theta, bias_mine, 0, 0));
-            bias_m = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(theta, bias_mine, P4, 0));
-            bias_v = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(theta, bias_mine, 2 * P4, 0));
+            bias_w = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(theta, bias_mine, 0, CREW_SC1));
+            bias_m = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(theta, bias_mine, P4, CREW_SC1));
+            bias_v = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(theta, bias_mine, 2 * P4, CREW_SC1));
         }
     }
 
@@ -724,15 +724,16 @@ struct CrewTile {
 };
 
 template <int F, int H1, int H2, bool FEAT_BF16>
-__global__ __launch_bounds__(CREW_THREADS) void steps_crew_kernel(StepArgs a, CrewState *state, unsigned pick, int n_steps, uint64_t n_pairs)
+__global__ __launch_bounds__(CREW_THREADS) void steps_crew_kernel(StepArgs a, CrewState *state, unsigned pick, int n_steps, uint64_t n_pairs, unsigned at_once)
 {
     using Cut = CrewCut<F, H1, H2>;
     extern __shared__ __attribute__((aligned(16))) unsigned char crew_lds[];
     if (blockIdx.x % CREW_DIES != pick || *a.bad != 0) return;
     Crew crew;
-    if (!crew.join(state, reinterpret_cast<uint32_t *>(crew_lds))) return;
+    const int first_step = crew.join(state, at_once, reinterpret_cast<uint32_t *>(crew_lds));
+    if (first_step < 0) return;
     __syncthreads(); // (the words are read)
-    const int rank = (int)crew.rank, members = (int)crew.size, row_blocks = a.padded / 32;
+    const int rank = (int)crew.rank, row_blocks = a.padded / 32;
     // The rows' features and labels come from memory, some 2 us: the wavefronts that have no tile of a layer fetch those of a
     // member's first rows of a step during the step before, into the other half of the buffers.
     constexpr int STAGERS = CREW_THREADS - CREW_MAIN;
@@ -747,13 +748,14 @@ __global__ __launch_bounds__(CREW_THREADS) void steps_crew_kernel(StepArgs a, Cr
         inputs.keep(a, t, x_of(step), xt_of(step), r0);
         if (t < 32) y_of(step)[t] = inputs.y;
     };
-    uint64_t row0 = 0;
+    uint64_t row0 = first_step == 0 ? 0 : (uint32_t)first_step % ((uint32_t)n_pairs / (uint32_t)a.rows) * (uint32_t)a.rows;
     if (rank < row_blocks) {
         const int t = crew_thread() - CREW_MAIN;
-        if (t >= 0) stage(0, 0, 32 * rank, t);
+        if (t >= 0) stage(first_step, row0, 32 * rank, t);
         lds_barrier();
     }
-    for (int step = 0; step < n_steps; ++step) {
+    int step = first_step, members = (int)crew.size;
+    auto one_step = [&] __attribute__((always_inline)) {
         uint64_t next_row0 = row0 + a.rows;
         if (next_row0 == n_pairs) next_row0 = 0;
         for (int i = rank; i < row_blocks; i += members) {
@@ -823,10 +825,16 @@ __global__ __launch_bounds__(CREW_THREADS) void steps_crew_kernel(StepArgs a, Cr
             if (members < Cut::ITEMS) lds_barrier(); // (the LDS is free again)
         }
         if (!last) {
+            crew.summon(step + 1);
             crew.arrive();
             crew.meet();
         }
-    }
+    };
+    // (two loops, so that what follows from the number of members is worked out where it changes, not in every step)
+    for (; step < n_steps; members = (int)crew.size)
+        do one_step();
+        while (++step < n_steps && !crew.grown());
+    crew.dismiss();
 }
 
 // The last block: labels; the others: bf16 copies of W1 and W2 in the fragment order the rows kernel multiplies with
@@ -862,7 +870,7 @@ bool crew_takes(int minibatch, int n_steps, int width) { return n_steps >= 4 && 
 
 template <int F, int H1, int H2>
 int32_t launch_steps(const eck_model *m, StepArgs a, int32_t feat_dtype, int32_t n_steps, uint64_t n_pairs, float *loss_scalar,
-                     hipStream_t st)
+                     CrewSize crew, hipStream_t st)
 {
     constexpr int NW = (H1 > H2 ? H1 : H2) / 32;
     constexpr size_t lds = rows_lds_bytes<F, H1, H2>() + 32 * (F + 8) * sizeof(uint16_t);
@@ -878,7 +886,8 @@ int32_t launch_steps(const eck_model *m, StepArgs a, int32_t feat_dtype, int32_t
             ECK_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(crew_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)crew_lds));
             CrewState *state = reinterpret_cast<CrewState *>(a.scales);
             a.loss_out = loss_scalar;
-            hipLaunchKernelGGL(crew_kernel, dim3(CREW_GRID), dim3(CREW_THREADS), crew_lds, st, a, state, crew_pick(state), n_steps, n_pairs);
+            hipLaunchKernelGGL(crew_kernel, dim3(CREW_DIES * crew.candidates), dim3(CREW_THREADS), crew_lds, st, a, state, crew_pick(state), n_steps, n_pairs,
+                               crew.at_once);
             ECK_HIP_TRY(hipGetLastError());
             return ECK_OK;
         }
@@ -963,7 +972,7 @@ int32_t eck::refit_begin(const eck_model *m, const float *energy, uint64_t n_pai
 
 int32_t eck::refit_steps(const eck_model *m, const void *feat, int32_t feat_dtype, uint64_t ld, const float *y, uint64_t n_pairs,
                          int32_t n_steps, int32_t minibatch, float lr, float beta1, float beta2, float eps,
-                         const uint32_t *bad_flag, float *loss_scalar, void *features, void *ws, hipStream_t st)
+                         const uint32_t *bad_flag, float *loss_scalar, void *features, void *ws, CrewSize crew, hipStream_t st)
 {
     const int F = m->widths[0], H1 = m->widths[1], H2 = m->widths[2];
     StepArgs a = step_buffers(m, minibatch, ws);
@@ -978,9 +987,9 @@ int32_t eck::refit_steps(const eck_model *m, const void *feat, int32_t feat_dtyp
     a.beta1 = beta1;
     a.beta2 = beta2;
     a.eps = eps;
-    if (F == 64 && H1 == 512 && H2 == 512) return launch_steps<64, 512, 512>(m, a, feat_dtype, n_steps, n_pairs, loss_scalar, st);
-    if (F == 64 && H1 == 256 && H2 == 256) return launch_steps<64, 256, 256>(m, a, feat_dtype, n_steps, n_pairs, loss_scalar, st);
-    if (F == 64 && H1 == 128 && H2 == 128) return launch_steps<64, 128, 128>(m, a, feat_dtype, n_steps, n_pairs, loss_scalar, st);
-    if (F == 32 && H1 == 64 && H2 == 64) return launch_steps<32, 64, 64>(m, a, feat_dtype, n_steps, n_pairs, loss_scalar, st);
+    if (F == 64 && H1 == 512 && H2 == 512) return launch_steps<64, 512, 512>(m, a, feat_dtype, n_steps, n_pairs, loss_scalar, crew, st);
+    if (F == 64 && H1 == 256 && H2 == 256) return launch_steps<64, 256, 256>(m, a, feat_dtype, n_steps, n_pairs, loss_scalar, crew, st);
+    if (F == 64 && H1 == 128 && H2 == 128) return launch_steps<64, 128, 128>(m, a, feat_dtype, n_steps, n_pairs, loss_scalar, crew, st);
+    if (F == 32 && H1 == 64 && H2 == 64) return launch_steps<32, 64, 64>(m, a, feat_dtype, n_steps, n_pairs, loss_scalar, crew, st);
     return ECK_EUNSUPPORTED;
 }

@@ -445,7 +445,7 @@ __device__ __forceinline__ void tile_part(const float *A, const float *D, int M,
 }
 
 // The update of a tile's parameters by THREADS threads: the parts of its sums added in order, then Adam
-template <int THREADS>
+template <int THREADS, bool FRESH>
 struct TileUpdate {
     static constexpr int PER = TILE * TILE / THREADS; // parameters of a thread, TILE / PER rows apart
     const StepF32 &a;
@@ -460,10 +460,10 @@ struct TileUpdate {
         bias_at = (uint32_t)(second ? a.off_b2 : a.off_b1) + min(n0 + tid % TILE, N - 1);
     }
 
-    __device__ __forceinline__ AdamNext load(uint32_t i) const
+    __device__ __forceinline__ AdamNext load(uint32_t i) const // (past the L1: as a crew grows, a tile passes from member to member)
     {
         const __amdgpu_buffer_rsrc_t theta = crew_buffer(a.theta);
-        auto get = [&](uint32_t moment) { return __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(theta, 4 * i, 4 * moment * (uint32_t)a.P, 0)); };
+        auto get = [&](uint32_t moment) { return __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(theta, 4 * i, 4 * moment * (uint32_t)a.P, FRESH ? CREW_SC1 : 0)); };
         return {get(0), get(1), get(2)};
     }
 
@@ -524,9 +524,10 @@ struct OutputBlock {
 
     __device__ __forceinline__ void request()
     {
-        w = a.theta[parameter()];
-        m = a.theta[a.P + parameter()];
-        v = a.theta[2 * a.P + parameter()];
+        const uint32_t at = 4u * (uint32_t)parameter(), P4 = 4u * (uint32_t)a.P;
+        w = fresh_float<FRESH>(a.theta, at, 0);
+        m = fresh_float<FRESH>(a.theta, at, P4);
+        v = fresh_float<FRESH>(a.theta, at, 2 * P4);
     }
 
     __device__ __forceinline__ void sum(float *psum) const // [OUT_GROUPS / 4][16]
@@ -611,7 +612,7 @@ __global__ __launch_bounds__(64 * WAVES) void step_weights_f32_kernel(StepF32 a,
         if (!second) block -= blocks2;
         const int M = second ? a.H1 : a.F, N = second ? a.H2 : a.H1;
         const int nt = (N + TILE - 1) / TILE, m0 = block / nt * TILE, n0 = block % nt * TILE;
-        TileUpdate<64 * WAVES> tile(a, second, m0, n0, tid);
+        TileUpdate<64 * WAVES, false> tile(a, second, m0, n0, tid);
         tile.request();
         tile_part<false>(second ? a.h1 : a.x, second ? a.d2 : a.d1, M, N, m0, n0, a.padded / 16, wave, lane, part[wave], colsum[wave]);
         lds_barrier();
@@ -649,15 +650,18 @@ struct CrewLds { // byte offsets: either part's buffers from 0, behind them what
     }
 };
 
-__global__ __launch_bounds__(CREW_THREADS) void steps_f32_crew_kernel(StepF32 a, CrewState *state, unsigned pick, int n_steps, uint64_t n_pairs)
+// FULL: all members have been there from the start, as in most calls (one code for all, and so a number of members that varies,
+// takes 0.1 to 0.25 us a step more)
+template <bool FULL>
+__device__ __forceinline__ void crew_steps(const StepF32 &a, Crew crew, int first_step, int n_steps, uint64_t n_pairs, unsigned char *crew_lds)
 {
-    extern __shared__ __attribute__((aligned(16))) unsigned char crew_lds[];
-    if (blockIdx.x % CREW_DIES != pick || *a.bad != 0) return;
-    Crew crew;
-    if (!crew.join(state, reinterpret_cast<uint32_t *>(crew_lds))) return;
-    __syncthreads(); // (the words are read)
+    if (FULL) {
+        crew.size = CREW_MOST;
+        crew.barriers = 0;
+        first_step = 0;
+    }
     const CrewLds at(a.F, a.H1, a.H2);
-    const int rank = (int)crew.rank, members = (int)crew.size, row_blocks = a.padded / ROWS, items = a.F / 4 * ROWS;
+    const int rank = (int)crew.rank, row_blocks = a.padded / ROWS, items = a.F / 4 * ROWS;
     const int widest = a.H1 > a.H2 ? a.H1 : a.H2, row_waves = (widest + 15) / 16;
     const int groups1 = copy_groups(a.H1), groups2 = copy_groups(a.H2);
     auto over = [](int v) { return (v + TILE - 1) / TILE; };
@@ -673,13 +677,14 @@ __global__ __launch_bounds__(CREW_THREADS) void steps_f32_crew_kernel(StepF32 a,
         for (int e = t; e < items; e += CREW_SIDE) x_of(step)[e] = row_features(a, row0, r0, e);
         if (t < ROWS) y_of(step)[t] = y;
     };
-    uint64_t row0 = 0;
+    uint64_t row0 = first_step == 0 ? 0 : (uint32_t)first_step % ((uint32_t)n_pairs / (uint32_t)a.rows) * (uint32_t)a.rows;
     if (rank < row_blocks) {
         const int t = crew_thread() - CREW_MAIN;
-        if (t >= 0) stage(0, 0, ROWS * rank, t);
+        if (t >= 0) stage(first_step, row0, ROWS * rank, t);
         lds_barrier();
     }
-    for (int step = 0; step < n_steps; ++step) {
+    int step = first_step, members = FULL ? (int)CREW_MOST : (int)crew.size;
+    auto one_step = [&] __attribute__((always_inline)) {
         const bool last = step + 1 == n_steps;
         uint64_t next_row0 = row0 + a.rows;
         if (next_row0 == n_pairs) next_row0 = 0;
@@ -719,7 +724,7 @@ __global__ __launch_bounds__(CREW_THREADS) void steps_f32_crew_kernel(StepF32 a,
                 const bool mine = item < tiles, second = item < tiles2;
                 const int block = second ? item : item - tiles2, across = second ? across2 : across1;
                 const int m0 = block / across * TILE, n0 = block % across * TILE;
-                TileUpdate<CREW_MAIN> tile(a, second, m0, n0, tid);
+                TileUpdate<CREW_MAIN, true> tile(a, second, m0, n0, tid);
                 if (mine) tile.request();
                 together(base);
                 if (mine) tile_part<true>(second ? a.h1 : a.x, second ? a.d2 : a.d1, tile.M, tile.N, m0, n0, a.padded / 16, wave, lane, part[wave], colsum[wave]);
@@ -751,10 +756,29 @@ __global__ __launch_bounds__(CREW_THREADS) void steps_f32_crew_kernel(StepF32 a,
             if (members < items_most) lds_barrier(); // (the LDS is free again)
         }
         if (!last) {
+            if (!FULL) crew.summon(step + 1);
             crew.arrive();
             crew.meet();
         }
+    };
+    for (; step < n_steps; ++step) {
+        one_step();
+        if (!FULL && step + 1 < n_steps && crew.grown()) members = (int)crew.size;
     }
+    if (!FULL) crew.dismiss();
+}
+
+__global__ __launch_bounds__(CREW_THREADS) void steps_f32_crew_kernel(StepF32 a, CrewState *state, unsigned pick, int n_steps, uint64_t n_pairs,
+                                                                      unsigned at_once)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char crew_lds[];
+    if (blockIdx.x % CREW_DIES != pick || *a.bad != 0) return;
+    Crew crew;
+    const int first_step = crew.join(state, at_once, reinterpret_cast<uint32_t *>(crew_lds));
+    if (first_step < 0) return;
+    __syncthreads(); // (the words are read)
+    if (first_step == 0 && crew.size == CREW_MOST) crew_steps<true>(a, crew, 0, n_steps, n_pairs, crew_lds);
+    else crew_steps<false>(a, crew, first_step, n_steps, n_pairs, crew_lds);
 }
 
 // the buffers behind the others in costmodel_update's workspace; every matrix is padded by one tile width, because a
@@ -870,7 +894,7 @@ uint64_t eck::refit_f32_workspace_bytes(const eck_model *m, int minibatch) { ret
 
 int32_t eck::refit_f32_steps(const eck_model *m, const float *feat, uint64_t ld, const float *y, uint64_t n_pairs,
                              int32_t n_steps, int32_t minibatch, float lr, float beta1, float beta2, float eps,
-                             const uint32_t *bad_flag, float *loss_scalar, void *ws, hipStream_t st)
+                             const uint32_t *bad_flag, float *loss_scalar, void *ws, CrewSize crew, hipStream_t st)
 {
     const Buffers w = buffers_for(m, minibatch);
     char *base = static_cast<char *>(ws);
@@ -918,7 +942,8 @@ int32_t eck::refit_f32_steps(const eck_model *m, const float *feat, uint64_t ld,
         const CrewLds at(a.F, a.H1, a.H2);
         ECK_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(steps_f32_crew_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)at.total));
         CrewState *state = crew_state(m, minibatch, ws);
-        hipLaunchKernelGGL(steps_f32_crew_kernel, dim3(CREW_GRID), dim3(CREW_THREADS), at.total, st, a, state, crew_pick(state), n_steps, n_pairs);
+        hipLaunchKernelGGL(steps_f32_crew_kernel, dim3(CREW_DIES * crew.candidates), dim3(CREW_THREADS), at.total, st, a, state, crew_pick(state), n_steps,
+                           n_pairs, crew.at_once);
         ECK_HIP_TRY(hipGetLastError());
         return ECK_OK;
     }

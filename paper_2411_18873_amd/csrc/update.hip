@@ -16,7 +16,7 @@
 #include <algorithm>
 #include <cmath>
 
-#include "eck_internal.h"
+#include "crew.h"
 #include "refit_labels.h"
 
 using namespace eck;
@@ -344,11 +344,15 @@ extern "C" uint64_t costmodel_update_workspace_bytes(const eck_model *m, uint64_
     return upd_layout(m, n_pairs, minibatch).total;
 }
 
-extern "C" int32_t costmodel_update(eck_model *m, const void *feat, int32_t feat_dtype, uint64_t ld,
-                                    const float *energy_measured, uint64_t n_pairs, int32_t n_steps, int32_t minibatch,
-                                    float lr, float beta1, float beta2, float eps, float *snr_out, float *loss_out,
-                                    void *ws, uint64_t ws_bytes, void *stream)
+// costmodel_update, its steps by a crew of at most `candidates` blocks, `at_once` of them taken on at a time, where one takes them.
+// What a busy chip does to a crew, for the tests: not part of the interface.
+extern "C" int32_t eck_update_by_crew(eck_model *m, const void *feat, int32_t feat_dtype, uint64_t ld, const float *energy_measured,
+                                      uint64_t n_pairs, int32_t n_steps, int32_t minibatch, float lr, float beta1, float beta2,
+                                      float eps, float *snr_out, float *loss_out, void *ws, uint64_t ws_bytes, uint32_t candidates,
+                                      uint32_t at_once, void *stream)
 {
+    if (candidates < 1 || candidates > CREW_MOST || at_once < 1 || at_once > CREW_MOST) return ECK_EINVAL;
+    const CrewSize crew = {candidates, at_once};
     if (!m || !feat || !energy_measured || !snr_out || !loss_out) return ECK_EINVAL;
     if (n_pairs == 0 || minibatch <= 0 || n_steps < 0 || n_pairs > (1u << 30)) return ECK_EINVAL;
     if (feat_dtype != ECK_F32 && feat_dtype != ECK_BF16) return ECK_EINVAL;
@@ -388,9 +392,9 @@ extern "C" int32_t costmodel_update(eck_model *m, const void *feat, int32_t feat
     if (rc != ECK_OK) return rc;
     if (two_launches || m->dtype == ECK_F32) {
         rc = two_launches ? refit_steps(m, feat, feat_dtype, ld, y, n_pairs, n_steps, minibatch, lr, beta1, beta2, eps, &sc->bad,
-                                        &sc->loss, base + place.features, base + place.ws, st)
+                                        &sc->loss, base + place.features, base + place.ws, crew, st)
                           : refit_f32_steps(m, static_cast<const float *>(feat), ld, y, n_pairs, n_steps, minibatch, lr, beta1, beta2,
-                                            eps, &sc->bad, &sc->loss, base + w.refit, st);
+                                            eps, &sc->bad, &sc->loss, base + w.refit, crew, st);
         if (rc != ECK_OK) return rc;
         return refit_finish(m, pred, y, n_pairs, n_steps, sc, snr_out, loss_out, st);
     }
@@ -426,6 +430,15 @@ extern "C" int32_t costmodel_update(eck_model *m, const void *feat, int32_t feat
     }
     ECK_HIP_TRY(hipGetLastError());
     return refit_finish(m, nullptr, y, n_pairs, n_steps, sc, snr_out, loss_out, st);
+}
+
+extern "C" int32_t costmodel_update(eck_model *m, const void *feat, int32_t feat_dtype, uint64_t ld,
+                                    const float *energy_measured, uint64_t n_pairs, int32_t n_steps, int32_t minibatch,
+                                    float lr, float beta1, float beta2, float eps, float *snr_out, float *loss_out,
+                                    void *ws, uint64_t ws_bytes, void *stream)
+{
+    return eck_update_by_crew(m, feat, feat_dtype, ld, energy_measured, n_pairs, n_steps, minibatch, lr, beta1, beta2, eps, snr_out, loss_out,
+                              ws, ws_bytes, CREW_MOST, CREW_MOST, stream);
 }
 
 extern "C" int32_t eck_k_count(double k, int64_t M, int64_t *count_out)

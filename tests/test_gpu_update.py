@@ -478,3 +478,33 @@ def test_a_state_of_many_steps(G, widths, dtype, mb, steps, done):
     got = model.get_state().cpu().numpy().astype(np.float64)
     assert np.isfinite(got).all()
     assert np.quantile(np.abs(got[:P] - st[:P]), 0.99) <= (1e-7 + 2.0 ** -24 * np.abs(theta).max()) * steps
+
+
+@pytest.mark.parametrize("widths,dtype,mb,epoch", [([64, 256, 256, 1], "bf16", 512, 2), ([64, 128, 128, 1], "bf16", 250, 1), ([32, 64, 64, 1], "bf16", 64, 3),
+                                                   ([64, 128, 128, 1], "f32", 250, 2), ([32, 50, 30, 1], "f32", 497, 1), ([64, 128, 128, 1], "f32", 16, 1)])
+@pytest.mark.parametrize("candidates,at_once", [(1, 1), (3, 3), (7, 7), (32, 1), (32, 5)])
+def test_steps_of_small_and_growing_crews(G, widths, dtype, mb, epoch, candidates, at_once):
+    """Crews of fewer members than there are blocks of rows and tiles of weights, and such as take members on between steps, as
+    beside other work on the chip: the bits of two launches a step."""
+    import ctypes as C
+    import torch
+    f32, b16, e = _pairs(mb * epoch + (mb * epoch & 1))
+    F, n, e = widths[0], mb * epoch, e[:mb * epoch]
+    x = G.bf16_dev(b16[:F].copy()) if dtype == "bf16" else G.to_dev(np.ascontiguousarray(f32[:F]))
+    kind = eck.BF16 if dtype == "bf16" else eck.F32
+    theta = synth.mlp_theta(widths, 4, bf16=dtype == "bf16", bias_scale=0.1)
+    a, b = G.make_model(widths, kind, theta), G.make_model(widths, kind, theta)
+    steps = 12
+    energy, out = G.to_dev(e.astype(np.float32)), torch.zeros(2, device="cuda")
+    ws = torch.empty(eck.costmodel_update_workspace_bytes(a, n, mb), dtype=torch.uint8, device="cuda")
+    update = eck.lib().eck_update_by_crew
+    update.restype = C.c_int32
+    update.argtypes = [C.c_void_p, C.c_void_p, C.c_int32, C.c_uint64, C.c_void_p, C.c_uint64, C.c_int32, C.c_int32] + [C.c_float] * 4 + \
+        [C.c_void_p, C.c_void_p, C.c_void_p, C.c_uint64, C.c_uint32, C.c_uint32, C.c_void_p]
+    assert update(a.h, x.data_ptr(), kind, x.shape[1], energy.data_ptr(), n, steps, mb, 1e-3, 0.9, 0.999, 1e-8, out.data_ptr(),
+                  out.data_ptr() + 4, ws.data_ptr(), ws.numel(), candidates, at_once, torch.cuda.current_stream().cuda_stream) == eck.OK
+    short = epoch if epoch > 1 else 2  # steps of a call that launches each: as many as bring the minibatches round, or the same one again
+    for _ in range(steps // short):
+        _, loss_b = G.update_gpu(b, x, e, short, mb)
+    assert np.array_equal(a.get_state().cpu().numpy(), b.get_state().cpu().numpy())
+    assert float(out[1]) == loss_b
