@@ -467,16 +467,7 @@ struct OutputBlock {
     }
 };
 
-// The mean of the Eq.-(1) terms, by one wavefront, in a fixed order
-template <bool FRESH>
-__device__ __forceinline__ void report_loss(const StepArgs &a, int lane)
-{
-    double s = 0.0;
-    for (int r = lane; r < a.rows; r += 64) s += (double)fresh_float<FRESH>(a.lterm, 4u * r, 0);
-#pragma unroll
-    for (uint32_t off = 32; off > 0; off >>= 1) s += lane_exchange(s, off);
-    if (lane == 0) *a.loss_out = (float)(s / a.rows);
-}
+constexpr int LOSS_PARTS = 4; // the loss's sum, as many as a block of the weights kernel has wavefronts
 
 // Blocks, in order: the 32 x 32 tiles of W2 (H1/32 x H2/32), the tiles of W1 (F/32 x H1/32), then blocks of 16
 // columns of the output layer.  A tile block: C[m][n] = sum_r A[m][r] B[r][n] with both operands stored row-index
@@ -489,6 +480,7 @@ __global__ __launch_bounds__(256) void step_weights_kernel(StepArgs a)
 {
     __shared__ float part[4][16][64];   // partial tiles of the four wavefronts
     __shared__ float colsum[4][32];     // partial bias gradients
+    __shared__ double loss[LOSS_PARTS];
     const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, c = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     constexpr int TILES_W2 = (H1 / 32) * (H2 / 32), TILES_W1 = (F / 32) * (H1 / 32);
@@ -579,10 +571,15 @@ __global__ __launch_bounds__(256) void step_weights_kernel(StepArgs a)
     OutputBlock<H2, false> out(a, block - (TILES_W2 + TILES_W1), tid);
     out.request();
     out.sum(&part[0][0][0]);
+    const bool report = a.report_loss && out.block == 0;
+    if (report) {
+        const double s = loss_part<LOSS_PARTS>(a.lterm, a.rows, wave, lane);
+        if (lane == 0) loss[wave] = s;
+    }
     lds_barrier();
     if (bad) return;
     out.update(&part[0][0][0], scales);
-    if (a.report_loss && out.block == 0 && wave == 3) report_loss<false>(a, lane);
+    if (report && tid == 64) *a.loss_out = (float)((((loss[0] + loss[1]) + loss[2]) + loss[3]) / a.rows);
 }
 
 // ------------------------------------------------------------------------------------- all steps in one launch
@@ -819,7 +816,10 @@ __global__ __launch_bounds__(CREW_THREADS) void steps_crew_kernel(StepArgs a, Cr
                 lds_barrier();
                 if (mine) {
                     out.update(parts, adam());
-                    if (last && out.block == 0 && wave == CREW_THREADS / 64 - 1) report_loss<true>(a, lane);
+                    if (last && out.block == 0 && wave == CREW_THREADS / 64 - 1) {
+                        const double s = loss_sum_fresh<LOSS_PARTS>(a.lterm, a.rows, lane);
+                        if (lane == 0) *a.loss_out = (float)(s / a.rows);
+                    }
                 }
             }
             if (members < Cut::ITEMS) lds_barrier(); // (the LDS is free again)

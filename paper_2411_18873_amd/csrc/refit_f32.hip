@@ -587,22 +587,11 @@ struct OutputBlock {
     }
 };
 
-// The mean of the Eq.-(1) terms, by one wavefront, in a fixed order
-template <bool FRESH>
-__device__ __forceinline__ void report_loss(const StepF32 &a, int lane)
-{
-    double s = 0.0;
-#pragma unroll 8
-    for (int r = lane; r < a.rows; r += 64) s += (double)fresh_float<FRESH>(a.lterm, 4u * r, 0);
-#pragma unroll
-    for (uint32_t off = 32; off > 0; off >>= 1) s += lane_exchange(s, off);
-    if (lane == 0) *a.loss_out = (float)(s / a.rows);
-}
-
 __global__ __launch_bounds__(64 * WAVES) void step_weights_f32_kernel(StepF32 a, int blocks2, int blocks1)
 {
     __shared__ float part[WAVES][TILE][TILE];
     __shared__ float colsum[WAVES][TILE];
+    __shared__ double loss[WAVES];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bool bad = *a.bad != 0;
     const AdamScales scales = *a.scales;
@@ -623,10 +612,20 @@ __global__ __launch_bounds__(64 * WAVES) void step_weights_f32_kernel(StepF32 a,
     OutputBlock<64 * WAVES, false> out(a, block, tid);
     out.request();
     out.sum(&part[0][0][0]);
+    const bool report = a.report_loss && block == 0;
+    if (report) {
+        const double s = loss_part<WAVES>(a.lterm, a.rows, wave, lane);
+        if (lane == 0) loss[wave] = s;
+    }
     lds_barrier();
     if (bad) return;
     out.update(&part[0][0][0], scales);
-    if (block == 0 && a.report_loss && wave == WAVES - 1) report_loss<false>(a, lane);
+    if (report && tid == 64) {
+        double s = loss[0];
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w) s += loss[w];
+        *a.loss_out = (float)(s / a.rows);
+    }
 }
 
 // ------------------------------------------------------------------------------------- all steps in one launch
@@ -750,7 +749,10 @@ __device__ __forceinline__ void crew_steps(const StepF32 &a, Crew crew, int firs
                 lds_barrier();
                 if (mine) {
                     out.update(psum, *scales_of);
-                    if (last && item == 0 && wave == CREW_THREADS / 64 - 1) report_loss<true>(a, lane);
+                    if (last && item == 0 && wave == CREW_THREADS / 64 - 1) {
+                        const double s = loss_sum_fresh<WAVES>(a.lterm, a.rows, lane);
+                        if (lane == 0) *a.loss_out = (float)(s / a.rows);
+                    }
                 }
             }
             if (members < items_most) lds_barrier(); // (the LDS is free again)

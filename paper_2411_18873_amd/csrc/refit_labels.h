@@ -1,6 +1,6 @@
 // What the refits of all model forms share (HIP, gfx950): the measured energies made labels, and sums over a block.
 #pragma once
-#include "eck_internal.h"
+#include "crew.h"
 #include "lanes.h"
 
 namespace eck {
@@ -71,6 +71,40 @@ __device__ __forceinline__ void make_labels(const float *__restrict__ e, uint64_
         sc->bad = bad;
         sc->snr = sc->loss = __builtin_nanf("");
     }
+}
+
+// The sum of the Eq.-(1) terms of a minibatch in double, in a fixed order: PARTS sums, of every PARTS-th 64 rows each, along a wavefront,
+// then the parts in order.  Part by part, by a wavefront each ...
+template <int PARTS>
+__device__ __forceinline__ double loss_part(const float *terms, int rows, int part, int lane)
+{
+    double s = 0.0;
+#pragma unroll 8
+    for (int r = 64 * part + lane; r < rows; r += 64 * PARTS) s += (double)terms[r];
+#pragma unroll
+    for (uint32_t off = 32; off > 0; off >>= 1) s += lane_exchange(s, off);
+    return s;
+}
+// ... or all by one wavefront of a crew, whose rows are few
+template <int PARTS>
+__device__ __forceinline__ double loss_sum_fresh(const float *terms, int rows, int lane)
+{
+    double s[PARTS] = {};
+    for (int r = lane; r < rows; r += 64 * PARTS) {
+#pragma unroll
+        for (int p = 0; p < PARTS; ++p) {
+            const float term = fresh_float<true>(terms, 4u * min(r + 64 * p, rows - 1), 0);
+            s[p] += r + 64 * p < rows ? (double)term : 0.0; // (no term is below zero)
+        }
+    }
+#pragma unroll
+    for (uint32_t off = 32; off > 0; off >>= 1) {
+#pragma unroll
+        for (int p = 0; p < PARTS; ++p) s[p] += lane_exchange(s[p], off);
+    }
+#pragma unroll
+    for (int p = 1; p < PARTS; ++p) s[0] += s[p];
+    return s[0];
 }
 
 // One block of 1024 threads: sum y^2 / sum (p - y)^2, thread 0's
