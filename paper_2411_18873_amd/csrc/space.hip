@@ -1176,34 +1176,51 @@ namespace {
 //
 // Stores past the caches leave at once, a wavefront's 128 or 256 bytes of a row by themselves, so where they do not start on 64
 // bytes, their ends are written to memory as pieces, twice: every column a wavefront starts at has to lie there in every row.
-// A matrix that the memory-side cache holds (256 MB) is better written through the caches, small ones apart.  Small blocks
-// bring a small launch to more compute units and share a unit better, each stages the space's tables for itself, and a row's
-// stores that start anywhere want long runs.  us, 64 features of one space:
-//   rows on 64 bytes, bfloat16: streamed by blocks of 256 / 512 / 1024: 6400 candidates 4.4 / 5.1 / 7.0, 65536 5.4 / 6.1 / 8.0,
-//     262144 9.3 / 8.8 / 8.5, 2^21 51 / 52 / 63; blocks of 512 streamed / through the caches: 400000 12.7 / 13.9, 600000 17.7 / 16.7,
-//     1398144 38 / 33, 1800000 49 / 47, 1966080 49 / 56, 2^22 97 / 139
-//   fp32: blocks of 256 streamed / through the caches: 131072 8.6 / 9.3, 300032 16.8 / 14.9, 600000 32 / 26, 1200000 64 / 61, 1398144
-//     72 / 76, 2^21 100 / 115, 2^22 191 / 237; of 256 / 1024:
-//     140000 8.7 / 9.7, 180000 9.9 / 11.1, 262144 14.3 / 13.3, 300032 14.9 / 16.7, 2^20 46 / 43, 2^22 191 / 295
-//   8 bytes beside them: fp32 by 1024 streamed / through the caches 260001 23.5 / 13.9, 777777 80 / 35, 2^20 + 2 143 / 52, by 256
-//     through the caches 14.3, 35, and 3000003 242 for 221; bfloat16 777777 56 / 20.7, by 256 22.2
+// A matrix that the memory-side cache holds (256 MB) is better written through the caches, where a program writes the same one
+// round after round or scores it next; small ones apart, and those of 32 bfloat16 features (2^20 by 512: 17.6 / 21.1).
+// A matrix that is written once, among others, takes as long either way.  us, 64 features of one space, streamed / through the
+// caches: each alone, again and again; among 1.2 GB of others; with the scorer of 64-128-128 behind it, again and again
+//   bfloat16, blocks of 512: 400000 candidates 13.4 / 14.1; 13.5 / 14.7.  1398144: 39 / 33; 38 / 38; 104 / 93.  1835008: 49 / 42; 49 / 49;
+//     131 / 118.  1966080: 49 / 58; 49 / 55
+//   fp32, of 512: 262144 14.1 / 14.2; 14.3 / 14.9.  700032: 36 / 30; 36 / 37; 252 / 233.  2^20: 61 / 55; 61 / 63; 382 / 364.  1200000: 63 / 59;
+//     65 / 68
+// Small blocks bring a small launch to more compute units and share a unit better, each stages the space's tables for itself.  Rows
+// a multiple of megabytes apart begin in the same channels, and which blocks meet there depends on their size.  Streamed by blocks
+// of 1024 / 512 / 256, but where said otherwise, again and again:
+//   bfloat16, 64 features: 6400 7.0 / 5.1 / 4.4, 65536 8.0 / 6.1 / 5.4, 262144 9.6 / 9.6 / 10.1, 524288 15.6 / 16.5 / 16.4, 2^20 through the caches
+//     24.6 / 27.6 / 26.3, 2^21 62 / 51 / 52, 2^22 105 / 95 / 99; 32 features: 400000 11.7 / 11.1 / 10.0, 850048 18.4 / 15.5 / 14.8
+//   fp32, 64 features: 262144 14.6 / 14.1 / 15.1, 524288 through the caches 23.0 / 23.3 / 25.1 (among others 26.2 / 25.2 / 26.8), 2^20 so 55 / 55 / 46,
+//     1200000 60 / 63 / 63, 1398144 77 / 73 / 72, 2^21 129 / 108 / 98, 2^22 293 / 197 / 187
+//   8 bytes beside 64: fp32 by 1024 streamed / through the caches 260001 23.5 / 13.9, 777777 80 / 35, by 256 through the caches 14.3, 35, and
+//     3000003 242 for 221; bfloat16 777777 56 / 20.7, by 256 22.2
+// Raw features are stored past the caches, eight bytes a lane; transformed ones beside them go through.  By blocks of 1024 / 512 / 256:
+//   bfloat16 and raw: 262144 streamed 33.8 / 36.4 / 33.3, through the caches 30.6 / 32.8 / 31.0; 700032 87 / 88 / 87 and 70 / 74 / 71; 2^20 152 / 149 / 129
+//     and 131 / 128 / 108
+//   raw alone: 262144 27.1 / 26.7 / 23.7, 400000 39.8 / 41.8 / 39.8, 2^20 127 / 128 / 103; 524288 by 1024 / 256 52.6 / 59.3
 struct FeatureStores {
     bool stream;
     uint32_t block;
 };
-FeatureStores feature_stores(const void *feat_out, uint64_t ld, uint64_t n, uint32_t n_spaces, int32_t n_feat, uint64_t elem,
+FeatureStores feature_stores(const void *feat_out, bool raw, uint64_t ld, uint64_t n, uint32_t n_spaces, int32_t n_feat, uint64_t elem,
                              uint32_t table_entries)
 {
     constexpr uint64_t PIECE = 64, MB = 1u << 20;
     const uint64_t all = n * n_spaces, bytes = all * n_feat * elem;
     const bool whole = ((uintptr_t)feat_out | (ld * elem) | (n_spaces > 1 ? n * elem : 0)) % PIECE == 0;
+    const bool apart_1mb = ld * elem % MB == 0, apart_4mb = ld * elem % (4 * MB) == 0, all64 = n_feat == 64;
     FeatureStores s;
-    s.stream = whole && (elem == 2 ? bytes < 70 * MB || bytes > 225 * MB : bytes < 49 * MB || bytes > 310 * MB);
+    if (raw) s.stream = false;
+    else if (elem == 2) s.stream = whole && (!all64 || bytes < 70 * MB || bytes > 225 * MB);
+    else s.stream = whole && (bytes < (all64 ? 70 : 60) * MB || bytes > (all64 ? 275 : 225) * MB);
     if (table_entries > 2048) s.block = kFeatBlock; // 16 KB and more of tables
     else if (all <= 131072) s.block = 256;
+    else if (!feat_out) s.block = ld * 8 % (8 * MB) == 4 * MB ? kFeatBlock : 256;
+    else if (raw) s.block = ld * 8 % (8 * MB) == 0 ? 256 : kFeatBlock;
     else if (!whole) s.block = kFeatBlock;
-    else if (elem == 2) s.block = 512;
-    else s.block = all > 196608 && all <= 262144 ? kFeatBlock : 256; // (one block on nearly each of 256 units)
+    else if (elem == 2) s.block = apart_4mb ? 512 : !all64 ? 256 : apart_1mb ? kFeatBlock : 512;
+    else if (apart_4mb) s.block = 256;
+    else if (apart_1mb) s.block = 512;
+    else s.block = all64 && s.stream && bytes > 275 * MB && bytes < 310 * MB ? kFeatBlock : 256;
     return s;
 }
 
@@ -1230,7 +1247,8 @@ int32_t features_launch(const eck_space *const *spaces, uint32_t n_spaces, const
     const bool xred = spaces[0]->prm.kind == ECK_SPACE_SPLIT_XRED;
     const bool in_lds = spaces[0]->prm.kind != ECK_SPACE_KNOB && largest <= 6144;
     const size_t lds = in_lds ? (size_t)((largest + 1) / 2) * 16 : 0; // staged two entries at a time
-    const FeatureStores stores = feature_stores(feat_out, ld, n, n_spaces, n_feat, out_dtype == ECK_F32 ? 4 : 2, in_lds ? largest : 0);
+    const FeatureStores stores = feature_stores(feat_out, raw_out != nullptr, ld, n, n_spaces, n_feat, out_dtype == ECK_F32 ? 4 : 2,
+                                                in_lds ? largest : 0);
     const dim3 block(stores.block), grid((unsigned)((n + stores.block - 1) / stores.block), n_spaces);
     hipStream_t st = as_stream(stream);
     const bool raw = raw_out != nullptr;

@@ -541,3 +541,30 @@ def test_features_streamed_and_through_the_caches(G, dtype):
             assert np.array_equal(mine_bits.numpy(), want)
         else:
             assert np.array_equal(mine_bits.view(torch.int16).numpy().view(np.uint16), bits)
+
+
+@pytest.mark.parametrize("n_feat", [32, 64])
+@pytest.mark.parametrize("n", [140000, 262144, 524288, 1 << 20])
+def test_features_beside_raw_ones(G, n, n_feat):
+    """Sizes at which transformed and raw features, together or alone, are stored by different blocks and by the caches or past
+    them: the same values in every form, and the oracle's at both ends."""
+    import torch
+    mine, ref = _spaces("c2", eck.SPACE_SPLIT)
+    genes = torch.zeros((mine.n_genes, n), dtype=torch.int16, device="cuda")
+    eck.candidate_enumerate(mine, eck.MODE_SAMPLE, n, genes, seed=7)
+    raw_alone = torch.zeros((n_feat, n), dtype=torch.int64, device="cuda")
+    eck.features_compute(mine, genes, n, n_feat, eck.F32, raw_out=raw_alone)
+    for code, kind in ((eck.F32, torch.float32), (eck.BF16, torch.bfloat16)):
+        alone, beside = (torch.full((n_feat, n), -1.0, dtype=kind, device="cuda") for _ in range(2))
+        raw = torch.zeros_like(raw_alone)
+        eck.features_compute(mine, genes, n, n_feat, code, feat_out=alone)
+        eck.features_compute(mine, genes, n, n_feat, code, feat_out=beside, raw_out=raw)
+        assert torch.equal(alone, beside) and torch.equal(raw, raw_alone)
+        for at in (0, n - 1500):
+            want_raw, want, bits, _ = oracle.features(ref, np.ascontiguousarray(genes[:, at:at + 1500].cpu().numpy().view(np.uint16)), n_feat)
+            assert np.array_equal(raw[:, at:at + 1500].cpu().numpy().view(np.uint64), want_raw)
+            got = alone[:, at:at + 1500].contiguous().cpu()
+            if code == eck.F32:
+                assert np.array_equal(got.numpy(), want)
+            else:
+                assert np.array_equal(got.view(torch.int16).numpy().view(np.uint16), bits)
