@@ -25,10 +25,10 @@ constexpr unsigned CREW_MOST = 32; // members, one per compute unit of a die
 
 struct CrewState { // device memory, zero before the launch: two lines
     uint32_t home;      // the members' die + 1, 0: none yet
-    uint32_t over;      // nobody is taken on any more
+    uint32_t pad;
     uint64_t muster;    // the founder's: who belongs to the crew and since which step (Crew::call)
     uint32_t roll[16];  // by die: candidates that signed
-    uint32_t pad[12];
+    uint32_t pad2[12];
     uint32_t met[CREW_MOST]; // by member: barriers it has reached
 };
 static_assert(sizeof(CrewState) == 256, "fits the place behind a workspace's last buffer");
@@ -46,7 +46,9 @@ struct Crew {
     CrewState *s;
     uint32_t rank, size, barriers;
 
-    // `members` belong to the crew from `step` on, `before` of them already did; at_once: so many may be taken on together
+    // `members` belong to the crew from `step` on, `before` of them already did; at_once: so many may be taken on together.  OVER:
+    // nobody is any more.
+    static constexpr uint64_t OVER = 1u << 24;
     static __device__ __forceinline__ uint64_t call(uint32_t step, uint32_t at_once, uint32_t before, uint32_t members)
     {
         return (uint64_t)step << 32 | at_once << 16 | before << 8 | members;
@@ -76,12 +78,8 @@ struct Crew {
                     muster = call(0, at_once, 0, min(there, at_once));
                     __hip_atomic_store(&s->muster, muster, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 } else {
-                    // (The founder runs.  `over` is read behind a muster without this block, and set when all of the last one's
-                    // members have reached a barrier.)
-                    do {
-                        muster = relaxed(&s->muster);
-                        asm volatile("" ::: "memory");
-                    } while (members(muster) <= place && !relaxed(&s->over));
+                    do muster = relaxed(&s->muster); // (the founder runs)
+                    while (members(muster) <= place && !(muster & OVER));
                 }
             }
             slot[0] = place;
@@ -118,9 +116,9 @@ struct Crew {
         size = all;
         return true;
     }
-    __device__ __forceinline__ void dismiss() const // behind the last step's first barrier
+    __device__ __forceinline__ void dismiss() const // behind the last step's first barrier: who was called has come
     {
-        if (founder()) __hip_atomic_store(&s->over, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (founder()) __hip_atomic_store(&s->muster, relaxed(&s->muster) | OVER, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __device__ __forceinline__ bool full() const { return __builtin_expect(size == CREW_MOST, true); }
     __device__ __forceinline__ bool founder() const { return rank == 0 && threadIdx.x == 0; } // its first thread
