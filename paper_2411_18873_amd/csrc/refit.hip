@@ -861,12 +861,12 @@ __global__ __launch_bounds__(1024) void step_prepare_kernel(const float *theta, 
     }
 }
 
-// A crew's launch and roll take as long as three steps gain; with more rows the chip's other dies are missed.  us a call (replayed
-// graphs), two launches a step / crew:
-//   64-256-256, 512 rows: 2 steps 44.0 / 45.6, 3 steps 56.8 / 56.8, 8 steps 121 / 107; 8 steps of 1024 rows 139 / 132, 2048: 180 / 232
-//   64-128-128, 64 rows: 3 steps 36.2 / 37.9; 8 steps of 64 rows 77.8 / 70.9, 1024: 105 / 87, 2048: 137 / 130, 4096: 201 / 253
-//   32-64-64, 8 steps of 64 rows 69.3 / 61.3, 2048: 119 / 112, 4096: 170 / 183
-bool crew_takes(int minibatch, int n_steps, int width) { return n_steps >= 4 && minibatch <= 2048 && minibatch * width <= 1 << 18; }
+// A crew's launch and roll take as long as three steps gain; with more blocks of rows than members the chip's other dies are missed.
+// us a call (replayed graphs), two launches a step / crew:
+//   64-256-256, 512 rows: 2 steps 44.0 / 45.6, 3 steps 56.8 / 56.8, 4 steps 75.7 / 72.7, 8 steps 127 / 114; 1024 rows: 84.1 / 83.8, 144 / 138
+//   64-128-128, 64 rows: 3 steps 36.2 / 37.9, 4 steps 52.4 / 50.5, 8 steps 86.5 / 78.1; 1024: 63.2 / 58.8, 107 / 92; 1536: 71 / 76, 123 / 126; 2048: 77 / 81, 135 / 135
+//   32-64-64, 64 rows: 4 steps 47.8 / 44.5, 8 steps 78.8 / 68.8; 1024: 55.0 / 53.5, 93 / 84; 2048: 66.6 / 73.1, 116 / 122
+bool crew_takes(int minibatch, int n_steps) { return n_steps >= 4 && minibatch <= 32 * (int)CREW_MOST; }
 
 template <int F, int H1, int H2>
 int32_t launch_steps(const eck_model *m, StepArgs a, int32_t feat_dtype, int32_t n_steps, uint64_t n_pairs, float *loss_scalar,
@@ -880,7 +880,7 @@ int32_t launch_steps(const eck_model *m, StepArgs a, int32_t feat_dtype, int32_t
                                     (int)lds));
     const int B = a.rows;
     if constexpr (H1 <= 256 && H2 <= 256) {
-        if (crew_takes(a.padded, n_steps, H1 > H2 ? H1 : H2)) {
+        if (crew_takes(a.padded, n_steps)) {
             constexpr size_t crew_lds = CrewCut<F, H1, H2>::LDS;
             auto crew_kernel = feat_dtype == ECK_BF16 ? steps_crew_kernel<F, H1, H2, true> : steps_crew_kernel<F, H1, H2, false>;
             ECK_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(crew_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)crew_lds));

@@ -858,7 +858,8 @@ __device__ __forceinline__ void select_and_emit(const SelectArgs &a, uint32_t s,
 // launch works on the lists.  (Letting the block that finishes a segment last merge the lists inside the same
 // launch was tried: on this chip blocks of one launch sit on eight dies with separate L2 caches, so lists and
 // tickets have to be written through to memory -- device-scope stores and atomics, or a release fence, which
-// writes the whole L2 back -- and that costs far more than the second launch: 73 us and 400 us against 32.)
+// writes the whole L2 back -- and that costs far more than the second launch: 73 us and 400 us against 32.  Blocks of one
+// die can hand over in its L2, 0.73 us (crew.h); a merge of each die's lists before the last launch has not been tried.)
 template <int T, int SRC, int PRED, bool CROWDED = false>
 __global__ __launch_bounds__(T, CROWDED ? 8 : 1) void select_kernel(SelectArgs a)
 {

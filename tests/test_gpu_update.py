@@ -346,8 +346,8 @@ def test_data_error_leaves_an_fp32_model_alone(G, widths, minibatch):
     ([64, 256, 256, 1], 250, 500, "bf16"), ([64, 128, 128, 1], 333, 666, "f32"), ([32, 64, 64, 1], 201, 402, "bf16"),
     ([32, 64, 64, 1], 2048, 2048, "f32")])
 def test_bf16_steps_of_a_crew_are_those_of_two_launches(G, widths, mb, n_pairs, feat):
-    """Calls of a few steps launch each step by itself, longer ones run all steps in one launch on one die: the same bits,
-    with one block of rows and with two a member, and with minibatches that come round again."""
+    """Calls of a few steps launch each step by itself, longer ones of up to 1024 rows run all steps in one launch on one die: the same
+    bits, and with minibatches that come round again.  (Several blocks of rows a member: small crews, below.)"""
     f32, b16, e = _pairs(n_pairs)
     F, epoch = widths[0], n_pairs // mb
     x = G.bf16_dev(b16[:F].copy()) if feat == "bf16" else G.to_dev(np.ascontiguousarray(f32[:F]))
