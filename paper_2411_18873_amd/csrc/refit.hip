@@ -18,7 +18,7 @@
 // What bounds a step is the latency of loads right after a launch or a barrier and the chain of dependent phases, so both
 // parts request all that they can name before they wait for any of it, and values become bfloat16 two at a time by the
 // hardware's conversion.  Measured, 64-256-256-1, 8 steps of 512 rows, a whole call with the state in and out: 145.0 us with
-// two launches a step, 114.9 by a crew.  Of a crew's step of some 10 us the rows take 5.3 (the weights of a block of rows,
+// two launches a step, 115.5 by a crew (114.9 while its number of members was fixed at the start).  Of a crew's step of some 10 us the rows take 5.3 (the weights of a block of rows,
 // 288 KB through one unit's 130 GB/s, 2.2), the weights 3.5, the two barriers what is left.
 #include "crew.h"
 #include "refit_labels.h"

@@ -11,7 +11,7 @@
 // sixteen rows of the reduction at a time.  Every sum has a fixed order, the same in both forms.
 // Measured, 64-128-128-1, 16 steps of 250 rows, a whole call with the state in and out: 252.4 us with two launches a step
 // (a block of its own for the bias corrections took 0.85 us a step off the rows kernel; the features requested first and
-// the biases' moments with the tile's, 0.6), 192.4 by a crew (crew.h).  One product at a time: 136 us a step.
+// the biases' moments with the tile's, 0.6), 195.7 by a crew (crew.h; 192.4 while its number of members was fixed at the start).  One product at a time: 136 us a step.
 // 64-512-512-1, 512 rows, two launches: 70 us a step.
 #include "crew.h"
 #include "f32_tiles.h"
@@ -821,8 +821,8 @@ int tiles_a_wave(const eck_model *m)
 
 // Up to 128 units (copies are kept for those) and 32 blocks of rows, one a member; a crew's launch and roll take as long as two
 // steps gain.  us a call (replayed graphs), two launches a step / crew:
-//   64-128-128, 250 rows: 2 steps 38.6 / 40.1, 3 steps 52.3 / 50.4, 8 steps 121 / 103; 512: 135 / 119, 1000: 159 / 218
-//   32-64-64, 8 steps of 16 rows 80 / 70, 512: 105 / 93; 64-16-16, 8 steps of 64 rows 79.6 / 65.9
+//   64-128-128, 250 rows: 2 steps 38.6 / 40.1, 3 steps 59.0 / 56.5, 8 steps 126 / 110; 512: 141 / 126, 1000: 159 / 218
+//   32-64-64, 8 steps of 16 rows 89 / 77, 512: 111 / 103; 64-16-16, 8 steps of 64 rows 85.3 / 73.4
 //   64-256-256, 8 steps of 128 rows 211 / 205, 250: 219 / 227 (its weights, 0.6 MB a block of rows, are what a unit is slow with)
 bool crew_takes(const eck_model *m, int minibatch, int n_steps) { return m->d_copies && n_steps >= 3 && minibatch <= 512; }
 
